@@ -1,7 +1,7 @@
-// Offline preprocessing kernels (Algorithm 1 of the paper): quantize-round the
+// Preprocessing kernels (Algorithm 1 of the paper): quantize-round the
 // fp32 weights to B-bit two's-complement codes (Section 3.3), split the codes
 // into B bitlayers, sign layer first (Section 3.2), and pack 32 columns per word
-// (Section 3.4).  Not on the timed path ("done offline", Section 3.3).
+// (Section 3.4); and the way back (pb_unpack).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -9,72 +9,95 @@
 
 namespace pb {
 
-// Scratch for the reductions of the quantizers: 64 uint64 at the start of `packed` (every packed matrix is at
-// least 512 bytes; the packing kernel overwrites them last).
-enum { kSlotAbsMax = 0, kSlotMax = 1, kSlotMin = 2, kSlotAbsSum = 3, kSlotClip = 4, kScratchWords = 64 };
+// The quantizers reduce over all weights before anything can be packed.  What those passes leave for the next launch
+// lives at the start of `packed`, which the packing kernel overwrites last (a packed matrix has at least 512 bytes, and at
+// least 1 KB per statistics block from two blocks on): 32 sums of the clipping search, then per block the partial
+// statistics and the partial sum of the +-1 code.  Every block writes its own slot, so nothing has to be cleared first.
 constexpr int kClipSteps = 32;
-
-__global__ void k_fill_u64(unsigned long long *p, int n, unsigned long long v)
+constexpr int kStatsFloats = 8192;      // weights that a block of the reductions takes at a time (32 per thread)
+constexpr int kMaxStatsBlocks = 2048;   // eight workgroups per compute unit
+struct Partial {
+    float absmax, hi, lo, unused;
+};
+struct Scratch {
+    unsigned long long *clip;      // [kClipSteps]
+    Partial *stats;                // [blocks]
+    unsigned long long *abssum;    // [blocks]
+};
+__host__ __device__ __forceinline__ Scratch scratch_of(void *packed, int blocks)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = (i == kSlotMin) ? ~0ull : v;
+    Scratch s;
+    s.clip = static_cast<unsigned long long *>(packed);
+    s.stats = reinterpret_cast<Partial *>(s.clip + kClipSteps);
+    s.abssum = reinterpret_cast<unsigned long long *>(s.stats + blocks);
+    return s;
 }
 
-// a float as an unsigned key that orders like the float (NaN excluded by the caller)
-__device__ __forceinline__ uint32_t ordered_key(float f)
+// `f` on the weights of this block: 32 per thread, eight 16-byte loads in flight
+template <typename F>
+__device__ __forceinline__ void for_each_weight(const float *__restrict__ W, size_t n, F f)
 {
-    const uint32_t b = __float_as_uint(f);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-__device__ __forceinline__ float from_ordered_key(uint32_t k)
-{
-    return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
-}
-
-// max |W|, max W and min W in one pass (Section 3.3: the step of every quantizer comes from these).
-// 16-byte loads, one set of atomics per workgroup.
-__global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size_t n, unsigned long long *scratch)
-{
-    __shared__ uint32_t part[3][4];
-    uint32_t am = 0, hi = 0, lo = 0xFFFFFFFFu;
-    auto take = [&](float w) {
-        if (w == w) {
-            const uint32_t a = __float_as_uint(fabsf(w)), k = ordered_key(w);
-            am = a > am ? a : am;
-            hi = k > hi ? k : hi;
-            lo = k < lo ? k : lo;
-        }
-    };
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    const size_t n4 = n / 4;
     const float4 *W4 = reinterpret_cast<const float4 *>(W);   // W is 16-byte aligned (checked on the host)
-    for (size_t i = tid; i < n4; i += stride) {
-        const float4 w = W4[i];
-        take(w.x); take(w.y); take(w.z); take(w.w);
-    }
-    for (size_t i = n4 * 4 + tid; i < n; i += stride) take(W[i]);
-    for (int off = 32; off > 0; off >>= 1) {
-        const uint32_t a = (uint32_t)__shfl_xor((int)am, off, 64), h = (uint32_t)__shfl_xor((int)hi, off, 64);
-        const uint32_t l = (uint32_t)__shfl_xor((int)lo, off, 64);
-        am = a > am ? a : am;
-        hi = h > hi ? h : hi;
-        lo = l < lo ? l : lo;
-    }
-    if ((threadIdx.x & 63) == 0) {
-        part[0][threadIdx.x >> 6] = am; part[1][threadIdx.x >> 6] = hi; part[2][threadIdx.x >> 6] = lo;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) {
-            am = part[0][w] > am ? part[0][w] : am;
-            hi = part[1][w] > hi ? part[1][w] : hi;
-            lo = part[2][w] < lo ? part[2][w] : lo;
+    for (size_t base = (size_t)blockIdx.x * kStatsFloats; base < n; base += (size_t)gridDim.x * kStatsFloats) {
+        if (base + kStatsFloats <= n) {
+            float4 v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = W4[base / 4 + k * 256 + threadIdx.x];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { f(v[k].x); f(v[k].y); f(v[k].z); f(v[k].w); }
+        } else {
+            for (size_t i = base + threadIdx.x; i < n; i += 256) f(W[i]);
         }
-        atomicMax(&scratch[kSlotAbsMax], (unsigned long long)am);
-        atomicMax(&scratch[kSlotMax], (unsigned long long)hi);
-        atomicMin(&scratch[kSlotMin], (unsigned long long)lo);
     }
+}
+
+// the same reduction over a workgroup of 256 threads, result in every thread
+template <typename T, typename F>
+__device__ __forceinline__ T block_reduce(T v, T *part, F combine)
+{
+    for (int off = 32; off > 0; off >>= 1) v = combine(v, __shfl_xor(v, off, 64));
+    __syncthreads();   // (`part` may still be read from the reduction before)
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return combine(combine(part[0], part[1]), combine(part[2], part[3]));
+}
+__device__ __forceinline__ float max_of(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ float min_of(float a, float b) { return fminf(a, b); }
+__device__ __forceinline__ unsigned long long sum_of(unsigned long long a, unsigned long long b) { return a + b; }
+
+// max |W|, max W and min W in one pass (Section 3.3: the step of every quantizer comes from these; fmaxf and fminf
+// drop NaN).  Bound: the read of W; 4096 x 4096: 11.8 us = 5.7 TB/s (43.7 us
+// with one load in flight per thread).
+__global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size_t n, Partial *stats)
+{
+    __shared__ float part[4];
+    float am = 0.0f, hi = -INFINITY, lo = INFINITY;
+    for_each_weight(W, n, [&](float w) {
+        am = fmaxf(am, fabsf(w));
+        hi = fmaxf(hi, w);
+        lo = fminf(lo, w);
+    });
+    am = block_reduce(am, part, max_of);
+    hi = block_reduce(hi, part, max_of);
+    lo = block_reduce(lo, part, min_of);
+    if (threadIdx.x == 0) stats[blockIdx.x] = Partial{am, hi, lo, 0.0f};
+}
+
+// the statistics of all blocks, in every thread of a workgroup of 256
+__device__ __forceinline__ Partial all_stats(const Partial *stats, int blocks)
+{
+    __shared__ float part[4];
+    float am = 0.0f, hi = -INFINITY, lo = INFINITY;
+    for (int i = threadIdx.x; i < blocks; i += 256) {
+        const Partial p = stats[i];
+        am = fmaxf(am, p.absmax);
+        hi = fmaxf(hi, p.hi);
+        lo = fminf(lo, p.lo);
+    }
+    am = block_reduce(am, part, max_of);
+    hi = block_reduce(hi, part, max_of);
+    lo = block_reduce(lo, part, min_of);
+    return Partial{am, hi, lo, 0.0f};
 }
 
 __device__ __forceinline__ int quantize_code(float w, float d, int qmin, int qmax)
@@ -86,6 +109,35 @@ __device__ __forceinline__ int quantize_code(float w, float d, int qmin, int qma
     return (int)r;
 }
 
+// The division of quantize_code by a multiplication where that cannot change the code.  t = w * (1 / d) differs from the
+// rounded quotient by less than |t| 2^-22, so rint(t) is the code's rounding unless t is that close to a half-integer
+// (for |t| up to qmax + 2; beyond, both clamp).  `off` is the largest distance of the t's from their integers: above
+// `limit` (or NaN) the caller divides.
+struct Quantizer {
+    float d, inv, limit;
+    int qmin, qmax;
+    __device__ __forceinline__ Quantizer(float step, int bits) : d(step)
+    {
+        qmax = (1 << (bits - 1)) - 1;
+        qmin = -(1 << (bits - 1));
+        inv = __fdiv_rn(1.0f, d);
+        limit = 0.5f - (float)(qmax + 2) * 0x1p-22f;
+        // (a step or an inverse outside the normal range: always divide)
+        if (!(d >= 0x1p-125f && d <= 0x1p125f)) limit = -1.0f;
+    }
+    __device__ __forceinline__ float rounded(float w, float &off) const
+    {
+        const float t = w * inv, r = rintf(t), f = fabsf(t - r);
+        off = !(f <= off) ? f : off;   // (a NaN goes through to the comparison)
+        return r;
+    }
+    __device__ __forceinline__ bool must_divide(float off) const { return !(off <= limit); }
+    __device__ __forceinline__ int code(float r) const
+    {
+        return (int)fminf(fmaxf(r, (float)qmin), (float)qmax);
+    }
+};
+
 // trunc(|a| * 2^(30 - e)) for |a| < 2^(e + 1): an integer below 2^31, so that the sums below are exact in 64 bits
 // and do not depend on the order of the additions
 __device__ __forceinline__ unsigned long long fix30(float a, int e)
@@ -96,35 +148,29 @@ __device__ __forceinline__ unsigned long long fix30(float a, int e)
 
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 {
-    for (int off = 32; off > 0; off >>= 1) {
-        const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, off, 64);
-        const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), off, 64);
-        v += ((unsigned long long)hi << 32) | lo;
-    }
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
 }
 
 // 1-bit +-1 code (Section 3.3): sum of |W| for the scale d = mean |W|
-__global__ __launch_bounds__(256) void k_abs_sum(const float *__restrict__ W, size_t n, unsigned long long *scratch)
+__global__ __launch_bounds__(256) void k_abs_sum(const float *__restrict__ W, size_t n, Scratch s)
 {
-    const float M = __uint_as_float((uint32_t)scratch[kSlotAbsMax]);
+    __shared__ unsigned long long part[4];
+    const float M = all_stats(s.stats, gridDim.x).absmax;
     const int e = M > 0.0f ? ilogbf(M) : 0;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    unsigned long long s = 0;
-    for (; i < n; i += stride) {
-        const float w = W[i];
-        if (w == w) s += fix30(w, e);
-    }
-    s = wave_sum_u64(s);
-    if ((threadIdx.x & 63) == 0 && s) atomicAdd(&scratch[kSlotAbsSum], s);
+    unsigned long long sum = 0;
+    for_each_weight(W, n, [&](float w) { sum += fix30(w, e); });
+    sum = block_reduce(sum, part, sum_of);
+    if (threadIdx.x == 0) s.abssum[blockIdx.x] = sum;
 }
+
+__global__ void k_clear_clip(unsigned long long *clip) { clip[threadIdx.x] = 0ull; }
 
 // clipping search (Section 3.3): summed |W - d_k q| for the thresholds T_k = max|W| k / 32, k = 1..32
 __global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, size_t n, int bits,
-                                                  unsigned long long *scratch)
+                                                  int blocks, Scratch s)
 {
-    const float M = __uint_as_float((uint32_t)scratch[kSlotAbsMax]);
+    const float M = all_stats(s.stats, blocks).absmax;
     if (M == 0.0f) return;
     const int e = ilogbf(M);
     const int qmax = (1 << (bits - 1)) - 1, qmin = -(1 << (bits - 1));
@@ -146,92 +192,40 @@ __global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, s
     }
 #pragma unroll
     for (int k = 0; k < kClipSteps; ++k) {
-        const unsigned long long s = wave_sum_u64(acc[k]);
-        if ((threadIdx.x & 63) == 0 && s) atomicAdd(&scratch[kSlotClip + k], s);
+        const unsigned long long sum = wave_sum_u64(acc[k]);
+        if ((threadIdx.x & 63) == 0 && sum) atomicAdd(&s.clip[k], sum);
     }
 }
 
-// the step d of the chosen quantizer, left in scales[0] for the packing kernel
-__global__ void k_step(const unsigned long long *scratch, int bits, int quantizer, size_t n, float *scales)
+// the step d of the chosen quantizer, as the layer scales: scales[bits - 1] = d (-d if bits is 1)
+__global__ __launch_bounds__(256) void k_step(Scratch s, int blocks, int bits, int quantizer, size_t n, float *scales)
 {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    const float M = __uint_as_float((uint32_t)scratch[kSlotAbsMax]);
+    __shared__ unsigned long long part[4];
+    const Partial st = all_stats(s.stats, blocks);
+    const float M = st.absmax;
     const int qmax = (1 << (bits - 1)) - 1;
     const float qm = (float)(qmax > 0 ? qmax : 1);
     float d;
     if (quantizer == PB_QUANT_RANGE) {
-        const float hi = from_ordered_key((uint32_t)scratch[kSlotMax]), lo = from_ordered_key((uint32_t)scratch[kSlotMin]);
-        d = (scratch[kSlotMax] != 0 && hi > lo) ? __fdiv_rn(__fsub_rn(hi, lo), (float)(1 << (bits - 1))) : 1.0f;
+        d = st.hi > st.lo ? __fdiv_rn(__fsub_rn(st.hi, st.lo), (float)(1 << (bits - 1))) : 1.0f;
     } else if (quantizer == PB_QUANT_SIGN) {
+        unsigned long long sum = 0;
+        for (int i = threadIdx.x; i < blocks; i += 256) sum += s.abssum[i];
+        sum = block_reduce(sum, part, sum_of);
         const int e = M > 0.0f ? ilogbf(M) : 0;
-        d = (float)(ldexp((double)scratch[kSlotAbsSum], e - 30) / (double)n);
+        d = (float)(ldexp((double)sum, e - 30) / (double)n);
     } else if (quantizer == PB_QUANT_CLIP_SEARCH && M != 0.0f) {
         int best = kClipSteps;
-        unsigned long long best_err = scratch[kSlotClip + kClipSteps - 1];
+        unsigned long long best_err = s.clip[kClipSteps - 1];
         for (int k = kClipSteps - 1; k >= 1; --k)
-            if (scratch[kSlotClip + k - 1] < best_err) { best = k; best_err = scratch[kSlotClip + k - 1]; }
+            if (s.clip[k - 1] < best_err) { best = k; best_err = s.clip[k - 1]; }
         d = __fdiv_rn(__fmul_rn(M, __fmul_rn((float)best, 0.03125f)), qm);
     } else {
         d = (M == 0.0f) ? 1.0f : __fdiv_rn(M, qm);
     }
-    scales[0] = d;
-}
-
-// One wave per (packed row, 64 columns): a lane quantizes one weight (a coalesced 256-byte read), the ballot of
-// bit B-1-i over the wave IS two packed words of bitlayer i; lane i keeps and stores them (8 bytes).
-__global__ __launch_bounds__(256) void k_pack(const float *__restrict__ W, uint32_t layout, int rows, int cols,
-                                              int bits, int cwp, int rows_p, int gate_h, size_t layer_words,
-                                              int quantizer, const float *__restrict__ step,
-                                              uint32_t *__restrict__ packed)
-{
-    const int lane = threadIdx.x & 63;
-    const int groups = cwp / 2;
-    const long long tasks = (long long)rows_p * groups;
-    const long long wave0 = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const long long nwaves = ((long long)gridDim.x * blockDim.x) >> 6;
-    const float d = *step;
-    const int qmax = (1 << (bits - 1)) - 1, qmin = -(1 << (bits - 1));
-    for (long long task = wave0; task < tasks; task += nwaves) {
-        const int pr = (int)(task / groups), g = (int)(task % groups);
-        const int r = gate_h ? gates_matrix_row(pr, gate_h) : pr;   // matrix row (-1 or >= rows: padding)
-        const int c = 64 * g + lane;
-        uint32_t u = 0;
-        if (r >= 0 && r < rows && c < cols) {
-            const float w = W[(size_t)r * (size_t)cols + c];
-            u = (uint32_t)(quantizer == PB_QUANT_SIGN ? ((w >= 0.0f || w != w) ? 1 : -1) : quantize_code(w, d, qmin, qmax));
-        }
-        uint32_t lo = 0, hi = 0;
-        for (int i = 0; i < bits; ++i) {
-            const unsigned long long bal = __ballot((u >> (bits - 1 - i)) & 1u);
-            lo = (lane == i) ? (uint32_t)bal : lo;
-            hi = (lane == i) ? (uint32_t)(bal >> 32) : hi;
-        }
-        int stored = bits;
-        if (is_pairs(layout)) {
-            // lanes 2p, 2p + 1 hold the bitlayers of pair p (zeros beyond the last bitlayer); the even lane ends up
-            // with the digits of the even columns, the odd lane with those of the odd columns, for both words
-            stored = (bits + 1) & ~1;
-            if (lane == 0) { lo = ~lo; hi = ~hi; }      // the sign bitlayer enters as 1 - w
-            const uint32_t plo = (uint32_t)__shfl_xor((int)lo, 1, 64), phi = (uint32_t)__shfl_xor((int)hi, 1, 64);
-            const bool upper = !(lane & 1);              // this lane holds the upper bitlayer of its pair
-            uint32_t e0, o0, e1, o1;
-            digits_of_pair(upper ? lo : plo, upper ? plo : lo, &e0, &o0);   // columns 0-31 of the group
-            digits_of_pair(upper ? hi : phi, upper ? phi : hi, &e1, &o1);   // columns 32-63
-            lo = upper ? e0 : o0;
-            hi = upper ? e1 : o1;
-        }
-        if (lane < stored)
-            *reinterpret_cast<uint2 *>(packed + word_index(layout, cwp, layer_words, lane, pr, 2 * g)) = make_uint2(lo, hi);
-    }
-}
-
-// reads the step from scales[0] (where k_step left it) and writes the layer scales
-__global__ void k_scales(float *scales, int bits)
-{
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    const float d = scales[0];
-    for (int i = 0; i < bits; ++i) {
-        float v = d * ldexpf(1.0f, bits - 1 - i);
+    const int i = threadIdx.x;
+    if (i < bits) {
+        const float v = d * ldexpf(1.0f, bits - 1 - i);
         scales[i] = (i == 0) ? -v : v;
     }
 }
@@ -247,6 +241,132 @@ __device__ __forceinline__ size_t tile_piece(uint32_t layout, int cwp, int rt, i
     if (layout == PB_LAYOUT_ROWMAJOR_V1)
         return (size_t)(rt * kTileRows + (lane & 15)) * (size_t)cwp + (size_t)(q * kChunkWords + 4 * (lane >> 4));
     return ((size_t)rt * (size_t)(cwp / kChunkWords) + (size_t)q) * 256 + (size_t)lane * 4;
+}
+
+// The 8 x 8 bit transpose in each of the four bytes of x[0 .. 7]: afterwards bit r of byte k of x[b] is what bit b of
+// byte k of x[r] was.
+template <int S>
+__device__ __forceinline__ void transpose_step(uint32_t (&x)[8])
+{
+    constexpr uint32_t m = S == 4 ? 0x0F0F0F0Fu : S == 2 ? 0x33333333u : 0x55555555u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = (i & (S - 1)) | ((i & ~(S - 1)) << 1);
+        const uint32_t a = x[r], b = x[r + S];
+        x[r] = (a & m) | ((b << S) & ~m);
+        x[r + S] = ((a >> S) & m) | (b & ~m);
+    }
+}
+__device__ __forceinline__ void transpose_bytes(uint32_t (&x)[8])
+{
+    transpose_step<4>(x);
+    transpose_step<2>(x);
+    transpose_step<1>(x);
+}
+
+// Quantize, split into bitlayers, pack.  Bound: the read of W.  A workgroup takes one tile of 16 packed rows x 512
+// columns: a lane quantizes four columns of a row at a time (16-byte loads, eight in flight) and leaves the codes in LDS
+// byte by byte, where column 8 k + r of a word is byte k of dword r; a thread then owns one word position of the tile:
+// it reads the 32 codes of its word and transposes them as bits, which delivers the words of eight bitlayers with 1.5
+// operations per weight (a ballot per bitlayer and 64 weights, with a select to keep it, took 0.6 operations per weight
+// and BITLAYER and stored 8 bytes at a time).  The stores of a bitlayer are contiguous over the threads.
+// PL: bytes of a stored code.  4096 x 4096, 8 bits: 15.8 us = 5.1 TB/s (55.6 us with the ballots and a division per weight).
+template <int PL>
+__global__ __launch_bounds__(256) void k_pack(const float *__restrict__ W, uint32_t layout, int rows, int cols, int bits,
+                                              int cwp, int rows_p, int gate_h, size_t layer_words, int quantizer,
+                                              const float *__restrict__ scales, uint32_t *__restrict__ packed)
+{
+    constexpr int kRowBytes = 512 + 16;   // (16 more, so that the rows of a word column start in different banks)
+    __shared__ __align__(16) uint8_t codes[PL][kTileRows][kRowBytes];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int chunks = cwp / kChunkWords;
+    const int rt = (int)(blockIdx.x / (unsigned)chunks), ch = (int)(blockIdx.x % (unsigned)chunks);
+    u32x4 w4[4][2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int pr = rt * kTileRows + wave * 4 + k;
+        const int r = gate_h ? gates_matrix_row(pr, gate_h) : pr;   // matrix row (-1 or >= rows: padding)
+        const bool ok = r >= 0 && r < rows;
+        // (loads beyond the end of a row, and of absent rows, return 0)
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(W + (ok ? (size_t)r * (size_t)cols : 0)), 0, ok ? cols * 4 : 0, 0x00020000);
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+            w4[k][half] = __builtin_amdgcn_raw_buffer_load_b128(rs, (ch * 512 + half * 256 + lane * 4) * 4, 0, 0);
+    }
+    const Quantizer Q(fabsf(scales[bits - 1]), bits);
+    const int stored = is_pairs(layout) ? (bits + 1) & ~1 : bits;   // (an odd number of bitlayers is paired with zeros)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int j = wave * 4 + k;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            int u[4];
+            if (quantizer == PB_QUANT_SIGN) {
+                const int pr = rt * kTileRows + j;
+                const int r = gate_h ? gates_matrix_row(pr, gate_h) : pr;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float w = __uint_as_float(w4[k][half][e]);
+                    const bool in = r >= 0 && r < rows && ch * 512 + half * 256 + lane * 4 + e < cols;
+                    u[e] = !in ? 0 : (w >= 0.0f || w != w) ? 1 : -1;
+                }
+            } else {
+                float off = 0.0f, r[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[e] = Q.rounded(__uint_as_float(w4[k][half][e]), off);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) u[e] = Q.code(r[e]);
+                if (Q.must_divide(off)) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) u[e] = quantize_code(__uint_as_float(w4[k][half][e]), Q.d, Q.qmin, Q.qmax);
+                }
+            }
+            // columns 4 i .. 4 i + 3 of word w: byte i / 2 of the dwords 4 (i % 2) .. + 3
+            const int w = half * 8 + (lane >> 3), i = lane & 7;
+            const int at = w * 32 + 16 * (i & 1) + (i >> 1);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t c = (uint32_t)u[e] << (stored - bits);
+                codes[0][j][at + 4 * e] = (uint8_t)c;
+                if constexpr (PL == 2) codes[1][j][at + 4 * e] = (uint8_t)(c >> 8);
+            }
+        }
+    }
+    __syncthreads();
+    // thread -> word position: in the order of the block for the tiled layouts, row by row for the row-major one
+    const bool rowmajor = layout == PB_LAYOUT_ROWMAJOR_V1;
+    const int j = rowmajor ? threadIdx.x >> 4 : (threadIdx.x >> 2) & 15;
+    const int w = rowmajor ? threadIdx.x & 15 : 4 * (threadIdx.x >> 6) + (threadIdx.x & 3);
+    if (rt * kTileRows + j >= rows_p) return;
+    uint32_t *dst = packed + (rowmajor ? (size_t)(rt * kTileRows + j) * (size_t)cwp + (size_t)(ch * kChunkWords + w)
+                                       : (size_t)blockIdx.x * 256 + threadIdx.x);
+#pragma unroll
+    for (int p = PL - 1; p >= 0; --p) {
+        uint32_t x[8];
+        const u32x4 *src = reinterpret_cast<const u32x4 *>(&codes[p][j][w * 32]);
+        const u32x4 a = src[0], b = src[1];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { x[r] = a[r]; x[4 + r] = b[r]; }
+        transpose_bytes(x);
+        if (is_pairs(layout)) {
+#pragma unroll
+            for (int b2 = 6; b2 >= 0; b2 -= 2) {   // bits 8 p + b2 + 1 (upper bitlayer of the pair) and 8 p + b2
+                const int layer = stored - 2 - 8 * p - b2;
+                if (layer < 0) continue;
+                uint32_t even, odd;
+                digits_of_pair(layer == 0 ? ~x[b2 + 1] : x[b2 + 1], x[b2], &even, &odd);   // (the sign bitlayer enters as 1 - w)
+                dst[(size_t)layer * layer_words] = even;
+                dst[(size_t)(layer + 1) * layer_words] = odd;
+            }
+        } else {
+#pragma unroll
+            for (int b1 = 7; b1 >= 0; --b1) {
+                const int layer = bits - 1 - 8 * p - b1;
+                if (layer >= 0) dst[(size_t)layer * layer_words] = x[b1];
+            }
+        }
+    }
 }
 
 // Packed words -> int32 codes.  Bound: the 4-byte stores (a code of B bits takes 4 bytes out and B / 8 in).  A workgroup
@@ -331,22 +451,21 @@ int launch_quantize_pack(const float *W, const Layout &L, int quantizer, uint32_
                          hipStream_t st)
 {
     const size_t n = (size_t)L.rows * (size_t)L.cols;
-    unsigned long long *scratch = reinterpret_cast<unsigned long long *>(packed);
-    hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(kScratchWords), 0, st, scratch, (int)kScratchWords, 0ull);
-    int blocks = (int)((n + 256 * 16 - 1) / (256 * 16));
-    if (blocks > 4096) blocks = 4096;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_stats, dim3(blocks < 1024 ? blocks : 1024), dim3(256), 0, st, W, n, scratch);
-    if (quantizer == PB_QUANT_SIGN) hipLaunchKernelGGL(k_abs_sum, dim3(blocks), dim3(256), 0, st, W, n, scratch);
-    if (quantizer == PB_QUANT_CLIP_SEARCH)
-        hipLaunchKernelGGL(k_clip_err, dim3(blocks), dim3(256), 0, st, W, n, L.bits, scratch);
-    hipLaunchKernelGGL(k_step, dim3(1), dim3(64), 0, st, scratch, L.bits, quantizer, n, scales);
-    const long long tasks = (long long)L.rows_p * (L.cwp / 2);
-    long long pblocks = (tasks + 3) / 4;            // four waves per block, one task per wave and pass
-    if (pblocks > 16384) pblocks = 16384;
-    hipLaunchKernelGGL(k_pack, dim3((unsigned)pblocks), dim3(256), 0, st, W, L.layout, L.rows, L.cols, L.bits, L.cwp,
-                       L.rows_p, L.gate_h, L.layer_words, quantizer, scales, packed);
-    hipLaunchKernelGGL(k_scales, dim3(1), dim3(64), 0, st, scales, L.bits);
+    const size_t want = (n + kStatsFloats - 1) / kStatsFloats;
+    const int blocks = (int)(want < (size_t)kMaxStatsBlocks ? want : (size_t)kMaxStatsBlocks);
+    const Scratch s = scratch_of(packed, blocks);
+    hipLaunchKernelGGL(k_stats, dim3(blocks), dim3(256), 0, st, W, n, s.stats);
+    if (quantizer == PB_QUANT_SIGN) hipLaunchKernelGGL(k_abs_sum, dim3(blocks), dim3(256), 0, st, W, n, s);
+    if (quantizer == PB_QUANT_CLIP_SEARCH) {
+        hipLaunchKernelGGL(k_clear_clip, dim3(1), dim3(kClipSteps), 0, st, s.clip);
+        int cblocks = (int)((n + 256 * 16 - 1) / (256 * 16));
+        if (cblocks > 4096) cblocks = 4096;
+        hipLaunchKernelGGL(k_clip_err, dim3(cblocks), dim3(256), 0, st, W, n, L.bits, blocks, s);
+    }
+    hipLaunchKernelGGL(k_step, dim3(1), dim3(256), 0, st, s, blocks, L.bits, quantizer, n, scales);
+    const unsigned tiles = (unsigned)((L.rows_p + kTileRows - 1) / kTileRows) * (unsigned)(L.cwp / kChunkWords);
+    hipLaunchKernelGGL(L.stored_bits > 8 ? k_pack<2> : k_pack<1>, dim3(tiles), dim3(256), 0, st, W, L.layout, L.rows,
+                       L.cols, L.bits, L.cwp, L.rows_p, L.gate_h, L.layer_words, quantizer, scales, packed);
     return (int)hipGetLastError();
 }
 
