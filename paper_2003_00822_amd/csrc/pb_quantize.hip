@@ -12,91 +12,130 @@ namespace pb {
 // The quantizers reduce over all weights before anything can be packed.  What those passes leave for the next launch
 // lives at the start of `packed`, which the packing kernel overwrites last (a packed matrix has at least 512 bytes, and at
 // least 1 KB per statistics block from two blocks on): 32 sums of the clipping search, then per block the partial
-// statistics and the partial sum of the +-1 code.  Every block writes its own slot, so nothing has to be cleared first.
+// statistics and the partial sum of the +-1 code, then, if there is room, the histogram of the clipping search.
 constexpr int kClipSteps = 32;
+constexpr int kClipBins = 4096;
 constexpr int kStatsFloats = 8192;      // weights that a block of the reductions takes at a time (32 per thread)
 constexpr int kMaxStatsBlocks = 2048;   // eight workgroups per compute unit
 struct Partial {
     float absmax, hi, lo, unused;
 };
 struct Scratch {
-    unsigned long long *clip;      // [kClipSteps]
+    unsigned long long *clip;      // [kClipSteps] sums of the errors
     Partial *stats;                // [blocks]
     unsigned long long *abssum;    // [blocks]
+    double *lower, *upper;         // [kClipSteps] bounds of those sums; null: no room (or no need) for the histogram
+    unsigned long long *bins;      // [kClipBins] number of weights (upper 28 bits), sum of their distances from the bin's lower edge
+    int blocks;
 };
-__host__ __device__ __forceinline__ Scratch scratch_of(void *packed, int blocks)
+static Scratch scratch_of(void *packed, size_t bytes, size_t n, int blocks)
 {
     Scratch s;
+    s.blocks = blocks;
     s.clip = static_cast<unsigned long long *>(packed);
     s.stats = reinterpret_cast<Partial *>(s.clip + kClipSteps);
     s.abssum = reinterpret_cast<unsigned long long *>(s.stats + blocks);
+    s.lower = reinterpret_cast<double *>(s.abssum + blocks);
+    s.upper = s.lower + kClipSteps;
+    s.bins = reinterpret_cast<unsigned long long *>(s.upper + kClipSteps);
+    // (up to 2^17 weights the exact sums of all thresholds take less time than two more launches; beyond 2^27 the fields
+    // of a workgroup's bins would overflow)
+    const size_t end = (size_t)(reinterpret_cast<char *>(s.bins + kClipBins) - static_cast<char *>(packed));
+    if (end > bytes || n <= (1u << 17) || n > (1u << 27)) s.lower = s.upper = nullptr;
     return s;
 }
 
-// `f` on the weights of this block: 32 per thread, eight 16-byte loads in flight
-template <typename F>
-__device__ __forceinline__ void for_each_weight(const float *__restrict__ W, size_t n, F f)
+// 32 weights per thread, all in flight together; weights past the end read as `pad`
+__device__ __forceinline__ void load_weights(const float *__restrict__ W, size_t n, size_t base, float pad, float (&w)[32])
 {
-    const float4 *W4 = reinterpret_cast<const float4 *>(W);   // W is 16-byte aligned (checked on the host)
-    for (size_t base = (size_t)blockIdx.x * kStatsFloats; base < n; base += (size_t)gridDim.x * kStatsFloats) {
-        if (base + kStatsFloats <= n) {
-            float4 v[8];
+    if (base + kStatsFloats <= n) {
+        const float4 *W4 = reinterpret_cast<const float4 *>(W);   // W is 16-byte aligned (checked on the host)
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = W4[base / 4 + k * 256 + threadIdx.x];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) { f(v[k].x); f(v[k].y); f(v[k].z); f(v[k].w); }
-        } else {
-            for (size_t i = base + threadIdx.x; i < n; i += 256) f(W[i]);
+        for (int k = 0; k < 8; ++k) {
+            const float4 v = W4[base / 4 + k * 256 + threadIdx.x];
+            w[4 * k] = v.x; w[4 * k + 1] = v.y; w[4 * k + 2] = v.z; w[4 * k + 3] = v.w;
         }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 32; ++k) {
+            const size_t i = base + k * 256 + threadIdx.x;
+            w[k] = W[i < n ? i : 0];
+        }
+#pragma unroll
+        for (int k = 0; k < 32; ++k)
+            if (base + k * 256 + threadIdx.x >= n) w[k] = pad;
     }
 }
 
-// the same reduction over a workgroup of 256 threads, result in every thread
-template <typename T, typename F>
+// `f` on the weights of this block (NaN: as if absent)
+template <typename F>
+__device__ __forceinline__ void for_each_weight(const float *__restrict__ W, size_t n, F f)
+{
+    for (size_t base = (size_t)blockIdx.x * kStatsFloats; base < n; base += (size_t)gridDim.x * kStatsFloats) {
+        float w[32];
+        load_weights(W, n, base, NAN, w);
+#pragma unroll
+        for (int k = 0; k < 32; ++k) f(w[k]);
+    }
+}
+
+// a reduction over a workgroup of WAVES waves, result in every thread
+template <int WAVES, typename T, typename F>
 __device__ __forceinline__ T block_reduce(T v, T *part, F combine)
 {
     for (int off = 32; off > 0; off >>= 1) v = combine(v, __shfl_xor(v, off, 64));
     __syncthreads();   // (`part` may still be read from the reduction before)
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
     __syncthreads();
-    return combine(combine(part[0], part[1]), combine(part[2], part[3]));
+    v = part[threadIdx.x & (WAVES - 1)];
+    for (int off = WAVES / 2; off > 0; off >>= 1) v = combine(v, __shfl_xor(v, off, 64));
+    return v;
 }
 __device__ __forceinline__ float max_of(float a, float b) { return fmaxf(a, b); }
 __device__ __forceinline__ float min_of(float a, float b) { return fminf(a, b); }
-__device__ __forceinline__ unsigned long long sum_of(unsigned long long a, unsigned long long b) { return a + b; }
+template <typename T>
+__device__ __forceinline__ T sum_of(T a, T b) { return a + b; }
 
 // max |W|, max W and min W in one pass (Section 3.3: the step of every quantizer comes from these; fmaxf and fminf
 // drop NaN).  Bound: the read of W; 4096 x 4096: 11.8 us = 5.7 TB/s (43.7 us
 // with one load in flight per thread).
-__global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size_t n, Partial *stats)
+// The blocks also clear the sums and the histogram of the clipping search, where they are used.
+__global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size_t n, int clip_search, Scratch s)
 {
     __shared__ float part[4];
+    if (clip_search) {
+        const int i0 = (int)(blockIdx.x * 256 + threadIdx.x), step = (int)(gridDim.x * 256);
+        for (int i = i0; i < kClipSteps; i += step) s.clip[i] = 0ull;
+        if (s.lower)
+            for (int i = i0; i < kClipBins; i += step) s.bins[i] = 0ull;
+    }
     float am = 0.0f, hi = -INFINITY, lo = INFINITY;
     for_each_weight(W, n, [&](float w) {
         am = fmaxf(am, fabsf(w));
         hi = fmaxf(hi, w);
         lo = fminf(lo, w);
     });
-    am = block_reduce(am, part, max_of);
-    hi = block_reduce(hi, part, max_of);
-    lo = block_reduce(lo, part, min_of);
-    if (threadIdx.x == 0) stats[blockIdx.x] = Partial{am, hi, lo, 0.0f};
+    am = block_reduce<4>(am, part, max_of);
+    hi = block_reduce<4>(hi, part, max_of);
+    lo = block_reduce<4>(lo, part, min_of);
+    if (threadIdx.x == 0) s.stats[blockIdx.x] = Partial{am, hi, lo, 0.0f};
 }
 
-// the statistics of all blocks, in every thread of a workgroup of 256
-__device__ __forceinline__ Partial all_stats(const Partial *stats, int blocks)
+// the statistics of all blocks, in every thread of a workgroup
+template <int WAVES>
+__device__ __forceinline__ Partial all_stats(const Scratch &s)
 {
-    __shared__ float part[4];
+    __shared__ float part[WAVES];
     float am = 0.0f, hi = -INFINITY, lo = INFINITY;
-    for (int i = threadIdx.x; i < blocks; i += 256) {
-        const Partial p = stats[i];
+    for (int i = threadIdx.x; i < s.blocks; i += WAVES * 64) {
+        const Partial p = s.stats[i];
         am = fmaxf(am, p.absmax);
         hi = fmaxf(hi, p.hi);
         lo = fminf(lo, p.lo);
     }
-    am = block_reduce(am, part, max_of);
-    hi = block_reduce(hi, part, max_of);
-    lo = block_reduce(lo, part, min_of);
+    am = block_reduce<WAVES>(am, part, max_of);
+    hi = block_reduce<WAVES>(hi, part, max_of);
+    lo = block_reduce<WAVES>(lo, part, min_of);
     return Partial{am, hi, lo, 0.0f};
 }
 
@@ -156,52 +195,171 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 __global__ __launch_bounds__(256) void k_abs_sum(const float *__restrict__ W, size_t n, Scratch s)
 {
     __shared__ unsigned long long part[4];
-    const float M = all_stats(s.stats, gridDim.x).absmax;
+    const float M = all_stats<4>(s).absmax;
     const int e = M > 0.0f ? ilogbf(M) : 0;
     unsigned long long sum = 0;
     for_each_weight(W, n, [&](float w) { sum += fix30(w, e); });
-    sum = block_reduce(sum, part, sum_of);
+    sum = block_reduce<4>(sum, part, sum_of<unsigned long long>);
     if (threadIdx.x == 0) s.abssum[blockIdx.x] = sum;
 }
 
-__global__ void k_clear_clip(unsigned long long *clip) { clip[threadIdx.x] = 0ull; }
+// ---- Clipping search (Section 3.3): the threshold T_k = max|W| k / 32, k = 1 .. 32, with the smallest summed
+// |W - d_k q|.  The sums are exact integers (fix30), 32 of them over all weights: 2.3 ms at 3001 x 5003.  Most thresholds
+// can be ruled out from a histogram, rigorously: inside a bin where q does not change and W - d_k q keeps its sign, the sum
+// of the errors follows from the number of weights and their sum; in any other bin |W - d_k q| changes by no more than W
+// does.  That bounds every sum from both sides (k_clip_hist, k_clip_bounds), and only the thresholds whose lower bound
+// does not exceed the smallest upper bound are summed exactly (k_clip_err): one to three of the 32 with 2 to 8 bits,
+// all of them with so many bits that a bin holds many steps (then 0.16 ms).  3001 x 5003, 4 bits, whole call: 2405 ->
+// 61 us, of which the histogram takes 19 (LDS atomics), statistics and packing 30.
 
-// clipping search (Section 3.3): summed |W - d_k q| for the thresholds T_k = max|W| k / 32, k = 1..32
-__global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, size_t n, int bits,
-                                                  int blocks, Scratch s)
+// the step of threshold k + 1
+__device__ __forceinline__ float clip_step(float M, int k, int bits)
 {
-    const float M = all_stats(s.stats, blocks).absmax;
-    if (M == 0.0f) return;
+    const int qmax = (1 << (bits - 1)) - 1;
+    return __fdiv_rn(__fmul_rn(M, __fmul_rn((float)(k + 1), 0.03125f)), (float)(qmax > 0 ? qmax : 1));
+}
+__device__ __forceinline__ bool finite_nonzero(float M) { return M != 0.0f && M < INFINITY; }
+
+// Weights in units of 2^(e - 30) (2^e <= max|W| < 2^(e + 1)) are integers of 32 bits, the upper 12 of which are the bin.
+// One LDS atomic per weight: 24 bits of count over 40 bits of summed distances; at the end one global atomic per bin and
+// workgroup (28 and 36 bits, the distances in multiples of 2^12).
+__global__ __launch_bounds__(1024) void k_clip_hist(const float *__restrict__ W, size_t n, Scratch s)
+{
+    __shared__ unsigned long long bins[kClipBins];
+    const float M = all_stats<16>(s).absmax;
+    if (!finite_nonzero(M)) return;
     const int e = ilogbf(M);
-    const int qmax = (1 << (bits - 1)) - 1, qmin = -(1 << (bits - 1));
-    const float qm = (float)(qmax > 0 ? qmax : 1);
-    unsigned long long acc[kClipSteps];
+    for (int i = threadIdx.x; i < kClipBins; i += 1024) bins[i] = 0ull;
+    __syncthreads();
+    auto take = [&](float w) {
+        const int u = w != w ? 0 : (int)ldexpf(w, 30 - e);
+        atomicAdd(&bins[(u >> 20) + kClipBins / 2], (1ull << 40) | (unsigned long long)(u & 0xFFFFF));
+    };
+    const size_t n4 = n / 4;
+    const float4 *W4 = reinterpret_cast<const float4 *>(W);
+    for (size_t base = (size_t)blockIdx.x * 4096; base < n4; base += (size_t)gridDim.x * 4096) {
+        float4 v[4];
 #pragma unroll
-    for (int k = 0; k < kClipSteps; ++k) acc[k] = 0;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) {
-        const float w = W[i];
-        if (w != w) continue;
-#pragma unroll
-        for (int k = 0; k < kClipSteps; ++k) {
-            const float d = __fdiv_rn(__fmul_rn(M, __fmul_rn((float)(k + 1), 0.03125f)), qm);
-            const float p = __fmul_rn(d, (float)quantize_code(w, d, qmin, qmax));
-            acc[k] += fix30(__fsub_rn(w, p), e);
+        for (int k = 0; k < 4; ++k) {
+            const size_t i = base + k * 1024 + threadIdx.x;
+            v[k] = W4[i < n4 ? i : 0];
         }
-    }
 #pragma unroll
-    for (int k = 0; k < kClipSteps; ++k) {
-        const unsigned long long sum = wave_sum_u64(acc[k]);
-        if ((threadIdx.x & 63) == 0 && sum) atomicAdd(&s.clip[k], sum);
+        for (int k = 0; k < 4; ++k)
+            if (base + k * 1024 + threadIdx.x < n4) { take(v[k].x); take(v[k].y); take(v[k].z); take(v[k].w); }
+    }
+    if (blockIdx.x == 0 && threadIdx.x < (n & 3)) take(W[n4 * 4 + threadIdx.x]);
+    __syncthreads();
+    for (int i = threadIdx.x; i < kClipBins; i += 1024) {
+        const unsigned long long b = bins[i];
+        if (b) atomicAdd(&s.bins[i], (b >> 40 << 36) | (b & ((1ull << 40) - 1)) >> 12);
     }
 }
 
+// One workgroup per threshold: bounds of its sum, in the units of fix30.  The slack per weight covers the conversion of
+// the weight and of its error to integers (1 each), the roundings of d q and W - d q (below 400) and, in bins with a
+// change of q, a quotient that rounds the other way (below 1024); per bin, 2^12 for each of at most 256 workgroups whose
+// sum of distances was cut to multiples of 2^12.
+__global__ __launch_bounds__(1024) void k_clip_bounds(int bits, Scratch s)
+{
+    __shared__ double part[16];
+    const float M = all_stats<16>(s).absmax;
+    const int k = blockIdx.x;
+    double lo = 0.0, hi = 0.0;
+    if (finite_nonzero(M)) {
+        const double d = ldexp((double)clip_step(M, k, bits), 30 - ilogbf(M));
+        const double qmax = (double)((1 << (bits - 1)) - 1), qmin = -(double)(1 << (bits - 1));
+        const double inv = 1.0 / d;   // (an error of 2^-52 in the quotient: far inside the slack)
+        auto q_of = [&](double u) { return fmin(fmax(rint(u * inv), qmin), qmax); };
+        for (int i = threadIdx.x; i < kClipBins; i += 1024) {
+            const unsigned long long bin = s.bins[i];
+            if (bin == 0) continue;
+            const double n = (double)(bin >> 36), dist = (double)(bin & ((1ull << 36) - 1)) * 4096.0;
+            const double u0 = (double)(i - kClipBins / 2) * 0x1p20, u1 = u0 + 0x1p20;
+            const double qa = q_of(u0 - 2048.0), qb = q_of(u1 + 2048.0);
+            const double ra = u0 - 2048.0 - d * qa, rb = u1 + 2048.0 - d * qb;
+            if (qa == qb && (ra >= 0.0) == (rb >= 0.0)) {
+                const double sum = fabs(n * (u0 - d * qa) + dist), slack = n * 1024.0 + 0x1p20;
+                lo += fmax(sum - slack, 0.0);
+                hi += sum + slack;
+            } else {
+                const double mid = u0 + 0x1p19, g = fabs(mid - d * q_of(mid));
+                lo += n * fmax(g - (0x1p19 + 2048.0), 0.0);
+                hi += n * (g + (0x1p19 + 2048.0));
+            }
+        }
+    }
+    lo = block_reduce<16>(lo, part, sum_of<double>);
+    hi = block_reduce<16>(hi, part, sum_of<double>);
+    if (threadIdx.x == 0) {
+        s.lower[k] = lo * (1.0 - 1e-9);   // (the sums above are rounded)
+        s.upper[k] = hi * (1.0 + 1e-9);
+    }
+}
+
+// the thresholds that may be the best one, as a mask
+__device__ __forceinline__ uint32_t clip_candidates(const Scratch &s)
+{
+    if (!s.lower) return 0xFFFFFFFFu;
+    const int k = threadIdx.x & 31;
+    const double lo = s.lower[k];
+    double best = s.upper[k];
+    for (int off = 16; off > 0; off >>= 1) best = fmin(best, __shfl_xor(best, off, 64));
+    return (uint32_t)__ballot(lo <= best);
+}
+
+// The exact sums of the candidates, unless there is only one.  Bound: the vector ALU, 11 operations per weight and
+// candidate; a thread keeps its 32 weights in registers over all candidates.
+__global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, size_t n, int bits, Scratch s)
+{
+    __shared__ unsigned long long sums[kClipSteps];
+    const uint32_t candidates = clip_candidates(s);
+    if (__popc(candidates) == 1) return;
+    const float M = all_stats<4>(s).absmax;
+    if (!finite_nonzero(M)) return;
+    const int e = ilogbf(M);
+    if (threadIdx.x < kClipSteps) sums[threadIdx.x] = 0ull;
+    __syncthreads();
+    for (size_t base = (size_t)blockIdx.x * kStatsFloats; base < n; base += (size_t)gridDim.x * kStatsFloats) {
+        float w[32];
+        load_weights(W, n, base, 0.0f, w);   // (a weight 0 has the code 0 and no error)
+        for (uint32_t left = candidates; left; left &= left - 1) {
+            const int c = __builtin_ctz(left);
+            const Quantizer Q(clip_step(M, c, bits), bits);
+            const float qmax = (float)Q.qmax, qmin = (float)Q.qmin;
+            float off = 0.0f;
+            unsigned long long sum = 0;
+#pragma unroll
+            for (int k = 0; k < 32; ++k) {
+                const float t = w[k] * Q.inv, r = rintf(t);
+                off = fmaxf(off, fabsf(t - r));
+                const float p = __fmul_rn(Q.d, fminf(fmaxf(r, qmin), qmax));
+                const float err = ldexpf(fabsf(__fsub_rn(w[k], p)), 30 - e);
+                uint32_t v;   // (toward zero, NaN -> 0)
+                asm("v_cvt_u32_f32 %0, %1" : "=v"(v) : "v"(err));
+                sum += v;
+            }
+            if (Q.must_divide(off)) {
+                sum = 0;
+#pragma unroll
+                for (int k = 0; k < 32; ++k) {
+                    const float p = __fmul_rn(Q.d, (float)quantize_code(w[k], Q.d, Q.qmin, Q.qmax));
+                    sum += fix30(__fsub_rn(w[k], p), e);
+                }
+            }
+            sum = wave_sum_u64(sum);
+            if ((threadIdx.x & 63) == 0) atomicAdd(&sums[c], sum);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kClipSteps && sums[threadIdx.x]) atomicAdd(&s.clip[threadIdx.x], sums[threadIdx.x]);
+}
+
 // the step d of the chosen quantizer, as the layer scales: scales[bits - 1] = d (-d if bits is 1)
-__global__ __launch_bounds__(256) void k_step(Scratch s, int blocks, int bits, int quantizer, size_t n, float *scales)
+__global__ __launch_bounds__(256) void k_step(Scratch s, int bits, int quantizer, size_t n, float *scales)
 {
     __shared__ unsigned long long part[4];
-    const Partial st = all_stats(s.stats, blocks);
+    const Partial st = all_stats<4>(s);
     const float M = st.absmax;
     const int qmax = (1 << (bits - 1)) - 1;
     const float qm = (float)(qmax > 0 ? qmax : 1);
@@ -210,16 +368,18 @@ __global__ __launch_bounds__(256) void k_step(Scratch s, int blocks, int bits, i
         d = st.hi > st.lo ? __fdiv_rn(__fsub_rn(st.hi, st.lo), (float)(1 << (bits - 1))) : 1.0f;
     } else if (quantizer == PB_QUANT_SIGN) {
         unsigned long long sum = 0;
-        for (int i = threadIdx.x; i < blocks; i += 256) sum += s.abssum[i];
-        sum = block_reduce(sum, part, sum_of);
+        for (int i = threadIdx.x; i < s.blocks; i += 256) sum += s.abssum[i];
+        sum = block_reduce<4>(sum, part, sum_of<unsigned long long>);
         const int e = M > 0.0f ? ilogbf(M) : 0;
         d = (float)(ldexp((double)sum, e - 30) / (double)n);
     } else if (quantizer == PB_QUANT_CLIP_SEARCH && M != 0.0f) {
-        int best = kClipSteps;
-        unsigned long long best_err = s.clip[kClipSteps - 1];
-        for (int k = kClipSteps - 1; k >= 1; --k)
-            if (s.clip[k - 1] < best_err) { best = k; best_err = s.clip[k - 1]; }
-        d = __fdiv_rn(__fmul_rn(M, __fmul_rn((float)best, 0.03125f)), qm);
+        // (the larger threshold on a tie)
+        const uint32_t candidates = clip_candidates(s);
+        int best = -1;
+        unsigned long long best_err = 0;
+        for (int k = kClipSteps - 1; k >= 0; --k)
+            if ((candidates >> k & 1) && (best < 0 || s.clip[k] < best_err)) { best = k; best_err = s.clip[k]; }
+        d = clip_step(M, best, bits);
     } else {
         d = (M == 0.0f) ? 1.0f : __fdiv_rn(M, qm);
     }
@@ -453,16 +613,19 @@ int launch_quantize_pack(const float *W, const Layout &L, int quantizer, uint32_
     const size_t n = (size_t)L.rows * (size_t)L.cols;
     const size_t want = (n + kStatsFloats - 1) / kStatsFloats;
     const int blocks = (int)(want < (size_t)kMaxStatsBlocks ? want : (size_t)kMaxStatsBlocks);
-    const Scratch s = scratch_of(packed, blocks);
-    hipLaunchKernelGGL(k_stats, dim3(blocks), dim3(256), 0, st, W, n, s.stats);
+    const Scratch s = scratch_of(packed, packed_bytes(L), n, blocks);
+    const bool search = quantizer == PB_QUANT_CLIP_SEARCH;
+    hipLaunchKernelGGL(k_stats, dim3(blocks), dim3(256), 0, st, W, n, search ? 1 : 0, s);
     if (quantizer == PB_QUANT_SIGN) hipLaunchKernelGGL(k_abs_sum, dim3(blocks), dim3(256), 0, st, W, n, s);
-    if (quantizer == PB_QUANT_CLIP_SEARCH) {
-        hipLaunchKernelGGL(k_clear_clip, dim3(1), dim3(kClipSteps), 0, st, s.clip);
-        int cblocks = (int)((n + 256 * 16 - 1) / (256 * 16));
-        if (cblocks > 4096) cblocks = 4096;
-        hipLaunchKernelGGL(k_clip_err, dim3(cblocks), dim3(256), 0, st, W, n, L.bits, blocks, s);
+    if (search) {
+        if (s.lower) {
+            const size_t hblocks = (n + 16383) / 16384;   // (a workgroup per compute unit: each empties 4096 bins at its end)
+            hipLaunchKernelGGL(k_clip_hist, dim3((unsigned)(hblocks < 256 ? hblocks : 256)), dim3(1024), 0, st, W, n, s);
+            hipLaunchKernelGGL(k_clip_bounds, dim3(kClipSteps), dim3(1024), 0, st, L.bits, s);
+        }
+        hipLaunchKernelGGL(k_clip_err, dim3(blocks), dim3(256), 0, st, W, n, L.bits, s);
     }
-    hipLaunchKernelGGL(k_step, dim3(1), dim3(256), 0, st, s, blocks, L.bits, quantizer, n, scales);
+    hipLaunchKernelGGL(k_step, dim3(1), dim3(256), 0, st, s, L.bits, quantizer, n, scales);
     const unsigned tiles = (unsigned)((L.rows_p + kTileRows - 1) / kTileRows) * (unsigned)(L.cwp / kChunkWords);
     hipLaunchKernelGGL(L.stored_bits > 8 ? k_pack<2> : k_pack<1>, dim3(tiles), dim3(256), 0, st, W, L.layout, L.rows,
                        L.cols, L.bits, L.cwp, L.rows_p, L.gate_h, L.layer_words, quantizer, scales, packed);

@@ -1,0 +1,52 @@
+"""Packing and unpacking at the edges of their tiles (16 rows x 512 columns), and the clipping search around the size from
+which a histogram rules thresholds out, against the oracle's codes and scales."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import pb_oracle as po
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pb():
+    assert torch.cuda.is_available(), "gpu tests need a GPU"
+    from paper_2003_00822_amd import pb as _pb
+    _pb.lib()
+    return _pb
+
+
+def check(pb, W, bits, layout, quantizer=0):
+    prep = po.prepare(W, bits, quantizer)
+    lin = pb.PackedLinear(torch.from_numpy(W).cuda(), bits, layout=layout, quantizer=quantizer)
+    assert (lin.unpack().cpu().numpy() == prep["q"]).all()
+    assert (lin.scales[:bits].cpu().numpy().view(np.int32) == prep["scales"].view(np.int32)).all()
+
+
+@pytest.mark.parametrize("layout", [0x50420001, 0x50420002, 0x50420003, 0x50420004])
+@pytest.mark.parametrize("bits", [1, 5, 8, 9, 16])
+def test_tile_edges(pb, layout, bits):
+    g = np.random.default_rng(bits)
+    for rows, cols in ((4, 1), (16, 512), (20, 513), (12, 511), (36, 1027), (64, 2046)):
+        print("pack", hex(layout), bits, rows, cols, flush=True)
+        W = g.normal(0, 0.05, size=(rows, cols)).astype(np.float32)
+        # quotients at and next to half-integers, where the code follows the rounding of the division
+        qmax = max(1, 2 ** (bits - 1) - 1)
+        W[0, 0] = qmax * 0.125
+        W[1, :] = (g.integers(-qmax, qmax + 1, size=cols) + 0.5) * np.float32(0.125)
+        W[2, :] = np.nextafter(W[1, :], np.float32(0))
+        W = np.clip(W, -qmax * 0.125, qmax * 0.125).astype(np.float32)
+        check(pb, W, bits, layout)
+
+
+@pytest.mark.parametrize("bits", [1, 4, 8, 12])
+def test_clipping_search_with_and_without_histogram(pb, bits):
+    g = np.random.default_rng(bits + 50)
+    for rows, cols, outlier in ((512, 256, 0.9), (363, 363, 0.9), (400, 701, 30.0), (420, 1000, 0.0)):
+        print("clip search", bits, rows, cols, outlier, flush=True)
+        W = g.normal(0, 0.05, size=(rows, cols)).astype(np.float32)
+        if outlier:
+            W[7, 11] = -outlier
+        check(pb, W, bits, 0x50420002, quantizer=3)
