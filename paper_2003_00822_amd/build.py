@@ -4,7 +4,8 @@
 `paper_2003_00822_amd/libpbatch.so` with hipcc (cross-compiles without a GPU):
 one object per source, compiled in parallel, then one link; and the calibration
 loop of the benchmark (`csrc/calib/`, not part of the product) into
-`paper_2003_00822_amd/libpbatch_calib.so`.
+`paper_2003_00822_amd/libpbatch_calib.so`; and the host code of the Python binding (`csrc/binding/`, with the host
+compiler against torch's headers) into `paper_2003_00822_amd/_binding.so`.
 """
 from __future__ import annotations
 
@@ -12,6 +13,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -19,6 +21,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpbatch.so")
 CALIB_LIB = os.path.join(HERE, "libpbatch_calib.so")
+BINDING_LIB = os.path.join(HERE, "_binding.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -73,8 +76,31 @@ def build(verbose: bool = True, extra_flags=(), out: str = LIB, srcs=None) -> st
     return out
 
 
+def build_binding(verbose: bool = True, out: str = BINDING_LIB) -> str:
+    import torch
+    from torch.utils import cpp_extension
+    tmp = out + ".tmp.%d" % os.getpid()
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",     # (what torch's and HIP's own headers ask of a host compiler)
+           "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"]]
+    for path in cpp_extension.include_paths() + ["/opt/rocm/include"]:
+        cmd += ["-isystem", path]
+    cmd += ["-o", tmp, os.path.join(CSRC, "binding", "pb_binding.cpp"), "-L", lib_dir, "-ltorch_python", "-ltorch_cpu",
+            "-lc10_hip", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, out)
+    return out
+
+
 def build_all(verbose: bool = True):
-    return [build(verbose), build(verbose, out=CALIB_LIB, srcs=calib_sources())]
+    with ThreadPoolExecutor(max_workers=1) as pool:
+        binding = pool.submit(build_binding, verbose)
+        libs = [build(verbose), build(verbose, out=CALIB_LIB, srcs=calib_sources())]
+        return libs + [binding.result()]
 
 
 if __name__ == "__main__":

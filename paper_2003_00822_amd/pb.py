@@ -3,6 +3,10 @@
 Every step of the path runs in the HIP kernels of libpbatch.so; torch is used for
 device memory and streams.  There is no CPU fallback: if the library is not built the
 first call raises.
+
+The calls that launch kernels go through `_binding` (csrc/binding/pb_binding.cpp), which checks the usual
+arguments and calls the library natively; the functions below of the same names take what it does not
+(keywords, an explicit stream, wrong arguments) and raise the errors.
 """
 from __future__ import annotations
 
@@ -10,6 +14,12 @@ import ctypes
 import os
 
 import torch
+
+try:
+    from . import _binding
+except ImportError as e:   # not built: every call raises (see _require_binding)
+    _binding = None
+    _binding_error = e
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # PBATCH_LIB points the binding at another build of the same library (e.g. one compiled with other tuning macros)
@@ -96,8 +106,17 @@ def lib():
         L.pb_strerror.restype = ctypes.c_char_p
         L.pb_last_hip_error.argtypes = []
         L.pb_last_hip_error.restype = _I
+        _require_binding().bind(pb_desc, PbError,
+                                {n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in _NATIVE})
         _lib = L
     return _lib
+
+
+def _require_binding():
+    if _binding is None:
+        raise RuntimeError("the native binding is not built: run `python -m paper_2003_00822_amd.build` (%s)"
+                           % _binding_error)
+    return _binding
 
 
 def strerror(status: int) -> str:
@@ -265,6 +284,9 @@ class PackedLinear:
         pb_quantize_pack_mode(W, self.desc, quantizer, self.packed, self.scales)
 
     def __call__(self, X: torch.Tensor, bits_used: int | None = None, out: torch.Tensor | None = None):
+        return _linear(self, X, bits_used, out)
+
+    def _call_checked(self, X, bits_used, out):
         X = X.reshape(-1, self.cols)
         batch = X.shape[0]
         assert batch <= self.max_batch
@@ -293,3 +315,14 @@ class PackedLinear:
         q = torch.empty((self.rows, self.cols), dtype=torch.int32, device=self.packed.device)
         pb_unpack(self.packed, self.desc, q)
         return q
+
+
+# The functions above stay behind the native ones (same arguments and results); `_linear` is PackedLinear's call.
+_NATIVE = ["pb_quantize_pack", "pb_quantize_pack_desc", "pb_quantize_pack_mode", "pb_unpack", "pb_matmul",
+           "pb_matmul_static", "pb_matmul_bias_act", "pb_matmul_acc", "pb_matmul_acc_pairs", "pb_act_prep",
+           "pb_matmul_prepared", "pb_fixed_point", "pb_lstm_cell"]
+_linear = PackedLinear._call_checked
+if _binding is not None:
+    _binding.set_slow({**{n: globals()[n] for n in _NATIVE}, "linear": _linear})
+    globals().update({n: getattr(_binding, n) for n in _NATIVE})
+    _linear = _binding.linear

@@ -1,0 +1,66 @@
+"""The native calling side of pb.py against its Python functions: unusual and wrong arguments."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def pb():
+    from paper_2003_00822_amd import pb as _pb
+    _pb.lib()
+    return _pb
+
+
+def test_arguments_that_are_no_gpu_tensors(pb):
+    d = pb.pb_desc_init(8, 64, 3)
+    t = torch.zeros(64)
+    with pytest.raises(TypeError, match="packed must be a CUDA/HIP tensor"):
+        pb.pb_unpack(t, d, t)
+    with pytest.raises(TypeError, match="X must be a CUDA/HIP tensor"):
+        pb.pb_act_prep(d, [1.0], 1, t, stream=0)
+    with pytest.raises(TypeError):
+        pb.pb_unpack(t, d)                       # an argument missing
+    with pytest.raises(TypeError):
+        pb.pb_unpack(t, d, t, None, 5)           # one too many
+
+
+@pytest.mark.gpu
+def test_native_and_python_calls_agree(pb):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    W = torch.randn((50, 300), device="cuda", generator=g)
+    X = torch.randn((6, 300), device="cuda", generator=g)
+    lin = pb.PackedLinear(W, 5, max_batch=6)
+    Y = lin(X)
+    want = torch.empty_like(Y)
+    # keywords and an explicit stream take the Python function
+    pb.pb_matmul(packed=lin.packed, scales=lin.scales, d=lin.desc, bits_used=5, X=X, batch=6, Y=want, workspace=lin.workspace,
+                 stream=torch.cuda.current_stream())
+    assert torch.equal(Y, want)
+    out = torch.empty_like(Y)
+    assert lin(X, 5, out) is out and torch.equal(out, Y)
+    assert torch.equal(lin(X.reshape(2, 3, 300)), Y) and torch.equal(lin(X[0]), lin(X[:1]))
+    assert torch.equal(lin(X, bits_used=3), lin(X, np.int64(3)))
+    assert torch.equal(lin(X.t().contiguous().t().clone(memory_format=torch.contiguous_format)), Y)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        on_side = lin(X)
+    side.synchronize()
+    assert torch.equal(on_side, Y)
+    with pytest.raises(AssertionError):
+        lin(torch.zeros((7, 300), device="cuda"))
+    with pytest.raises(ValueError, match="X must be contiguous"):
+        pb.pb_matmul(lin.packed, lin.scales, lin.desc, 5, X.t(), 6, Y, lin.workspace)
+    with pytest.raises(TypeError, match="Y must have dtype"):
+        pb.pb_matmul(lin.packed, lin.scales, lin.desc, 5, X, 6, Y.double(), lin.workspace)
+    with pytest.raises(pb.PbError) as e:
+        pb.pb_matmul(lin.packed, lin.scales, lin.desc, 6, X, 6, Y, lin.workspace)
+    assert e.value.status == pb.PB_EINVAL
+    with pytest.raises(pb.PbError):
+        lin(X, bits_used=6)
+    with pytest.raises(pb.PbError) as e:
+        pb.pb_matmul(lin.packed, None, lin.desc, 5, X, 6, Y, lin.workspace)
+    assert e.value.status == pb.PB_EINVAL
+    torch.cuda.synchronize()
