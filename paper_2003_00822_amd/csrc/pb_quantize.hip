@@ -111,6 +111,7 @@ __global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size
     }
     float am = 0.0f, hi = -INFINITY, lo = INFINITY;
     for_each_weight(W, n, [&](float w) {
+        w = __builtin_canonicalizef(w);   // (a maximum with a signalling NaN is a NaN)
         am = fmaxf(am, fabsf(w));
         hi = fmaxf(hi, w);
         lo = fminf(lo, w);
@@ -151,7 +152,7 @@ __device__ __forceinline__ int quantize_code(float w, float d, int qmin, int qma
 // The division of quantize_code by a multiplication where that cannot change the code.  t = w * (1 / d) differs from the
 // rounded quotient by less than |t| 2^-22, so rint(t) is the code's rounding unless t is that close to a half-integer
 // (for |t| up to qmax + 2; beyond, both clamp).  `off` is the largest distance of the t's from their integers: above
-// `limit` (or NaN) the caller divides.
+// `limit` the caller divides.
 struct Quantizer {
     float d, inv, limit;
     int qmin, qmax;
@@ -167,13 +168,14 @@ struct Quantizer {
     __device__ __forceinline__ float rounded(float w, float &off) const
     {
         const float t = w * inv, r = rintf(t), f = fabsf(t - r);
-        off = !(f <= off) ? f : off;   // (a NaN goes through to the comparison)
+        off = fmaxf(off, f);   // (an infinite or NaN weight has no distance: code() is right for it)
         return r;
     }
     __device__ __forceinline__ bool must_divide(float off) const { return !(off <= limit); }
     __device__ __forceinline__ int code(float r) const
     {
-        return (int)fminf(fmaxf(r, (float)qmin), (float)qmax);
+        const float c = fminf(fmaxf(r, (float)qmin), (float)qmax);
+        return r == r ? (int)c : 0;
     }
 };
 

@@ -50,3 +50,23 @@ def test_clipping_search_with_and_without_histogram(pb, bits):
         if outlier:
             W[7, 11] = -outlier
         check(pb, W, bits, 0x50420002, quantizer=3)
+
+
+@pytest.mark.parametrize("nan", [0x7FC00000, 0x7FA00000, 0xFFA00000], ids=["quiet", "signalling", "negative signalling"])
+@pytest.mark.parametrize("bits,quantizer", [(8, 0), (16, 0), (5, 1), (2, 2), (4, 3)])
+def test_nan_weights_count_as_zero(pb, bits, quantizer, nan):
+    """NaN has the code of 0 wherever it stands among the four columns that a lane quantizes together, and does not
+    touch the step, also where it follows the largest weight."""
+    W = np.random.default_rng(bits).normal(0, 0.05, size=(530, 531)).astype(np.float32)
+    W[0, 0], W[0, 5] = -0.9, 0.8
+    where = np.zeros(W.shape, dtype=bool)
+    for j in range(16):   # every subset of a group of four columns
+        for e in range(4):
+            where[j + 1, 4 * j + e] = j >> e & 1
+            where[j + 514, 512 + e] = j >> e & 1
+    where[1:16, 5] = True
+    prep = po.prepare(np.where(where, np.float32(0), W), bits, quantizer)
+    bitsW = np.where(where, np.uint32(nan), W.view(np.uint32)).view(np.int32)
+    lin = pb.PackedLinear(torch.from_numpy(bitsW).cuda().view(torch.float32), bits, quantizer=quantizer)
+    assert (lin.unpack().cpu().numpy() == prep["q"]).all()
+    assert (lin.scales[:bits].cpu().numpy().view(np.int32) == prep["scales"].view(np.int32)).all()
