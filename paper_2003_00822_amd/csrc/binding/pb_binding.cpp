@@ -133,15 +133,21 @@ PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t nargs, PyObject *kw
 
 PyObject *s_rows, *s_cols, *s_bits, *s_max_batch, *s_desc, *s_packed, *s_scales, *s_workspace;
 
-template <typename T>
-bool load_attr(PyObject *self, PyObject *name, T &x)
-{
-    PyObject *o = PyObject_GetAttr(self, name);
-    if (!o) { PyErr_Clear(); return false; }
-    const bool ok = x.load(o);
-    Py_DECREF(o);   // (the object that `self` holds stays alive through the call)
-    return ok;
-}
+// The attributes of `self` that a call uses, held until it returns: one that is computed on access, or replaced by another
+// thread meanwhile, must not give its memory back before the launch.
+struct Held {
+    PyObject *o[8];
+    int n = 0;
+    ~Held() { while (n) Py_DECREF(o[--n]); }
+    template <typename T>
+    bool load(PyObject *self, PyObject *name, T &x)
+    {
+        PyObject *a = PyObject_GetAttr(self, name);
+        if (!a) { PyErr_Clear(); return false; }
+        o[n++] = a;
+        return x.load(a);
+    }
+};
 
 // linear(self, X, bits_used, out): PackedLinear.__call__
 PyObject *linear(PyObject *, PyObject *const *args, Py_ssize_t nargs)
@@ -153,13 +159,14 @@ PyObject *linear(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             Bytes packed, workspace;
             In scales, x;
             Out y;
+            Held held;   // (eight attributes at most)
             PyObject *self = args[0];
             const at::Tensor &X = THPVariable_Unpack(args[1]);
-            bool ok = x.load(args[1]) && load_attr(self, s_rows, rows) && load_attr(self, s_cols, cols) &&
-                      load_attr(self, s_max_batch, max_batch) && load_attr(self, s_desc, d) &&
-                      load_attr(self, s_packed, packed) && load_attr(self, s_scales, scales) &&
-                      load_attr(self, s_workspace, workspace) &&
-                      (args[2] == Py_None ? load_attr(self, s_bits, m) : m.load(args[2]) && m.v != 0);
+            bool ok = x.load(args[1]) && held.load(self, s_rows, rows) && held.load(self, s_cols, cols) &&
+                      held.load(self, s_max_batch, max_batch) && held.load(self, s_desc, d) &&
+                      held.load(self, s_packed, packed) && held.load(self, s_scales, scales) &&
+                      held.load(self, s_workspace, workspace) &&
+                      (args[2] == Py_None ? held.load(self, s_bits, m) : m.load(args[2]) && m.v != 0);
             const int64_t n = X.numel();
             ok = ok && cols.v > 0 && n > 0 && n % cols.v == 0 && n / cols.v <= max_batch.v;
             if (ok) {

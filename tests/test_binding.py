@@ -64,3 +64,29 @@ def test_native_and_python_calls_agree(pb):
         pb.pb_matmul(lin.packed, None, lin.desc, 5, X, 6, Y, lin.workspace)
     assert e.value.status == pb.PB_EINVAL
     torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+def test_computed_attributes_stay_alive(pb):
+    """A layer whose tensors are made on access: none of them may share memory with the output."""
+    class Computed(pb.PackedLinear):
+        pass
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    W = torch.randn((50, 300), device="cuda", generator=g)
+    X = torch.randn((1, 300), device="cuda", generator=g)
+    want = pb.PackedLinear(W, 5)(X)
+    lin = Computed(W, 5)
+    packed, scales, used = lin.packed, lin.scales, []
+
+    def fresh(t):
+        t = t.clone()
+        used.append(t.data_ptr())
+        return t
+
+    Computed.packed = property(lambda self: fresh(packed))
+    Computed.scales = property(lambda self: fresh(scales))
+    Y = lin(X)
+    assert len(used) == 2 and Y.data_ptr() not in used
+    assert torch.equal(Y, want)
