@@ -122,17 +122,29 @@ __global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size
     if (threadIdx.x == 0) s.stats[blockIdx.x] = Partial{am, hi, lo, 0.0f};
 }
 
-// the statistics of all blocks, in every thread of a workgroup
+// the statistics of all blocks, in every thread of a workgroup.  All loads of up to 2048 blocks in flight (past the end the last
+// block's once more): one memory latency for 2048 blocks, which every kernel that needs the step waits for first (4096 x 4096,
+// 8 bits, whole call: 31.1 -> 29.5 us against one load after the other).
 template <int WAVES>
 __device__ __forceinline__ Partial all_stats(const Scratch &s)
 {
     __shared__ float part[WAVES];
     float am = 0.0f, hi = -INFINITY, lo = INFINITY;
-    for (int i = threadIdx.x; i < s.blocks; i += WAVES * 64) {
-        const Partial p = s.stats[i];
-        am = fmaxf(am, p.absmax);
-        hi = fmaxf(hi, p.hi);
-        lo = fminf(lo, p.lo);
+    const float4 *stats = reinterpret_cast<const float4 *>(s.stats);   // absmax, hi, lo, unused
+    constexpr int K = kMaxStatsBlocks / (WAVES * 64);
+    for (int i = threadIdx.x; i < s.blocks; i += K * WAVES * 64) {
+        float4 p[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int at = i + k * WAVES * 64;
+            p[k] = stats[at < s.blocks ? at : s.blocks - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            am = fmaxf(am, p[k].x);
+            hi = fmaxf(hi, p[k].y);
+            lo = fminf(lo, p[k].z);
+        }
     }
     am = block_reduce<WAVES>(am, part, max_of);
     hi = block_reduce<WAVES>(hi, part, max_of);
@@ -212,7 +224,7 @@ __global__ __launch_bounds__(256) void k_abs_sum(const float *__restrict__ W, si
 // does.  That bounds every sum from both sides (k_clip_hist, k_clip_bounds), and only the thresholds whose lower bound
 // does not exceed the smallest upper bound are summed exactly (k_clip_err): one to three of the 32 with 2 to 8 bits,
 // all of them with so many bits that a bin holds many steps (then 0.16 ms).  3001 x 5003, 4 bits, whole call: 2405 ->
-// 61 us, of which the histogram takes 19 (LDS atomics), statistics and packing 30.
+// 60 us, of which the histogram takes 19 (LDS atomics), statistics and packing 30.
 
 // the step of threshold k + 1
 __device__ __forceinline__ float clip_step(float M, int k, int bits)
