@@ -84,6 +84,7 @@ def build_binding(verbose: bool = True, out: str = BINDING_LIB) -> str:
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",     # (what torch's and HIP's own headers ask of a host compiler)
+           '-DPB_BUILT_FOR="%s %s"' % (torch.__version__, sys.implementation.cache_tag),
            "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"]]
     for path in cpp_extension.include_paths() + ["/opt/rocm/include"]:
         cmd += ["-isystem", path]

@@ -6,7 +6,8 @@
 //
 // A function here takes the call if every argument is what it expects (positional, CUDA tensor of the right type,
 // contiguous, ...).  Anything else, wrong or merely unusual, goes to the Python function of the same name in pb.py, which
-// raises the errors: one place for their texts.
+// raises the errors: one place for their texts.  pb.py does without this extension where it is not built or was built for
+// another torch or Python.
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>
@@ -272,5 +273,7 @@ PyMODINIT_FUNC PyInit__binding()
     s_packed = PyUnicode_InternFromString("packed");
     s_scales = PyUnicode_InternFromString("scales");
     s_workspace = PyUnicode_InternFromString("workspace");
-    return PyModule_Create(&kModule);
+    PyObject *m = PyModule_Create(&kModule);
+    if (m && PyModule_AddStringConstant(m, "BUILT_FOR", PB_BUILT_FOR) != 0) Py_CLEAR(m);   // (pb.py compares it)
+    return m;
 }

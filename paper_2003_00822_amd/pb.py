@@ -6,20 +6,18 @@ first call raises.
 
 The calls that launch kernels go through `_binding` (csrc/binding/pb_binding.cpp), which checks the usual
 arguments and calls the library natively; the functions below of the same names take what it does not
-(keywords, an explicit stream, wrong arguments) and raise the errors.
+(keywords, an explicit stream, wrong arguments) and raise the errors.  They serve every call where the extension
+is not built, or was built for another torch or Python; a call then takes 6 to 8 us more of host time.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import sys
+import warnings
 
 import torch
-
-try:
-    from . import _binding
-except ImportError as e:   # not built: every call raises (see _require_binding)
-    _binding = None
-    _binding_error = e
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # PBATCH_LIB points the binding at another build of the same library (e.g. one compiled with other tuning macros)
@@ -106,17 +104,14 @@ def lib():
         L.pb_strerror.restype = ctypes.c_char_p
         L.pb_last_hip_error.argtypes = []
         L.pb_last_hip_error.restype = _I
-        _require_binding().bind(pb_desc, PbError,
-                                {n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in _NATIVE})
+        binding, why_not = _use_binding()   # (once more: it may have been built since this module was imported)
+        if binding is not None:
+            binding.bind(pb_desc, PbError, {n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in _NATIVE})
+        else:
+            warnings.warn("calls go through ctypes, 6 to 8 us slower each: %s (python -m paper_2003_00822_amd.build)"
+                          % why_not, RuntimeWarning, stacklevel=2)
         _lib = L
     return _lib
-
-
-def _require_binding():
-    if _binding is None:
-        raise RuntimeError("the native binding is not built: run `python -m paper_2003_00822_amd.build` (%s)"
-                           % _binding_error)
-    return _binding
 
 
 def strerror(status: int) -> str:
@@ -322,7 +317,23 @@ _NATIVE = ["pb_quantize_pack", "pb_quantize_pack_desc", "pb_quantize_pack_mode",
            "pb_matmul_static", "pb_matmul_bias_act", "pb_matmul_acc", "pb_matmul_acc_pairs", "pb_act_prep",
            "pb_matmul_prepared", "pb_fixed_point", "pb_lstm_cell"]
 _linear = PackedLinear._call_checked
-if _binding is not None:
-    _binding.set_slow({**{n: globals()[n] for n in _NATIVE}, "linear": _linear})
-    globals().update({n: getattr(_binding, n) for n in _NATIVE})
-    _linear = _binding.linear
+_PYTHON = {**{n: globals()[n] for n in _NATIVE}, "linear": _linear}
+
+
+def _use_binding():
+    """Put the native functions in front of the Python ones: (the extension, None), or (None, why it is not used)."""
+    importlib.invalidate_caches()
+    try:
+        binding = importlib.import_module(__package__ + "._binding")
+    except ImportError as e:
+        return None, "no native binding (%s)" % e
+    here = "%s %s" % (torch.__version__, sys.implementation.cache_tag)
+    if getattr(binding, "BUILT_FOR", None) != here:   # (it takes tensors apart by torch's headers)
+        return None, "the native binding is built for %s, not for %s" % (getattr(binding, "BUILT_FOR", "?"), here)
+    binding.set_slow(_PYTHON)
+    globals().update({n: getattr(binding, n) for n in _NATIVE})
+    globals()["_linear"] = binding.linear
+    return binding, None
+
+
+_use_binding()

@@ -1,4 +1,10 @@
 """The native calling side of pb.py against its Python functions: unusual and wrong arguments."""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
 import numpy as np
 import pytest
 
@@ -23,6 +29,49 @@ def test_arguments_that_are_no_gpu_tensors(pb):
         pb.pb_unpack(t, d)                       # an argument missing
     with pytest.raises(TypeError):
         pb.pb_unpack(t, d, t, None, 5)           # one too many
+
+
+def test_the_library_serves_without_the_extension(tmp_path):
+    """A package without `_binding.so` answers size queries and argument errors; the extension is taken up if it is built
+    between the import and the first use, and left alone if it is built for another torch."""
+    from paper_2003_00822_amd import build
+    src = os.path.dirname(build.LIB)
+    pkg = tmp_path / "paper_2003_00822_amd"
+    pkg.mkdir()
+    for f in os.listdir(src):
+        if f.endswith(".py"):
+            shutil.copy(os.path.join(src, f), pkg)
+    os.symlink(build.LIB, pkg / "libpbatch.so")
+    code = """
+        import os, sys, warnings
+        import torch
+        what, ext = sys.argv[1:]
+        if what == "other torch":
+            os.symlink(ext, "paper_2003_00822_amd/_binding.so")
+            torch.__version__ = "0.0.1"
+        from paper_2003_00822_amd import pb
+        assert os.path.realpath(pb.__file__).startswith(os.getcwd())
+        if what == "built later":
+            os.symlink(ext, "paper_2003_00822_amd/_binding.so")
+        with warnings.catch_warnings(record=True) as w:
+            warnings.simplefilter("always")
+            assert pb.pb_packed_bytes(pb.pb_desc_init(4096, 4096, 8)) == 4096 * 4096
+        native = what == "built later"
+        assert isinstance(pb.pb_matmul, type(len)) == native, pb.pb_matmul
+        assert [x.category for x in w] == ([] if native else [RuntimeWarning])
+        try:
+            pb.pb_unpack(torch.zeros(4), pb.pb_desc_init(8, 64, 3), torch.zeros(4))
+            raise SystemExit("not refused")
+        except TypeError as e:
+            assert "packed must be a CUDA/HIP tensor" in str(e)
+    """
+    env = {k: v for k, v in os.environ.items() if k != "PBATCH_LIB"}
+    for what in ("missing", "other torch", "built later"):
+        ext = pkg / "_binding.so"
+        if ext.is_symlink():
+            ext.unlink()
+        subprocess.run([sys.executable, "-c", textwrap.dedent(code), what, build.BINDING_LIB], check=True, cwd=tmp_path,
+                       env=env, timeout=300)
 
 
 @pytest.mark.gpu
