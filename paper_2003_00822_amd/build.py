@@ -104,6 +104,14 @@ def build_all(verbose: bool = True):
         return libs + [binding.result()]
 
 
+def ensure(verbose: bool = True):
+    """Build those of the libraries that are not there (a tree may hold some of them from before the others existed)."""
+    for path, make in ((LIB, build), (BINDING_LIB, build_binding),
+                       (CALIB_LIB, lambda verbose: build(verbose, out=CALIB_LIB, srcs=calib_sources()))):
+        if not os.path.exists(path):
+            make(verbose=verbose)
+
+
 if __name__ == "__main__":
     for lib in build_all():
         print("built", lib)

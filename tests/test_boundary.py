@@ -11,11 +11,30 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.fixture(scope="module")
 def pb():
+    from paper_2003_00822_amd import build
+    build.ensure(verbose=False)
     from paper_2003_00822_amd import pb as pbmod
-    if not os.path.exists(pbmod.LIB_PATH):
-        from paper_2003_00822_amd import build
-        build.build(verbose=False)
     return pbmod
+
+
+def test_missing_libraries_are_built(tmp_path, monkeypatch):
+    """Each library is built for itself: a tree with only some of them is completed."""
+    from paper_2003_00822_amd import build
+    names = {"LIB": "lib", "BINDING_LIB": "binding", "CALIB_LIB": "calib"}
+    for attr, name in names.items():
+        monkeypatch.setattr(build, attr, str(tmp_path / name))
+    made = []
+    monkeypatch.setattr(build, "build", lambda verbose, out=None, srcs=None: made.append(out or build.LIB))
+    monkeypatch.setattr(build, "build_binding", lambda verbose: made.append(build.BINDING_LIB))
+    build.ensure()
+    assert made == [build.LIB, build.BINDING_LIB, build.CALIB_LIB]
+    for there in names.values():
+        for n in names.values():
+            (tmp_path / n).unlink(missing_ok=True)
+        (tmp_path / there).touch()
+        made.clear()
+        build.ensure()
+        assert sorted(os.path.basename(m) for m in made) == sorted(n for n in names.values() if n != there)
 
 
 def declared_functions():
