@@ -38,10 +38,11 @@ static Scratch scratch_of(void *packed, size_t bytes, size_t n, int blocks)
     s.lower = reinterpret_cast<double *>(s.abssum + blocks);
     s.upper = s.lower + kClipSteps;
     s.bins = reinterpret_cast<unsigned long long *>(s.upper + kClipSteps);
-    // (up to 2^17 weights the exact sums of all thresholds take less time than two more launches; beyond 2^27 the fields
-    // of a workgroup's bins would overflow)
+    // (up to 2^18 weights the exact sums of all thresholds take less time than two more launches: whole call without / with
+    // the histogram at 2^18 weights 25 / 25 us with 4 bits, 27 / 34 with 8, 34 / 40 with 16; at 420 000 28 / 26, 32 / 34 and
+    // 37 / 43; at 2^20 36 / 26, 45 / 39 and 66 / 54.  Beyond 2^27 the fields of a workgroup's bins would overflow)
     const size_t end = (size_t)(reinterpret_cast<char *>(s.bins + kClipBins) - static_cast<char *>(packed));
-    if (end > bytes || n <= (1u << 17) || n > (1u << 27)) s.lower = s.upper = nullptr;
+    if (end > bytes || n <= (1u << 18) || n > (1u << 27)) s.lower = s.upper = nullptr;
     return s;
 }
 
@@ -322,8 +323,10 @@ __device__ __forceinline__ uint32_t clip_candidates(const Scratch &s)
     return (uint32_t)__ballot(lo <= best);
 }
 
-// The exact sums of the candidates, unless there is only one.  Bound: the vector ALU, 11 operations per weight and
-// candidate; a thread keeps its 32 weights in registers over all candidates.
+// The exact sums of the candidates, unless there is only one.  Bound: the vector ALU, per weight and candidate 11
+// operations, and a division more where one of a lane's 32 quotients comes close to a half-integer (Quantizer): hardly ever
+// up to 8 bits, in half of the waves with 10 bits, in all of them with 16.  A thread keeps its 32 weights in registers over
+// its candidates; the second dimension of the grid shares the candidates out (launch_quantize_pack).
 __global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, size_t n, int bits, Scratch s)
 {
     __shared__ unsigned long long sums[kClipSteps];
@@ -339,6 +342,7 @@ __global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, s
         load_weights(W, n, base, 0.0f, w);   // (a weight 0 has the code 0 and no error)
         for (uint32_t left = candidates; left; left &= left - 1) {
             const int c = __builtin_ctz(left);
+            if ((unsigned)c % gridDim.y != blockIdx.y) continue;
             const Quantizer Q(clip_step(M, c, bits), bits);
             const float qmax = (float)Q.qmax, qmin = (float)Q.qmin;
             float off = 0.0f;
@@ -637,7 +641,13 @@ int launch_quantize_pack(const float *W, const Layout &L, int quantizer, uint32_
             hipLaunchKernelGGL(k_clip_hist, dim3((unsigned)(hblocks < 256 ? hblocks : 256)), dim3(1024), 0, st, W, n, s);
             hipLaunchKernelGGL(k_clip_bounds, dim3(kClipSteps), dim3(1024), 0, st, L.bits, s);
         }
-        hipLaunchKernelGGL(k_clip_err, dim3(blocks), dim3(256), 0, st, W, n, L.bits, s);
+        // A workgroup takes 8192 weights, so that up to 2^21 of them leave compute units without one, or with one that has
+        // all thresholds to sum: they are shared out until there are two workgroups per unit.  Whole call, one share / this
+        // rule: 2^16 weights 54 / 21 us with 4 bits, 198 / 24 with 12, 137 / 24 with 16; 2^20 weights 26 / 26, 91 / 54 and
+        // 89 / 56; from 2^22 on there is one share.
+        int shares = 1;
+        while (shares < kClipSteps && blocks * shares < 512) shares *= 2;
+        hipLaunchKernelGGL(k_clip_err, dim3(blocks, shares), dim3(256), 0, st, W, n, L.bits, s);
     }
     hipLaunchKernelGGL(k_step, dim3(1), dim3(256), 0, st, s, L.bits, quantizer, n, scales);
     const unsigned tiles = (unsigned)((L.rows_p + kTileRows - 1) / kTileRows) * (unsigned)(L.cwp / kChunkWords);

@@ -1,5 +1,5 @@
-"""Packing and unpacking at the edges of their tiles (16 rows x 512 columns), and the clipping search around the size from
-which a histogram rules thresholds out, against the oracle's codes and scales."""
+"""Packing and unpacking at the edges of their tiles (16 rows x 512 columns), and the clipping search around the sizes from
+which a histogram rules thresholds out and the thresholds are no longer shared out, against the oracle's codes and scales."""
 import numpy as np
 import pytest
 
@@ -49,6 +49,19 @@ def test_clipping_search_with_and_without_histogram(pb, bits):
         W = g.normal(0, 0.05, size=(rows, cols)).astype(np.float32)
         if outlier:
             W[7, 11] = -outlier
+        check(pb, W, bits, 0x50420002, quantizer=3)
+
+
+@pytest.mark.parametrize("bits", [1, 4, 10, 12, 16])
+def test_clipping_search_with_thresholds_shared_out(pb, bits):
+    """Grids with 32, 16, 4 and 1 workgroups per block of weights, one weight and a single one past a block among them."""
+    g = np.random.default_rng(bits + 80)
+    for rows, cols in ((1, 1), (91, 90), (8193, 1), (360, 364), (400, 701), (1025, 1024), (2051, 2049)):
+        if rows * cols > 1 << 21 and bits not in (4, 16):
+            continue
+        print("clip search", bits, rows, cols, flush=True)
+        W = g.normal(0, 0.05, size=(rows, cols)).astype(np.float32)
+        W[0, 0] = 0.3
         check(pb, W, bits, 0x50420002, quantizer=3)
 
 
