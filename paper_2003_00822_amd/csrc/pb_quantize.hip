@@ -323,7 +323,7 @@ __device__ __forceinline__ uint32_t clip_candidates(const Scratch &s)
     return (uint32_t)__ballot(lo <= best);
 }
 
-// The exact sums of the candidates, unless there is only one.  Bound: the vector ALU, per weight and candidate 11
+// The exact sums of the candidates, unless there is only one.  Bound: the vector ALU, per weight and candidate 12
 // operations, and a division more where one of a lane's 32 quotients comes close to a half-integer (Quantizer): hardly ever
 // up to 8 bits, in half of the waves with 10 bits, in all of them with 16.  A thread keeps its 32 weights in registers over
 // its candidates; the second dimension of the grid shares the candidates out (launch_quantize_pack).
@@ -347,12 +347,17 @@ __global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, s
             const float qmax = (float)Q.qmax, qmin = (float)Q.qmin;
             float off = 0.0f;
             unsigned long long sum = 0;
+            auto error = [&](float w, float q) {
+                // (the product is rounded before the subtraction: __fmul_rn alone leaves that to the compiler)
+#pragma clang fp contract(off)
+                const float p = Q.d * q;
+                return w - p;
+            };
 #pragma unroll
             for (int k = 0; k < 32; ++k) {
                 const float t = w[k] * Q.inv, r = rintf(t);
                 off = fmaxf(off, fabsf(t - r));
-                const float p = __fmul_rn(Q.d, fminf(fmaxf(r, qmin), qmax));
-                const float err = ldexpf(fabsf(__fsub_rn(w[k], p)), 30 - e);
+                const float err = ldexpf(fabsf(error(w[k], fminf(fmaxf(r, qmin), qmax))), 30 - e);
                 uint32_t v;   // (toward zero, NaN -> 0)
                 asm("v_cvt_u32_f32 %0, %1" : "=v"(v) : "v"(err));
                 sum += v;
@@ -360,10 +365,7 @@ __global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, s
             if (Q.must_divide(off)) {
                 sum = 0;
 #pragma unroll
-                for (int k = 0; k < 32; ++k) {
-                    const float p = __fmul_rn(Q.d, (float)quantize_code(w[k], Q.d, Q.qmin, Q.qmax));
-                    sum += fix30(__fsub_rn(w[k], p), e);
-                }
+                for (int k = 0; k < 32; ++k) sum += fix30(error(w[k], (float)quantize_code(w[k], Q.d, Q.qmin, Q.qmax)), e);
             }
             sum = wave_sum_u64(sum);
             if ((threadIdx.x & 63) == 0) atomicAdd(&sums[c], sum);

@@ -65,6 +65,15 @@ def test_clipping_search_with_thresholds_shared_out(pb, bits):
         check(pb, W, bits, 0x50420002, quantizer=3)
 
 
+@pytest.mark.parametrize("bits", [1, 3, 4, 8])
+def test_clipping_search_between_equal_errors(pb, bits):
+    """A few weights, for which several thresholds have the same summed error, or one that differs by the rounding of d q
+    alone: -9 with 4 bits is met exactly by the thresholds 32 / 32 (7 steps of RN(9 / 7)) and 28 / 32 (8 steps of 1.125)."""
+    for values in ([-9.0], [9.0, -9.0], [1.0, 3.0], [-0.7, 0.1], [5.0, -5.0, 2.5], [0.3], [1e-30, -3e-31]):
+        print("clip search", bits, values, flush=True)
+        check(pb, np.array([values], dtype=np.float32), bits, 0x50420002, quantizer=3)
+
+
 @pytest.mark.parametrize("nan", [0x7FC00000, 0x7FA00000, 0xFFA00000], ids=["quiet", "signalling", "negative signalling"])
 @pytest.mark.parametrize("bits,quantizer", [(8, 0), (16, 0), (5, 1), (2, 2), (4, 3)])
 def test_nan_weights_count_as_zero(pb, bits, quantizer, nan):
