@@ -74,6 +74,19 @@ def test_clipping_search_between_equal_errors(pb, bits):
         check(pb, np.array([values], dtype=np.float32), bits, 0x50420002, quantizer=3)
 
 
+@pytest.mark.parametrize("bits,quantizer", [(8, 0), (5, 1), (2, 2), (4, 3)])
+def test_statistics_at_the_end_of_the_weights(pb, bits, quantizer):
+    """Last blocks of 1 to 8192 weights: all of one sign, so that a weight past the end would change the range or the mean,
+    and the largest or smallest one last."""
+    g = np.random.default_rng(bits + 20)
+    for rows, cols in ((1, 1), (1, 3), (3, 341), (1, 1025), (1, 8191), (1, 8192), (1, 8193), (5, 3277), (3, 8193)):
+        for sign, last in ((1, 9.0), (1, 0.25), (-1, 9.0), (-1, 0.25)):
+            print("statistics", quantizer, rows, cols, sign, last, flush=True)
+            W = (sign * g.uniform(0.5, 1.0, size=(rows, cols))).astype(np.float32)
+            W[-1, -1] = sign * last
+            check(pb, W, bits, 0x50420002, quantizer)
+
+
 @pytest.mark.parametrize("nan", [0x7FC00000, 0x7FA00000, 0xFFA00000], ids=["quiet", "signalling", "negative signalling"])
 @pytest.mark.parametrize("bits,quantizer", [(8, 0), (16, 0), (5, 1), (2, 2), (4, 3)])
 def test_nan_weights_count_as_zero(pb, bits, quantizer, nan):
