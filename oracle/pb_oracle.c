@@ -147,8 +147,9 @@ int pbo_quantize_mode(const float *W, int64_t n, int bits, int mode, int32_t *q,
             uint64_t E = 0;
             for (int64_t i = 0; i < n; ++i) {
                 if (W[i] != W[i]) continue;
-                float p = d * (float)pbo_round_clamp(W[i], d, qmin, qmax);
-                E += pbo_fix30(W[i] - p, e);
+                /* (in units of 2^(e-30), which rounds the same but keeps d q finite next to the largest float) */
+                float p = ldexpf(d, 30 - e) * (float)pbo_round_clamp(W[i], d, qmin, qmax);
+                E += pbo_fix30(ldexpf(W[i], 30 - e) - p, 30);
             }
             if (k == 32 || E < best_err) { best = k; best_err = E; }
         }

@@ -326,7 +326,7 @@ __device__ __forceinline__ uint32_t clip_candidates(const Scratch &s)
     return (uint32_t)__ballot(lo <= best);
 }
 
-// The exact sums of the candidates, unless there is only one.  Bound: the vector ALU, per weight and candidate 12
+// The exact sums of the candidates, unless there is only one.  Bound: the vector ALU, per weight and candidate 11
 // operations, and a division more where one of a lane's 32 quotients comes close to a half-integer (Quantizer): hardly ever
 // up to 8 bits, in half of the waves with 10 bits, in all of them with 16.  A thread keeps its 32 weights in registers over
 // its candidates; the second dimension of the grid shares the candidates out (launch_quantize_pack).
@@ -343,10 +343,13 @@ __global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, s
     for (size_t base = (size_t)blockIdx.x * kStatsFloats; base < n; base += (size_t)gridDim.x * kStatsFloats) {
         float w[32];
         load_weights(W, n, base, 0.0f, w);   // (a weight 0 has the code 0 and no error)
+        // weights and steps in units of 2^(e - 30): every rounding as without, but d q cannot overflow next to the largest float
+#pragma unroll
+        for (int k = 0; k < 32; ++k) w[k] = ldexpf(w[k], 30 - e);
         for (uint32_t left = candidates; left; left &= left - 1) {
             const int c = __builtin_ctz(left);
             if ((unsigned)c % gridDim.y != blockIdx.y) continue;
-            const Quantizer Q(clip_step(M, c, bits), bits);
+            const Quantizer Q(ldexpf(clip_step(M, c, bits), 30 - e), bits);
             const float qmax = (float)Q.qmax, qmin = (float)Q.qmin;
             float off = 0.0f;
             unsigned long long sum = 0;
@@ -360,7 +363,7 @@ __global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, s
             for (int k = 0; k < 32; ++k) {
                 const float t = w[k] * Q.inv, r = rintf(t);
                 off = fmaxf(off, fabsf(t - r));
-                const float err = ldexpf(fabsf(error(w[k], fminf(fmaxf(r, qmin), qmax))), 30 - e);
+                const float err = fabsf(error(w[k], fminf(fmaxf(r, qmin), qmax)));
                 uint32_t v;   // (toward zero, NaN -> 0)
                 asm("v_cvt_u32_f32 %0, %1" : "=v"(v) : "v"(err));
                 sum += v;
@@ -368,7 +371,7 @@ __global__ __launch_bounds__(256) void k_clip_err(const float *__restrict__ W, s
             if (Q.must_divide(off)) {
                 sum = 0;
 #pragma unroll
-                for (int k = 0; k < 32; ++k) sum += fix30(error(w[k], (float)quantize_code(w[k], Q.d, Q.qmin, Q.qmax)), e);
+                for (int k = 0; k < 32; ++k) sum += fix30(error(w[k], (float)quantize_code(w[k], Q.d, Q.qmin, Q.qmax)), 30);
             }
             sum = wave_sum_u64(sum);
             if ((threadIdx.x & 63) == 0) atomicAdd(&sums[c], sum);

@@ -74,6 +74,17 @@ def test_clipping_search_between_equal_errors(pb, bits):
         check(pb, np.array([values], dtype=np.float32), bits, 0x50420002, quantizer=3)
 
 
+@pytest.mark.parametrize("bits", [1, 4, 8, 10, 16])
+def test_clipping_search_next_to_the_largest_float(pb, bits):
+    """Weights up to the largest float, where d q, rounded, can be beyond it: below and above the size for the histogram."""
+    top = np.finfo(np.float32).max
+    for rows, cols, std in ((1, 1, 0.0), (20, 513, 2.0 ** 125), (20, 513, 0.05), (512, 600, 2.0 ** 125)):
+        print("clip search", bits, rows, cols, std, flush=True)
+        W = np.clip(np.random.default_rng(bits).normal(0, 1, size=(rows, cols)) * std, -top, top).astype(np.float32)
+        W[-1, -1], W[0, 0] = -top, top
+        check(pb, W, bits, 0x50420002, quantizer=3)
+
+
 @pytest.mark.parametrize("bits,quantizer", [(8, 0), (5, 1), (2, 2), (4, 3)])
 def test_statistics_at_the_end_of_the_weights(pb, bits, quantizer):
     """Last blocks of 1 to 8192 weights: all of one sign, so that a weight past the end would change the range or the mean,

@@ -487,6 +487,22 @@ def test_clip_search_invariances():
         assert np.abs(W.astype(np.float64) + float(dn) * qn).mean() <= np.abs(W.astype(np.float64)).mean()
 
 
+def test_clip_search_next_to_the_largest_float():
+    """Scaling by 2^p leaves the codes also where d q, rounded, would be beyond the largest float."""
+    top = np.float32(2) - np.float32(2.0 ** -23)
+    for bits in (4, 8, 10, 16):
+        W = np.random.default_rng(bits).normal(0, 0.3, size=300).clip(-1.5, 1.5).astype(np.float32)
+        W[7], W[11] = top, -top
+        q, d = po.quantize_mode(W, bits, po.QUANT_CLIP)
+        qs, ds = po.quantize_mode((W * np.float32(2.0 ** 127)).astype(np.float32), bits, po.QUANT_CLIP)
+        assert ds == np.float32(d * np.float32(2.0 ** 127)) and (qs == q).all()
+    # 6 bits: 31 RN(top / 31) rounds to 2, so the weights at 30.6 steps must not count as met by the largest threshold
+    W = np.concatenate([[top], np.full(50, top * 30.6 / 31), np.full(50, top * 0.5)]).astype(np.float32)
+    q, d = po.quantize_mode(W, 6, po.QUANT_CLIP)
+    qs, ds = po.quantize_mode(W * np.float32(2.0 ** 127), 6, po.QUANT_CLIP)
+    assert ds == np.float32(d * np.float32(2.0 ** 127)) and (qs == q).all()
+
+
 def test_clip_search_keeps_an_exact_grid():
     # weights already on the grid of the unclipped quantizer: zero error at k = 32, nothing smaller exists
     bits = 4
