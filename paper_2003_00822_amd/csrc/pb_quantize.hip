@@ -95,10 +95,27 @@ __device__ __forceinline__ T block_reduce(T v, T *part, F combine)
     for (int off = WAVES / 2; off > 0; off >>= 1) v = combine(v, __shfl_xor(v, off, 64));
     return v;
 }
-__device__ __forceinline__ float max_of(float a, float b) { return fmaxf(a, b); }
-__device__ __forceinline__ float min_of(float a, float b) { return fminf(a, b); }
 template <typename T>
 __device__ __forceinline__ T sum_of(T a, T b) { return a + b; }
+
+// the same for the three statistics together, once per kernel: one exchange through LDS
+template <int WAVES>
+__device__ __forceinline__ Partial reduce_stats(float am, float hi, float lo)
+{
+    __shared__ float4 part[WAVES];
+    auto step = [&](int off) {
+        am = fmaxf(am, __shfl_xor(am, off, 64));
+        hi = fmaxf(hi, __shfl_xor(hi, off, 64));
+        lo = fminf(lo, __shfl_xor(lo, off, 64));
+    };
+    for (int off = 32; off > 0; off >>= 1) step(off);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_float4(am, hi, lo, 0.0f);
+    __syncthreads();
+    const float4 p = part[threadIdx.x & (WAVES - 1)];
+    am = p.x; hi = p.y; lo = p.z;
+    for (int off = WAVES / 2; off > 0; off >>= 1) step(off);
+    return Partial{am, hi, lo, 0.0f};
+}
 
 // max |W|, max W and min W in one pass (Section 3.3: the step of every quantizer comes from these; fmaxf and fminf
 // drop NaN).  Bound: the read of W; 4096 x 4096: 11.8 us = 5.7 TB/s (43.7 us
@@ -106,7 +123,6 @@ __device__ __forceinline__ T sum_of(T a, T b) { return a + b; }
 // The blocks also clear the sums and the histogram of the clipping search, where they are used.
 __global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size_t n, int clip_search, Scratch s)
 {
-    __shared__ float part[4];
     if (clip_search) {
         const int i0 = (int)(blockIdx.x * 256 + threadIdx.x), step = (int)(gridDim.x * 256);
         for (int i = i0; i < kClipSteps; i += step) s.clip[i] = 0ull;
@@ -120,10 +136,8 @@ __global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size
         hi = fmaxf(hi, w);
         lo = fminf(lo, w);
     });
-    am = block_reduce<4>(am, part, max_of);
-    hi = block_reduce<4>(hi, part, max_of);
-    lo = block_reduce<4>(lo, part, min_of);
-    if (threadIdx.x == 0) s.stats[blockIdx.x] = Partial{am, hi, lo, 0.0f};
+    const Partial p = reduce_stats<4>(am, hi, lo);
+    if (threadIdx.x == 0) s.stats[blockIdx.x] = p;
 }
 
 // the statistics of all blocks, in every thread of a workgroup.  All loads of up to 2048 blocks in flight (past the end the last
@@ -132,7 +146,6 @@ __global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size
 template <int WAVES>
 __device__ __forceinline__ Partial all_stats(const Scratch &s)
 {
-    __shared__ float part[WAVES];
     float am = 0.0f, hi = -INFINITY, lo = INFINITY;
     const float4 *stats = reinterpret_cast<const float4 *>(s.stats);   // absmax, hi, lo, unused
     constexpr int K = kMaxStatsBlocks / (WAVES * 64);
@@ -150,10 +163,7 @@ __device__ __forceinline__ Partial all_stats(const Scratch &s)
             lo = fminf(lo, p[k].z);
         }
     }
-    am = block_reduce<WAVES>(am, part, max_of);
-    hi = block_reduce<WAVES>(hi, part, max_of);
-    lo = block_reduce<WAVES>(lo, part, min_of);
-    return Partial{am, hi, lo, 0.0f};
+    return reduce_stats<WAVES>(am, hi, lo);
 }
 
 __device__ __forceinline__ int quantize_code(float w, float d, int qmin, int qmax)
@@ -213,10 +223,19 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 __global__ __launch_bounds__(256) void k_abs_sum(const float *__restrict__ W, size_t n, Scratch s)
 {
     __shared__ unsigned long long part[4];
+    float w[32];   // (the first weights are on their way while the statistics come)
+    size_t base = (size_t)blockIdx.x * kStatsFloats;
+    load_weights(W, n, base, NAN, w);
     const float M = all_stats<4>(s).absmax;
     const int e = M > 0.0f ? ilogbf(M) : 0;
     unsigned long long sum = 0;
-    for_each_weight(W, n, [&](float w) { sum += fix30(w, e); });
+    for (;;) {
+#pragma unroll
+        for (int k = 0; k < 32; ++k) sum += fix30(w[k], e);
+        base += (size_t)gridDim.x * kStatsFloats;
+        if (base >= n) break;
+        load_weights(W, n, base, NAN, w);
+    }
     sum = block_reduce<4>(sum, part, sum_of<unsigned long long>);
     if (threadIdx.x == 0) s.abssum[blockIdx.x] = sum;
 }
