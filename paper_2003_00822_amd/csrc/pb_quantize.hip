@@ -475,20 +475,23 @@ __device__ __forceinline__ void transpose_bytes(uint32_t (&x)[8])
 // operations per weight (a ballot per bitlayer and 64 weights, with a select to keep it, took 0.6 operations per weight
 // and BITLAYER and stored 8 bytes at a time).  The stores of a bitlayer are contiguous over the threads.
 // PL: bytes of a stored code.  4096 x 4096, 8 bits: 15.8 us = 5.1 TB/s (55.6 us with the ballots and a division per weight).
-template <int PL>
+// ROWS: rows per wave; 4 take the whole tile, 1 takes a quarter of it, for matrices of few tiles (launch_quantize_pack).
+template <int PL, int ROWS>
 __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ W, uint32_t layout, int rows, int cols, int bits,
                                               int cwp, int rows_p, int gate_h, size_t layer_words, int quantizer,
                                               const float *__restrict__ scales, uint32_t *__restrict__ packed)
 {
     constexpr int kRowBytes = 512 + 16;   // (16 more, so that the rows of a word column start in different banks)
-    __shared__ __align__(16) uint8_t codes[PL][kTileRows][kRowBytes];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int NR = 4 * ROWS;          // rows of the workgroup: NR blockIdx.y .. of the tile
+    __shared__ __align__(16) uint8_t codes[PL][NR][kRowBytes];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int chunks = cwp / kChunkWords;
     const int rt = (int)(blockIdx.x / (unsigned)chunks), ch = (int)(blockIdx.x % (unsigned)chunks);
-    u32x4 w4[4][2];
+    const int row0 = rt * kTileRows + NR * (int)blockIdx.y;   // first packed row
+    u32x4 w4[ROWS][2];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int pr = rt * kTileRows + wave * 4 + k;
+    for (int k = 0; k < ROWS; ++k) {
+        const int pr = row0 + wave * ROWS + k;
         const int r = gate_h ? gates_matrix_row(pr, gate_h) : pr;   // matrix row (-1 or >= rows: padding)
         const bool ok = r >= 0 && r < rows;
         // (loads beyond the end of a row, and of absent rows, return 0)
@@ -501,13 +504,13 @@ __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ W, uint3
     const Quantizer Q(fabsf(scales[bits - 1]), bits);
     const int stored = is_pairs(layout) ? (bits + 1) & ~1 : bits;   // (an odd number of bitlayers is paired with zeros)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int j = wave * 4 + k;
+    for (int k = 0; k < ROWS; ++k) {
+        const int j = wave * ROWS + k;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             int u[4];
             if (quantizer == PB_QUANT_SIGN) {
-                const int pr = rt * kTileRows + j;
+                const int pr = row0 + j;
                 const int r = gate_h ? gates_matrix_row(pr, gate_h) : pr;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -539,14 +542,17 @@ __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ W, uint3
     }
     __syncthreads();
     // thread -> word position: in the order of the block for the tiled layouts, row by row for the row-major one
+    // (with a quarter of a tile a wave has all words, and the waves take a byte each)
     const bool rowmajor = layout == PB_LAYOUT_ROWMAJOR_V1;
-    const int j = rowmajor ? threadIdx.x >> 4 : (threadIdx.x >> 2) & 15;
-    const int w = rowmajor ? threadIdx.x & 15 : 4 * (threadIdx.x >> 6) + (threadIdx.x & 3);
-    if (rt * kTileRows + j >= rows_p) return;
-    uint32_t *dst = packed + (rowmajor ? (size_t)(rt * kTileRows + j) * (size_t)cwp + (size_t)(ch * kChunkWords + w)
-                                       : (size_t)blockIdx.x * 256 + threadIdx.x);
+    const int t = threadIdx.x & (16 * NR - 1);
+    const int j = rowmajor ? t >> 4 : (t >> 2) & (NR - 1);
+    const int w = rowmajor ? t & 15 : 4 * (t / (4 * NR)) + (t & 3);
+    if (row0 + j >= rows_p || (ROWS == 1 && wave >= PL)) return;
+    uint32_t *dst = packed + (rowmajor ? (size_t)(row0 + j) * (size_t)cwp + (size_t)(ch * kChunkWords + w)
+                                       : (size_t)blockIdx.x * 256 + 64 * (w >> 2) + 4 * (NR * (int)blockIdx.y + j) + (w & 3));
 #pragma unroll
-    for (int p = PL - 1; p >= 0; --p) {
+    for (int p0 = ROWS == 1 ? 0 : PL - 1; p0 >= 0; --p0) {
+        const int p = ROWS == 1 ? wave : p0;
         uint32_t x[8];
         const u32x4 *src = reinterpret_cast<const u32x4 *>(&codes[p][j][w * 32]);
         const u32x4 a = src[0], b = src[1];
@@ -579,7 +585,9 @@ __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ W, uint3
 // multiplication, one accumulating shift per bitlayer) and stores them with 16 bytes, a wave 1 KB of one row.
 // 8192 x 8192, 8 bits: 69 us = 4.9 TB/s (594 us with a thread per
 // element that fetched one word per bitlayer itself).
-template <int BITS>
+// ROWS: rows per wave; 4 take the whole tile, 1 takes a quarter of it, for matrices of few tiles (launch_unpack): the words
+// of up to 16 bitlayers then come with one load.
+template <int BITS, int ROWS>
 __global__ __launch_bounds__(256) void k_unpack(const uint32_t *__restrict__ packed, uint32_t layout, int rows, int cols,
                                                 int rows_p, int cwp, int gate_h, size_t layer_words,
                                                 int32_t *__restrict__ q)
@@ -588,10 +596,14 @@ __global__ __launch_bounds__(256) void k_unpack(const uint32_t *__restrict__ pac
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int chunks = (cols + 511) / 512;
     const int rt = (int)(blockIdx.x / (unsigned)chunks), ch = (int)(blockIdx.x % (unsigned)chunks);
-    const uint32_t *src = packed + tile_piece(layout, cwp, rt, ch, lane);
-    const bool stored_row = layout != PB_LAYOUT_ROWMAJOR_V1 || rt * kTileRows + (lane & 15) < rows_p;
+    // this thread's piece of the tile's blocks, and the bitlayers (or pairs of them) first, first + step, ..
+    const int part = ROWS == 1 ? 4 * (int)blockIdx.y : 0;   // first row of the tile that the workgroup takes
+    const int piece = ROWS == 1 ? 16 * ((threadIdx.x >> 2) & 3) + part + (threadIdx.x & 3) : lane;
+    const int first = ROWS == 1 ? threadIdx.x >> 4 : wave, step = ROWS == 1 ? 16 : 4;
+    const uint32_t *src = packed + tile_piece(layout, cwp, rt, ch, piece);
+    const bool stored_row = layout != PB_LAYOUT_ROWMAJOR_V1 || rt * kTileRows + (piece & 15) < rows_p;
     if (is_pairs(layout)) {
-        for (int p = wave; p < (BITS + 1) / 2; p += 4) {
+        for (int p = first; p < (BITS + 1) / 2; p += step) {
             const u32x4 even = *reinterpret_cast<const u32x4 *>(src + (size_t)(2 * p) * layer_words);
             const u32x4 odd = *reinterpret_cast<const u32x4 *>(src + (size_t)(2 * p + 1) * layer_words);
             u32x4 upper, lower;
@@ -602,19 +614,19 @@ __global__ __launch_bounds__(256) void k_unpack(const uint32_t *__restrict__ pac
                 upper[t] = p == 0 ? ~u : u;   // (bitlayer 0 is stored complemented)
                 lower[t] = l;
             }
-            *reinterpret_cast<u32x4 *>(&words[2 * p][lane * 4]) = upper;
-            *reinterpret_cast<u32x4 *>(&words[2 * p + 1][lane * 4]) = lower;
+            *reinterpret_cast<u32x4 *>(&words[2 * p][piece * 4]) = upper;
+            *reinterpret_cast<u32x4 *>(&words[2 * p + 1][piece * 4]) = lower;
         }
     } else {
-        for (int i = wave; i < BITS; i += 4)
-            *reinterpret_cast<u32x4 *>(&words[i][lane * 4]) =
+        for (int i = first; i < BITS; i += step)
+            *reinterpret_cast<u32x4 *>(&words[i][piece * 4]) =
                 stored_row ? *reinterpret_cast<const u32x4 *>(src + (size_t)i * layer_words) : u32x4{0, 0, 0, 0};
     }
     __syncthreads();
     constexpr int HI = BITS > 8 ? BITS - 8 : 0;   // bitlayers of the upper byte
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int j = wave * 4 + k;
+    for (int k = 0; k < ROWS; ++k) {
+        const int j = part + wave * ROWS + k;
         const int pr = rt * kTileRows + j;
         const int r = gate_h ? gates_matrix_row(pr, gate_h) : pr;   // matrix row (-1 or >= rows: padding)
         if (r < 0 || r >= rows) continue;
@@ -651,6 +663,13 @@ __global__ __launch_bounds__(256) void k_unpack(const uint32_t *__restrict__ pac
     }
 }
 
+// Up to this many tiles four workgroups share one: fewer workgroups than compute units leave a tile's four rows per wave
+// in sequence.  Graph of packing calls, whole tiles / quarters: 128 x 1000, 8 bits 9.2 / 8.1 us, 16 bits 13.6 / 9.1 (11.9
+// with the kernel before the tiles); 1024 x 2048 = 256 tiles, 8 bits 10.2 / 9.5; 1000 x 16384 = 2016 tiles, 8 bits 28.2 / 30.4.
+// Unpacking: 363 x 361, 1 bit 3.6 / 2.8 us, 16 bits 5.7 / 3.3 (2.8 and 4.7 with a thread per element); 1024 x 2048, 8 bits
+// 5.2 / 4.2; 8192 x 64 = 512 tiles, 1 bit 3.4 / 3.6; 1000 x 16384, 8 bits 14.2 / 15.8.
+constexpr unsigned kMaxQuarteredTiles = 256;
+
 int launch_quantize_pack(const float *W, const Layout &L, int quantizer, uint32_t *packed, float *scales,
                          hipStream_t st)
 {
@@ -677,20 +696,27 @@ int launch_quantize_pack(const float *W, const Layout &L, int quantizer, uint32_
     }
     hipLaunchKernelGGL(k_step, dim3(1), dim3(256), 0, st, s, L.bits, quantizer, n, scales);
     const unsigned tiles = (unsigned)((L.rows_p + kTileRows - 1) / kTileRows) * (unsigned)(L.cwp / kChunkWords);
-    hipLaunchKernelGGL(L.stored_bits > 8 ? k_pack<2> : k_pack<1>, dim3(tiles), dim3(256), 0, st, W, L.layout, L.rows,
-                       L.cols, L.bits, L.cwp, L.rows_p, L.gate_h, L.layer_words, quantizer, scales, packed);
+    const bool quarters = tiles <= kMaxQuarteredTiles;
+    hipLaunchKernelGGL(quarters ? (L.stored_bits > 8 ? k_pack<2, 1> : k_pack<1, 1>)
+                                : (L.stored_bits > 8 ? k_pack<2, 4> : k_pack<1, 4>),
+                       dim3(tiles, quarters ? 4 : 1), dim3(256), 0, st, W, L.layout, L.rows, L.cols, L.bits, L.cwp, L.rows_p,
+                       L.gate_h, L.layer_words, quantizer, scales, packed);
     return (int)hipGetLastError();
 }
 
 int launch_unpack(const uint32_t *packed, const Layout &L, int32_t *q, hipStream_t st)
 {
     typedef void (*Unpack)(const uint32_t *, uint32_t, int, int, int, int, int, size_t, int32_t *);
-    static const Unpack by_bits[PB_MAX_BITS] = {k_unpack<1>, k_unpack<2>, k_unpack<3>, k_unpack<4>, k_unpack<5>, k_unpack<6>,
-                                                k_unpack<7>, k_unpack<8>, k_unpack<9>, k_unpack<10>, k_unpack<11>,
-                                                k_unpack<12>, k_unpack<13>, k_unpack<14>, k_unpack<15>, k_unpack<16>};
+    // (whole tiles, quarters of tiles)
+#define PB_UNPACK(B) {k_unpack<B, 4>, k_unpack<B, 1>}
+    static const Unpack by_bits[PB_MAX_BITS][2] = {
+        PB_UNPACK(1), PB_UNPACK(2), PB_UNPACK(3), PB_UNPACK(4), PB_UNPACK(5), PB_UNPACK(6), PB_UNPACK(7), PB_UNPACK(8),
+        PB_UNPACK(9), PB_UNPACK(10), PB_UNPACK(11), PB_UNPACK(12), PB_UNPACK(13), PB_UNPACK(14), PB_UNPACK(15), PB_UNPACK(16)};
+#undef PB_UNPACK
     const unsigned tiles = (unsigned)((L.rows_p + kTileRows - 1) / kTileRows) * (unsigned)((L.cols + 511) / 512);
-    hipLaunchKernelGGL(by_bits[L.bits - 1], dim3(tiles), dim3(256), 0, st, packed, L.layout, L.rows, L.cols, L.rows_p, L.cwp,
-                       L.gate_h, L.layer_words, q);
+    const bool quarters = tiles <= kMaxQuarteredTiles;
+    hipLaunchKernelGGL(by_bits[L.bits - 1][quarters], dim3(tiles, quarters ? 4 : 1), dim3(256), 0, st, packed, L.layout,
+                       L.rows, L.cols, L.rows_p, L.cwp, L.gate_h, L.layer_words, q);
     return (int)hipGetLastError();
 }
 

@@ -41,6 +41,16 @@ def test_tile_edges(pb, layout, bits):
         check(pb, W, bits, layout)
 
 
+@pytest.mark.parametrize("layout", [0x50420001, 0x50420002, 0x50420003, 0x50420004])
+@pytest.mark.parametrize("bits", [1, 8, 9, 16])
+def test_whole_tiles_and_quarters(pb, layout, bits):
+    """256 tiles, of which workgroups take quarters, and 257 or more, of which they take the whole."""
+    g = np.random.default_rng(bits + 30)
+    for rows, cols in ((4092, 3), (4096, 512), (4100, 511), (2064, 513)):
+        print("pack", hex(layout), bits, rows, cols, flush=True)
+        check(pb, g.normal(0, 0.05, size=(rows, cols)).astype(np.float32), bits, layout)
+
+
 @pytest.mark.parametrize("bits", [1, 4, 8, 12])
 def test_clipping_search_with_and_without_histogram(pb, bits):
     g = np.random.default_rng(bits + 50)
