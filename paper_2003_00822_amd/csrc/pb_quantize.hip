@@ -12,9 +12,10 @@ namespace pb {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // The quantizers reduce over all weights before anything can be packed.  What those passes leave for the next launch
-// lives at the start of `packed`, which the packing kernel overwrites last (a packed matrix has at least 512 bytes, and at
-// least 1 KB per statistics block from two blocks on): 32 sums of the clipping search, then per block the partial
-// statistics and the partial sum of the +-1 code, then, if there is room, the histogram of the clipping search.
+// lives at the start of `packed`, which the packing kernel overwrites last: 32 sums of the clipping search, then per block the
+// partial statistics and the partial sum of the +-1 code (256 bytes and 24 per block), then, if there is room, the histogram of
+// the clipping search.  A packed matrix has at least 512 bytes, and with B blocks more than B - 1 KB: a bit for each of more
+// than 8192 (B - 1) weights.
 constexpr int kClipSteps = 32;
 constexpr int kClipBins = 4096;
 constexpr int kStatsFloats = 8192;      // weights that a block of the reductions takes at a time (32 per thread)
@@ -40,6 +41,7 @@ static Scratch scratch_of(void *packed, size_t bytes, size_t n, int blocks)
     s.lower = reinterpret_cast<double *>(s.abssum + blocks);
     s.upper = s.lower + kClipSteps;
     s.bins = reinterpret_cast<unsigned long long *>(s.upper + kClipSteps);
+    if ((size_t)(reinterpret_cast<char *>(s.lower) - static_cast<char *>(packed)) > bytes) s.clip = nullptr;   // (never: above)
     // (up to 2^18 weights the exact sums of all thresholds take less time than two more launches: whole call without / with
     // the histogram at 2^18 weights 25 / 25 us with 4 bits, 27 / 34 with 8, 34 / 40 with 16; at 420 000 28 / 26, 32 / 34 and
     // 37 / 43; at 2^20 36 / 26, 45 / 39 and 66 / 54.  Beyond 2^27 the fields of a workgroup's bins would overflow)
@@ -474,7 +476,7 @@ __device__ __forceinline__ void transpose_bytes(uint32_t (&x)[8])
 // it reads the 32 codes of its word and transposes them as bits, which delivers the words of eight bitlayers with 1.5
 // operations per weight (a ballot per bitlayer and 64 weights, with a select to keep it, took 0.6 operations per weight
 // and BITLAYER and stored 8 bytes at a time).  The stores of a bitlayer are contiguous over the threads.
-// PL: bytes of a stored code.  4096 x 4096, 8 bits: 15.8 us = 5.1 TB/s (55.6 us with the ballots and a division per weight).
+// PL: bytes of a stored code.  4096 x 4096, 8 bits: 15.8 us = 5.3 TB/s (55.6 us with the ballots and a division per weight).
 // ROWS: rows per wave; 4 take the whole tile, 1 takes a quarter of it, for matrices of few tiles (launch_quantize_pack).
 template <int PL, int ROWS>
 __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ W, uint32_t layout, int rows, int cols, int bits,
@@ -677,6 +679,7 @@ int launch_quantize_pack(const float *W, const Layout &L, int quantizer, uint32_
     const size_t want = (n + kStatsFloats - 1) / kStatsFloats;
     const int blocks = (int)(want < (size_t)kMaxStatsBlocks ? want : (size_t)kMaxStatsBlocks);
     const Scratch s = scratch_of(packed, packed_bytes(L), n, blocks);
+    if (!s.clip) return (int)hipErrorInvalidValue;
     const bool search = quantizer == PB_QUANT_CLIP_SEARCH;
     hipLaunchKernelGGL(k_stats, dim3(blocks), dim3(256), 0, st, W, n, search ? 1 : 0, s);
     if (quantizer == PB_QUANT_SIGN) hipLaunchKernelGGL(k_abs_sum, dim3(blocks), dim3(256), 0, st, W, n, s);
