@@ -14,6 +14,7 @@
 #include <c10/hip/HIPStream.h>
 
 #include <tuple>
+#include <type_traits>
 #include <utility>
 
 #include "pb.h"
@@ -237,22 +238,41 @@ PyObject *set_slow(PyObject *, PyObject *fns)
     Py_RETURN_NONE;
 }
 
-#define PB_FAST(E, ...) \
-    {kNames[E], reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&call<E, __VA_ARGS__>)), METH_FASTCALL | METH_KEYWORDS, nullptr}
+// as many arguments as the C function has, each convertible to the parameter in its place, and the stream as the last
+template <typename F>
+struct Params;
+template <typename... P>
+struct Params<int (*)(P...)> {
+    template <typename... A>
+    static constexpr bool take()
+    {
+        if constexpr (sizeof...(P) == sizeof...(A) + 1)
+            return std::is_invocable_v<int (*)(P...), decltype(std::declval<const A &>().get())..., void *>;
+        else
+            return false;
+    }
+};
+template <auto F, int E, typename... A>
+PyMethodDef fast()
+{
+    static_assert(Params<decltype(F)>::template take<A...>(), "not the arguments of the C function");
+    return {kNames[E], reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&call<E, A...>)), METH_FASTCALL | METH_KEYWORDS,
+            nullptr};
+}
 PyMethodDef kMethods[] = {
-    PB_FAST(kQuantizePack, In, Int, Int, Int, Bytes, Out),
-    PB_FAST(kQuantizePackDesc, In, Desc, Bytes, Out),
-    PB_FAST(kQuantizePackMode, In, Desc, Int, Bytes, Out),
-    PB_FAST(kUnpack, Bytes, Desc, Ints),
-    PB_FAST(kMatmul, Bytes, In, Desc, Int, In, Int, Out, Bytes),
-    PB_FAST(kMatmulStatic, Bytes, In, Desc, Int, In, Int, Out),
-    PB_FAST(kMatmulBiasAct, Bytes, In, Desc, Int, In, Int, InOrNone, Int, Out, Bytes),
-    PB_FAST(kMatmulAcc, Bytes, Desc, Int, In, Int, Longs, Bytes),
-    PB_FAST(kMatmulAccPairs, Bytes, Desc, Int, In, Int, Longs, Bytes),
-    PB_FAST(kActPrep, Desc, In, Int, Bytes),
-    PB_FAST(kMatmulPrepared, Bytes, In, Desc, Int, Int, Out, Bytes),
-    PB_FAST(kFixedPoint, Desc, In, Int, Ints, Bytes),
-    PB_FAST(kLstmCell, Bytes, In, Desc, Int, In, Int, In, In, InOrNone, Out, Out, Int, Bytes),
+    fast<&pb_quantize_pack, kQuantizePack, In, Int, Int, Int, Bytes, Out>(),
+    fast<&pb_quantize_pack_desc, kQuantizePackDesc, In, Desc, Bytes, Out>(),
+    fast<&pb_quantize_pack_mode, kQuantizePackMode, In, Desc, Int, Bytes, Out>(),
+    fast<&pb_unpack, kUnpack, Bytes, Desc, Ints>(),
+    fast<&pb_matmul, kMatmul, Bytes, In, Desc, Int, In, Int, Out, Bytes>(),
+    fast<&pb_matmul_static, kMatmulStatic, Bytes, In, Desc, Int, In, Int, Out>(),
+    fast<&pb_matmul_bias_act, kMatmulBiasAct, Bytes, In, Desc, Int, In, Int, InOrNone, Int, Out, Bytes>(),
+    fast<&pb_matmul_acc, kMatmulAcc, Bytes, Desc, Int, In, Int, Longs, Bytes>(),
+    fast<&pb_matmul_acc_pairs, kMatmulAccPairs, Bytes, Desc, Int, In, Int, Longs, Bytes>(),
+    fast<&pb_act_prep, kActPrep, Desc, In, Int, Bytes>(),
+    fast<&pb_matmul_prepared, kMatmulPrepared, Bytes, In, Desc, Int, Int, Out, Bytes>(),
+    fast<&pb_fixed_point, kFixedPoint, Desc, In, Int, Ints, Bytes>(),
+    fast<&pb_lstm_cell, kLstmCell, Bytes, In, Desc, Int, In, Int, In, In, InOrNone, Out, Out, Int, Bytes>(),
     {"linear", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&linear)), METH_FASTCALL, nullptr},
     {"bind", bind, METH_VARARGS, nullptr},
     {"set_slow", set_slow, METH_O, nullptr},

@@ -115,6 +115,84 @@ def test_native_and_python_calls_agree(pb):
     torch.cuda.synchronize()
 
 
+def test_python_functions_have_the_parameters_of_the_header(pb):
+    """Names and order, and the argument types that ctypes converts to."""
+    import ctypes
+    import inspect
+    import re
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    text = re.sub(r"/\*.*?\*/", "", open(os.path.join(root, "include", "pb.h")).read(), flags=re.S)
+    assert len(pb._NATIVE) == 13
+    for name in pb._NATIVE:
+        args = [re.sub(r"\s+", " ", a).strip() for a in re.search(r"\bint %s\(([^)]*)\)" % name, text).group(1).split(",")]
+        names = [re.search(r"(\w+)$", a).group(1) for a in args]
+        assert list(inspect.signature(pb._PYTHON[name]).parameters) == names, name
+        want = [ctypes.POINTER(pb.pb_desc) if "pb_desc *" in a else ctypes.c_void_p if "*" in a else ctypes.c_int for a in args]
+        assert getattr(pb.lib(), name).argtypes == want, name
+
+
+@pytest.mark.gpu
+def test_every_entry_point_by_keywords(pb):
+    """Keywords and an explicit stream go to the Python functions: the same results as the native calls, all thirteen."""
+    import inspect
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    H, I, N, bits, m = 12, 88, 3, 5, 4
+    R, C = 4 * H, I + H
+    normal = lambda *shape: torch.randn(shape, device="cuda", generator=g)   # noqa: E731
+    W, X, bias, h, c = normal(R, C), normal(N, C), normal(R), normal(N, H), normal(N, H)
+    W3 = normal(R, 2)
+    d, d2 = pb.pb_desc_init(R, C, bits), pb.pb_desc_init(R, 2, 2)
+    rows = pb.pb_desc_init_layout(R, C, bits, pb.PB_LAYOUT_ROWMAJOR_V1)
+    lin, lin_rows = pb.PackedLinear(W, bits, max_batch=N), pb.PackedLinear(W, bits, max_batch=N, layout=rows.layout)
+    prepared = pb.alloc_workspace(rows, N)
+    pb.pb_act_prep(rows, X, N, prepared)
+    p, s = lin.packed, lin.scales
+
+    def zeros(*shape, dtype=torch.float32):
+        return lambda: torch.zeros(shape, dtype=dtype, device="cuda")
+
+    def nbytes(n):
+        return zeros(n, dtype=torch.uint8)
+
+    work, codes = nbytes(lin.workspace.numel()), nbytes(p.numel())
+    # a callable makes a fresh buffer; the workspace (last but for pb_act_prep) is not a result
+    calls = {
+        "pb_quantize_pack": [W, R, C, bits, codes, zeros(bits)],
+        "pb_quantize_pack_desc": [W, d, codes, zeros(bits)],
+        "pb_quantize_pack_mode": [W3, d2, pb.PB_QUANT_SIGN, nbytes(pb.pb_packed_bytes(d2)), zeros(2)],
+        "pb_unpack": [p, d, zeros(R, C, dtype=torch.int32)],
+        "pb_matmul": [p, s, d, m, X, N, zeros(N, R), work],
+        "pb_matmul_static": [p, s, d, m, X, N, zeros(N, R)],
+        "pb_matmul_bias_act": [p, s, d, m, X, N, bias, pb.PB_ACT_RELU, zeros(N, R), work],
+        "pb_matmul_acc": [p, d, m, X, N, zeros(m, N, R, dtype=torch.int64), work],
+        "pb_matmul_acc_pairs": [p, d, m, X, N, zeros(m // 2, N, R, dtype=torch.int64), work],
+        "pb_act_prep": [rows, X, N, nbytes(prepared.numel())],
+        "pb_matmul_prepared": [lin_rows.packed, lin_rows.scales, rows, m, N, zeros(N, R), prepared],
+        "pb_fixed_point": [rows, X, N, zeros(N, C, dtype=torch.int32), work],
+        "pb_lstm_cell": [p, s, d, m, X[:, :I].contiguous(), I, h, c, bias, zeros(N, H), zeros(N, H), N, work],
+    }
+    assert sorted(calls) == sorted(pb._NATIVE)
+    side = torch.cuda.Stream()
+    for name, args in calls.items():
+        print(name, flush=True)
+        made = [i for i, a in enumerate(args) if callable(a)]
+        keep = [i for i in made if args[i] is not work]
+        names = list(inspect.signature(pb._PYTHON[name]).parameters)
+        native = [a() if callable(a) else a for a in args]
+        getattr(pb, name)(*native)
+        side.wait_stream(torch.cuda.current_stream())
+        for stream in (torch.cuda.current_stream(), side, side.cuda_stream):
+            with torch.cuda.stream(side):
+                byname = [a() if callable(a) else a for a in args]
+            side.synchronize()
+            getattr(pb, name)(stream=stream, **dict(zip(names, byname)))
+            torch.cuda.synchronize()
+            for i in keep:
+                assert native[i].view(torch.uint8).any(), (name, names[i])
+                assert torch.equal(native[i], byname[i]), (name, names[i])
+
+
 @pytest.mark.gpu
 def test_computed_attributes_stay_alive(pb):
     """A layer whose tensors are made on access: none of them may share memory with the output."""
