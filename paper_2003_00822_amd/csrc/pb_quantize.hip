@@ -42,9 +42,10 @@ static Scratch scratch_of(void *packed, size_t bytes, size_t n, int blocks)
     s.upper = s.lower + kClipSteps;
     s.bins = reinterpret_cast<unsigned long long *>(s.upper + kClipSteps);
     if ((size_t)(reinterpret_cast<char *>(s.lower) - static_cast<char *>(packed)) > bytes) s.clip = nullptr;   // (never: above)
-    // (up to 2^18 weights the exact sums of all thresholds take less time than two more launches: whole call without / with
-    // the histogram at 2^18 weights 25 / 25 us with 4 bits, 27 / 34 with 8, 34 / 40 with 16; at 420 000 28 / 26, 32 / 34 and
-    // 37 / 43; at 2^20 36 / 26, 45 / 39 and 66 / 54.  Beyond 2^27 the fields of a workgroup's bins would overflow)
+    // (up to 2^18 weights the exact sums of all thresholds take less time than two more launches, or as little: whole call
+    // without / with the histogram at 2^17 weights 19 / 19 us with 2 bits, 21 / 31 with 8, 22 / 31 with 16; at 2^18 22 / 21,
+    // 25 / 31 and 29 / 34.  Then few bits gain and many lose, at 420 000 26 / 22, 27 / 33 and 33 / 40; at 2^20 all gain, 33 / 23,
+    // 45 / 39 and 62 / 56.  Beyond 2^27 the fields of a workgroup's bins would overflow)
     const size_t end = (size_t)(reinterpret_cast<char *>(s.bins + kClipBins) - static_cast<char *>(packed));
     if (end > bytes || n <= (1u << 18) || n > (1u << 27)) s.lower = s.upper = nullptr;
     return s;
@@ -52,7 +53,7 @@ static Scratch scratch_of(void *packed, size_t bytes, size_t n, int blocks)
 
 // 32 weights per thread, all in flight together; weights past the end read as `pad`.  One way for full and partial blocks:
 // loads of 4 bytes each, with their bounds, for the last block took every pass over the weights 2 us more where their number is
-// no multiple of 8192 (363 x 361, whole call 12.1 -> 10.3 us with 8 bits, sign quantizer 18.3 -> 14.7; 3001 x 5003 32.1 -> 28.2).
+// no multiple of 8192 (363 x 361, whole call 9.9 -> 8.2 us with 8 bits, sign quantizer 13.6 -> 11.7; 3001 x 5003 32.2 -> 27.4).
 __device__ __forceinline__ void load_weights(const float *__restrict__ W, size_t n, size_t base, float pad, float (&w)[32])
 {
     const size_t left = n - base;
@@ -120,7 +121,7 @@ __device__ __forceinline__ Partial reduce_stats(float am, float hi, float lo)
 }
 
 // max |W|, max W and min W in one pass (Section 3.3: the step of every quantizer comes from these; fmaxf and fminf
-// drop NaN).  Bound: the read of W; 4096 x 4096: 11.8 us = 5.7 TB/s (43.7 us
+// drop NaN).  Bound: the read of W; 4096 x 4096: 11.5 us = 5.8 TB/s (43.7 us
 // with one load in flight per thread).
 // The blocks also clear the sums and the histogram of the clipping search, where they are used.
 __global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size_t n, int clip_search, Scratch s)
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(256) void k_stats(const float *__restrict__ W, size
 
 // the statistics of all blocks, in every thread of a workgroup.  All loads of up to 2048 blocks in flight (past the end the last
 // block's once more): one memory latency for 2048 blocks, which every kernel that needs the step waits for first (4096 x 4096,
-// 8 bits, whole call: 31.1 -> 29.5 us against one load after the other).
+// 8 bits, whole call: 1.6 us less than one load after the other).
 template <int WAVES>
 __device__ __forceinline__ Partial all_stats(const Scratch &s)
 {
@@ -247,9 +248,10 @@ __global__ __launch_bounds__(256) void k_abs_sum(const float *__restrict__ W, si
 // can be ruled out from a histogram, rigorously: inside a bin where q does not change and W - d_k q keeps its sign, the sum
 // of the errors follows from the number of weights and their sum; in any other bin |W - d_k q| changes by no more than W
 // does.  That bounds every sum from both sides (k_clip_hist, k_clip_bounds), and only the thresholds whose lower bound
-// does not exceed the smallest upper bound are summed exactly (k_clip_err): one to three of the 32 with 2 to 8 bits,
-// all of them with so many bits that a bin holds many steps (then 0.16 ms).  3001 x 5003, 4 bits, whole call: 2405 ->
-// 60 us, of which the histogram takes 19 (LDS atomics), statistics and packing 30.
+// does not exceed the smallest upper bound are summed exactly (k_clip_err): of N(0, s) weights 3001 x 5003, one or two of
+// the 32 with 2 to 5 bits, ten with 8, half of them from 10 bits on, where a bin holds many steps.  Whole call: 2405 -> 54 us
+// where one is left, of which the histogram takes 18 (LDS atomics), statistics, step and packing 29; 85 us where two are, 123
+// with 8 bits, 350 with 12 and 16.
 
 // the step of threshold k + 1
 __device__ __forceinline__ float clip_step(float M, int k, int bits)
@@ -476,7 +478,7 @@ __device__ __forceinline__ void transpose_bytes(uint32_t (&x)[8])
 // it reads the 32 codes of its word and transposes them as bits, which delivers the words of eight bitlayers with 1.5
 // operations per weight (a ballot per bitlayer and 64 weights, with a select to keep it, took 0.6 operations per weight
 // and BITLAYER and stored 8 bytes at a time).  The stores of a bitlayer are contiguous over the threads.
-// PL: bytes of a stored code.  4096 x 4096, 8 bits: 15.8 us = 5.3 TB/s (55.6 us with the ballots and a division per weight).
+// PL: bytes of a stored code.  4096 x 4096, 8 bits: 14.4 us = 5.8 TB/s (55.6 us with the ballots and a division per weight).
 // ROWS: rows per wave; 4 take the whole tile, 1 takes a quarter of it, for matrices of few tiles (launch_quantize_pack).
 template <int PL, int ROWS>
 __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ W, uint32_t layout, int rows, int cols, int bits,
@@ -585,7 +587,7 @@ __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ W, uint3
 // takes one tile: the blocks of all bitlayers go to LDS with one 16-byte load per lane, then a lane puts together four
 // adjacent columns of a row (a nibble of one word per bitlayer, spread to the low bits of four bytes by one 24-bit
 // multiplication, one accumulating shift per bitlayer) and stores them with 16 bytes, a wave 1 KB of one row.
-// 8192 x 8192, 8 bits: 69 us = 4.9 TB/s (594 us with a thread per
+// 8192 x 8192, 8 bits: 64 us = 5.2 TB/s (594 us with a thread per
 // element that fetched one word per bitlayer itself).
 // ROWS: rows per wave; 4 take the whole tile, 1 takes a quarter of it, for matrices of few tiles (launch_unpack): the words
 // of up to 16 bitlayers then come with one load.
@@ -691,8 +693,8 @@ int launch_quantize_pack(const float *W, const Layout &L, int quantizer, uint32_
         }
         // A workgroup takes 8192 weights, so that up to 2^21 of them leave compute units without one, or with one that has
         // all thresholds to sum: they are shared out until there are two workgroups per unit.  Whole call, one share / this
-        // rule: 2^16 weights 54 / 21 us with 4 bits, 198 / 24 with 12, 137 / 24 with 16; 2^20 weights 26 / 26, 91 / 54 and
-        // 89 / 56; from 2^22 on there is one share.
+        // rule: 2^16 weights 56 / 18 us with 4 bits, 203 / 20 with 12, 138 / 20 with 16; 2^20 weights 31 / 30, 104 / 54 and
+        // 98 / 56; from 2^22 on there is one share.
         int shares = 1;
         while (shares < kClipSteps && blocks * shares < 512) shares *= 2;
         hipLaunchKernelGGL(k_clip_err, dim3(blocks, shares), dim3(256), 0, st, W, n, L.bits, s);
