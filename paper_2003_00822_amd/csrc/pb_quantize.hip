@@ -181,7 +181,8 @@ __device__ __forceinline__ int quantize_code(float w, float d, int qmin, int qma
 // The division of quantize_code by a multiplication where that cannot change the code.  t = w * (1 / d) differs from the
 // rounded quotient by less than |t| 2^-22, so rint(t) is the code's rounding unless t is that close to a half-integer
 // (for |t| up to qmax + 2; beyond, both clamp).  `off` is the largest distance of the t's from their integers: above
-// `limit` the caller divides.
+// `limit` the caller divides: in k_pack, whose waves decide over 256 weights, one wave in 60 with 8 bits, one in 5 with 12 and
+// nearly all with 16.
 struct Quantizer {
     float d, inv, limit;
     int qmin, qmax;
