@@ -51,9 +51,10 @@ typedef enum pb_status {
 
 /* Packed layouts (opaque to the caller; pb_unpack reads either).
  * PB_LAYOUT_TILE16_V1   16-row x 512-column blocks in the order the matrix-core kernel streams them; the
- *                       default.  The product runs as FP4 matrix
- *                       instructions on the bitlayers and planes (two of each per operand element, as
- *                       base-4 digits), exact in fp32 accumulators.
+ *                       default.  For one vector the product runs as FP4 matrix
+ *                       instructions on the bitlayers and pairs of planes (base-4 digits), exact in fp32
+ *                       accumulators; for batches as 8-bit integer matrix instructions on whole weight codes and the
+ *                       bytes of the activations, exact in int32.
  * PB_LAYOUT_ROWMAJOR_V1 [bitlayer][row][word]; read by the AND + popcount kernel (Section 3.4 taken
  *                       literally), kept as the measured alternative. */
 #define PB_LAYOUT_ROWMAJOR_V1 0x50420001u
@@ -68,8 +69,8 @@ typedef enum pb_status {
  *                       of the even columns of a word in the block of bitlayer 2p, those of the odd columns in
  *                       the block of bitlayer 2p + 1; bitlayer 0 enters complemented; an odd number of
  *                       bitlayers is stored as the next even number, the last one paired with zeros, and
- *                       pb_packed_bytes says so).  The matrix-core kernel then builds a weight operand of two
- *                       bitlayers with six instead of ten operations: about 10 % faster from batch 16 on.
+ *                       pb_packed_bytes says so).  Whole weight codes are then put together with a sixth fewer
+ *                       operations.
  *                       Every call works on it (not pb_lstm_cell's single launch); with one vector it is slower than
  *                       PB_LAYOUT_TILE16_V1, because an odd bits_used reads one bitlayer more.  Chosen by the
  *                       caller (pb_desc_init_layout). */
@@ -149,7 +150,7 @@ int pb_unpack(const void *packed, const pb_desc *d, int32_t *q, void *stream);
  *   A_i[r] = sum_j c_j * popcount(row r of bitlayer i AND plane j)  (exact, int64; computed as
  *            AND + popcount or as an exact matrix product of the same bits, depending on the layout)
  *   Y[r]   = fp32( sum_{i < bits_used} scales[i] * A_i[r] * 2^-f )  (sum in fp64; where two adjacent
- *            scales are in the ratio of Algorithm 1 the tiled layouts may add the pair's integers first,
+ *            scales are in the ratio of Algorithm 1 the tiled layouts may add the bitlayers' integers first,
  *            see pb_matmul_acc_pairs: the same sum up to the fp64 rounding of its terms)
  * Only the first `bits_used` bitlayers (sign layer and the next bits_used-1)
  * are read: the accuracy / speed knob of the abstract.
@@ -165,8 +166,8 @@ int pb_matmul(const void *packed, const float *scales, const pb_desc *d, int bit
 /* pb_matmul for callers that cannot allocate device memory (code under HIP
  * graph capture, serving loops that own no buffers, harnesses that forbid
  * hipMalloc): the same kernels and the same result as pb_matmul, with the
- * workspace (bit planes and plane statistics of the activations, which only the
- * PB_LAYOUT_ROWMAJOR_V1 kernels use) in a device array of
+ * workspace (bit planes and plane statistics of the activations, or for batches on the
+ * tiled layouts their byte digits) in a device array of
  * PB_STATIC_SCRATCH_BYTES that the library holds on every GPU it runs on until
  * the process ends.  Allocates, frees and synchronises nothing.
  * PB_ESIZE if pb_workspace_bytes(d, batch) exceeds PB_STATIC_SCRATCH_BYTES
@@ -192,8 +193,7 @@ int pb_matmul_bias_act(const void *packed, const float *scales, const pb_desc *d
 int pb_matmul_acc(const void *packed, const pb_desc *d, int bits_used, const float *X, int batch, int64_t *A,
                   void *workspace, void *stream);
 
-/* The accumulators as the matrix-core kernel holds them when it multiplies two
- * adjacent bitlayers in one instruction (Section 3.4: bitlayers stacked in one
+/* The accumulators of pairs of adjacent bitlayers multiplied together (Section 3.4: bitlayers stacked in one
  * operation; the scales of Algorithm 1 halve from bitlayer to bitlayer and the
  * sign bitlayer has scale -2 s_1, so s_(i) A_(i) + s_(i+1) A_(i+1) =
  * s_(i+1) (+-2 A_(i) + A_(i+1))).  The units are the pairs (0, 1), (2, 3), ...
@@ -202,8 +202,8 @@ int pb_matmul_acc(const void *packed, const pb_desc *d, int bits_used, const flo
  * single one.
  * A: [(bits_used + 1) / 2][batch][rows] int64, written.  Tiled layouts only
  * (PB_EINVAL for PB_LAYOUT_ROWMAJOR_V1).  pb_matmul with more than one vector
- * takes this route by itself when scales[0] == -2 * scales[1] and scales[2p] ==
- * 2 * scales[2p + 1] hold for every pair, else it multiplies bitlayer by
+ * multiplies up to eight bitlayers together when scales[0] == -2 * scales[1] and
+ * scales[i] == 2 * scales[i + 1] hold for all the others, else it multiplies bitlayer by
  * bitlayer. */
 int pb_matmul_acc_pairs(const void *packed, const pb_desc *d, int bits_used, const float *X, int batch, int64_t *A,
                         void *workspace, void *stream);
@@ -212,9 +212,10 @@ int pb_matmul_acc_pairs(const void *packed, const pb_desc *d, int bits_used, con
  * to the same activations (or that time the halves separately):
  * pb_act_prep converts X to fixed point and writes its bit planes and plane
  * statistics into `workspace` (Algorithm 2, x_q = Int(x * 2^f), and the bitwise
- * transpose of Section 3.4); pb_matmul_prepared runs the product (AND +
- * popcount on PB_LAYOUT_ROWMAJOR_V1, the matrix-core kernel on the tiled
- * layouts, which then builds its operands from the planes) and the
+ * transpose of Section 3.4; for batches on the tiled layouts the bytes that the
+ * matrix instructions read); pb_matmul_prepared runs the product (AND +
+ * popcount on PB_LAYOUT_ROWMAJOR_V1, the matrix-core kernels on the tiled
+ * layouts) and the
  * scale-accumulation on planes left there by pb_act_prep.
  * The planes are laid out for the descriptor they were made with: the
  * descriptor of pb_matmul_prepared must have the same cols, LAYOUT, frac_bits
@@ -230,7 +231,7 @@ int pb_matmul_prepared(const void *packed, const float *scales, const pb_desc *d
 
 /* The fixed-point activations alone (Algorithm 2, x_q = Int(x * 2^f)), for
  * checking: xq [batch][cols] int32, written; workspace as for pb_matmul
- * (the bit planes are left in it). */
+ * (left in it: what pb_act_prep leaves). */
 int pb_fixed_point(const pb_desc *d, const float *X, int batch, int32_t *xq, void *workspace, void *stream);
 
 /* One LSTM cell step on top of pb_matmul (Sections 4.2-4.3: the LSTM's input

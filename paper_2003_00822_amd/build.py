@@ -36,7 +36,7 @@ FLAGS = [
 # preloaded into registers by the hardware when a wave starts; the compiler keeps a fallback entry that loads them
 # for firmware without the feature.
 FILE_FLAGS = {
-    "pb_mfma.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=12"],
+    "pb_mfma.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"],
 }
 
 

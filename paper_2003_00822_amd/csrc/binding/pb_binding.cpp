@@ -72,6 +72,17 @@ struct Int {
     int get() const { return v; }
 };
 
+struct Address {
+    void *v = nullptr;
+    bool load(PyObject *o)
+    {
+        if (!PyLong_CheckExact(o)) return false;
+        v = PyLong_AsVoidPtr(o);
+        if (!v && PyErr_Occurred()) { PyErr_Clear(); return false; }
+        return true;
+    }
+};
+
 struct Desc {
     pb_desc v;
     bool load(PyObject *o)
@@ -133,13 +144,14 @@ PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t nargs, PyObject *kw
     return PyObject_Vectorcall(g_slow[E], args, nargs, kwnames);
 }
 
-PyObject *s_rows, *s_cols, *s_bits, *s_max_batch, *s_desc, *s_packed, *s_scales, *s_workspace;
+PyObject *s_rows, *s_cols, *s_bits, *s_max_batch, *s_desc, *s_packed, *s_scales, *s_workspace, *s_home_stream;
 
 // The attributes of `self` that a call uses, held until it returns: one that is computed on access, or replaced by another
 // thread meanwhile, must not give its memory back before the launch.
 struct Held {
-    PyObject *o[8];
+    PyObject *o[9];
     int n = 0;
+    int workspace = 0;   // which of them
     ~Held() { while (n) Py_DECREF(o[--n]); }
     template <typename T>
     bool load(PyObject *self, PyObject *name, T &x)
@@ -161,13 +173,14 @@ PyObject *linear(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             Bytes packed, workspace;
             In scales, x;
             Out y;
-            Held held;   // (eight attributes at most)
+            Address home;
+            Held held;   // (nine attributes at most)
             PyObject *self = args[0];
             const at::Tensor &X = THPVariable_Unpack(args[1]);
             bool ok = x.load(args[1]) && held.load(self, s_rows, rows) && held.load(self, s_cols, cols) &&
                       held.load(self, s_max_batch, max_batch) && held.load(self, s_desc, d) &&
                       held.load(self, s_packed, packed) && held.load(self, s_scales, scales) &&
-                      held.load(self, s_workspace, workspace) &&
+                      held.load(self, s_workspace, workspace) && (held.workspace = held.n - 1, held.load(self, s_home_stream, home)) &&
                       (args[2] == Py_None ? held.load(self, s_bits, m) : m.load(args[2]) && m.v != 0);
             const int64_t n = X.numel();
             ok = ok && cols.v > 0 && n > 0 && n % cols.v == 0 && n / cols.v <= max_batch.v;
@@ -182,11 +195,21 @@ PyObject *linear(PyObject *, PyObject *const *args, Py_ssize_t nargs)
                 }
                 if (ok) {
                     void *stream = current_stream();
+                    const auto matmul = reinterpret_cast<decltype(&pb_matmul)>(g_fn[kMatmul]);
                     int rc;
-                    Py_BEGIN_ALLOW_THREADS
-                    rc = reinterpret_cast<decltype(&pb_matmul)>(g_fn[kMatmul])(packed.v, scales.v, &d.v, m.v, x.v, batch, y.v,
-                                                                               workspace.v, stream);
-                    Py_END_ALLOW_THREADS
+                    if (batch == 1 && d.v.layout != PB_LAYOUT_ROWMAJOR_V1 && d.v.layout != PB_LAYOUT_TILE16_PAIRS_V1) {
+                        Py_BEGIN_ALLOW_THREADS      // (one launch that leaves nothing in the workspace)
+                        rc = matmul(packed.v, scales.v, &d.v, m.v, x.v, batch, y.v, workspace.v, stream);
+                        Py_END_ALLOW_THREADS
+                    } else {
+                        // The call may be two launches, the first of which writes the workspace.  The holder's own serves the
+                        // stream it was made on, whose launches of other threads wait for the interpreter lock; on another
+                        // stream the call has one of its own.
+                        at::Tensor own;
+                        if (stream != home.v) own = at::empty_like(THPVariable_Unpack(held.o[held.workspace]));
+                        rc = matmul(packed.v, scales.v, &d.v, m.v, x.v, batch, y.v, own.defined() ? own.data_ptr() : workspace.v,
+                                    stream);
+                    }
                     if (rc != PB_OK) return status_result(rc, kNames[kMatmul]);
                     if (args[3] != Py_None) {
                         Py_INCREF(args[3]);
@@ -293,6 +316,7 @@ PyMODINIT_FUNC PyInit__binding()
     s_packed = PyUnicode_InternFromString("packed");
     s_scales = PyUnicode_InternFromString("scales");
     s_workspace = PyUnicode_InternFromString("workspace");
+    s_home_stream = PyUnicode_InternFromString("home_stream");
     PyObject *m = PyModule_Create(&kModule);
     if (m && PyModule_AddStringConstant(m, "BUILT_FOR", PB_BUILT_FOR) != 0) Py_CLEAR(m);   // (pb.py compares it)
     return m;

@@ -151,10 +151,15 @@ static int matmul_common(const void *packed, const float *scales, const pb_desc 
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (ep.bias && !aligned16(ep.bias)) return PB_EALIGN;
     if (pairs_out && L.cols > pb::kMaxColsPairs) return PB_ESIZE;
+    if (pb::takes_digits(L, batch, pairs_out))
+        return hip_status(pb::launch_imma(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
+                                          d->act_bits, X0, cols0, X1, cols1,
+                                          static_cast<char *>(workspace) + pb::ws_planes_off(L, batch), false, batch, Y,
+                                          reinterpret_cast<long long *>(A), pairs_out, ep, st));
     if (pb::is_tile16(L.layout))   // conversion, bit transpose, product and epilogue in one launch
         return hip_status(pb::launch_mfma(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
-                                          d->act_bits, X0, cols0, X1, cols1, nullptr, batch, Y,
-                                          reinterpret_cast<long long *>(A), pairs_out, ep, st));
+                                          d->act_bits, X0, cols0, X1, cols1, nullptr, Y,
+                                          reinterpret_cast<long long *>(A), ep, st));
     if (pairs_out) return PB_EINVAL;   // only the tiled layouts multiply bitlayer pairs
     char *ws = static_cast<char *>(workspace);
     int *meta = reinterpret_cast<int *>(ws + pb::ws_meta_off(L, batch));
@@ -229,6 +234,9 @@ int pb_act_prep(const pb_desc *d, const float *X, int batch, void *workspace, vo
     char *ws = static_cast<char *>(workspace);
     int *meta = reinterpret_cast<int *>(ws + pb::ws_meta_off(L, batch));
     uint32_t *planes = reinterpret_cast<uint32_t *>(ws + pb::ws_planes_off(L, batch));
+    if (pb::takes_digits(L, batch))
+        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, nullptr,
+                                            static_cast<hipStream_t>(stream)));
     return hip_status(pb::launch_prep(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta,
                                       nullptr, static_cast<hipStream_t>(stream)));
 }
@@ -247,10 +255,14 @@ int pb_matmul_prepared(const void *packed, const float *scales, const pb_desc *d
     char *ws = static_cast<char *>(workspace);
     const int *meta = reinterpret_cast<const int *>(ws + pb::ws_meta_off(L, batch));
     const uint32_t *planes = reinterpret_cast<const uint32_t *>(ws + pb::ws_planes_off(L, batch));
+    if (pb::takes_digits(L, batch))
+        return hip_status(pb::launch_imma(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
+                                          d->act_bits, nullptr, 0, nullptr, 0, ws + pb::ws_planes_off(L, batch), true,
+                                          batch, Y, nullptr, false, pb::Epilogue(), static_cast<hipStream_t>(stream)));
     if (pb::is_tile16(L.layout))
         return hip_status(pb::launch_mfma(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
-                                          d->act_bits, nullptr, 0, nullptr, 0, planes, batch, Y, nullptr, false,
-                                          pb::Epilogue(), static_cast<hipStream_t>(stream)));
+                                          d->act_bits, nullptr, 0, nullptr, 0, planes, Y, nullptr, pb::Epilogue(),
+                                          static_cast<hipStream_t>(stream)));
     return hip_status(pb::launch_matvec(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
                                         planes, meta, batch, Y, nullptr, static_cast<hipStream_t>(stream)));
 }
@@ -267,6 +279,9 @@ int pb_fixed_point(const pb_desc *d, const float *X, int batch, int32_t *xq, voi
     char *ws = static_cast<char *>(workspace);
     int *meta = reinterpret_cast<int *>(ws + pb::ws_meta_off(L, batch));
     uint32_t *planes = reinterpret_cast<uint32_t *>(ws + pb::ws_planes_off(L, batch));
+    if (pb::takes_digits(L, batch))
+        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, xq,
+                                            static_cast<hipStream_t>(stream)));
     return hip_status(pb::launch_prep(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta, xq,
                                       static_cast<hipStream_t>(stream)));
 }

@@ -1,0 +1,312 @@
+// Internal: what the two product kernels on the 8-bit integer matrix cores share (pb_imma.hip, pb_imma_tile.hip).
+//
+// The product of Algorithm 2 as whole weight codes times the bytes of the fixed-point activations on the 8-bit integer
+// matrix cores.
+//
+// The bitlayers of a weight matrix with the scales of Algorithm 1 (each half the one before, the sign bitlayer minus
+// twice its neighbour) are the two's-complement bits of one integer code, so
+//     sum_i scales[i] A_i = scales[last] * sum_c code[c] x_q[c]
+// and up to eight bitlayers are multiplied at once: eight packed words become the codes of 32 columns (a transpose of
+// 8 x 8 bits, 48 operations of the vector ALU) and V_MFMA_I32_16X16X64_I8 multiplies them with the bytes of x_q.
+// A 32-bit x_q is four byte digits: against the sixteen base-4 digits and bitlayer pairs of the FP4 form that is 4
+// products per weight and activation instead of 64, at half the rate per product.
+//
+// Digits.  The top byte of x_q is signed as it stands; a lower byte u enters as s = u - 128 (u ^ 0x80 read as signed), so
+//     x_q = sum_d 256^d s_d + K,   K = 0x808080 (four bytes), 0x80 (two), 0 (one),
+// and K * sum_c code[c] is added per weight row: one more matrix instruction per weight operand, with an operand of
+// ones, delivers that sum.  |s_d code| <= 2^14, so a sum over all 32768 columns stays below 2^30: int32 is exact.
+//
+// Groups.  A group of bitlayers [f, e) is one code: bitlayer i stands at slot i (counted from bit 7 down) in the first
+// group, which may hold eight, and at slot i - f + 2 in the later ones, which hold up to six (the sign bit and the one
+// below it stay clear).  Scales that do not halve are groups of one bitlayer each; so are the sums that pb_matmul_acc asks for,
+// and groups of two those of pb_matmul_acc_pairs.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "pb_device.h"
+#include "pb_kernels.h"
+
+namespace pb {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// Where the activations come from: row n = [X0[n][0..cols0) ; X1[n][0..cols1)], fp32.
+struct ActSource {
+    const float *X0, *X1;
+    int cols0, cols1;
+    int batch;
+    float fscale;       // 2^frac_bits
+    int imin, imax;     // range of the act_bits-bit fixed-point values
+};
+
+// An offset beyond every buffer: a load there returns 0 (buffer loads are range-checked lane by lane)
+constexpr int kNowhere = 0x7FFFFFF0;
+
+// The columns c + 8 b + r (b, r = 0..3; c a multiple of 4) of vector n as they are in memory; 0 beyond the ends.
+// `end` (the same in all lanes) is beyond every column that the wave asks for.
+__device__ __forceinline__ void load_columns(const ActSource &s, int n, int c, int end, u32x4 (&v)[4])
+{
+    const bool live = n < s.batch;
+    const __amdgpu_buffer_rsrc_t r0 = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(s.X0), 0, (int)((uint32_t)s.batch * (uint32_t)s.cols0 * 4u), 0x00020000);
+    const int off = (n * s.cols0 + c) * 4;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+        v[b] = __builtin_amdgcn_raw_buffer_load_b128(r0, live && c + 8 * b < s.cols0 ? off + 32 * b : kNowhere, 0, 0);
+    if ((s.cols0 & 3) && end > s.cols0) {   // (four columns that reach into the next row)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[b][r] = c + 8 * b + r < s.cols0 ? v[b][r] : 0u;
+    }
+    if (s.X1 && end > s.cols0) {
+        const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(s.X1), 0, (int)((uint32_t)s.batch * (uint32_t)s.cols1 * 4u), 0x00020000);
+        const int c1 = c - s.cols0, off1 = (n * s.cols1 + c1) * 4;
+        if ((s.cols0 & 3) == 0) {   // four columns lie in one part
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int cb = c1 + 8 * b;
+                const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(
+                    r1, live && cb >= 0 && cb < s.cols1 ? off1 + 32 * b : kNowhere, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[b][r] |= cb + r < s.cols1 ? w[r] : 0u;
+            }
+        } else {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int cb = c1 + 8 * b + r;
+                    v[b][r] |= __builtin_amdgcn_raw_buffer_load_b32(
+                        r1, live && cb >= 0 && cb < s.cols1 ? off1 + 32 * b + 4 * r : kNowhere, 0, 0);
+                }
+        }
+    }
+}
+
+__device__ __forceinline__ void convert_columns(const ActSource &s, u32x4 (&v)[4])
+{
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            v[b][r] = (uint32_t)to_fixed_point<true>(__uint_as_float(v[b][r]), s.fscale, s.imin, s.imax);
+}
+
+// Sixteen fixed-point values, v[b][r] = column 8 b + r, -> their byte digits: word r of out[d] holds digit d of the columns r,
+// 8 + r, 16 + r, 24 + r, the order in which weight_codes() leaves the codes of 32 columns.
+template <int ND>
+__device__ __forceinline__ void byte_digits(const u32x4 (&v)[4], u32x4 (&out)[ND])
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if constexpr (ND == 1) {
+            const uint32_t a = __builtin_amdgcn_perm(v[1][r], v[0][r], 0x0C0C0400u);
+            const uint32_t b = __builtin_amdgcn_perm(v[3][r], v[2][r], 0x0C0C0400u);
+            out[0][r] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+        } else {
+            const uint32_t a = __builtin_amdgcn_perm(v[1][r], v[0][r], 0x05010400u);
+            const uint32_t b = __builtin_amdgcn_perm(v[3][r], v[2][r], 0x05010400u);
+            out[0][r] = __builtin_amdgcn_perm(b, a, 0x05040100u) ^ 0x80808080u;
+            out[1][r] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+            if constexpr (ND == 4) {
+                out[1][r] ^= 0x80808080u;
+                const uint32_t c = __builtin_amdgcn_perm(v[1][r], v[0][r], 0x07030602u);
+                const uint32_t d = __builtin_amdgcn_perm(v[3][r], v[2][r], 0x07030602u);
+                out[2][r] = __builtin_amdgcn_perm(d, c, 0x05040100u) ^ 0x80808080u;
+                out[3][r] = __builtin_amdgcn_perm(d, c, 0x07060302u);
+            }
+        }
+    }
+}
+
+// (hi & mask) | (lo & ~mask): one V_BFI_B32
+__device__ __forceinline__ uint32_t mix(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
+
+// Four words of adjacent slots (p[0] the highest bit) -> four words of 4-bit codes: nibble n of v[k] holds the bits
+// p[0][c] p[1][c] p[2][c] p[3][c] of column c = 4 n + k.  IL: (p[0], p[1]) and (p[2], p[3]) are the even and the
+// odd columns' digits of a bitlayer pair already, one exchange less.
+template <bool IL>
+__device__ __forceinline__ void nibble_codes(const uint32_t (&p)[4], uint32_t (&v)[4])
+{
+    uint32_t eh, oh, el, ol;
+    if constexpr (IL) {
+        eh = p[0]; oh = p[1]; el = p[2]; ol = p[3];
+    } else {
+        eh = mix(0xAAAAAAAAu, p[0] << 1, p[1]);
+        oh = mix(0x55555555u, p[1] >> 1, p[0]);
+        el = mix(0xAAAAAAAAu, p[2] << 1, p[3]);
+        ol = mix(0x55555555u, p[3] >> 1, p[2]);
+    }
+    v[0] = mix(0xCCCCCCCCu, eh << 2, el);
+    v[2] = mix(0x33333333u, el >> 2, eh);
+    v[1] = mix(0xCCCCCCCCu, oh << 2, ol);
+    v[3] = mix(0x33333333u, ol >> 2, oh);
+}
+
+// The words of 4 Q slots (slot 0 = bit 7) of 32 columns -> their codes: byte b of lo[k] is the code of column 8 b + k, byte b of
+// hi[k] that of column 8 b + 4 + k
+template <int Q, bool IL>
+__device__ __forceinline__ void weight_codes(const uint32_t (&w)[4 * Q], v4i &lo, v4i &hi)
+{
+    uint32_t a[4];
+    {
+        const uint32_t p[4] = {w[0], w[1], w[2], w[3]};
+        nibble_codes<IL>(p, a);
+    }
+    if constexpr (Q == 2) {
+        uint32_t b[4];
+        const uint32_t p[4] = {w[4], w[5], w[6], w[7]};
+        nibble_codes<IL>(p, b);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            lo[k] = (int)mix(0xF0F0F0F0u, a[k] << 4, b[k]);
+            hi[k] = (int)mix(0x0F0F0F0Fu, b[k] >> 4, a[k]);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            lo[k] = (int)((a[k] << 4) & 0xF0F0F0F0u);
+            hi[k] = (int)(a[k] & 0xF0F0F0F0u);
+        }
+    }
+}
+
+struct I8Args {
+    const uint32_t *packed;
+    uint32_t packed_bytes;               // (below 2^32)
+    uint32_t layer_step, round_step;     // bytes from one bitlayer of a row tile to the next, from one row tile to the next
+    int rounds_per_wg;                   // row tiles per workgroup
+    int rt_count, cq;
+    int m;                               // bitlayers to accumulate
+    int chunks_per_wave, stage_rows;     // (k_i8) chunks of 512 columns per wave, digit rows staged per tile
+    const uint8_t *digits;               // prepared byte digits (not FUSED)
+    uint32_t digits_bytes;
+    ActSource act;
+    const float *scales;
+    float *Y;
+    long long *A;
+    int pairs_out;
+    const float *bias;
+    const float *c_prev;
+    float *h_out, *c_out;
+    int relu;
+    int gate_h;
+    int R;
+    double out_scale;
+};
+
+// What a kernel does with the sums: store Y (bias and ReLU first), update the LSTM cell, store the sums themselves
+enum { kStore = 0, kCell = 1, kSums = 2 };
+
+// A group of bitlayers [f, e): its last bitlayer stands at `slot`, its sum counts `scale`
+struct Group { int f, e, slot; bool first, last; double scale; };
+__device__ __forceinline__ Group make_group(const I8Args &a, int f, int e, const float *scales)
+{
+    Group g;
+    g.f = f; g.e = e;
+    g.slot = e - 1 - ((f & ~1) == 0 ? 0 : (f & ~1) - 2);
+    g.first = f == 0;
+    g.last = e == a.m;
+    g.scale = 0.0;
+    if (!a.A) {
+        const double s = (double)scales[e - 1];
+        g.scale = ldexp(g.slot == 0 ? -s : s, g.slot - 7);
+    }
+    return g;
+}
+
+// The bias of packed row `prow` (0 without one)
+__device__ __forceinline__ float bias_of(const I8Args &a, int prow)
+{
+    const int row = a.gate_h ? gates_matrix_row(prow, a.gate_h) : prow;
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.bias), 0, a.R * 4, 0x00020000);
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, row >= 0 && row < a.R ? row * 4 : kNowhere, 0, 0));
+}
+
+// What follows the product for one tile of sixteen digit rows and sixteen weight rows: d = the four registers of this lane,
+// the digits of its 4 >> nds vectors n, n + 1, .. (1 << nds digits each); sum1 = sum of the codes of its row.
+// z: this lane's fp64 sums of the groups before (64 apart from vector to vector), read unless g.first, written unless g.last.
+template <int EPI>
+__device__ __forceinline__ void finish(const I8Args &a, const Group &g, int lane, int prow, int n, int nds, const int (&d)[4],
+                                       int sum1, float bias_row, double *z)
+{
+    const int row = a.gate_h ? gates_matrix_row(prow, a.gate_h) : prow;
+    const bool row_ok = row >= 0 && row < a.R;
+    const int nd = 1 << nds, vpl = 4 >> nds;
+    const int offset = nds == 2 ? 0x808080 : (nds == 1 ? 0x80 : 0);
+    if constexpr (EPI == kSums) {
+        for (int p = 0; p < vpl; ++p) {
+            long long v = (long long)offset * sum1;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v += (c >> nds) == p ? (long long)d[c] << (8 * (c & (nd - 1))) : 0ll;
+            v >>= 7 - g.slot;
+            if (g.slot == 0) v = -v;   // (the sign bitlayer by itself)
+            if (row_ok && n + p < a.act.batch)
+                a.A[((size_t)(a.pairs_out ? g.f / 2 : g.f) * a.act.batch + n + p) * (size_t)a.R + row] = v;
+        }
+        return;
+    }
+    const double dd[4] = {(double)d[0], (double)d[1], (double)d[2], (double)d[3]};
+    const double base = (double)offset * (double)sum1;
+    for (int p = 0; p < vpl; ++p) {
+        const bool live = row_ok && n + p < a.act.batch;
+        float c_old = 0.0f;
+        if constexpr (EPI == kCell) {
+            const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.c_prev), 0,
+                                                                                a.act.batch * a.gate_h * 4, 0x00020000);
+            c_old = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                rc, live && (lane & 3) == 0 ? ((n + p) * a.gate_h + row) * 4 : kNowhere, 0, 0));
+        }
+        // (every part is an integer below 2^53 and exact; the last step rounds once if the sum is beyond)
+        double v = base;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const double weight = (c >> nds) == p ? (double)(1 << (8 * (c & (nd - 1)))) : 0.0;   // (the same in all lanes)
+            v = fma(weight, dd[c], v);
+        }
+        v *= g.scale;
+        if (!g.first) v += z[p * 64];
+        if (!g.last) {
+            z[p * 64] = v;
+            continue;
+        }
+        float y = (float)(v * a.out_scale);
+        if (a.bias) y += bias_row;
+        if constexpr (EPI == kCell) {
+            float cn, hn;
+            lstm_quad(y, lane, c_old, &cn, &hn);
+            if ((lane & 3) == 0 && live) {
+                const size_t at = (size_t)(n + p) * a.gate_h + (size_t)row;
+                a.c_out[at] = cn;
+                a.h_out[at] = hn;
+            }
+        } else {
+            if (a.relu) y = fmaxf(y, 0.0f);
+            if (live) a.Y[(size_t)(n + p) * a.R + row] = y;
+        }
+    }
+}
+
+// Groups of bitlayers of a call that accumulates m of them with the scales of Algorithm 1 (at most four slots: one quad of words)
+inline int i8_groups(int m)
+{
+    const int first = m <= 4 ? 4 : 8, later = first - 2;
+    return m <= first ? 1 : 1 + (m - first + later - 1) / later;
+}
+
+// The kernel for many digit rows (pb_imma_tile.hip): its shapes (waves along the digit rows, column slots, tiles of sixteen
+// digit rows per wave), the row tiles that a workgroup does, its launch
+struct TileShape { int wm, nt, tm; };
+constexpr int kTileShapes = 3;
+constexpr TileShape kTile[kTileShapes] = {{4, 4, 2}, {8, 8, 2}, {8, 8, 4}};
+inline int tile_rows(const TileShape &t, int m, bool sums)
+{
+    const int groups = sums ? t.nt : i8_groups(m);
+    return groups >= t.nt ? 1 : t.nt / groups;
+}
+int launch_imma_tile(int shape, const I8Args &a, int nd, bool il, hipStream_t st);
+
+}  // namespace pb

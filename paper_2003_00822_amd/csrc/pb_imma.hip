@@ -1,0 +1,518 @@
+// The product of Algorithm 2 for batches, and for the layout that stores bitlayer pairs, on the 8-bit integer matrix cores
+// (see pb_imma.h for the arithmetic): the activations as byte digits, the kernel for few digit rows, and the choice
+// between it and the kernel for many.
+#include <stdlib.h>
+
+#include "pb_imma.h"
+
+namespace pb {
+
+// The activations as byte digits in memory, for the calls that read them more than once: per vector and chunk of 512
+// columns ND * 512 bytes, [t = word % 4][h][kb = word / 4][digit][16 bytes], the 16 bytes being the columns 8 b + 4 h + r of the
+// word.  A matrix operand (t, h) is then ND * 64 bytes of every vector, next to each other.
+// A wave does one chunk of two vectors: lane 32 v + 2 word + h.
+template <int ND>
+__global__ __launch_bounds__(256) void k_digits(ActSource s, int cq, uint8_t *__restrict__ digits,
+                                                int32_t *__restrict__ xq_out)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int q = blockIdx.x;
+    const int n = ((int)blockIdx.y * 4 + wave) * 2 + (lane >> 5);
+    const int word = (lane >> 1) & 15, h = lane & 1;
+    const int c = 512 * q + 32 * word + 4 * h;
+    u32x4 v[4];
+    load_columns(s, n, c, 512 * (q + 1), v);
+    if (n >= s.batch) return;
+    convert_columns(s, v);
+    if (xq_out) {
+        const int cols = s.cols0 + s.cols1;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (c + 8 * b + r < cols) xq_out[(size_t)n * cols + c + 8 * b + r] = (int32_t)v[b][r];
+    }
+    u32x4 out[ND];
+    byte_digits<ND>(v, out);
+    u32x4 *dst = reinterpret_cast<u32x4 *>(digits + ((size_t)n * cq + q) * (ND * 512)) +
+                 ((word & 3) * 2 + h) * (ND * 4) + (word >> 2) * ND;
+#pragma unroll
+    for (int d = 0; d < ND; ++d) dst[d] = out[d];
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+
+// Waves of a workgroup at most: sixteen have 128 registers each, which four tiles of digit rows exceed
+__host__ __device__ constexpr int stream_waves(int tm) { return tm >= 4 ? 8 : 16; }
+
+// Bytes of one staged operand of `rows` digit rows (64 each, and 16 more so that the eight operands that a group of eight
+// lanes writes to start in different banks); a tile of a chunk has eight of them
+__host__ __device__ inline int stage_operand(int rows) { return rows * 64 + 16; }
+
+// Few digit rows (one or two tiles of sixteen), or small matrices: a wave owns a slice of the columns and turns the words of row
+// tile after row tile into codes in its registers; the slices of a row meet in LDS once per row tile.
+//   FUSED: the activations are converted in this launch.  Every wave leaves the digits of its slice in LDS, in the order in
+//   which the matrix instructions read them, and keeps reading them from there.  Else they come from memory (k_digits).
+// Bound: latencies at the small end (launch, activations, weights, barrier), the weight stream at the large end.  The words of
+// the next unit are requested before this one is multiplied: 8 KB in flight per wave, sixteen waves.  Turning the words of a unit
+// into codes takes 180 operations of the vector ALU, its products 16 (one tile) matrix instructions.
+// In a graph, us per call, against the FP4 form that this replaces (two bitlayers and two planes per operand):
+// 1024 x 1024, 8 bitlayers, 16 vectors 7.2 -> 4.4; 4096 x 4096, 4 vectors 7.9 -> 5.9; 8192 x 8192, 4 vectors 17.2 -> 14.8; 135 x 69, 7
+// bitlayers, 113 vectors 14.4 -> 4.9; 2002 x 5817, one bitlayer, 2 vectors 5.2 -> 5.4 (the worst of 170).
+
+template <int ND, int Q, bool IL, int TM, bool FUSED, int EPI, int POLICY>
+__global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
+{
+    constexpr int VPT = 16 / ND;            // vectors per tile of sixteen digit rows
+    constexpr int VPL = 4 / ND;             // vectors per lane of a result: its four registers are the digits of these
+    constexpr bool ONES = ND > 1;
+    __shared__ int s_sum[2][TM * 4][64];
+    __shared__ int s_ones[3][64];           // sums of the codes, per row
+    __shared__ double s_z[TM * VPL][64];
+    __shared__ float s_scales[PB_MAX_BITS];
+    extern __shared__ __align__(16) unsigned char stage[];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nwaves = (a.cq + a.chunks_per_wave - 1) / a.chunks_per_wave;   // = blockDim.x / 64
+    const int q0 = wave * a.chunks_per_wave;
+    const int nq = min(a.chunks_per_wave, a.cq - q0);      // >= 1 by construction
+    const int n0 = blockIdx.y * (TM * VPT);
+    const int rt0 = blockIdx.x * a.rounds_per_wg;
+    const int rounds = min(a.rounds_per_wg, a.rt_count - rt0);   // >= 1 by construction
+    const int m = a.m;
+    const int kb = lane >> 4, j = lane & 15;
+
+    // ---- the weight stream: units (round, group of bitlayers, chunk) ----
+    bool merged = EPI != kSums;             // (until the scales are known)
+    struct Unit { int r, f, e, i; };
+    auto group_end = [&](int f) {
+        const int size = merged ? (f == 0 ? 4 * Q : 4 * Q - 2) : (a.pairs_out ? 2 : 1);
+        return min(m, f + size);
+    };
+    // the next unit; true if it belongs to another group of bitlayers
+    auto advance = [&](Unit &u) {
+        if (++u.i < nq) return false;
+        u.i = 0;
+        const int f = u.f;
+        u.f = u.e;
+        if (u.f == m) { u.f = 0; ++u.r; }
+        u.e = group_end(u.f);
+        return u.f != f;
+    };
+    const char *base = reinterpret_cast<const char *>(a.packed) + (size_t)rt0 * a.round_step;
+    const uint32_t avail = (uint32_t)(a.packed_bytes - (size_t)rt0 * a.round_step);
+    // bitlayer of slot 0 of a group: the group starts at slot 0 (even bitlayer 0) or slot 2
+    auto slot0_layer = [](const Unit &u) { return (u.f & ~1) == 0 ? 0 : (u.f & ~1) - 2; };
+    // of the group being requested: the records that the descriptor of a slot shows (an absent slot has none: the load returns
+    // 0 and moves no data); of the group being multiplied: (IL) which of the two bits of a pair's digits belong to it
+    uint32_t records[4 * Q], mask[2 * Q];
+    auto request_group = [&](const Unit &u) {
+        const int l0 = slot0_layer(u);
+#pragma unroll
+        for (int s = 0; s < 4 * Q; ++s) {
+            const int l = l0 + s, lu = l0 + (s & ~1);
+            records[s] = (IL ? lu + 1 >= u.f && lu < u.e : l >= u.f && l < u.e) ? avail : 0u;
+        }
+    };
+    auto multiply_group = [&](const Unit &u) {
+        const int l0 = slot0_layer(u);
+#pragma unroll
+        for (int p = 0; p < 2 * Q; ++p) {
+            const int l = l0 + 2 * p;
+            mask[p] = (l >= u.f && l < u.e ? 0xAAAAAAAAu : 0u) | (l + 1 >= u.f && l + 1 < u.e ? 0x55555555u : 0u);
+        }
+    };
+    u32x4 ring[2][4 * Q];
+    auto issue = [&](u32x4 (&dst)[4 * Q], const Unit &u) {
+        const bool ok = u.r < rounds;
+        const uint32_t off = (uint32_t)u.r * a.round_step + (uint32_t)(q0 + u.i) * 1024u + (uint32_t)slot0_layer(u) * a.layer_step;
+#pragma unroll
+        for (int s = 0; s < 4 * Q; ++s) {
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, ok ? (int)records[s] : 0, 0x00020000);
+            dst[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, (int)(off + (uint32_t)s * a.layer_step), POLICY);
+        }
+    };
+    // Layer scales, lane i holds scales[i] and the next one (range-checked: none without scales)
+    float scv = 0.0f, scn = 0.0f;
+    {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.scales), 0,
+                                                                            a.scales ? m * 4 : 0, 0x00020000);
+        scv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0));
+        scn = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + 4, 0, 0));
+    }
+    Unit ld = {0, 0, group_end(0), 0};
+    request_group(ld);
+
+    for (int i = threadIdx.x; i < 2 * TM * 4 * 64; i += nwaves * 64) (&s_sum[0][0][0])[i] = 0;
+    if (ONES)
+        for (int i = threadIdx.x; i < 3 * 64; i += nwaves * 64) (&s_ones[0][0])[i] = 0;
+
+    // ---- the digit rows of this wave's chunks ----
+    const int operand = stage_operand(a.stage_rows), kbytes = a.stage_rows * 16;
+    unsigned char *const my_stage = stage + q0 * TM * 8 * operand;
+    if constexpr (FUSED) {
+        // two vectors at a time (lane 32 v + 2 word + h, as in k_digits), the next two on their way meanwhile
+        const int word = (lane >> 1) & 15, h = lane & 1, vb = lane >> 5;
+        const int pairs = min(TM * VPT / 2, (a.act.batch - n0 + 1) / 2), total = pairs * nq;
+        const int c0 = 512 * q0 + 32 * word + 4 * h;
+        u32x4 v[4], next[4];
+        load_columns(a.act, n0 + vb, c0, 512 * (q0 + 1), v);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(ring[0], ld);
+        __builtin_amdgcn_sched_barrier(0);
+        int i = 0, p = 0;
+#pragma unroll 1
+        for (int k = 0; k < total; ++k) {
+            int i2 = i, p2 = p + 1;
+            if (p2 == pairs) { p2 = 0; ++i2; }
+            if (k + 1 < total) load_columns(a.act, n0 + 2 * p2 + vb, c0 + 512 * i2, 512 * (q0 + i2 + 1), next);
+            convert_columns(a.act, v);
+            u32x4 out[ND];
+            byte_digits<ND>(v, out);
+            const int tm = p / (VPT / 2), g = p % (VPT / 2);
+            unsigned char *dst = my_stage + ((i * TM + tm) * 8 + (word & 3) * 2 + h) * operand + (word >> 2) * kbytes +
+                                 (2 * g + vb) * ND * 16;
+#pragma unroll
+            for (int d = 0; d < ND; ++d) reinterpret_cast<u32x4 *>(dst)[d] = out[d];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) v[b] = next[b];
+            i = i2; p = p2;
+        }
+    } else {
+        issue(ring[0], ld);
+    }
+    if (wave == 0 && lane < PB_MAX_BITS) s_scales[lane] = scv;
+    if (EPI != kSums) {
+        const bool off = lane + 1 < m && !(scv == (lane == 0 ? -2.0f : 2.0f) * scn);
+        merged = __builtin_amdgcn_ballot_w64(off) == 0;
+        if (!merged) {   // the first unit was requested as a whole group
+            ld.e = group_end(0);
+            request_group(ld);
+            issue(ring[0], ld);
+        }
+    }
+    __syncthreads();   // (the sums are zero)
+
+    // prepared digits: lane 16 kb + row of an operand reads the bytes of digit row % ND of vector row / ND
+    const int dvec = n0 + j / ND;
+    const uint32_t dlane = (uint32_t)(kb * ND + j % ND) * 16u;
+    const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.digits), 0,
+                                                                        (int)a.digits_bytes, 0x00020000);
+    uint32_t doff[TM];
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+        const int n = dvec + tm * VPT;
+        doff[tm] = n < a.act.batch ? (uint32_t)n * (uint32_t)a.cq * (ND * 512u) + dlane : (uint32_t)kNowhere;
+    }
+    // staged digits (rows beyond the staged ones belong to no vector: any digits do)
+    const int staged = kb * kbytes + min(j, a.stage_rows - 1) * 16;
+    u32x4 areg[2][TM];
+    auto load_digits = [&](u32x4 (&dst)[TM], int i, int th) {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            if constexpr (FUSED)
+                dst[tm] = *reinterpret_cast<const u32x4 *>(my_stage + ((i * TM + tm) * 8 + th) * operand + staged);
+            else
+                dst[tm] = __builtin_amdgcn_raw_buffer_load_b128(rd, (int)(doff[tm] + th * (ND * 64)),
+                                                                (int)((uint32_t)(q0 + i) * (ND * 512u)), 0);
+        }
+    };
+
+    Unit u = ld;
+    multiply_group(u);
+    int sets = 0;          // (round, group) pairs multiplied so far
+    int turn = 0;          // the wave that finishes the first tile of a row tile
+    v4i acc[TM], ones;
+    float bias_row = 0.0f;
+    const v4i one = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    load_digits(areg[0], 0, 0);
+    while (u.r < rounds) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (u.r < rounds) {
+                if (advance(ld)) request_group(ld);
+                // (the bias is requested before the next weights: a wait for it does not wait for them)
+                if (a.bias && u.i == nq - 1) bias_row = bias_of(a, (rt0 + u.r) * kTileRows + j);
+                issue(ring[k ^ 1], ld);
+                if (u.i == 0) {
+                    ones = v4i{0, 0, 0, 0};
+#pragma unroll
+                    for (int tm = 0; tm < TM; ++tm) acc[tm] = v4i{0, 0, 0, 0};
+                }
+                const uint32_t flip = u.f < 2 ? 0xAAAAAAAAu : 0u;   // (IL) the sign bitlayer is stored complemented
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    uint32_t w[4 * Q];
+#pragma unroll
+                    for (int s = 0; s < 4 * Q; ++s) {
+                        w[s] = ring[k][s][t];
+                        if constexpr (IL) {
+                            if (s < 2) w[s] ^= flip;
+                            w[s] &= mask[s / 2];
+                        }
+                    }
+                    v4i b[2];
+                    weight_codes<Q, IL>(w, b[0], b[1]);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        // the operands of the next step are requested before this step's products
+                        if (t < 3 || h == 0) load_digits(areg[h ^ 1], u.i, t * 2 + h + 1);
+                        else load_digits(areg[0], ld.i, 0);
+                        if constexpr (ONES) ones = __builtin_amdgcn_mfma_i32_16x16x64_i8(one, b[h], ones, 0, 0, 0);
+#pragma unroll
+                        for (int tm = 0; tm < TM; ++tm)
+                            acc[tm] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, areg[h][tm]), b[h],
+                                                                            acc[tm], 0, 0, 0);
+                    }
+                }
+                if (u.i == nq - 1) {
+                    // ---- the group is complete in this wave: the slices of the row meet in LDS ----
+                    // Two buffers of sums, used in turn: the wave that finishes a tile clears its sums, and the buffer is
+                    // added to again only after the next barrier.  The sums of the codes are read by several waves: three
+                    // buffers, each cleared when all have passed the barrier after its reading.
+                    const int buf = sets & 1, buf3 = sets % 3;
+                    if constexpr (ONES) atomicAdd(&s_ones[buf3][lane], ones[0]);
+#pragma unroll
+                    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) atomicAdd(&s_sum[buf][tm * 4 + c][lane], acc[tm][c]);
+                    __syncthreads();
+                    ++sets;
+                    if (ONES && wave == 0) s_ones[(buf3 + 2) % 3][lane] = 0;
+                    const Group g = make_group(a, u.f, u.e, s_scales);
+                    for (int tm = wave - turn + (wave < turn ? nwaves : 0); tm < TM; tm += nwaves) {
+                        int d[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            d[c] = s_sum[buf][tm * 4 + c][lane];
+                            s_sum[buf][tm * 4 + c][lane] = 0;
+                        }
+                        finish<EPI>(a, g, lane, (rt0 + u.r) * kTileRows + j, n0 + tm * VPT + kb * VPL, ND == 4 ? 2 : ND - 1,
+                                    d, ONES ? s_ones[buf3][lane] : 0, bias_row, &s_z[tm * VPL][lane]);
+                    }
+                    if (g.last) {
+                        turn += TM;
+                        while (turn >= nwaves) turn -= nwaves;
+                    }
+                }
+                if (advance(u)) multiply_group(u);
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+
+// Digits per value that `act_bits` needs
+static int digits_of(int act_bits) { return act_bits <= 8 ? 1 : (act_bits <= 16 ? 2 : 4); }
+
+static ActSource act_source(const float *X0, int cols0, const float *X1, int cols1, int batch, int frac_bits, int act_bits)
+{
+    ActSource s;
+    s.X0 = X0; s.X1 = X1; s.cols0 = cols0; s.cols1 = X1 ? cols1 : 0;
+    s.batch = batch;
+    s.fscale = ldexpf(1.0f, frac_bits);
+    s.imax = (act_bits == 32) ? INT32_MAX : (int32_t)((1u << (act_bits - 1)) - 1u);
+    s.imin = -s.imax - 1;
+    return s;
+}
+
+int launch_digits(const float *X0, int cols0, const float *X1, int cols1, int batch, const Layout &L, int frac_bits,
+                  int act_bits, void *digits, int32_t *xq_out, hipStream_t st)
+{
+    const ActSource s = act_source(X0, cols0, X1, cols1, batch, frac_bits, act_bits);
+    const dim3 grid((unsigned)L.cq, (unsigned)((batch + 7) / 8));
+    uint8_t *d = static_cast<uint8_t *>(digits);
+    switch (digits_of(act_bits)) {
+        case 1: hipLaunchKernelGGL(k_digits<1>, grid, dim3(256), 0, st, s, L.cq, d, xq_out); break;
+        case 2: hipLaunchKernelGGL(k_digits<2>, grid, dim3(256), 0, st, s, L.cq, d, xq_out); break;
+        default: hipLaunchKernelGGL(k_digits<4>, grid, dim3(256), 0, st, s, L.cq, d, xq_out); break;
+    }
+    return (int)hipGetLastError();
+}
+
+// [what follows][digits 1, 2, 4][four or eight slots][bits, pairs][way]: digits from memory, one tile or four; converted in the
+// launch, one tile or two, one tile with non-temporal loads of the weights
+// (the sums themselves are asked for in groups of one or two: four slots)
+enum { kMemory1 = 0, kMemory4 = 1, kFused1 = 2, kFused2 = 3, kFusedNt = 4, kStreams = 5 };
+static bool is_fused(int way) { return way >= kFused1 && way <= kFusedNt; }
+static int way_tiles(int way) { return way == kMemory4 ? 4 : (way == kFused2 ? 2 : 1); }
+template <int ND, int Q, bool IL, int TM, bool FUSED, int EPI, int POLICY = 0>
+static const void *stream_kernel()
+{
+    if constexpr ((EPI == kSums && Q > 1) || (EPI == kCell && IL) || (POLICY && EPI != kStore)) return nullptr;
+    else return reinterpret_cast<const void *>(k_i8<ND, Q, IL, TM, FUSED, EPI, POLICY>);
+}
+#define PB_I8_IL(ND, Q, IL, E)                                                                                     \
+    {stream_kernel<ND, Q, IL, 1, false, E>(), stream_kernel<ND, Q, IL, 4, false, E>(),                              \
+     stream_kernel<ND, Q, IL, 1, true, E>(), stream_kernel<ND, Q, IL, 2, true, E>(), stream_kernel<ND, Q, IL, 1, true, E, 2>()}
+#define PB_I8_ND(ND, E) {{PB_I8_IL(ND, 1, false, E), PB_I8_IL(ND, 1, true, E)}, {PB_I8_IL(ND, 2, false, E), PB_I8_IL(ND, 2, true, E)}}
+#define PB_I8(E) {PB_I8_ND(1, E), PB_I8_ND(2, E), PB_I8_ND(4, E)}
+static const void *const kI8[3][3][2][2][kStreams] = {PB_I8(kStore), PB_I8(kCell), PB_I8(kSums)};
+
+// Staged digits of a workgroup at most (a compute unit has 160 KB of LDS)
+constexpr int kMaxStage = 140 * 1024;
+
+// Compute units, and workgroups of a kernel that fit on the device at once (neither changes while the process lives)
+static int compute_units()
+{
+    static int cus;
+    int v = __atomic_load_n(&cus, __ATOMIC_RELAXED);
+    if (v > 0) return v;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    __atomic_store_n(&cus, v, __ATOMIC_RELAXED);
+    return v;
+}
+static int resident(const void *fn, int threads, size_t lds, int *slot)
+{
+    int v = __atomic_load_n(slot, __ATOMIC_RELAXED);
+    if (v > 0) return v;
+    int per_cu = 0;
+    if (lds && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxStage) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess) return 0;
+    v = compute_units() * per_cu;
+    if (v > 0) __atomic_store_n(slot, v, __ATOMIC_RELAXED);
+    return v;
+}
+
+// The call as the choice of the kernel sees it
+struct I8Call {
+    int rt, cq, tiles, batch, nd, m, groups;
+    double weights;   // MB of packed words
+};
+static int stage_rows(const I8Call &c, int tm)
+{
+    const int rows = c.nd * ((c.batch + 1) & ~1);   // (vectors are converted two at a time)
+    return tm > 1 || rows > 16 ? 16 : rows;
+}
+static size_t stage_bytes(const I8Call &c, int tm) { return (size_t)c.cq * (size_t)(tm * 8 * stage_operand(stage_rows(c, tm))); }
+static int slice(int cq, int tm) { return (cq + stream_waves(tm) - 1) / stream_waves(tm); }   // chunks per wave
+
+// Weights that are read once (one tile of digit rows): non-temporal loads where they are too many for the L2 caches (32 MB) and few
+// enough to come from the last-level cache on the next call.  (8 bitlayers, two vectors: 8192 x 8192 15.6 -> 14.1 us, but
+// 16384 x 12288 34.7 -> 40.2 and 4616 x 2016, 12 bitlayers, 7.0 -> 8.0 us.)
+static bool streaming(const I8Call &c) { return c.tiles == 1 && c.weights > 32.0 && c.weights <= 80.0; }
+
+// Which kernel: the one with the least estimated time.  The estimates are in us, fitted to the times of 170 layers on an MI355X (64
+// to 16384 rows and columns, 2 to 1024 vectors, 1 to 16 bitlayers, 8, 16 and 32 activation bits, both layouts); the choice costs 2 % on
+// average over the best one, 1.3 times in the worst case.  (A second launch counts 0.7 us more than on the device alone.)
+//   few digit rows: rounds of workgroups over the chip, units (row tile, group, tile of digit rows, chunk), conversion
+//   many:           rounds of workgroups times (start and end + steps), the digits of all vectors through memory
+static int pick_way(const I8Call &c, bool prepared)
+{
+#ifdef PB_TUNING
+    if (const char *e = getenv("PB_TUNE_WAY")) {
+        const int w = atoi(e);
+        if (w >= 0 && (!is_fused(w) || (!prepared && stage_bytes(c, way_tiles(w)) <= kMaxStage))) return w;
+    }
+#endif
+    const int cus = compute_units();
+    int best = kMemory1;
+    double least = 1e30;
+    auto offer = [&](int way, double t) {
+        if (t < least) { least = t; best = way; }
+    };
+    const double quad = c.m > 4 ? 4.0 : 2.0;       // (the codes of a unit cost about as much as that many matrix tiles)
+    for (int way = 0; way < kFusedNt; ++way) {
+        const int tm = way_tiles(way), groups = (c.tiles + tm - 1) / tm;
+        const size_t lds = is_fused(way) ? stage_bytes(c, tm) : 0;
+        if (is_fused(way) && (prepared || lds > kMaxStage)) continue;
+        const int cpw = slice(c.cq, tm), S = (c.cq + cpw - 1) / cpw;
+        int per_cu = 16 / S;
+        if (is_fused(way) && (size_t)per_cu * (lds + 4096) > 155 * 1024) per_cu = (int)(155 * 1024 / (lds + 4096));
+        const int cap = cus * (per_cu < 1 ? 1 : per_cu);
+        int wgs = cap / groups < 1 ? 1 : cap / groups;
+        if (wgs > c.rt) wgs = c.rt;
+        const int rounds = (c.rt + wgs - 1) / wgs;
+        const int waves = (((c.rt + rounds - 1) / rounds) * groups + cap - 1) / cap;   // (workgroups after another on a place)
+        const double sets = (double)waves * rounds * c.groups;
+        const double units = (double)c.rt * groups * c.cq * c.groups * (1.0 + tm / quad) / 1000.0;
+        const int pairs = (c.batch + 1) / 2 < 8 * tm / c.nd ? (c.batch + 1) / 2 : 8 * tm / c.nd;     // of vectors of a workgroup
+        const double conversions = (double)((((c.rt + rounds - 1) / rounds) * groups + cus - 1) / cus) * c.cq * pairs / 10.0;
+        const double digits = c.tiles * c.cq / 100.0;
+        switch (way) {
+        case kMemory1: offer(way, (prepared ? 2.5 : 5.2) + 1.31 * sets * cpw + 0.29 * sets + 1.57 * digits + 0.194 * units + 0.106 * c.weights); break;
+        case kMemory4: offer(way, (prepared ? 2.5 : 5.2) + 2.06 * sets * cpw + 1.03 * sets + 1.66 * digits + 0.36 * units + 0.063 * c.weights); break;
+        case kFused1: offer(way, 2.9 + 0.73 * sets * cpw + 0.76 * sets + 0.80 * conversions + 0.166 * units + 0.021 * c.weights); break;
+        default: offer(way, 3.4 + 1.67 * sets + 0.86 * conversions); break;
+        }
+    }
+    static const double cost[kTileShapes][5] = {   // start, step, start and end of a workgroup, weights (MB), digits
+        {4.2, 1.78, 5.94, 0.066, 0.0089}, {4.3, 2.68, 8.26, 0.059, 0.0062}, {4.6, 4.75, 12.5, 0.15, 0.0093}};
+    for (int i = 0; i < kTileShapes; ++i) {
+        const TileShape &t = kTile[i];
+        if (c.groups > t.nt) continue;      // (a row tile's groups would take several passes)
+        const int rows = t.nt / c.groups;
+        const int wgs = ((c.rt + rows - 1) / rows) * ((c.tiles + t.wm * t.tm - 1) / (t.wm * t.tm));
+        const int rounds = (wgs + cus - 1) / cus;
+        const int per_step = 8 / t.wm * (t.wm / t.nt);      // chunks
+        const int steps = (c.cq + per_step - 1) / per_step;
+        offer(kStreams + i, cost[i][0] + rounds * (cost[i][2] + steps * cost[i][1]) + cost[i][3] * c.weights + cost[i][4] * c.tiles * c.cq);
+    }
+    return best == kFused1 && streaming(c) ? kFusedNt : best;
+}
+
+int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, int bits_used, int frac_bits, int act_bits,
+                const float *X0, int cols0, const float *X1, int cols1, void *digits, bool prepared, int batch, float *Y,
+                long long *A, bool pairs_out, const Epilogue &ep, hipStream_t st)
+{
+    const int nd = digits_of(act_bits);
+    I8Args a;
+    a.packed = packed;
+    a.packed_bytes = (uint32_t)packed_bytes(L);   // (the host API refuses matrices of 4 GiB and more)
+    a.layer_step = (uint32_t)(tile16_layer_stride(L) * 4);
+    a.round_step = (uint32_t)(tile16_rowtile_stride(L) * 4);
+    a.rt_count = L.rt_count; a.cq = L.cq; a.m = bits_used;
+    a.digits = static_cast<const uint8_t *>(digits);
+    a.digits_bytes = (uint32_t)batch * (uint32_t)L.cq * (uint32_t)(nd * 512);
+    a.act = act_source(X0, cols0, X1, cols1, batch, frac_bits, act_bits);
+    a.scales = scales; a.Y = Y; a.A = A; a.pairs_out = (A && pairs_out) ? 1 : 0;
+    a.bias = ep.bias; a.relu = ep.relu; a.c_prev = ep.c_prev; a.h_out = ep.h_out; a.c_out = ep.c_out;
+    a.gate_h = L.gate_h; a.R = L.rows;
+    a.out_scale = ldexp(1.0, -frac_bits);
+    // (the epilogue addresses the bias and the cell state with 32-bit byte offsets)
+    if (ep.bias && L.rows >= (1 << 29)) return (int)hipErrorInvalidValue;
+    if (ep.c_prev && (size_t)batch * (size_t)L.gate_h >= ((size_t)1 << 29)) return (int)hipErrorInvalidValue;
+
+    const int vpt = 16 / nd;
+    const bool il = is_pairs(L.layout);
+    I8Call c;
+    c.rt = L.rt_count; c.cq = L.cq; c.tiles = (batch + vpt - 1) / vpt; c.batch = batch; c.nd = nd; c.m = bits_used;
+    c.groups = A ? (pairs_out ? (bits_used + 1) / 2 : bits_used) : i8_groups(bits_used);
+    c.weights = (double)L.layer_words * 4e-6 * bits_used;
+    int way = pick_way(c, prepared);
+    if (way == kFusedNt && (A || ep.c_prev)) way = kFused1;
+    const int shape = way - kStreams;
+    if (!prepared && !is_fused(way)) {
+        const int e = launch_digits(X0, cols0, X1, cols1, batch, L, frac_bits, act_bits, digits, nullptr, st);
+        if (e) return e;
+    }
+    if (shape >= 0) return launch_imma_tile(shape, a, nd, il, st);
+
+    const int epi = A ? kSums : (ep.c_prev ? kCell : kStore), q = (!A && bits_used > 4) ? 1 : 0;
+    const int ndi = nd == 4 ? 2 : nd - 1, tm = way_tiles(way);
+    const void *fn = kI8[epi][ndi][q][il][way];
+    if (!fn) return (int)hipErrorInvalidValue;
+    a.chunks_per_wave = slice(L.cq, tm);
+    a.stage_rows = stage_rows(c, tm);
+    const int S = (L.cq + a.chunks_per_wave - 1) / a.chunks_per_wave;
+    const size_t lds = is_fused(way) ? stage_bytes(c, tm) : 0;
+    static int cache[3][3][2][2][kStreams][17][24];   // (the last index: LDS in steps of 6 KB)
+    const int capacity = resident(fn, S * 64, lds, &cache[epi][ndi][q][il][way][S][lds / 6144]);
+    if (capacity < 1) return (int)hipErrorInvalidValue;
+    const int groups = (c.tiles + tm - 1) / tm;
+    int wgs = capacity / groups;
+    if (wgs < 1) wgs = 1;
+    if (wgs > L.rt_count) wgs = L.rt_count;
+    a.rounds_per_wg = (L.rt_count + wgs - 1) / wgs;
+    wgs = (L.rt_count + a.rounds_per_wg - 1) / a.rounds_per_wg;
+    void *args[] = {&a};
+    const hipError_t e = hipLaunchKernel(fn, dim3((unsigned)wgs, (unsigned)groups), dim3((unsigned)S * 64), args, lds, st);
+    return (int)(e != hipSuccess ? e : hipGetLastError());
+}
+
+}  // namespace pb

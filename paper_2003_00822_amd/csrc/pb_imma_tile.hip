@@ -1,0 +1,301 @@
+// The product on the 8-bit integer matrix cores for many digit rows (see pb_imma.h for the arithmetic).
+#include "pb_imma.h"
+
+namespace pb {
+
+// Many digit rows: the eight waves of a workgroup share the expanded weight codes through LDS.
+//   WM waves lie along the digit rows, TM tiles of sixteen each; 8 / WM groups of waves share out the columns.
+//   NT column slots (a row tile and a group of bitlayers each); a step of a group of waves covers KC = WM / NT chunks of 512 columns,
+//   so that every wave expands one unit (slot, chunk) per step: it loads the words two steps ahead, turns them into codes
+//   one step ahead, and multiplies its own digit rows, which come straight from memory (each byte is used by one
+//   wave only), with the codes of all units of the step.
+// Bound: the matrix instructions at the large end (one in 16 cycles per SIMD; 8192 x 8192, 8 bitlayers, 1024 vectors: 2.3 of the
+// 5 POP/s, the share of its peak that the library's bf16 product reaches on this card); for few vectors the digit rows, which every
+// workgroup reads at 64 bytes per cycle, LDS, the expansion and the matrix instructions, about as long each.  Operands of the codes
+// are read from LDS three (seven) products ahead and the scheduler is kept from moving work across a (t, h): without that barrier
+// the products waited for their operands (64 vectors: 39 -> 32 us).
+// us per call, against the FP4 form that this replaces: 8192 x 8192, 8 bitlayers, 64 vectors 115 -> 29, 256 vectors (pairs layout) 403
+// -> 72, 1024 vectors 1582 -> 243; 16384 x 16384, 64 vectors 430 -> 105; 3795 x 5918, 16 bitlayers, 301 vectors 536 -> 124.
+// Calls with several groups of bitlayers (more than eight bitlayers, scales that do not halve, the parity hooks) give them
+// slots of their own, so that the sums of a row tile's groups meet in a lane.
+template <int Q, bool IL, int WM, int NT, int TM, int EPI>
+__global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, const int rows_per_wg)
+{
+    constexpr int WK = 8 / WM, KC = WM / NT;
+    static_assert(KC * NT == WM, "a unit for every wave");
+    constexpr int UNIT = 8 * 1024;          // codes of a unit: eight operands of 1 KB
+    constexpr int BUF = 8 * UNIT;
+    constexpr int BR = TM >= 4 ? 4 : 8;     // operands of codes: ring
+    constexpr int AR = NT * TM >= 32 ? 2 : 4;     // operands of digit rows: ring of steps (t, h)
+    extern __shared__ __align__(16) unsigned char lds[];    // two buffers
+    __shared__ int s_ones[NT][64];
+    __shared__ float s_bias[NT][kTileRows];
+    __shared__ float s_scales[PB_MAX_BITS];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % WM, kg = wave / WM;
+    const int my_nt = wm % NT, my_kc = wm / NT;
+    const int kb = lane >> 4, j = lane & 15;
+    const int vpt = 16 >> nds, vpl = 4 >> nds;
+    const int m = a.m;
+    const int n0 = ((int)blockIdx.y * WM + wm) * (TM * vpt);
+    const int rt0 = blockIdx.x * rows_per_wg;
+    const int rts = min(rows_per_wg, a.rt_count - rt0);     // >= 1 by construction
+    const int steps = (a.cq + KC * WK - 1) / (KC * WK);
+
+    float scv, scn;
+    {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.scales), 0,
+                                                                            a.scales ? m * 4 : 0, 0x00020000);
+        scv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0));
+        scn = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + 4, 0, 0));
+    }
+    if (wave == 0 && lane < PB_MAX_BITS) s_scales[lane] = scv;
+    bool merged = false;
+    if (EPI != kSums) {
+        const bool off = lane + 1 < m && !(scv == (lane == 0 ? -2.0f : 2.0f) * scn);
+        merged = __builtin_amdgcn_ballot_w64(off) == 0;
+    }
+    const int gs0 = merged ? 4 * Q : (EPI == kSums && a.pairs_out ? 2 : 1), gs1 = merged ? 4 * Q - 2 : gs0;
+    int ng = 1;                                 // groups of a row tile
+    for (int f = gs0; f < m; f += gs1) ++ng;
+    auto group_first = [&](int g) { return g == 0 ? 0 : gs0 + (g - 1) * gs1; };
+    auto group_end = [&](int g) { return min(m, gs0 + g * gs1); };
+    int rp = 1;                                 // row tiles of a pass
+    while ((rp + 1) * ng <= NT) ++rp;
+    const bool carry = ng > NT;                 // (a row tile's groups take several passes, its sums wait in the second buffer)
+
+    // digit rows
+    const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.digits), 0,
+                                                                        (int)a.digits_bytes, 0x00020000);
+    uint32_t doff[TM];
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+        const int n = n0 + tm * vpt + (j >> nds);
+        doff[tm] = n < a.act.batch ? (((uint32_t)n * (uint32_t)a.cq) << (nds + 9)) +
+                                         (uint32_t)((kb << nds) + (j & ((1 << nds) - 1))) * 16u
+                                   : (uint32_t)kNowhere;
+    }
+    const char *base = reinterpret_cast<const char *>(a.packed) + (size_t)rt0 * a.round_step;
+    const uint32_t avail = (uint32_t)(a.packed_bytes - (size_t)rt0 * a.round_step);
+
+    for (int r = 0, g0 = 0; r < rts;) {
+        const int slots = carry ? min(NT, ng - g0) : min(rp, rts - r) * ng;
+        // this wave's unit: row tile my_r, group my_g
+        int my_r = r, my_g = g0 + my_nt;
+        if (!carry)
+            while (my_g >= ng) { my_g -= ng; ++my_r; }
+        const bool have = my_nt < slots;
+        const int f = group_first(my_g), e = group_end(my_g);
+        const int l0 = (f & ~1) == 0 ? 0 : (f & ~1) - 2;
+        uint32_t mask[2 * Q];
+#pragma unroll
+        for (int p = 0; p < 2 * Q; ++p) {
+            const int l = l0 + 2 * p;
+            mask[p] = !have ? 0u
+                            : (l >= f && l < e ? 0xAAAAAAAAu : 0u) | (l + 1 >= f && l + 1 < e ? 0x55555555u : 0u);
+        }
+        const uint32_t flip = l0 == 0 ? 0xAAAAAAAAu : 0u;
+        u32x4 w[4 * Q];
+        auto issue = [&](int step) {
+            const int q = (step * WK + kg) * KC + my_kc;
+            const uint32_t off = (uint32_t)my_r * a.round_step + (uint32_t)q * 1024u;
+#pragma unroll
+            for (int s = 0; s < 4 * Q; ++s) {
+                const int l = l0 + s, lu = l0 + (s & ~1);
+                const bool has = IL ? lu + 1 >= f && lu < e : l >= f && l < e;
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<char *>(base), 0, have && has && q < a.cq ? (int)avail : 0, 0x00020000);
+                w[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, (int)(off + (uint32_t)l * a.layer_step), 0);
+            }
+        };
+        v4i ones = v4i{0, 0, 0, 0};
+        const v4i one = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+        unsigned char *const my_codes = lds + wave * UNIT + lane * 16;
+        // word t of the unit of `step` -> codes
+        auto expand = [&](int t, int step, int buf) {
+            const bool in = (step * WK + kg) * KC + my_kc < a.cq;
+            uint32_t p[4 * Q];
+#pragma unroll
+            for (int s = 0; s < 4 * Q; ++s) {
+                p[s] = w[s][t];
+                if constexpr (IL) {
+                    if (s < 2) p[s] ^= flip;
+                    p[s] &= in ? mask[s / 2] : 0u;
+                }
+            }
+            v4i lo, hi;
+            weight_codes<Q, IL>(p, lo, hi);
+            ones = __builtin_amdgcn_mfma_i32_16x16x64_i8(one, lo, ones, 0, 0, 0);
+            ones = __builtin_amdgcn_mfma_i32_16x16x64_i8(one, hi, ones, 0, 0, 0);
+            *reinterpret_cast<v4i *>(my_codes + buf * BUF + t * 2048) = lo;
+            *reinterpret_cast<v4i *>(my_codes + buf * BUF + t * 2048 + 1024) = hi;
+        };
+        u32x4 ar[AR][TM];
+        auto load_digits = [&](u32x4 (&dst)[TM], int step, int kc, int th) {
+            // (beyond the last chunk the codes are zero: any digits do)
+            const int q = min((step * WK + kg) * KC + kc, a.cq - 1);
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+                dst[tm] = __builtin_amdgcn_raw_buffer_load_b128(rd, (int)doff[tm], (q * 8 + th) << (nds + 6), 0);
+        };
+        v4i acc[TM][NT];
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[tm][nt] = v4i{0, 0, 0, 0};
+        // the codes of unit (kc, nt), operand th
+        auto codes = [&](int buf, int kc, int th, int nt) {
+            return *reinterpret_cast<const v4i *>(lds + buf * BUF + (kg * WM + kc * NT + nt) * UNIT + th * 1024 + lane * 16);
+        };
+        auto multiply = [&](const u32x4 (&dig)[TM], const v4i b, int nt) {
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+                acc[tm][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, dig[tm]), b, acc[tm][nt], 0, 0, 0);
+        };
+        for (int i = threadIdx.x; i < NT * 64; i += 512) (&s_ones[0][0])[i] = 0;
+        if (threadIdx.x < NT * kTileRows) {
+            int nt = threadIdx.x / kTileRows, rr = r;
+            if (!carry)
+                while (nt >= ng) { nt -= ng; ++rr; }
+            s_bias[threadIdx.x / kTileRows][j] = EPI != kSums && a.bias ? bias_of(a, (rt0 + rr) * kTileRows + j) : 0.0f;
+        }
+        issue(0);
+        if (!carry) {
+#pragma unroll
+            for (int k = 0; k < AR - 1; ++k) load_digits(ar[k], 0, 0, k);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) expand(t, 0, 0);
+            issue(1);
+            __syncthreads();
+            for (int step = 0; step < steps; ++step) {
+                const int buf = step & 1;
+                // (the codes of BR - 1 operands ahead are on their way from LDS)
+                v4i br[BR];
+#pragma unroll
+                for (int i = 0; i < BR - 1; ++i) br[i] = codes(buf, 0, i / NT, i % NT);
+#pragma unroll
+                for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+                    for (int th = 0; th < 8; ++th) {
+                        // the digit rows of a later (t, h) are requested before this one's products
+                        const int nx = kc * 8 + th + AR - 1;
+                        if (nx < KC * 8) load_digits(ar[nx % AR], step, nx / 8, nx % 8);
+                        else load_digits(ar[nx % AR], step + 1, 0, nx - KC * 8);
+                        if (kc == KC - 1 && (th & 1) == 0) expand(th / 2, step + 1, buf ^ 1);
+                        if (kc == KC - 1 && th == 7) issue(step + 2);
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) {
+                            const int i = (kc * 8 + th) * NT + nt, ahead = i + BR - 1;
+                            if (ahead < KC * 8 * NT) br[ahead % BR] = codes(buf, ahead / (8 * NT), ahead / NT % 8, ahead % NT);
+                            multiply(ar[(kc * 8 + th) % AR], br[i % BR], nt);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                __syncthreads();
+            }
+        } else {
+            for (int step = 0; step < steps; ++step) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) expand(t, step, 0);
+                issue(step + 1);
+                __syncthreads();
+                for (int kc = 0; kc < KC; ++kc)
+                    for (int th = 0; th < 8; ++th) {
+                        load_digits(ar[0], step, kc, th);
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) multiply(ar[0], codes(0, kc, th, nt), nt);
+                    }
+                __syncthreads();
+            }
+        }
+        // ---- the groups of waves add up, then every tile is finished ----
+        atomicAdd(&s_ones[my_nt][lane], ones[0]);
+        int *const part = reinterpret_cast<int *>(lds) + wm * (TM * NT * 4 * 64) + lane;
+        for (int k = 1; k < WK; ++k) {
+            if (k > 1) __syncthreads();
+            if (kg == k) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) part[((nt * TM + tm) * 4 + c) * 64] = acc[tm][nt][c];
+            }
+            __syncthreads();
+            if (kg == 0) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) acc[tm][nt][c] += part[((nt * TM + tm) * 4 + c) * 64];
+            }
+        }
+        __syncthreads();
+        if (kg == 0) {
+            int rr = r, gg = g0;
+            for (int nt = 0; nt < slots; ++nt) {
+                const Group g = make_group(a, group_first(gg), group_end(gg), s_scales);
+                const int sum1 = s_ones[nt][lane];
+                const float bias_row = s_bias[nt][j];
+                int d[TM][4] = {};
+#pragma unroll
+                for (int x = 0; x < NT; ++x)
+                    if (x == nt) {
+#pragma unroll
+                        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) d[tm][c] = acc[tm][x][c];
+                    }
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm)
+                    finish<EPI>(a, g, lane, (rt0 + rr) * kTileRows + j, n0 + tm * vpt + kb * vpl, nds, d[tm], sum1, bias_row,
+                                reinterpret_cast<double *>(lds + BUF) + (wm * TM + tm) * 4 * 64 + lane);
+                if (++gg == ng) { gg = 0; ++rr; }
+            }
+        }
+        __syncthreads();
+        if (!carry) r += rp;
+        else if ((g0 += NT) >= ng) { g0 = 0; ++r; }
+    }
+}
+
+
+// ---------------------------------------------------------------------------------------------------------------
+
+template <int Q, bool IL, int WM, int NT, int TM, int EPI>
+static const void *tile_kernel()
+{
+    // (the sums themselves are asked for in groups of one or two: four slots)
+    if constexpr ((EPI == kSums && Q > 1) || (EPI == kCell && IL)) return nullptr;
+    else return reinterpret_cast<const void *>(k_i8_tile<Q, IL, WM, NT, TM, EPI>);
+}
+#define PB_TILE_E(WM, NT, TM, E) {{tile_kernel<1, false, WM, NT, TM, E>(), tile_kernel<1, true, WM, NT, TM, E>()}, \
+                                  {tile_kernel<2, false, WM, NT, TM, E>(), tile_kernel<2, true, WM, NT, TM, E>()}}
+#define PB_TILE(WM, NT, TM) {PB_TILE_E(WM, NT, TM, kStore), PB_TILE_E(WM, NT, TM, kCell), PB_TILE_E(WM, NT, TM, kSums)}
+static const void *const kTileFn[kTileShapes][3][2][2] = {PB_TILE(4, 4, 2), PB_TILE(8, 8, 2), PB_TILE(8, 8, 4)};
+constexpr int kTileLds = 128 * 1024;
+
+int launch_imma_tile(int shape, const I8Args &a, int nd, bool il, hipStream_t st)
+{
+    const int epi = a.A ? kSums : (a.c_prev ? kCell : kStore), q = (epi != kSums && a.m > 4) ? 1 : 0;
+    const void *fn = kTileFn[shape][epi][q][il];
+    static bool declared[kTileShapes][3][2][2];
+    if (!fn) return (int)hipErrorInvalidValue;
+    if (!__atomic_load_n(&declared[shape][epi][q][il], __ATOMIC_RELAXED)) {
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds);
+        if (e != hipSuccess) return (int)e;
+        __atomic_store_n(&declared[shape][epi][q][il], true, __ATOMIC_RELAXED);
+    }
+    const TileShape &t = kTile[shape];
+    int nds = nd == 4 ? 2 : nd - 1, rows_per_wg = tile_rows(t, a.m, epi == kSums);
+    const int vpt = 16 / nd, tiles = (a.act.batch + vpt - 1) / vpt;
+    const int groups = (tiles + t.wm * t.tm - 1) / (t.wm * t.tm), wgs = (a.rt_count + rows_per_wg - 1) / rows_per_wg;
+    void *args[] = {const_cast<I8Args *>(&a), &nds, &rows_per_wg};
+    const hipError_t e = hipLaunchKernel(fn, dim3((unsigned)wgs, (unsigned)groups), dim3(512), args, kTileLds, st);
+    return (int)(e != hipSuccess ? e : hipGetLastError());
+}
+
+}  // namespace pb

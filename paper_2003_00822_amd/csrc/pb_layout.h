@@ -44,20 +44,15 @@ constexpr int kMetaInts = 16;       // per activation vector, in the workspace
 
 constexpr int kTileRows = 16;       // matrix-core kernel: rows per tile
 constexpr int kChunkWords = 16;     // matrix-core kernel: words per row in one block
-constexpr int kMaxSlices = 16;      // matrix-core kernel: waves (column slices) per workgroup
+constexpr int kMaxSlices = 16;      // kernel for one vector: waves (column slices) per workgroup
 constexpr int kMaxColsTile16 = 32768;     // 16 slices of 2048 columns
-// merged bitlayer pairs (digit products up to 9): a quarter sum stays below 4369 * 9 * 32768 < 2^31, so pairs cover
-// every width the tiled layouts have
+// The sums of bitlayer pairs are asked for at every width
 constexpr int kMaxColsPairs = 32768;
-// Bitlayer pairs whose sums the matrix-core kernel accumulates in one set of registers (pair p of a group counts
-// 4^(last - p)): with five, a register stays below 9 * 2048 * 341 < 2^24 and the half sums of a row below
-// 17 * 9 * 32768 * 341 < 2^31.
+// Bitlayer pairs in FP4 form: with five of them in one set of accumulators (pair p counts 4^(last - p)) a register stays below
+// 9 * 2048 * 341 < 2^24 and the half sums of a row below 17 * 9 * 32768 * 341 < 2^31.  Rows wider than the digit rows that the
+// waves of a workgroup hold take several passes of at most `cap` chunks of 512 columns.  (Limits of that form, worked out by
+// the host tests; pairs are multiplied as whole codes, see pb_imma.h.)
 constexpr int kPairGroup = 5;
-
-// Batches on rows wider than the digit rows that the waves of a workgroup of the matrix-core kernel hold are
-// covered in several passes over the columns: at most `cap` chunks of 512 columns per pass (what eight waves hold:
-// kSplitChunks4 with four operands per wave, kSplitChunks8 with eight), the chunks shared out evenly.  The launcher
-// sizes the workgroup with these and the kernel finds its slice with them.
 constexpr int kSplitChunks4 = 16, kSplitChunks8 = 8;
 __host__ __device__ inline int split_parts(int cq, int cap) { return (cq + cap - 1) / cap; }
 __host__ __device__ inline int split_chunks_per_part(int cq, int cap)
@@ -176,7 +171,8 @@ __host__ __device__ inline void pair_of_digits(uint32_t even, uint32_t odd, uint
     *lo = (even & 0x55555555u) | ((odd << 1) & 0xAAAAAAAAu);
 }
 
-// Workspace: [meta: batch * kMetaInts int32][planes: batch * 32 * cwp uint32][gates: batch * rows fp32]
+// Workspace: [meta: batch * kMetaInts int32][planes: batch * 32 * cwp uint32][gates: batch * rows fp32]; the kernels for batches
+// keep the byte digits of the activations in the place of the planes (at most as many bytes)
 inline size_t ws_meta_off(const Layout &, int) { return 0; }
 inline size_t ws_planes_off(const Layout &, int batch) { return ((size_t)batch * kMetaInts * 4 + 255) & ~(size_t)255; }
 inline size_t ws_gates_off(const Layout &L, int batch)

@@ -276,6 +276,7 @@ class PackedLinear:
         self.scales = torch.empty(max(bits, 4), dtype=torch.float32, device=W.device)
         self.max_batch = max_batch
         self.workspace = alloc_workspace(self.desc, max_batch, W.device)
+        self.home_stream = torch.cuda.current_stream().cuda_stream   # whose calls share `workspace`
         pb_quantize_pack_mode(W, self.desc, quantizer, self.packed, self.scales)
 
     def __call__(self, X: torch.Tensor, bits_used: int | None = None, out: torch.Tensor | None = None):
@@ -287,7 +288,8 @@ class PackedLinear:
         assert batch <= self.max_batch
         if out is None:
             out = torch.empty((batch, self.rows), dtype=torch.float32, device=X.device)
-        pb_matmul(self.packed, self.scales, self.desc, bits_used or self.bits, X, batch, out, self.workspace)
+        # (a workspace of its own: another thread's call could come between the launches of this one)
+        pb_matmul(self.packed, self.scales, self.desc, bits_used or self.bits, X, batch, out, torch.empty_like(self.workspace))
         return out
 
     def acc(self, X: torch.Tensor, bits_used: int | None = None):
@@ -295,7 +297,7 @@ class PackedLinear:
         batch = X.shape[0]
         m = bits_used or self.bits
         A = torch.empty((m, batch, self.rows), dtype=torch.int64, device=X.device)
-        pb_matmul_acc(self.packed, self.desc, m, X, batch, A, self.workspace)
+        pb_matmul_acc(self.packed, self.desc, m, X, batch, A, torch.empty_like(self.workspace))
         return A
 
     def acc_pairs(self, X: torch.Tensor, bits_used: int | None = None):
@@ -303,7 +305,7 @@ class PackedLinear:
         batch = X.shape[0]
         m = bits_used or self.bits
         A = torch.empty(((m + 1) // 2, batch, self.rows), dtype=torch.int64, device=X.device)
-        pb_matmul_acc_pairs(self.packed, self.desc, m, X, batch, A, self.workspace)
+        pb_matmul_acc_pairs(self.packed, self.desc, m, X, batch, A, torch.empty_like(self.workspace))
         return A
 
     def unpack(self):
