@@ -392,6 +392,11 @@ static int stage_rows(const I8Call &c, int tm)
 static size_t stage_bytes(const I8Call &c, int tm) { return (size_t)c.cq * (size_t)(tm * 8 * stage_operand(stage_rows(c, tm))); }
 static int slice(int cq, int tm) { return (cq + stream_waves(tm) - 1) / stream_waves(tm); }   // chunks per wave
 
+// Workgroups of S waves per compute unit of the kernels that convert the activations: each repeats the conversion, so no more than
+// eight waves need.  (5003 x 3001, 5 vectors of 16 bits, six waves: one per compute unit 7.5 us, two 8.6; 4096 x 1024, 16
+// vectors, two waves: one 7.5, two 6.8, four 5.8 us.)
+static int fused_per_cu(int S) { return S >= 4 ? 1 : 8 / S; }
+
 // Weights that are read once (one tile of digit rows): non-temporal loads where they are too many for the L2 caches (32 MB) and few
 // enough to come from the last-level cache on the next call.  (8 bitlayers, two vectors: 8192 x 8192 15.6 -> 14.1 us, but
 // 16384 x 12288 34.7 -> 40.2 and 4616 x 2016, 12 bitlayers, 7.0 -> 8.0 us.)
@@ -422,7 +427,7 @@ static int pick_way(const I8Call &c, bool prepared)
         const size_t lds = is_fused(way) ? stage_bytes(c, tm) : 0;
         if (is_fused(way) && (prepared || lds > kMaxStage)) continue;
         const int cpw = slice(c.cq, tm), S = (c.cq + cpw - 1) / cpw;
-        int per_cu = 16 / S;
+        int per_cu = is_fused(way) ? fused_per_cu(S) : 16 / S;
         if (is_fused(way) && (size_t)per_cu * (lds + 4096) > 155 * 1024) per_cu = (int)(155 * 1024 / (lds + 4096));
         const int cap = cus * (per_cu < 1 ? 1 : per_cu);
         int wgs = cap / groups < 1 ? 1 : cap / groups;
@@ -436,9 +441,9 @@ static int pick_way(const I8Call &c, bool prepared)
         const double digits = c.tiles * c.cq / 100.0;
         switch (way) {
         case kMemory1: offer(way, (prepared ? 2.5 : 5.2) + 1.31 * sets * cpw + 0.29 * sets + 1.57 * digits + 0.194 * units + 0.106 * c.weights); break;
-        case kMemory4: offer(way, (prepared ? 2.5 : 5.2) + 2.06 * sets * cpw + 1.03 * sets + 1.66 * digits + 0.36 * units + 0.063 * c.weights); break;
-        case kFused1: offer(way, 2.9 + 0.73 * sets * cpw + 0.76 * sets + 0.80 * conversions + 0.166 * units + 0.021 * c.weights); break;
-        default: offer(way, 3.4 + 1.67 * sets + 0.86 * conversions); break;
+        case kMemory4: offer(way, (prepared ? 2.5 : 4.9) + 2.06 * sets * cpw + 1.03 * sets + 1.66 * digits + 0.36 * units + 0.063 * c.weights); break;
+        case kFused1: offer(way, 3.0 + 0.69 * sets * cpw + 0.32 * sets + 0.72 * conversions + 0.193 * units + 0.045 * c.weights); break;
+        default: offer(way, 3.2 + 1.54 * sets + 0.88 * conversions + 0.026 * units); break;
         }
     }
     static const double cost[kTileShapes][5] = {   // start, step, start and end of a workgroup, weights (MB), digits
@@ -502,8 +507,9 @@ int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, in
     const int S = (L.cq + a.chunks_per_wave - 1) / a.chunks_per_wave;
     const size_t lds = is_fused(way) ? stage_bytes(c, tm) : 0;
     static int cache[3][3][2][2][kStreams][17][24];   // (the last index: LDS in steps of 6 KB)
-    const int capacity = resident(fn, S * 64, lds, &cache[epi][ndi][q][il][way][S][lds / 6144]);
+    int capacity = resident(fn, S * 64, lds, &cache[epi][ndi][q][il][way][S][lds / 6144]);
     if (capacity < 1) return (int)hipErrorInvalidValue;
+    if (is_fused(way) && capacity > compute_units() * fused_per_cu(S)) capacity = compute_units() * fused_per_cu(S);
     const int groups = (c.tiles + tm - 1) / tm;
     int wgs = capacity / groups;
     if (wgs < 1) wgs = 1;
