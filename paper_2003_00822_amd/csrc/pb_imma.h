@@ -44,7 +44,7 @@ struct ActSource {
 constexpr int kNowhere = 0x7FFFFFF0;
 
 // The columns c + 8 b + r (b, r = 0..3; c a multiple of 4) of vector n as they are in memory; 0 beyond the ends.
-// `end` (the same in all lanes) is beyond every column that the wave asks for.
+// `end` (the same in all lanes) is beyond every column that the wave asks for, all of which lie in the 512 before it.
 __device__ __forceinline__ void load_columns(const ActSource &s, int n, int c, int end, u32x4 (&v)[4])
 {
     const bool live = n < s.batch;
@@ -64,7 +64,7 @@ __device__ __forceinline__ void load_columns(const ActSource &s, int n, int c, i
         const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(s.X1), 0, (int)((uint32_t)s.batch * (uint32_t)s.cols1 * 4u), 0x00020000);
         const int c1 = c - s.cols0, off1 = (n * s.cols1 + c1) * 4;
-        if ((s.cols0 & 3) == 0) {   // four columns lie in one part
+        if ((s.cols0 & 3) == 0 || end - 512 >= s.cols0) {   // four columns lie in one part
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
                 const int cb = c1 + 8 * b;
@@ -226,68 +226,64 @@ __device__ __forceinline__ float bias_of(const I8Args &a, int prow)
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, row >= 0 && row < a.R ? row * 4 : kNowhere, 0, 0));
 }
 
-// What follows the product for one tile of sixteen digit rows and sixteen weight rows: d = the four registers of this lane,
-// the digits of its 4 >> nds vectors n, n + 1, .. (1 << nds digits each); sum1 = sum of the codes of its row.
-// z: this lane's fp64 sums of the groups before (64 apart from vector to vector), read unless g.first, written unless g.last.
-template <int EPI>
-__device__ __forceinline__ void finish(const I8Args &a, const Group &g, int lane, int prow, int n, int nds, const int (&d)[4],
-                                       int sum1, float bias_row, double *z)
+// The sum of one vector and weight row from its digits' sums d[0 .. nd) and the sum of the row's codes, times the scale of the
+// group (every part is an integer below 2^53 and exact; the last step rounds once if the sum is beyond)
+template <int ND>
+__device__ __forceinline__ double scaled_sum(const Group &g, const int *d, int sum1)
 {
-    const int row = a.gate_h ? gates_matrix_row(prow, a.gate_h) : prow;
-    const bool row_ok = row >= 0 && row < a.R;
-    const int nd = 1 << nds, vpl = 4 >> nds;
-    const int offset = nds == 2 ? 0x808080 : (nds == 1 ? 0x80 : 0);
-    if constexpr (EPI == kSums) {
-        for (int p = 0; p < vpl; ++p) {
-            long long v = (long long)offset * sum1;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v += (c >> nds) == p ? (long long)d[c] << (8 * (c & (nd - 1))) : 0ll;
-            v >>= 7 - g.slot;
-            if (g.slot == 0) v = -v;   // (the sign bitlayer by itself)
-            if (row_ok && n + p < a.act.batch)
-                a.A[((size_t)(a.pairs_out ? g.f / 2 : g.f) * a.act.batch + n + p) * (size_t)a.R + row] = v;
-        }
-        return;
+    double v = (double)d[0];
+    if constexpr (ND == 2) v = fma(256.0, (double)d[1], fma(128.0, (double)sum1, v));
+    if constexpr (ND == 4) {
+        v = fma(65536.0, (double)d[2], fma(256.0, (double)d[1], v));
+        v = fma(16777216.0, (double)d[3], fma(8421504.0, (double)sum1, v));
     }
-    const double dd[4] = {(double)d[0], (double)d[1], (double)d[2], (double)d[3]};
-    const double base = (double)offset * (double)sum1;
-    for (int p = 0; p < vpl; ++p) {
-        const bool live = row_ok && n + p < a.act.batch;
-        float c_old = 0.0f;
-        if constexpr (EPI == kCell) {
-            const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.c_prev), 0,
-                                                                                a.act.batch * a.gate_h * 4, 0x00020000);
-            c_old = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                rc, live && (lane & 3) == 0 ? ((n + p) * a.gate_h + row) * 4 : kNowhere, 0, 0));
+    return v * g.scale;
+}
+template <int ND>
+__device__ __forceinline__ long long integer_sum(const Group &g, const int *d, int sum1)
+{
+    long long v = (long long)d[0];
+    if constexpr (ND == 2) v += ((long long)d[1] << 8) + 0x80ll * sum1;
+    if constexpr (ND == 4)
+        v += ((long long)d[1] << 8) + ((long long)d[2] << 16) + ((long long)d[3] << 24) + 0x808080ll * sum1;
+    v >>= 7 - g.slot;
+    return g.slot == 0 ? -v : v;   // (the sign bitlayer by itself)
+}
+
+// The previous cell state of vector n and the unit of this lane's quad (0 in the lanes that do not update it)
+__device__ __forceinline__ float cell_state(const I8Args &a, int lane, int row, bool row_ok, int n)
+{
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.c_prev), 0,
+                                                                        a.act.batch * a.gate_h * 4, 0x00020000);
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+        rc, row_ok && n < a.act.batch && (lane & 3) == 0 ? (n * a.gate_h + row) * 4 : kNowhere, 0, 0));
+}
+
+// What follows the product for vector n and matrix row `row` of this lane: v = its scaled sum over the groups up to this one
+template <int EPI>
+__device__ __forceinline__ void finish(const I8Args &a, int lane, int row, bool row_ok, int n, double v, float bias_row,
+                                       float c_old)
+{
+    const bool live = row_ok && n < a.act.batch;
+    float y = (float)(v * a.out_scale);
+    if (a.bias) y += bias_row;
+    if constexpr (EPI == kCell) {
+        float cn, hn;
+        lstm_quad(y, lane, c_old, &cn, &hn);
+        if ((lane & 3) == 0 && live) {
+            const size_t at = (size_t)n * a.gate_h + (size_t)row;
+            a.c_out[at] = cn;
+            a.h_out[at] = hn;
         }
-        // (every part is an integer below 2^53 and exact; the last step rounds once if the sum is beyond)
-        double v = base;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const double weight = (c >> nds) == p ? (double)(1 << (8 * (c & (nd - 1)))) : 0.0;   // (the same in all lanes)
-            v = fma(weight, dd[c], v);
-        }
-        v *= g.scale;
-        if (!g.first) v += z[p * 64];
-        if (!g.last) {
-            z[p * 64] = v;
-            continue;
-        }
-        float y = (float)(v * a.out_scale);
-        if (a.bias) y += bias_row;
-        if constexpr (EPI == kCell) {
-            float cn, hn;
-            lstm_quad(y, lane, c_old, &cn, &hn);
-            if ((lane & 3) == 0 && live) {
-                const size_t at = (size_t)(n + p) * a.gate_h + (size_t)row;
-                a.c_out[at] = cn;
-                a.h_out[at] = hn;
-            }
-        } else {
-            if (a.relu) y = fmaxf(y, 0.0f);
-            if (live) a.Y[(size_t)(n + p) * a.R + row] = y;
-        }
+    } else {
+        if (a.relu) y = fmaxf(y, 0.0f);
+        if (live) a.Y[(size_t)n * a.R + row] = y;
     }
+}
+__device__ __forceinline__ void store_sum(const I8Args &a, const Group &g, int row, bool row_ok, int n, long long v)
+{
+    if (row_ok && n < a.act.batch)
+        a.A[((size_t)(a.pairs_out ? g.f / 2 : g.f) * a.act.batch + n) * (size_t)a.R + row] = v;
 }
 
 // Groups of bitlayers of a call that accumulates m of them with the scales of Algorithm 1 (at most four slots: one quad of words)

@@ -225,7 +225,10 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
     int sets = 0;          // (round, group) pairs multiplied so far
     int turn = 0;          // the wave that finishes the first tile of a row tile
     v4i acc[TM], ones;
-    float bias_row = 0.0f;
+    float bias_row = 0.0f, c_old = 0.0f;
+    // the outputs of a row tile: vectors of a lane, tile after tile; the waves take them in turn
+    auto first_item = [&]() { return wave - turn + (wave < turn ? nwaves : 0); };
+    auto vector_of = [&](int item) { return n0 + item / VPL * VPT + kb * VPL + item % VPL; };
     const v4i one = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
     load_digits(areg[0], 0, 0);
     while (u.r < rounds) {
@@ -233,8 +236,12 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
         for (int k = 0; k < 2; ++k) {
             if (u.r < rounds) {
                 if (advance(ld)) request_group(ld);
-                // (the bias is requested before the next weights: a wait for it does not wait for them)
+                // (bias and cell state are requested before the next weights: a wait for them does not wait for those)
                 if (a.bias && u.i == nq - 1) bias_row = bias_of(a, (rt0 + u.r) * kTileRows + j);
+                if (EPI == kCell && u.i == nq - 1 && u.e == m) {
+                    const int row = gates_matrix_row((rt0 + u.r) * kTileRows + j, a.gate_h);
+                    c_old = cell_state(a, lane, row, row >= 0, vector_of(first_item()));
+                }
                 issue(ring[k ^ 1], ld);
                 if (u.i == 0) {
                     ones = v4i{0, 0, 0, 0};
@@ -282,18 +289,33 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
                     ++sets;
                     if (ONES && wave == 0) s_ones[(buf3 + 2) % 3][lane] = 0;
                     const Group g = make_group(a, u.f, u.e, s_scales);
-                    for (int tm = wave - turn + (wave < turn ? nwaves : 0); tm < TM; tm += nwaves) {
-                        int d[4];
+                    const int prow = (rt0 + u.r) * kTileRows + j;
+                    const int row = a.gate_h ? gates_matrix_row(prow, a.gate_h) : prow;
+                    const bool row_ok = row >= 0 && row < a.R;
+                    for (int item = first_item(); item < TM * VPL; item += nwaves) {
+                        const int c0 = item / VPL * 4 + item % VPL * ND, n = vector_of(item);
+                        int d[ND];
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            d[c] = s_sum[buf][tm * 4 + c][lane];
-                            s_sum[buf][tm * 4 + c][lane] = 0;
+                        for (int c = 0; c < ND; ++c) {
+                            d[c] = s_sum[buf][c0 + c][lane];
+                            s_sum[buf][c0 + c][lane] = 0;
                         }
-                        finish<EPI>(a, g, lane, (rt0 + u.r) * kTileRows + j, n0 + tm * VPT + kb * VPL, ND == 4 ? 2 : ND - 1,
-                                    d, ONES ? s_ones[buf3][lane] : 0, bias_row, &s_z[tm * VPL][lane]);
+                        const int sum1 = ONES ? s_ones[buf3][lane] : 0;
+                        if constexpr (EPI == kSums) {
+                            store_sum(a, g, row, row_ok, n, integer_sum<ND>(g, d, sum1));
+                        } else {
+                            double v = scaled_sum<ND>(g, d, sum1);
+                            if (!g.first) v += s_z[item][lane];
+                            if (!g.last) {
+                                s_z[item][lane] = v;
+                            } else {
+                                if (EPI == kCell && item >= nwaves) c_old = cell_state(a, lane, row, row_ok, n);
+                                finish<EPI>(a, lane, row, row_ok, n, v, bias_row, c_old);
+                            }
+                        }
                     }
                     if (g.last) {
-                        turn += TM;
+                        turn += TM * VPL;
                         while (turn >= nwaves) turn -= nwaves;
                     }
                 }

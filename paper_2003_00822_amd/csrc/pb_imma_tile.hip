@@ -1,4 +1,6 @@
 // The product on the 8-bit integer matrix cores for many digit rows (see pb_imma.h for the arithmetic).
+#include <type_traits>
+
 #include "pb_imma.h"
 
 namespace pb {
@@ -37,7 +39,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
     const int wm = wave % WM, kg = wave / WM;
     const int my_nt = wm % NT, my_kc = wm / NT;
     const int kb = lane >> 4, j = lane & 15;
-    const int vpt = 16 >> nds, vpl = 4 >> nds;
+    const int vpt = 16 >> nds;
     const int m = a.m;
     const int n0 = ((int)blockIdx.y * WM + wm) * (TM * vpt);
     const int rt0 = blockIdx.x * rows_per_wg;
@@ -249,10 +251,37 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
 #pragma unroll
                             for (int c = 0; c < 4; ++c) d[tm][c] = acc[tm][x][c];
                     }
+                const int prow = (rt0 + rr) * kTileRows + j;
+                const int row = a.gate_h ? gates_matrix_row(prow, a.gate_h) : prow;
+                const bool row_ok = row >= 0 && row < a.R;
+                auto outputs = [&](auto digits) {
+                    constexpr int ND = decltype(digits)::value, VPL = 4 / ND;
+                    const int n = n0 + kb * VPL;
+                    float c_old[TM][VPL] = {};
+                    if (EPI == kCell && g.last) {
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm)
-                    finish<EPI>(a, g, lane, (rt0 + rr) * kTileRows + j, n0 + tm * vpt + kb * vpl, nds, d[tm], sum1, bias_row,
-                                reinterpret_cast<double *>(lds + BUF) + (wm * TM + tm) * 4 * 64 + lane);
+                        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                            for (int p = 0; p < VPL; ++p) c_old[tm][p] = cell_state(a, lane, row, row_ok, n + tm * vpt + p);
+                    }
+#pragma unroll
+                    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                        for (int p = 0; p < VPL; ++p) {
+                            if constexpr (EPI == kSums) {
+                                store_sum(a, g, row, row_ok, n + tm * vpt + p, integer_sum<ND>(g, &d[tm][p * ND], sum1));
+                            } else {
+                                double *z = reinterpret_cast<double *>(lds + BUF) + ((wm * TM + tm) * 4 + p) * 64 + lane;
+                                double v = scaled_sum<ND>(g, &d[tm][p * ND], sum1);
+                                if (!g.first) v += *z;
+                                if (!g.last) *z = v;
+                                else finish<EPI>(a, lane, row, row_ok, n + tm * vpt + p, v, bias_row, c_old[tm][p]);
+                            }
+                        }
+                };
+                if (nds == 2) outputs(std::integral_constant<int, 4>{});
+                else if (nds == 1) outputs(std::integral_constant<int, 2>{});
+                else outputs(std::integral_constant<int, 1>{});
                 if (++gg == ng) { gg = 0; ++rr; }
             }
         }

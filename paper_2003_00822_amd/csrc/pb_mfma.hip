@@ -314,8 +314,8 @@ __global__ __launch_bounds__(MAXS * 64) void k_mfma(const uint32_t *packed, cons
         // Second part of a concatenated input [X0 ; X1].  Offsets of columns that belong to the first part
         // would be negative: they are clamped and the value dropped (a negative register offset that an
         // instruction offset brings back above zero is not range-checked lane by lane on this hardware).
-        // If cols0 is a multiple of 4 a lane's four columns lie in one part and one 16-byte load serves;
-        // else every column is loaded by itself.
+        // If cols0 is a multiple of 4, or the wave's slice begins beyond it, a lane's four columns lie in one part and one
+        // 16-byte load serves; else every column is loaded by itself.
         u32x4 xw[NQ][2];
         if (h.flags & kSecondPart) {
             const __amdgpu_buffer_rsrc_t rx1 =
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(MAXS * 64) void k_mfma(const uint32_t *packed, cons
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const int c1 = col0 + 512 * q + 256 * j - h.cols0;
-                    if ((h.cols0 & 3) == 0) {
+                    if ((h.cols0 & 3) == 0 || 512 * q0 >= h.cols0) {
                         xw[q][j] = __builtin_amdgcn_raw_buffer_load_b128(rx1, max(c1, 0) * 4, 0, 0);
                     } else {
 #pragma unroll

@@ -92,22 +92,26 @@ def test_every_way(pb, case, layout):
     check(pb, R, C, N, bits, m, act_bits, frac_bits, layout, sums=R * N < 200000)
 
 
-@pytest.mark.parametrize("H,I,N,act_bits", [(37, 100, 2, 32), (300, 700, 40, 32), (500, 1500, 100, 16), (1500, 1500, 64, 8), (1500, 1500, 64, 32)])
+@pytest.mark.parametrize("H,I,N,act_bits", [(37, 100, 2, 32), (300, 701, 40, 32), (500, 1500, 100, 16), (600, 79, 11, 8),
+                                            (40, 1301, 5, 8), (200, 601, 1, 32), (1500, 1500, 64, 8), (1500, 1500, 64, 32)])
 def test_lstm_cell_of_a_batch(pb, H, I, N, act_bits):
-    """The cell update at the end of either kernel, the second part of the input at an odd column: against the same call on
-    the default layout, whose update is a kernel of its own (2e-6: two evaluations of the same functions)."""
+    """The cell update at the end of every kernel, the second part of the input also at odd columns, in the chunk where it
+    begins and in the chunks behind (2e-6: the bound of the other cell tests)."""
     g = np.random.default_rng(200300822 + 61)
+    frac_bits = {32: 16, 16: 12, 8: 4}[act_bits]
     W = g.uniform(-0.04, 0.04, size=(4 * H, I + H)).astype(np.float32)
     x, h, c = (g.normal(size=(N, n)).astype(np.float32) for n in (I, H, H))
     bias = g.normal(0, 0.1, size=4 * H).astype(np.float32)
-    out = []
+    prep = po.prepare(W, 5)
+    _, Y = po.matmul_words(po.pack_words(prep["layers"]), prep["scales"], 5, I + H, np.concatenate([x, h], axis=1),
+                           frac_bits=frac_bits, act_bits=act_bits)
+    h_ref, c_ref = po.lstm_pointwise(Y, bias, c)
     for lay in (GATES, BITS):
-        lin = pb.PackedLinear(dev(W), 5, max_batch=N, act_bits=act_bits, frac_bits={32: 16, 16: 12, 8: 4}[act_bits], layout=lay)
+        lin = pb.PackedLinear(dev(W), 5, max_batch=N, act_bits=act_bits, frac_bits=frac_bits, layout=lay)
         ho, co = (torch.empty((N, H), dtype=torch.float32, device="cuda") for _ in range(2))
         pb.pb_lstm_cell(lin.packed, lin.scales, lin.desc, 5, dev(x), I, dev(h), dev(c), dev(bias), ho, co, N, lin.workspace)
-        out.append((ho.cpu().numpy(), co.cpu().numpy()))
-    for a, b in zip(*out):
-        assert np.isfinite(a).all() and np.abs(a - b).max() <= 2e-6
+        assert np.abs(ho.cpu().numpy() - h_ref).max() <= 2e-6
+        assert np.abs(co.cpu().numpy() - c_ref).max() <= 2e-6
 
 
 def test_calls_of_one_layer_on_two_streams(pb):
