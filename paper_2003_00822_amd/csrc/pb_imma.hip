@@ -424,9 +424,10 @@ static int fused_per_cu(int S) { return S >= 4 ? 1 : 8 / S; }
 // 16384 x 12288 34.7 -> 40.2 and 4616 x 2016, 12 bitlayers, 7.0 -> 8.0 us.)
 static bool streaming(const I8Call &c) { return c.tiles == 1 && c.weights > 32.0 && c.weights <= 80.0; }
 
-// Which kernel: the one with the least estimated time.  The estimates are in us, fitted to the times of 170 layers on an MI355X (64
-// to 16384 rows and columns, 2 to 1024 vectors, 1 to 16 bitlayers, 8, 16 and 32 activation bits, both layouts); the choice costs 2 % on
-// average over the best one, 1.3 times in the worst case.  (A second launch counts 0.7 us more than on the device alone.)
+// Which kernel: the one with the least estimated time.  The estimates are in us, fitted to the times of 280 layers on an MI355X (64
+// to 16384 rows, 64 to 32768 columns, 2 to 1024 vectors, 1 to 16 bitlayers, 8, 16 and 32 activation bits, both layouts); the choice
+// costs 1.5 % on average over the best one, 1.34 times in the worst case.  The bitlayers count by themselves: with one cost for all,
+// one and two bitlayers of a few vectors went to the wrong kernel (3841 x 7174, one bitlayer, 14 vectors: 13.4 us, here 10.9).
 //   few digit rows: rounds of workgroups over the chip, units (row tile, group, tile of digit rows, chunk), conversion
 //   many:           rounds of workgroups times (start and end + steps), the digits of all vectors through memory
 static int pick_way(const I8Call &c, bool prepared)
@@ -443,6 +444,7 @@ static int pick_way(const I8Call &c, bool prepared)
     auto offer = [&](int way, double t) {
         if (t < least) { least = t; best = way; }
     };
+    const double bits = (c.m < 8 ? c.m : 8) / 8.0;
     const double quad = c.m > 4 ? 4.0 : 2.0;       // (the codes of a unit cost about as much as that many matrix tiles)
     for (int way = 0; way < kFusedNt; ++way) {
         const int tm = way_tiles(way), groups = (c.tiles + tm - 1) / tm;
@@ -461,15 +463,16 @@ static int pick_way(const I8Call &c, bool prepared)
         const int pairs = (c.batch + 1) / 2 < 8 * tm / c.nd ? (c.batch + 1) / 2 : 8 * tm / c.nd;     // of vectors of a workgroup
         const double conversions = (double)((((c.rt + rounds - 1) / rounds) * groups + cus - 1) / cus) * c.cq * pairs / 10.0;
         const double digits = c.tiles * c.cq / 100.0;
+        const double steps = sets * cpw;
         switch (way) {
-        case kMemory1: offer(way, (prepared ? 2.5 : 5.2) + 1.31 * sets * cpw + 0.29 * sets + 1.57 * digits + 0.194 * units + 0.106 * c.weights); break;
-        case kMemory4: offer(way, (prepared ? 2.5 : 4.9) + 2.06 * sets * cpw + 1.03 * sets + 1.66 * digits + 0.36 * units + 0.063 * c.weights); break;
-        case kFused1: offer(way, 3.0 + 0.69 * sets * cpw + 0.32 * sets + 0.72 * conversions + 0.193 * units + 0.045 * c.weights); break;
-        default: offer(way, 3.2 + 1.54 * sets + 0.88 * conversions + 0.026 * units); break;
+        case kMemory1: offer(way, (prepared ? 2.9 : 4.9) + 1.34 * steps + 1.51 * digits + (0.10 + 0.27 * bits) * units + 0.051 * c.weights); break;
+        case kMemory4: offer(way, (prepared ? 3.6 : 5.6) + (1.55 + 0.48 * bits) * steps + 1.33 * digits + (0.24 + 0.34 * bits) * units + 0.019 * c.weights); break;
+        case kFused1: offer(way, 3.4 + (0.60 + 0.37 * bits) * steps + 0.69 * conversions + (0.20 + 0.15 * bits) * units); break;
+        default: offer(way, 3.4 + 0.69 * bits * steps + 0.87 * sets + 0.79 * conversions + 0.137 * units); break;
         }
     }
     static const double cost[kTileShapes][5] = {   // start, step, start and end of a workgroup, weights (MB), digits
-        {4.2, 1.78, 5.94, 0.066, 0.0089}, {4.3, 2.68, 8.26, 0.059, 0.0062}, {4.6, 4.75, 12.5, 0.15, 0.0093}};
+        {3.4, 1.67, 5.79, 0.074, 0.0094}, {3.6, 2.68, 7.80, 0.060, 0.0075}, {2.9, 4.31, 17.0, 0.100, 0.0143}};
     for (int i = 0; i < kTileShapes; ++i) {
         const TileShape &t = kTile[i];
         if (c.groups > t.nt) continue;      // (a row tile's groups would take several passes)
