@@ -28,6 +28,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0                       # MI355X HBM3E, published
 ALU_PEAK_GOPS = 256 * 4 * 16 * 2.4          # CUs x SIMDs x lanes x GHz = 39321.6 G int32 lane-ops/s
 FP4_PEAK_TFLOPS = 10100.0                   # dense FP4 matrix-core peak, published
+I8_PEAK_TOPS = 5030.0                       # dense 8-bit integer matrix-core peak, published
 LLC_BYTES = 256 << 20                       # last-level (Infinity) cache
 POOL_BYTES = 768 << 20                      # weight copies rotated through: 3x the last-level cache
 
@@ -544,11 +545,21 @@ def size_sweep(torch, pb, dev, layout):
     return {"workload": "FC n x n, B=8, batch 1, cold weights, whole call (one launch)", "rows": rows}
 
 
+def matrix_rate(size, m, N, t, fp4=False):
+    """What the matrix instructions of a call with m bitlayers come to: 16 digit rows per vector and bitlayer in FP4, or 4 byte
+    digits per vector for up to eight bitlayers together."""
+    issued = 2.0 * (16 * m if fp4 else 4) * size * size * N / t / 1e12
+    if fp4:
+        return {"mfma_issued_TFLOPs": round(issued, 1), "mfma_frac": round(issued / FP4_PEAK_TFLOPS, 4)}
+    return {"mfma_issued_TOPs": round(issued, 1), "mfma_frac": round(issued / I8_PEAK_TOPS, 4)}
+
+
 def batch_sweep(torch, pb, synth, dev):
     """Large FC layer (8192 x 8192, B = 8, bits_used = 8) at batch 1 .. 1024: the regime where the product is a
     dense contraction.  Both kernels, weights warm (the 64 MiB stay in the last-level cache between the passes
     of one call anyway).  Nominal work = rows * cols * bits_used * 32 planes * batch 1-bit multiply-accumulates.
-    Matrix-core rows: the FP4 instructions issued against the matrix peak.  Popcount rows: the vector-ALU lane
+    Matrix-core rows: the products issued (batch 1 on the default layout: FP4 digits, else whole weight codes times the
+    four bytes of an activation) against the peak of that type.  Popcount rows: the vector-ALU lane
     operations the kernel executes (one AND + one popcount-accumulate per 32-bit weight word and ACTIVE plane: planes
     that are empty or copies of the sign plane are skipped, the count comes from the plane statistics the activation
     kernel leaves in the workspace) against the integer vector-ALU peak.  Narrower activations (Section 3.1, Table 1)
@@ -595,11 +606,7 @@ def batch_sweep(torch, pb, synth, dev):
             row = {"kernel": name, "batch": N, "act_bits": 32, "us_per_call": round(t * 1e6, 1),
                    "us_per_vector": round(t * 1e6 / N, 2), "Tbitmac_per_s": round(macs / t / 1e12, 1)}
             if name.startswith("mfma"):
-                # matrix instructions issued: 16 digit rows (two planes each) per vector, and with more than one
-                # vector (on the pairs layout: always) two bitlayers per instruction
-                units = m if (N == 1 and name == "mfma") else (m + 1) // 2
-                row["mfma_issued_TFLOPs"] = round(2.0 * 16 * n * n * units * N / t / 1e12, 1)
-                row["mfma_frac"] = round(2.0 * 16 * n * n * units * N / t / 1e12 / FP4_PEAK_TFLOPS, 4)
+                row.update(matrix_rate(n, m, N, t, fp4=N == 1 and name == "mfma"))
             else:
                 meta = lin.workspace[:N * 64].view(torch.int32).view(N, 16).cpu().numpy()
                 planes = float(meta[:, 3].sum())                       # active planes, summed over the vectors
@@ -621,7 +628,7 @@ def batch_sweep(torch, pb, synth, dev):
                              "us_per_vector": round(t * 1e6 / N, 2),
                              "Tbitmac_per_s": round(float(n) * n * m * k * N / t / 1e12, 1)})
             del lin
-    # rows of 16384 columns: the kernels that take the columns in several passes (batch 16 and 64)
+    # rows of 16384 columns (batch 16 and 64)
     del Wd, X, Y
     nw = 16384
     W, _ = synth.fc_square(nw, 0.01, batch=1, cfg=6)
@@ -636,14 +643,13 @@ def batch_sweep(torch, pb, synth, dev):
             def f():
                 pb.pb_matmul(lin.packed, lin.scales, lin.desc, m, X[:N], N, Y[:N], lin.workspace)
             t = time_calls(f, N)
-            issued = 2.0 * 16 * nw * nw * ((m + 1) // 2) * N / t / 1e12
             wide.append({"kernel": name, "batch": N, "act_bits": 32, "us_per_call": round(t * 1e6, 1),
                          "us_per_vector": round(t * 1e6 / N, 2),
                          "Tbitmac_per_s": round(float(nw) * nw * m * 32 * N / t / 1e12, 1),
-                         "mfma_issued_TFLOPs": round(issued, 1), "mfma_frac": round(issued / FP4_PEAK_TFLOPS, 4)})
+                         **matrix_rate(nw, m, N, t)})
         del lin
     return {"workload": "FC 8192x8192, B=8, bits_used=8, x~N(0,1), batch 1..1024, weights warm",
-            "alu_peak_Gops": round(ALU_PEAK_GOPS, 1), "fp4_peak_TFLOPs": FP4_PEAK_TFLOPS, "rows": rows,
+            "alu_peak_Gops": round(ALU_PEAK_GOPS, 1), "fp4_peak_TFLOPs": FP4_PEAK_TFLOPS, "i8_peak_TOPs": I8_PEAK_TOPS, "rows": rows,
             "wide_rows": {"workload": "FC 16384x16384, B=8, bits_used=8, x~N(0,1), batch 16 and 64, weights warm",
                           "rows": wide}}
 
@@ -668,11 +674,10 @@ def batch_point(torch, pb, synth, dev, n, B, N, steps, layout):
     e1.record()
     torch.cuda.synchronize()
     t = e0.elapsed_time(e1) * 1e-3 / steps
-    units = B if (N == 1 and layout == "mfma") else (B + 1) // 2
     return {"workload": "FC %dx%d, B=bits_used=%d, batch %d, x~N(0,1), weights warm, kernel %s" % (n, n, B, N, layout),
             "steps": steps, "us_per_call": round(t * 1e6, 1),
             "Tbitmac_per_s": round(float(n) * n * B * 32 * N / t / 1e12, 1),
-            "mfma_issued_TFLOPs": round(2.0 * 16 * n * n * units * N / t / 1e12, 1) if layout != "popc" else None}
+            **(matrix_rate(n, B, N, t, fp4=N == 1 and layout == "mfma") if layout != "popc" else {})}
 
 
 def _host_threads():
