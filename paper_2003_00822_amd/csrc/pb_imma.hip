@@ -377,26 +377,29 @@ static const void *const kI8[3][3][2][2][kStreams] = {PB_I8(kStore), PB_I8(kCell
 // Staged digits of a workgroup at most (a compute unit has 160 KB of LDS)
 constexpr int kMaxStage = 140 * 1024;
 
-// Compute units, and workgroups of a kernel that fit on the device at once (neither changes while the process lives)
-static int compute_units()
+// Compute units (at least one, or an error), and workgroups of a kernel that fit on the device at once (0: the query failed);
+// neither changes while the process lives
+static hipError_t compute_units(int *cus)
 {
-    static int cus;
-    int v = __atomic_load_n(&cus, __ATOMIC_RELAXED);
-    if (v > 0) return v;
+    static int cache;
+    *cus = __atomic_load_n(&cache, __ATOMIC_RELAXED);
+    if (*cus > 0) return hipSuccess;
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    __atomic_store_n(&cus, v, __ATOMIC_RELAXED);
-    return v;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    if (*cus < 1) return hipErrorInvalidDevice;
+    __atomic_store_n(&cache, *cus, __ATOMIC_RELAXED);
+    return hipSuccess;
 }
-static int resident(const void *fn, int threads, size_t lds, int *slot)
+static int resident(const void *fn, int threads, size_t lds, int cus, int *slot)
 {
     int v = __atomic_load_n(slot, __ATOMIC_RELAXED);
     if (v > 0) return v;
     int per_cu = 0;
     if (lds && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxStage) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess) return 0;
-    v = compute_units() * per_cu;
+    v = cus * per_cu;
     if (v > 0) __atomic_store_n(slot, v, __ATOMIC_RELAXED);
     return v;
 }
@@ -430,7 +433,7 @@ static bool streaming(const I8Call &c) { return c.tiles == 1 && c.weights > 32.0
 // one and two bitlayers of a few vectors went to the wrong kernel (3841 x 7174, one bitlayer, 14 vectors: 13.4 us, here 10.9).
 //   few digit rows: rounds of workgroups over the chip, units (row tile, group, tile of digit rows, chunk), conversion
 //   many:           rounds of workgroups times (start and end + steps), the digits of all vectors through memory
-static int pick_way(const I8Call &c, bool prepared)
+static int pick_way(const I8Call &c, bool prepared, int cus)
 {
 #ifdef PB_TUNING
     if (const char *e = getenv("PB_TUNE_WAY")) {
@@ -438,7 +441,6 @@ static int pick_way(const I8Call &c, bool prepared)
         if (w >= 0 && (!is_fused(w) || (!prepared && stage_bytes(c, way_tiles(w)) <= kMaxStage))) return w;
     }
 #endif
-    const int cus = compute_units();
     int best = kMemory1;
     double least = 1e30;
     auto offer = [&](int way, double t) {
@@ -514,7 +516,10 @@ int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, in
     c.rt = L.rt_count; c.cq = L.cq; c.tiles = (batch + vpt - 1) / vpt; c.batch = batch; c.nd = nd; c.m = bits_used;
     c.groups = A ? (pairs_out ? (bits_used + 1) / 2 : bits_used) : i8_groups(bits_used);
     c.weights = (double)L.layer_words * 4e-6 * bits_used;
-    int way = pick_way(c, prepared);
+    int cus;
+    const hipError_t no_device = compute_units(&cus);
+    if (no_device != hipSuccess) return (int)no_device;
+    int way = pick_way(c, prepared, cus);
     if (way == kFusedNt && (A || ep.c_prev)) way = kFused1;
     const int shape = way - kStreams;
     if (!prepared && !is_fused(way)) {
@@ -532,9 +537,9 @@ int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, in
     const int S = (L.cq + a.chunks_per_wave - 1) / a.chunks_per_wave;
     const size_t lds = is_fused(way) ? stage_bytes(c, tm) : 0;
     static int cache[3][3][2][2][kStreams][17][24];   // (the last index: LDS in steps of 6 KB)
-    int capacity = resident(fn, S * 64, lds, &cache[epi][ndi][q][il][way][S][lds / 6144]);
+    int capacity = resident(fn, S * 64, lds, cus, &cache[epi][ndi][q][il][way][S][lds / 6144]);
     if (capacity < 1) return (int)hipErrorInvalidValue;
-    if (is_fused(way) && capacity > compute_units() * fused_per_cu(S)) capacity = compute_units() * fused_per_cu(S);
+    if (is_fused(way) && capacity > cus * fused_per_cu(S)) capacity = cus * fused_per_cu(S);
     const int groups = (c.tiles + tm - 1) / tm;
     int wgs = capacity / groups;
     if (wgs < 1) wgs = 1;

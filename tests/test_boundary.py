@@ -3,6 +3,9 @@ answers size queries and rejects bad arguments before launching anything (no GPU
 import ctypes
 import os
 import re
+import subprocess
+import sys
+import textwrap
 
 import pytest
 
@@ -203,3 +206,25 @@ def test_strerror(pb):
     for s in (pb.PB_EINVAL, pb.PB_EALIGN, pb.PB_ESIZE, pb.PB_EHIP):
         assert pb.strerror(s) and pb.strerror(s) != "unknown status"
     assert pb.strerror(-99) == "unknown status"
+
+
+def test_calls_without_a_device_return_an_error(pb):
+    """A HIP call that fails is PB_EHIP for every kernel that the host could choose; nothing ends the process."""
+    code = """
+        import ctypes
+        from paper_2003_00822_amd import pb
+        L, fake, null = pb.lib(), ctypes.c_void_p(0x1000), ctypes.c_void_p(0)
+        for layout in (pb.PB_LAYOUT_TILE16_V1, pb.PB_LAYOUT_TILE16_PAIRS_V1, pb.PB_LAYOUT_TILE16_GATES_V1,
+                       pb.PB_LAYOUT_ROWMAJOR_V1):
+            d = ctypes.byref(pb.pb_desc_init_layout(64, 64, 4, layout))
+            for batch in (1, 2, 64, 1000):
+                assert L.pb_matmul(fake, fake, d, 4, fake, batch, fake, fake, null) == pb.PB_EHIP
+                assert pb.lib().pb_last_hip_error() != 0
+                assert L.pb_matmul_acc(fake, d, 4, fake, batch, fake, fake, null) == pb.PB_EHIP
+                if layout != pb.PB_LAYOUT_ROWMAJOR_V1:
+                    assert L.pb_matmul_acc_pairs(fake, d, 4, fake, batch, fake, fake, null) == pb.PB_EHIP
+                assert L.pb_matmul_prepared(fake, fake, d, 4, batch, fake, fake, null) == pb.PB_EHIP
+                assert L.pb_lstm_cell(fake, fake, d, 4, fake, 48, fake, fake, null, fake, fake, batch, fake, null) == pb.PB_EHIP
+    """
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1", CUDA_VISIBLE_DEVICES="-1")
+    subprocess.run([sys.executable, "-W", "ignore", "-c", textwrap.dedent(code)], check=True, cwd=ROOT, env=env, timeout=300)
