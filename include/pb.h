@@ -19,6 +19,9 @@
  *    synchronises.  All work is enqueued on `stream` (a hipStream_t passed as
  *    void*, NULL = the default stream); calls on different streams may run
  *    concurrently as long as they use different workspaces and outputs.
+ *    A call may be several launches that hand data on through its workspace;
+ *    host threads that use one workspace on one stream each get theirs in one
+ *    piece (pb_act_prep ... pb_matmul_prepared are two calls).
  *  - Every function returns PB_OK (0) or a negative pb_status; nothing
  *    throws or aborts.  Argument errors are detected on the host before
  *    anything is launched.  A HIP launch failure returns PB_EHIP

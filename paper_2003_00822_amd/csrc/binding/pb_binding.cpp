@@ -197,19 +197,16 @@ PyObject *linear(PyObject *, PyObject *const *args, Py_ssize_t nargs)
                     void *stream = current_stream();
                     const auto matmul = reinterpret_cast<decltype(&pb_matmul)>(g_fn[kMatmul]);
                     int rc;
-                    if (batch == 1 && d.v.layout != PB_LAYOUT_ROWMAJOR_V1 && d.v.layout != PB_LAYOUT_TILE16_PAIRS_V1) {
-                        Py_BEGIN_ALLOW_THREADS      // (one launch that leaves nothing in the workspace)
-                        rc = matmul(packed.v, scales.v, &d.v, m.v, x.v, batch, y.v, workspace.v, stream);
-                        Py_END_ALLOW_THREADS
-                    } else {
-                        // The call may be two launches, the first of which writes the workspace.  The holder's own serves the
-                        // stream it was made on, whose launches of other threads wait for the interpreter lock; on another
-                        // stream the call has one of its own.
-                        at::Tensor own;
-                        if (stream != home.v) own = at::empty_like(THPVariable_Unpack(held.o[held.workspace]));
-                        rc = matmul(packed.v, scales.v, &d.v, m.v, x.v, batch, y.v, own.defined() ? own.data_ptr() : workspace.v,
-                                    stream);
-                    }
+                    // A batch goes through the workspace.  The holder's own serves the stream it was made on (the library keeps the
+                    // launches of two threads apart); on another stream the call has one of its own.
+                    at::Tensor own;
+                    if ((batch > 1 || d.v.layout == PB_LAYOUT_ROWMAJOR_V1 || d.v.layout == PB_LAYOUT_TILE16_PAIRS_V1) &&
+                        stream != home.v)
+                        own = at::empty_like(THPVariable_Unpack(held.o[held.workspace]));
+                    void *const work = own.defined() ? own.data_ptr() : workspace.v;
+                    Py_BEGIN_ALLOW_THREADS
+                    rc = matmul(packed.v, scales.v, &d.v, m.v, x.v, batch, y.v, work, stream);
+                    Py_END_ALLOW_THREADS
                     if (rc != PB_OK) return status_result(rc, kNames[kMatmul]);
                     if (args[3] != Py_None) {
                         Py_INCREF(args[3]);

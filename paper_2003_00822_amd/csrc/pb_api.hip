@@ -2,6 +2,7 @@
 // carving and kernel dispatch.  No device memory is allocated or freed here and
 // nothing synchronises; every kernel goes to the caller's stream.
 #include <hip/hip_runtime.h>
+#include <pthread.h>
 #include <stdint.h>
 
 #include "pb.h"
@@ -52,6 +53,27 @@ int scratch_address(void **out)
     *out = p;
     return 0;
 }
+
+// Held while the launches of one call that go through its workspace are made: another host thread's launches on the same
+// workspace and stream must not come between them (the stream then runs the calls one after the other).  By the address of
+// the workspace; two workspaces on one lock cost the second call the microseconds of the first one's launches.  Null: no lock.
+class Issuing {
+public:
+    explicit Issuing(const void *workspace) : m(workspace ? of(workspace) : nullptr) { if (m) pthread_mutex_lock(m); }
+    ~Issuing() { if (m) pthread_mutex_unlock(m); }
+    Issuing(const Issuing &) = delete;
+    Issuing &operator=(const Issuing &) = delete;
+
+private:
+    struct Lock { pthread_mutex_t m = PTHREAD_MUTEX_INITIALIZER; };
+    static pthread_mutex_t *of(const void *workspace)
+    {
+        static Lock locks[64];
+        const uint64_t a = reinterpret_cast<uintptr_t>(workspace);   // (blocks of 512 bytes and of 2 MB: all bits count)
+        return &locks[(a * 0x9E3779B97F4A7C15ull) >> 58].m;
+    }
+    pthread_mutex_t *m;
+};
 
 int hip_status(int err)
 {
@@ -136,7 +158,8 @@ int pb_unpack(const void *packed, const pb_desc *d, int32_t *q, void *stream)
 
 static int matmul_common(const void *packed, const float *scales, const pb_desc *d, int bits_used, const float *X0,
                          int cols0, const float *X1, int cols1, int batch, float *Y, int64_t *A, void *workspace,
-                         void *stream, const pb::Epilogue &ep = pb::Epilogue(), bool pairs_out = false)
+                         void *stream, const pb::Epilogue &ep = pb::Epilogue(), bool pairs_out = false,
+                         bool locked = false)
 {
     pb::Layout L;
     int rc = check_desc(d, &L);
@@ -151,7 +174,10 @@ static int matmul_common(const void *packed, const float *scales, const pb_desc 
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (ep.bias && !aligned16(ep.bias)) return PB_EALIGN;
     if (pairs_out && L.cols > pb::kMaxColsPairs) return PB_ESIZE;
-    if (pb::takes_digits(L, batch, pairs_out))
+    const bool digits = pb::takes_digits(L, batch, pairs_out);
+    const bool several = digits || !pb::is_tile16(L.layout);   // (launches)
+    const Issuing issuing(several && !locked ? workspace : nullptr);
+    if (digits)
         return hip_status(pb::launch_imma(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
                                           d->act_bits, X0, cols0, X1, cols1,
                                           static_cast<char *>(workspace) + pb::ws_planes_off(L, batch), false, batch, Y,
@@ -234,6 +260,7 @@ int pb_act_prep(const pb_desc *d, const float *X, int batch, void *workspace, vo
     char *ws = static_cast<char *>(workspace);
     int *meta = reinterpret_cast<int *>(ws + pb::ws_meta_off(L, batch));
     uint32_t *planes = reinterpret_cast<uint32_t *>(ws + pb::ws_planes_off(L, batch));
+    const Issuing issuing(workspace);   // (it writes what a call between its launches may have left there)
     if (pb::takes_digits(L, batch))
         return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, nullptr,
                                             static_cast<hipStream_t>(stream)));
@@ -279,6 +306,7 @@ int pb_fixed_point(const pb_desc *d, const float *X, int batch, int32_t *xq, voi
     char *ws = static_cast<char *>(workspace);
     int *meta = reinterpret_cast<int *>(ws + pb::ws_meta_off(L, batch));
     uint32_t *planes = reinterpret_cast<uint32_t *>(ws + pb::ws_planes_off(L, batch));
+    const Issuing issuing(workspace);   // (it writes what a call between its launches may have left there)
     if (pb::takes_digits(L, batch))
         return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, xq,
                                             static_cast<hipStream_t>(stream)));
@@ -320,9 +348,10 @@ int pb_lstm_cell(const void *packed, const float *scales, const pb_desc *d, int 
                                  workspace, stream, ep);
         }
     }
+    const Issuing issuing(workspace);
     float *gates = reinterpret_cast<float *>(static_cast<char *>(workspace) + pb::ws_gates_off(L, batch));
     rc = matmul_common(packed, scales, d, bits_used, x_t, input_size, h_prev, H, batch, gates, nullptr, workspace,
-                       stream);
+                       stream, pb::Epilogue(), false, true);
     if (rc != PB_OK) return rc;
     return hip_status(pb::launch_lstm_pointwise(gates, bias, c_prev, H, batch, h_out, c_out,
                                                 static_cast<hipStream_t>(stream)));

@@ -2,6 +2,8 @@
 the launcher can choose, rows and columns that do not fill the last tile, batches that leave digit rows empty, groups of
 bitlayers that share a code and groups of one, activations saturated at both ends.  Oracle: the definition of the
 per-bitlayer sums on sampled rows (exact integers), then the scales in fp64."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -128,6 +130,32 @@ def test_calls_of_one_layer_on_two_streams(pb):
         for i, st in enumerate(streams):
             with torch.cuda.stream(st):
                 got[i].append(lin(Xs[i]))
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert all(torch.equal(y, want[i]) for y in got[i])
+
+
+def test_two_threads_on_one_stream_and_workspace(pb):
+    """The launches of a call stay together: no thread's product reads the digits of the other's."""
+    R, C, N = 2000, 3000, 64
+    W, X = synth.ragged(R, C, batch=N, case=793, xdist="normal")
+    lin = pb.PackedLinear(dev(W), 8, max_batch=N)
+    Xs = [dev(X), dev(X[::-1].copy())]
+    want = [lin(x).clone() for x in Xs]
+    got = [[torch.empty_like(w) for _ in range(30)] for w in want]
+    start = threading.Barrier(2)
+
+    def work(i):
+        start.wait()
+        for k, y in enumerate(got[i]):
+            if k % 2:
+                lin(Xs[i], out=y)
+            else:
+                pb.pb_matmul(lin.packed, lin.scales, lin.desc, 8, Xs[i], N, y, lin.workspace)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
     torch.cuda.synchronize()
     for i in range(2):
         assert all(torch.equal(y, want[i]) for y in got[i])

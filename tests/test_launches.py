@@ -1,0 +1,109 @@
+"""Which kernels the host side launches, and in which order, worked out without a GPU: libpbatch.so on a HIP runtime that
+writes launches down (mock_hip.cpp), in a process of its own."""
+import json
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, json, sys, threading
+mock = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # before the library, which then finds these functions first
+mock.mock_launch.restype = ctypes.c_char_p
+L = ctypes.CDLL(sys.argv[2])
+ROWS, BITS, GATES, PAIRS = 0x50420001, 0x50420002, 0x50420003, 0x50420004
+F = ctypes.c_void_p(0x10000000)                               # an aligned address that nothing reads
+WORK = ctypes.c_void_p(0x20000000)
+
+class Desc(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("rows", "cols", "bits", "frac_bits", "act_bits")] + [("layout", ctypes.c_uint32)]
+
+def desc(rows, cols, bits, layout, act_bits=32):
+    d = Desc()
+    assert L.pb_desc_init_layout(ctypes.byref(d), rows, cols, bits, ctypes.c_uint32(layout)) == 0
+    d.act_bits = act_bits
+    return d
+
+def launches():
+    out, all_ = (ctypes.c_int * 5)(), []
+    for i in range(mock.mock_launches()):
+        name = mock.mock_launch(i, out).decode()
+        all_.append((name, out[4]))
+    mock.mock_clear()
+    return all_
+"""
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    from paper_2003_00822_amd import build
+    build.ensure(verbose=False)
+    mock = tmp_path_factory.mktemp("mock") / "libmock_hip.so"
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-pthread", "-o", str(mock),
+                           os.path.join(ROOT, "tests", "mock_hip.cpp")])
+
+    def run(code, *args):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(code), str(mock), build.LIB, *args],
+                           stdout=subprocess.PIPE, check=True, timeout=300)
+        return json.loads(r.stdout)
+    return run
+
+
+def test_calls_on_one_workspace_do_not_mix_their_launches(probe):
+    """A call of several launches hands data on through its workspace.  Two host threads that use one workspace on one stream
+    must each get their launches in one piece (the stream then keeps them apart)."""
+    got = probe("""
+        N = 64
+        d, p = desc(2000, 3000, 8, BITS), desc(2000, 3000, 8, PAIRS)
+        r, lb, lg, s = desc(300, 700, 4, ROWS), desc(400, 300, 4, BITS), desc(6000, 3000, 8, GATES), desc(4096, 4096, 8, BITS)
+        ref = ctypes.byref
+        cell = lambda l, i: lambda: L.pb_lstm_cell(F, F, ref(l), 4, F, i, ctypes.c_void_p(0x50000000), F, None,
+                                                   ctypes.c_void_p(0x60000000), F, N, WORK, None)
+        calls = {
+            "matmul": lambda: L.pb_matmul(F, F, ref(d), 8, F, N, F, WORK, None),
+            "matmul pairs": lambda: L.pb_matmul(F, F, ref(p), 8, F, N, F, WORK, None),
+            "matmul rows": lambda: L.pb_matmul(F, F, ref(r), 4, F, 2, F, WORK, None),
+            "bias": lambda: L.pb_matmul_bias_act(F, F, ref(d), 8, F, N, F, 1, F, WORK, None),
+            "bias rows": lambda: L.pb_matmul_bias_act(F, F, ref(r), 4, F, 2, F, 1, F, WORK, None),
+            "static": lambda: L.pb_matmul_static(F, F, ref(s), 8, F, 60, F, None),
+            "sums": lambda: L.pb_matmul_acc(F, ref(d), 8, F, N, F, WORK, None),
+            "sums of pairs": lambda: L.pb_matmul_acc_pairs(F, ref(d), 8, F, N, F, WORK, None),
+            "cell": cell(lb, 200), "cell one launch": cell(lg, 1500),
+            "prep": lambda: L.pb_act_prep(ref(d), F, N, WORK, None),
+            "fixed point": lambda: L.pb_fixed_point(ref(d), F, N, F, WORK, None),
+        }
+        single = {}
+        for name, f in calls.items():
+            assert f() == 0, name
+            single[name] = [k for k, _ in launches()]
+        mock.mock_pause(3)
+        mixed = []
+        for a, b in [(n, n) for n in calls] + [("matmul", "prep"), ("matmul", "fixed point"), ("cell", "matmul")]:
+            start = threading.Barrier(2)
+            def work(me, f):
+                mock.mock_caller(me)
+                start.wait()
+                for _ in range(3):
+                    assert f() == 0
+            threads = [threading.Thread(target=work, args=(i, calls[n])) for i, n in enumerate((a, b))]
+            [t.start() for t in threads]
+            [t.join() for t in threads]
+            mixed.append((a, b, launches()))
+        print(json.dumps([single, mixed]))
+    """)
+    single, mixed = got
+    assert len(single["matmul"]) == len(single["static"]) == len(single["sums"]) == len(single["cell one launch"]) == 2
+    assert len(single["bias rows"]) == 3 and len(single["cell"]) >= 2 and len(single["prep"]) == 1
+    for a, b, seen in mixed:
+        order = []
+        while seen:
+            me = seen[0][1]
+            want = single[(a, b)[me]]
+            assert [k for k, who in seen[:len(want)]] == want and {who for _, who in seen[:len(want)]} == {me}, (a, b, seen)
+            order.append(me)
+            seen = seen[len(want):]
+        assert sorted(order) == [0, 0, 0, 1, 1, 1]
