@@ -11,6 +11,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>
+#include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 
 #include <tuple>
@@ -99,6 +100,8 @@ struct Desc {
 };
 
 void *current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+
+bool capturing() { return c10::hip::currentStreamCaptureStatusMayInitCtx() != c10::hip::CaptureStatus::None; }
 
 PyObject *status_result(int rc, const char *where)
 {
@@ -198,10 +201,11 @@ PyObject *linear(PyObject *, PyObject *const *args, Py_ssize_t nargs)
                     const auto matmul = reinterpret_cast<decltype(&pb_matmul)>(g_fn[kMatmul]);
                     int rc;
                     // A batch goes through the workspace.  The holder's own serves the stream it was made on (the library keeps the
-                    // launches of two threads apart); on another stream the call has one of its own.
+                    // launches of two threads apart); on another stream the call has one of its own, and under capture: a graph
+                    // may be replayed on any stream (the memory is then the graph's, as that of the output).
                     at::Tensor own;
                     if ((batch > 1 || d.v.layout == PB_LAYOUT_ROWMAJOR_V1 || d.v.layout == PB_LAYOUT_TILE16_PAIRS_V1) &&
-                        stream != home.v)
+                        (stream != home.v || capturing()))
                         own = at::empty_like(THPVariable_Unpack(held.o[held.workspace]));
                     void *const work = own.defined() ? own.data_ptr() : workspace.v;
                     Py_BEGIN_ALLOW_THREADS

@@ -276,7 +276,7 @@ class PackedLinear:
         self.scales = torch.empty(max(bits, 4), dtype=torch.float32, device=W.device)
         self.max_batch = max_batch
         self.workspace = alloc_workspace(self.desc, max_batch, W.device)
-        self.home_stream = torch.cuda.current_stream().cuda_stream   # whose calls share `workspace`
+        self.home_stream = torch.cuda.current_stream().cuda_stream   # whose eager calls share `workspace`
         pb_quantize_pack_mode(W, self.desc, quantizer, self.packed, self.scales)
 
     def __call__(self, X: torch.Tensor, bits_used: int | None = None, out: torch.Tensor | None = None):

@@ -159,3 +159,28 @@ def test_two_threads_on_one_stream_and_workspace(pb):
     torch.cuda.synchronize()
     for i in range(2):
         assert all(torch.equal(y, want[i]) for y in got[i])
+
+
+def test_a_captured_call_has_a_workspace_of_its_own(pb):
+    """A graph may be replayed on any stream, beside other calls of the layer: also a call that is captured on the layer's
+    own stream must not write the workspace that eager calls use."""
+    R, C, N = 2000, 3000, 64                            # the digits travel through memory
+    W, X = synth.ragged(R, C, batch=N, case=791, xdist="normal")
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        lin = pb.PackedLinear(dev(W), 8, max_batch=N)
+        Xd = dev(X)
+        want = lin(Xd).clone()
+        Y = torch.zeros_like(want)
+        side.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            lin(Xd, out=Y)
+        lin.workspace.fill_(0xA5)
+    side.synchronize()
+    for _ in range(3):
+        Y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, want)
+    assert (lin.workspace == 0xA5).all()
