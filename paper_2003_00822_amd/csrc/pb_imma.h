@@ -227,7 +227,8 @@ __device__ __forceinline__ float bias_of(const I8Args &a, int prow)
 }
 
 // The sum of one vector and weight row from its digits' sums d[0 .. nd) and the sum of the row's codes, times the scale of the
-// group (every part is an integer below 2^53 and exact; the last step rounds once if the sum is beyond)
+// group (every part is an integer below 2^53 and exact; the last step rounds once if the sum is beyond).  The sum over the groups
+// starts at +0: no zero with the sign of a scale.
 template <int ND>
 __device__ __forceinline__ double scaled_sum(const Group &g, const int *d, int sum1)
 {
@@ -237,7 +238,7 @@ __device__ __forceinline__ double scaled_sum(const Group &g, const int *d, int s
         v = fma(65536.0, (double)d[2], fma(256.0, (double)d[1], v));
         v = fma(16777216.0, (double)d[3], fma(8421504.0, (double)sum1, v));
     }
-    return v * g.scale;
+    return fma(v, g.scale, 0.0);
 }
 template <int ND>
 __device__ __forceinline__ long long integer_sum(const Group &g, const int *d, int sum1)

@@ -184,3 +184,18 @@ def test_a_captured_call_has_a_workspace_of_its_own(pb):
         torch.cuda.synchronize()
         assert torch.equal(Y, want)
     assert (lin.workspace == 0xA5).all()
+
+
+@pytest.mark.parametrize("R,C,N", [(40, 700, 3), (2000, 3000, 64)])
+def test_zero_sums_keep_their_sign(pb, R, C, N):
+    """A sum of zeros is +0 whatever the signs of the scales: the fp64 sum starts at +0."""
+    W, _ = synth.ragged(R, C, batch=N, case=792, xdist="normal")
+    for bits in (1, 5, 12):
+        for layout in (BITS, PAIRS):
+            lin = pb.PackedLinear(dev(W), bits, max_batch=N, layout=layout)
+            halving = lin.scales.clone()
+            uneven = halving.clone()
+            uneven[0] *= 1.5
+            for scales in (halving, uneven):
+                lin.scales.copy_(-scales)
+                assert (lin(torch.zeros((N, C), device="cuda")).view(torch.int32) == 0).all(), (bits, hex(layout))
