@@ -173,7 +173,6 @@ static int matmul_common(const void *packed, const float *scales, const pb_desc 
         return PB_EALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (ep.bias && !aligned16(ep.bias)) return PB_EALIGN;
-    if (pairs_out && L.cols > pb::kMaxColsPairs) return PB_ESIZE;
     const bool digits = pb::takes_digits(L, batch, pairs_out);
     const bool several = digits || !pb::is_tile16(L.layout);   // (launches)
     const Issuing issuing(several && !locked ? workspace : nullptr);

@@ -46,20 +46,6 @@ constexpr int kTileRows = 16;       // matrix-core kernel: rows per tile
 constexpr int kChunkWords = 16;     // matrix-core kernel: words per row in one block
 constexpr int kMaxSlices = 16;      // kernel for one vector: waves (column slices) per workgroup
 constexpr int kMaxColsTile16 = 32768;     // 16 slices of 2048 columns
-// The sums of bitlayer pairs are asked for at every width
-constexpr int kMaxColsPairs = 32768;
-// Bitlayer pairs in FP4 form: with five of them in one set of accumulators (pair p counts 4^(last - p)) a register stays below
-// 9 * 2048 * 341 < 2^24 and the half sums of a row below 17 * 9 * 32768 * 341 < 2^31.  Rows wider than the digit rows that the
-// waves of a workgroup hold take several passes of at most `cap` chunks of 512 columns.  (Limits of that form, worked out by
-// the host tests; pairs are multiplied as whole codes, see pb_imma.h.)
-constexpr int kPairGroup = 5;
-constexpr int kSplitChunks4 = 16, kSplitChunks8 = 8;
-__host__ __device__ inline int split_parts(int cq, int cap) { return (cq + cap - 1) / cap; }
-__host__ __device__ inline int split_chunks_per_part(int cq, int cap)
-{
-    const int parts = split_parts(cq, cap);
-    return (cq + parts - 1) / parts;
-}
 
 struct Layout {
     uint32_t layout;

@@ -37,13 +37,11 @@ long long probe_workspace_bytes(unsigned layout, int rows, int cols, int bits, i
     return (long long)pb::workspace_bytes(L, batch);
 }
 
-// limits that the accumulator bounds depend on: {columns of a tiled matrix, columns with merged bitlayer pairs, column slices per row, bitlayer pairs that share accumulators}
+// limits that the accumulator bounds depend on: {columns of a tiled matrix, column slices per row}
 void probe_limits(int *out)
 {
     out[0] = pb::kMaxColsTile16;
-    out[1] = pb::kMaxColsPairs;
-    out[2] = pb::kMaxSlices;
-    out[3] = pb::kPairGroup;
+    out[1] = pb::kMaxSlices;
 }
 
 // PB_LAYOUT_TILE16_PAIRS_V1: the digit words of a bitlayer pair and back; out = {even, odd, upper, lower}
@@ -51,18 +49,6 @@ void probe_pair_digits(unsigned upper, unsigned lower, unsigned *out)
 {
     pb::digits_of_pair(upper, lower, &out[0], &out[1]);
     pb::pair_of_digits(out[0], out[1], &out[2], &out[3]);
-}
-
-// wide rows in several passes of at most cap chunks: out = {passes, chunks per pass} for a row of cq chunks
-void probe_split(int cq, int cap, int *out)
-{
-    out[0] = pb::split_parts(cq, cap);
-    out[1] = pb::split_chunks_per_part(cq, cap);
-}
-void probe_split_caps(int *out)
-{
-    out[0] = pb::kSplitChunks4;
-    out[1] = pb::kSplitChunks8;
 }
 
 }  // extern "C"

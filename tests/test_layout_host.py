@@ -150,28 +150,3 @@ def test_workspace_grows_with_batch(probe):
     a = probe.probe_workspace_bytes(TILE16, 100, 3000, 3, 1)
     b = probe.probe_workspace_bytes(TILE16, 100, 3000, 3, 7)
     assert a > 0 and b > a and a % 256 == 0 and b % 256 == 0
-
-
-
-def test_passes_over_wide_rows(probe):
-    """The geometry that the launcher and the matrix-core kernel share when batches on wide rows take the columns
-    in several passes (of what eight waves hold: 16 chunks with two chunks per wave, 8 with one): every chunk belongs
-    to exactly one pass, a pass never has more chunks than its capacity, the passes are as few as that allows and
-    evenly filled, and a row within the capacity needs one."""
-    caps = (ctypes.c_int * 2)()
-    probe.probe_split_caps(caps)
-    assert list(caps) == [16, 8]
-    out = (ctypes.c_int * 2)()
-    widest = layout_of(probe, TILE16, 16, 32768, 8)["cq"]
-    assert widest == 64
-    for cap, per_wave in ((16, 2), (8, 1)):
-        for cq in range(1, widest + 1):
-            probe.probe_split(cq, cap, out)
-            parts, per = list(out)
-            assert parts == -(-cq // cap) and 1 <= parts <= widest // cap
-            assert per <= cap and parts * per >= cq > (parts - 1) * per
-            waves = -(-per // per_wave)
-            assert 1 <= waves <= 8
-            # wave w of pass p owns per_wave chunks from per_wave (p * waves + w): all chunks once, in order
-            owned = [per_wave * (p * waves + w) + k for p in range(parts) for w in range(waves) for k in range(per_wave)]
-            assert sorted(set(owned)) == owned and set(range(cq)) <= set(owned)
