@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <chrono>
+#include <iterator>
 #include <map>
 #include <mutex>
 #include <string>
@@ -76,6 +77,8 @@ const char *mock_launch(int i, int *out)   // out: grid x, y, block, LDS, caller
     out[0] = (int)l.grid.x; out[1] = (int)l.grid.y; out[2] = (int)l.block.x; out[3] = (int)l.lds; out[4] = l.caller;
     return l.kernel.c_str();
 }
+int mock_kernels() { return (int)names().size(); }
+const char *mock_kernel(int i) { return std::next(names().begin(), i)->second.c_str(); }
 void mock_clear() { std::lock_guard<std::mutex> lock(g_mutex); g_launches.clear(); }
 
 }  // extern "C"

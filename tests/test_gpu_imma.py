@@ -1,7 +1,7 @@
-"""The kernels on the 8-bit integer matrix cores (csrc/pb_imma.hip, csrc/pb_imma_tile.hip) at the edges of their tiles: every way
-the launcher can choose, rows and columns that do not fill the last tile, batches that leave digit rows empty, groups of
-bitlayers that share a code and groups of one, activations saturated at both ends.  Oracle: the definition of the
-per-bitlayer sums on sampled rows (exact integers), then the scales in fp64."""
+"""The kernels on the 8-bit integer matrix cores (csrc/pb_imma.hip, csrc/pb_imma_tile.hip) at the edges of their tiles: every kernel
+that is compiled (test_launches.py works out on the host that the cases reach them all), rows and columns that do not fill the
+last tile, batches that leave digit rows empty, groups of bitlayers that share a code and groups of one, activations saturated
+at both ends.  Oracle: the definition of the per-bitlayer sums on sampled rows (exact integers), then the scales in fp64."""
 import threading
 
 import numpy as np
@@ -36,7 +36,9 @@ def check(pb, R, C, N, bits, m, act_bits, frac_bits, layout, sums):
     X[0, ::2], X[0, 1::2] = 3e38, -3e38                 # both ends of the fixed-point range
     X[N - 1, C - 1] = np.inf
     X[N // 2, :5] = np.nan
-    prep = po.prepare(W, bits)
+    rows = sorted({0, 1, R // 2, (R - 1) // 16 * 16, R - 1} | set(range(min(R, 20))))
+    # the codes of the sampled rows: the quantizer's step comes from the largest weight of all
+    prep = po.prepare(W[rows + [int(np.abs(W).max(axis=1).argmax())]], bits)
     lin = pb.PackedLinear(dev(W), bits, max_batch=N, frac_bits=frac_bits, act_bits=act_bits, layout=layout)
     Xd = dev(X)
     Y = lin(Xd, m).cpu().numpy()
@@ -49,9 +51,8 @@ def check(pb, R, C, N, bits, m, act_bits, frac_bits, layout, sums):
     A = lin.acc(Xd, m).cpu().numpy() if sums else None
     P = lin.acc_pairs(Xd, m).cpu().numpy() if sums else None
     xq = po.fixed_point(X, frac_bits=frac_bits, act_bits=act_bits)
-    rows = sorted({0, 1, R // 2, (R - 1) // 16 * 16, R - 1} | set(range(min(R, 20))))
-    for r in rows:
-        sub = po.layer_products_direct(prep["layers"][:, r:r + 1, :], m, xq)[:, :, 0]      # [m, N]
+    for k, r in enumerate(rows):
+        sub = po.layer_products_direct(prep["layers"][:, k:k + 1, :], m, xq)[:, :, 0]      # [m, N]
         assert_y_close(Y[:, r], po.dequant(sub, prep["scales"], m, frac_bits=frac_bits), sub, prep["scales"], frac_bits=frac_bits)
         want = sum(float(uneven[i]) * sub[i].astype(np.float64) for i in range(m)) * 2.0 ** -frac_bits
         assert_y_close(Y_uneven[:, r], want.astype(np.float32), sub, uneven, frac_bits=frac_bits)
@@ -74,29 +75,70 @@ CASES = [
     (4200, 8192, 2, 8, 8, 32, 16),       # too many weights for the L2 caches
     (4400, 3664, 13, 6, 6, 8, 4),        # digits from memory
     (4022, 2521, 61, 3, 2, 8, 4),        # ... four tiles per wave
-    (2100, 5000, 18, 7, 7, 32, 16),      # many digit rows, each shape of the kernel for them
-    (6000, 7871, 18, 7, 7, 16, 8),
+    (2100, 5000, 18, 7, 7, 32, 16),      # converted in the launch, two chunks per wave
+    (6000, 7871, 18, 7, 7, 16, 8),       # four tiles per wave, several row tiles
     (2000, 3000, 64, 8, 8, 32, 16),
     (4778, 6480, 13, 8, 5, 32, 16),
     (9000, 9000, 16, 6, 6, 32, 16),
-    (2620, 2697, 713, 8, 8, 32, 16),
+    (2620, 2697, 713, 8, 8, 32, 16),     # many digit rows, two tiles per wave
     (9347, 975, 686, 2, 1, 32, 16),
     (1500, 1600, 70, 12, 11, 32, 16),    # two groups per row tile there
     (1128, 1711, 71, 16, 16, 32, 16),    # three
 ]
 
+# One call for each compiled kernel that the calls above do not take.
+# rows, columns, vectors, bits, used, activation bits, position of the fixed point
+KERNELS = [
+    # many digit rows: four waves along them, eight, eight with four tiles each
+    (2669, 520, 187, 2, 1, 32, 16), (2207, 515, 67, 10, 8, 32, 16), (6326, 1189, 388, 8, 8, 32, 16), (4643, 3250, 491, 1, 1, 32, 16),
+    # four tiles per wave
+    (4379, 18, 105, 13, 1, 32, 16), (8300, 16, 57, 2, 1, 16, 12), (11051, 19, 81, 13, 5, 8, 4), (752, 2612, 168, 1, 1, 8, 4),
+    # one tile, digits from memory
+    (5782, 16, 34, 11, 9, 32, 16), (4130, 16, 49, 13, 6, 16, 12), (17, 4122, 7, 2, 1, 16, 12), (16, 2134, 13, 1, 1, 8, 4),
+    # two tiles, converted in the launch
+    (10319, 16, 5, 15, 2, 32, 16), (6172, 16, 9, 13, 7, 16, 12), (6202, 16, 9, 2, 1, 16, 12), (2352, 19, 17, 6, 5, 8, 4),
+    (2091, 16, 17, 9, 1, 8, 4), (430, 68, 443, 8, 8, 32, 16),
+    # one tile, converted in the launch
+    (16, 16, 2, 1, 1, 8, 4), (18, 16, 2, 8, 5, 8, 4),
+    # ... too many weights for the L2 caches
+    (8200, 8200, 2, 4, 4, 32, 16), (8200, 8200, 2, 4, 4, 16, 12), (8200, 8200, 2, 4, 4, 8, 4), (10694, 1040, 2, 16, 16, 16, 12),
+    (10745, 1035, 6, 16, 16, 8, 4),
+]
+
+
+def with_sums(R, N):
+    return R * N < 200000
+
 
 @pytest.mark.parametrize("layout", [BITS, PAIRS])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[:3])) + "-%d/%d-a%d" % (c[4], c[3], c[5]))
+@pytest.mark.parametrize("case", CASES + KERNELS, ids=lambda c: "x".join(map(str, c[:3])) + "-%d/%d-a%d" % (c[4], c[3], c[5]))
 def test_every_way(pb, case, layout):
     R, C, N, bits, m, act_bits, frac_bits = case
     print("way", case, hex(layout), flush=True)
-    check(pb, R, C, N, bits, m, act_bits, frac_bits, layout, sums=R * N < 200000)
+    check(pb, R, C, N, bits, m, act_bits, frac_bits, layout, sums=with_sums(R, N))
 
 
-@pytest.mark.parametrize("H,I,N,act_bits", [(37, 100, 2, 32), (300, 701, 40, 32), (500, 1500, 100, 16), (600, 79, 11, 8),
-                                            (40, 1301, 5, 8), (200, 601, 1, 32), (1500, 1500, 64, 8), (1500, 1500, 64, 32)])
-def test_lstm_cell_of_a_batch(pb, H, I, N, act_bits):
+# hidden units, inputs, vectors, activation bits, bits, used; from the second line on: each compiled kernel with the cell update
+CELLS = [
+    (37, 100, 2, 32, 5, 5), (300, 701, 40, 32, 5, 5), (500, 1500, 100, 16, 5, 5), (600, 79, 11, 8, 5, 5), (40, 1301, 5, 8, 5, 5),
+    (200, 601, 1, 32, 5, 5), (1500, 1500, 64, 8, 5, 5), (1500, 1500, 64, 32, 5, 5),
+    # many digit rows
+    (575, 39, 219, 32, 2, 1), (487, 31, 514, 32, 3, 1), (92, 18, 695, 32, 15, 15), (1036, 46, 449, 32, 12, 1), (485, 41, 272, 32, 15, 15),
+    # four tiles per wave
+    (1365, 177, 9, 32, 5, 5), (1027, 23, 29, 32, 2, 1), (465, 49, 155, 16, 7, 1), (293, 230, 433, 8, 10, 1),
+    # one tile, digits from memory
+    (1030, 25, 13, 32, 11, 5), (715, 335, 21, 32, 1, 1), (1029, 35, 9, 16, 5, 5), (516, 18, 41, 16, 1, 1), (17, 1528, 17, 8, 14, 5),
+    (16, 2153, 13, 8, 4, 1),
+    # two tiles, converted in the launch
+    (34, 17, 948, 32, 7, 5), (41, 17, 856, 32, 1, 1), (599, 16, 9, 16, 7, 5), (513, 16, 9, 16, 14, 1), (517, 19, 17, 8, 5, 5),
+    (518, 20, 17, 8, 4, 1),
+    # one tile, converted in the launch
+    (16, 16, 2, 32, 8, 1), (16, 17, 2, 16, 15, 5), (16, 16, 2, 16, 13, 1), (16, 17, 2, 8, 9, 1),
+]
+
+
+@pytest.mark.parametrize("H,I,N,act_bits,bits,m", CELLS)
+def test_lstm_cell_of_a_batch(pb, H, I, N, act_bits, bits, m):
     """The cell update at the end of every kernel, the second part of the input also at odd columns, in the chunk where it
     begins and in the chunks behind (2e-6: the bound of the other cell tests)."""
     g = np.random.default_rng(200300822 + 61)
@@ -104,14 +146,14 @@ def test_lstm_cell_of_a_batch(pb, H, I, N, act_bits):
     W = g.uniform(-0.04, 0.04, size=(4 * H, I + H)).astype(np.float32)
     x, h, c = (g.normal(size=(N, n)).astype(np.float32) for n in (I, H, H))
     bias = g.normal(0, 0.1, size=4 * H).astype(np.float32)
-    prep = po.prepare(W, 5)
-    _, Y = po.matmul_words(po.pack_words(prep["layers"]), prep["scales"], 5, I + H, np.concatenate([x, h], axis=1),
+    prep = po.prepare(W, bits)
+    _, Y = po.matmul_words(po.pack_words(prep["layers"]), prep["scales"], m, I + H, np.concatenate([x, h], axis=1),
                            frac_bits=frac_bits, act_bits=act_bits)
     h_ref, c_ref = po.lstm_pointwise(Y, bias, c)
     for lay in (GATES, BITS):
-        lin = pb.PackedLinear(dev(W), 5, max_batch=N, act_bits=act_bits, frac_bits=frac_bits, layout=lay)
+        lin = pb.PackedLinear(dev(W), bits, max_batch=N, act_bits=act_bits, frac_bits=frac_bits, layout=lay)
         ho, co = (torch.empty((N, H), dtype=torch.float32, device="cuda") for _ in range(2))
-        pb.pb_lstm_cell(lin.packed, lin.scales, lin.desc, 5, dev(x), I, dev(h), dev(c), dev(bias), ho, co, N, lin.workspace)
+        pb.pb_lstm_cell(lin.packed, lin.scales, lin.desc, m, dev(x), I, dev(h), dev(c), dev(bias), ho, co, N, lin.workspace)
         assert np.abs(ho.cpu().numpy() - h_ref).max() <= 2e-6
         assert np.abs(co.cpu().numpy() - c_ref).max() <= 2e-6
 

@@ -13,7 +13,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PRELUDE = """
 import ctypes, json, sys, threading
 mock = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # before the library, which then finds these functions first
-mock.mock_launch.restype = ctypes.c_char_p
+mock.mock_launch.restype = mock.mock_kernel.restype = ctypes.c_char_p
 L = ctypes.CDLL(sys.argv[2])
 ROWS, BITS, GATES, PAIRS = 0x50420001, 0x50420002, 0x50420003, 0x50420004
 F = ctypes.c_void_p(0x10000000)                               # an aligned address that nothing reads
@@ -107,3 +107,35 @@ def test_calls_on_one_workspace_do_not_mix_their_launches(probe):
             order.append(me)
             seen = seen[len(want):]
         assert sorted(order) == [0, 0, 0, 1, 1, 1]
+
+
+def test_the_gpu_tests_reach_every_kernel_for_batches(probe):
+    """Every compiled kernel for batches is taken by a case that the GPU tests compare with the oracle: the choice of the kernel
+    is fitted, and a change to it must not leave one untested (or unreachable) unnoticed."""
+    from tests.test_gpu_imma import CASES, CELLS, KERNELS, with_sums
+    products = [c[:6] + (with_sums(c[0], c[2]),) for c in CASES + KERNELS]
+    reached, compiled = probe("""
+        products, cells = json.loads(sys.argv[3])
+        reached, ref = set(), ctypes.byref
+        def took():
+            got = {k for k, _ in launches()}
+            reached.update(got)
+            return got
+        for R, C, N, bits, m, act, sums in products:
+            for layout in (BITS, PAIRS):
+                d = desc(R, C, bits, layout, act)
+                assert L.pb_matmul(F, F, ref(d), m, F, N, F, WORK, None) == 0
+                if sums:
+                    assert L.pb_matmul_acc(F, ref(d), m, F, N, F, WORK, None) == 0
+                    assert L.pb_matmul_acc_pairs(F, ref(d), m, F, N, F, WORK, None) == 0
+                took()
+        for H, I, N, act, bits, m in cells:
+            d = desc(4 * H, I + H, bits, GATES, act)
+            assert L.pb_lstm_cell(F, F, ref(d), m, F, I, ctypes.c_void_p(0x50000000), F, None, ctypes.c_void_p(0x60000000), F, N,
+                                  WORK, None) == 0
+            took()
+        compiled = [mock.mock_kernel(i).decode() for i in range(mock.mock_kernels())]
+        print(json.dumps([sorted(reached), [k for k in compiled if "k_i8" in k or "k_digits" in k]]))
+    """, json.dumps([products, CELLS]))
+    assert len(compiled) > 100
+    assert not sorted(set(compiled) - set(reached))
