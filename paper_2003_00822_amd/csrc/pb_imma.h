@@ -294,11 +294,11 @@ inline int i8_groups(int m)
     return m <= first ? 1 : 1 + (m - first + later - 1) / later;
 }
 
-// The kernel for many digit rows (pb_imma_tile.hip): its shapes (waves along the digit rows, column slots, tiles of sixteen
-// digit rows per wave), the row tiles that a workgroup does, its launch
-struct TileShape { int wm, nt, tm; };
+// The kernel for many digit rows (pb_imma_tile.hip): its shapes (waves along the digit rows and as many column slots, tiles of
+// sixteen digit rows per wave), the row tiles that a workgroup does, its launch
+struct TileShape { int nt, tm; };
 constexpr int kTileShapes = 3;
-constexpr TileShape kTile[kTileShapes] = {{4, 4, 2}, {8, 8, 2}, {8, 8, 4}};
+constexpr TileShape kTile[kTileShapes] = {{4, 2}, {8, 2}, {8, 4}};
 inline int tile_rows(const TileShape &t, int m, bool sums)
 {
     const int groups = sums ? t.nt : i8_groups(m);

@@ -479,9 +479,9 @@ static int pick_way(const I8Call &c, bool prepared, int cus)
         const TileShape &t = kTile[i];
         if (c.groups > t.nt) continue;      // (a row tile's groups would take several passes)
         const int rows = t.nt / c.groups;
-        const int wgs = ((c.rt + rows - 1) / rows) * ((c.tiles + t.wm * t.tm - 1) / (t.wm * t.tm));
+        const int wgs = ((c.rt + rows - 1) / rows) * ((c.tiles + t.nt * t.tm - 1) / (t.nt * t.tm));
         const int rounds = (wgs + cus - 1) / cus;
-        const int per_step = 8 / t.wm * (t.wm / t.nt);      // chunks
+        const int per_step = 8 / t.nt;      // chunks
         const int steps = (c.cq + per_step - 1) / per_step;
         offer(kStreams + i, cost[i][0] + rounds * (cost[i][2] + steps * cost[i][1]) + cost[i][3] * c.weights + cost[i][4] * c.tiles * c.cq);
     }

@@ -6,9 +6,9 @@
 namespace pb {
 
 // Many digit rows: the eight waves of a workgroup share the expanded weight codes through LDS.
-//   WM waves lie along the digit rows, TM tiles of sixteen each; 8 / WM groups of waves share out the columns.
-//   NT column slots (a row tile and a group of bitlayers each); a step of a group of waves covers KC = WM / NT chunks of 512 columns,
-//   so that every wave expands one unit (slot, chunk) per step: it loads the words two steps ahead, turns them into codes
+//   NT waves lie along the digit rows, TM tiles of sixteen each; 8 / NT groups of waves share out the columns.
+//   NT column slots (a row tile and a group of bitlayers each); a step of a group of waves covers a chunk of 512 columns,
+//   and every wave expands one unit (slot, chunk) per step: it loads the words two steps ahead, turns them into codes
 //   one step ahead, and multiplies its own digit rows, which come straight from memory (each byte is used by one
 //   wave only), with the codes of all units of the step.
 // Bound: the matrix instructions at the large end (one in 16 cycles per SIMD; 8192 x 8192, 8 bitlayers, 1024 vectors: 2.3 of the
@@ -20,11 +20,10 @@ namespace pb {
 // -> 72, 1024 vectors 1582 -> 243; 16384 x 16384, 64 vectors 430 -> 105; 3795 x 5918, 16 bitlayers, 301 vectors 536 -> 124.
 // Calls with several groups of bitlayers (more than eight bitlayers, scales that do not halve, the parity hooks) give them
 // slots of their own, so that the sums of a row tile's groups meet in a lane.
-template <int Q, bool IL, int WM, int NT, int TM, int EPI>
+template <int Q, bool IL, int NT, int TM, int EPI>
 __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, const int rows_per_wg)
 {
-    constexpr int WK = 8 / WM, KC = WM / NT;
-    static_assert(KC * NT == WM, "a unit for every wave");
+    constexpr int WK = 8 / NT;
     constexpr int UNIT = 8 * 1024;          // codes of a unit: eight operands of 1 KB
     constexpr int BUF = 8 * UNIT;
     constexpr int BR = TM >= 4 ? 4 : 8;     // operands of codes: ring
@@ -36,15 +35,14 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave % WM, kg = wave / WM;
-    const int my_nt = wm % NT, my_kc = wm / NT;
+    const int wm = wave % NT, kg = wave / NT;     // (the wave's digit rows and the slot that it expands; its columns)
     const int kb = lane >> 4, j = lane & 15;
     const int vpt = 16 >> nds;
     const int m = a.m;
-    const int n0 = ((int)blockIdx.y * WM + wm) * (TM * vpt);
+    const int n0 = ((int)blockIdx.y * NT + wm) * (TM * vpt);
     const int rt0 = blockIdx.x * rows_per_wg;
     const int rts = min(rows_per_wg, a.rt_count - rt0);     // >= 1 by construction
-    const int steps = (a.cq + KC * WK - 1) / (KC * WK);
+    const int steps = (a.cq + WK - 1) / WK;
 
     float scv, scn;
     {
@@ -85,10 +83,10 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
     for (int r = 0, g0 = 0; r < rts;) {
         const int slots = carry ? min(NT, ng - g0) : min(rp, rts - r) * ng;
         // this wave's unit: row tile my_r, group my_g
-        int my_r = r, my_g = g0 + my_nt;
+        int my_r = r, my_g = g0 + wm;
         if (!carry)
             while (my_g >= ng) { my_g -= ng; ++my_r; }
-        const bool have = my_nt < slots;
+        const bool have = wm < slots;
         const int f = group_first(my_g), e = group_end(my_g);
         const int l0 = (f & ~1) == 0 ? 0 : (f & ~1) - 2;
         uint32_t mask[2 * Q];
@@ -101,7 +99,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
         const uint32_t flip = l0 == 0 ? 0xAAAAAAAAu : 0u;
         u32x4 w[4 * Q];
         auto issue = [&](int step) {
-            const int q = (step * WK + kg) * KC + my_kc;
+            const int q = step * WK + kg;
             const uint32_t off = (uint32_t)my_r * a.round_step + (uint32_t)q * 1024u;
 #pragma unroll
             for (int s = 0; s < 4 * Q; ++s) {
@@ -117,7 +115,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
         unsigned char *const my_codes = lds + wave * UNIT + lane * 16;
         // word t of the unit of `step` -> codes
         auto expand = [&](int t, int step, int buf) {
-            const bool in = (step * WK + kg) * KC + my_kc < a.cq;
+            const bool in = step * WK + kg < a.cq;
             uint32_t p[4 * Q];
 #pragma unroll
             for (int s = 0; s < 4 * Q; ++s) {
@@ -135,9 +133,9 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
             *reinterpret_cast<v4i *>(my_codes + buf * BUF + t * 2048 + 1024) = hi;
         };
         u32x4 ar[AR][TM];
-        auto load_digits = [&](u32x4 (&dst)[TM], int step, int kc, int th) {
+        auto load_digits = [&](u32x4 (&dst)[TM], int step, int th) {
             // (beyond the last chunk the codes are zero: any digits do)
-            const int q = min((step * WK + kg) * KC + kc, a.cq - 1);
+            const int q = min(step * WK + kg, a.cq - 1);
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm)
                 dst[tm] = __builtin_amdgcn_raw_buffer_load_b128(rd, (int)doff[tm], (q * 8 + th) << (nds + 6), 0);
@@ -147,9 +145,9 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[tm][nt] = v4i{0, 0, 0, 0};
-        // the codes of unit (kc, nt), operand th
-        auto codes = [&](int buf, int kc, int th, int nt) {
-            return *reinterpret_cast<const v4i *>(lds + buf * BUF + (kg * WM + kc * NT + nt) * UNIT + th * 1024 + lane * 16);
+        // the codes of slot nt, operand th
+        auto codes = [&](int buf, int th, int nt) {
+            return *reinterpret_cast<const v4i *>(lds + buf * BUF + (kg * NT + nt) * UNIT + th * 1024 + lane * 16);
         };
         auto multiply = [&](const u32x4 (&dig)[TM], const v4i b, int nt) {
 #pragma unroll
@@ -166,7 +164,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
         issue(0);
         if (!carry) {
 #pragma unroll
-            for (int k = 0; k < AR - 1; ++k) load_digits(ar[k], 0, 0, k);
+            for (int k = 0; k < AR - 1; ++k) load_digits(ar[k], 0, k);
 #pragma unroll
             for (int t = 0; t < 4; ++t) expand(t, 0, 0);
             issue(1);
@@ -176,25 +174,23 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
                 // (the codes of BR - 1 operands ahead are on their way from LDS)
                 v4i br[BR];
 #pragma unroll
-                for (int i = 0; i < BR - 1; ++i) br[i] = codes(buf, 0, i / NT, i % NT);
+                for (int i = 0; i < BR - 1; ++i) br[i] = codes(buf, i / NT, i % NT);
 #pragma unroll
-                for (int kc = 0; kc < KC; ++kc)
+                for (int th = 0; th < 8; ++th) {
+                    // the digit rows of a later (t, h) are requested before this one's products
+                    const int nx = th + AR - 1;
+                    if (nx < 8) load_digits(ar[nx % AR], step, nx);
+                    else load_digits(ar[nx % AR], step + 1, nx - 8);
+                    if ((th & 1) == 0) expand(th / 2, step + 1, buf ^ 1);
+                    if (th == 7) issue(step + 2);
 #pragma unroll
-                    for (int th = 0; th < 8; ++th) {
-                        // the digit rows of a later (t, h) are requested before this one's products
-                        const int nx = kc * 8 + th + AR - 1;
-                        if (nx < KC * 8) load_digits(ar[nx % AR], step, nx / 8, nx % 8);
-                        else load_digits(ar[nx % AR], step + 1, 0, nx - KC * 8);
-                        if (kc == KC - 1 && (th & 1) == 0) expand(th / 2, step + 1, buf ^ 1);
-                        if (kc == KC - 1 && th == 7) issue(step + 2);
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt) {
-                            const int i = (kc * 8 + th) * NT + nt, ahead = i + BR - 1;
-                            if (ahead < KC * 8 * NT) br[ahead % BR] = codes(buf, ahead / (8 * NT), ahead / NT % 8, ahead % NT);
-                            multiply(ar[(kc * 8 + th) % AR], br[i % BR], nt);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const int i = th * NT + nt, ahead = i + BR - 1;
+                        if (ahead < 8 * NT) br[ahead % BR] = codes(buf, ahead / NT, ahead % NT);
+                        multiply(ar[th % AR], br[i % BR], nt);
                     }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 __syncthreads();
             }
         } else {
@@ -203,17 +199,16 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
                 for (int t = 0; t < 4; ++t) expand(t, step, 0);
                 issue(step + 1);
                 __syncthreads();
-                for (int kc = 0; kc < KC; ++kc)
-                    for (int th = 0; th < 8; ++th) {
-                        load_digits(ar[0], step, kc, th);
+                for (int th = 0; th < 8; ++th) {
+                    load_digits(ar[0], step, th);
 #pragma unroll
-                        for (int nt = 0; nt < NT; ++nt) multiply(ar[0], codes(0, kc, th, nt), nt);
-                    }
+                    for (int nt = 0; nt < NT; ++nt) multiply(ar[0], codes(0, th, nt), nt);
+                }
                 __syncthreads();
             }
         }
         // ---- the groups of waves add up, then every tile is finished ----
-        atomicAdd(&s_ones[my_nt][lane], ones[0]);
+        atomicAdd(&s_ones[wm][lane], ones[0]);
         int *const part = reinterpret_cast<int *>(lds) + wm * (TM * NT * 4 * 64) + lane;
         for (int k = 1; k < WK; ++k) {
             if (k > 1) __syncthreads();
@@ -294,17 +289,17 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
 
 // ---------------------------------------------------------------------------------------------------------------
 
-template <int Q, bool IL, int WM, int NT, int TM, int EPI>
+template <int Q, bool IL, int NT, int TM, int EPI>
 static const void *tile_kernel()
 {
     // (the sums themselves are asked for in groups of one or two: four slots)
     if constexpr ((EPI == kSums && Q > 1) || (EPI == kCell && IL)) return nullptr;
-    else return reinterpret_cast<const void *>(k_i8_tile<Q, IL, WM, NT, TM, EPI>);
+    else return reinterpret_cast<const void *>(k_i8_tile<Q, IL, NT, TM, EPI>);
 }
-#define PB_TILE_E(WM, NT, TM, E) {{tile_kernel<1, false, WM, NT, TM, E>(), tile_kernel<1, true, WM, NT, TM, E>()}, \
-                                  {tile_kernel<2, false, WM, NT, TM, E>(), tile_kernel<2, true, WM, NT, TM, E>()}}
-#define PB_TILE(WM, NT, TM) {PB_TILE_E(WM, NT, TM, kStore), PB_TILE_E(WM, NT, TM, kCell), PB_TILE_E(WM, NT, TM, kSums)}
-static const void *const kTileFn[kTileShapes][3][2][2] = {PB_TILE(4, 4, 2), PB_TILE(8, 8, 2), PB_TILE(8, 8, 4)};
+#define PB_TILE_E(NT, TM, E) {{tile_kernel<1, false, NT, TM, E>(), tile_kernel<1, true, NT, TM, E>()}, \
+                              {tile_kernel<2, false, NT, TM, E>(), tile_kernel<2, true, NT, TM, E>()}}
+#define PB_TILE(NT, TM) {PB_TILE_E(NT, TM, kStore), PB_TILE_E(NT, TM, kCell), PB_TILE_E(NT, TM, kSums)}
+static const void *const kTileFn[kTileShapes][3][2][2] = {PB_TILE(4, 2), PB_TILE(8, 2), PB_TILE(8, 4)};
 constexpr int kTileLds = 128 * 1024;
 
 int launch_imma_tile(int shape, const I8Args &a, int nd, bool il, hipStream_t st)
@@ -321,7 +316,7 @@ int launch_imma_tile(int shape, const I8Args &a, int nd, bool il, hipStream_t st
     const TileShape &t = kTile[shape];
     int nds = nd == 4 ? 2 : nd - 1, rows_per_wg = tile_rows(t, a.m, epi == kSums);
     const int vpt = 16 / nd, tiles = (a.act.batch + vpt - 1) / vpt;
-    const int groups = (tiles + t.wm * t.tm - 1) / (t.wm * t.tm), wgs = (a.rt_count + rows_per_wg - 1) / rows_per_wg;
+    const int groups = (tiles + t.nt * t.tm - 1) / (t.nt * t.tm), wgs = (a.rt_count + rows_per_wg - 1) / rows_per_wg;
     void *args[] = {const_cast<I8Args *>(&a), &nds, &rows_per_wg};
     const hipError_t e = hipLaunchKernel(fn, dim3((unsigned)wgs, (unsigned)groups), dim3(512), args, kTileLds, st);
     return (int)(e != hipSuccess ? e : hipGetLastError());
