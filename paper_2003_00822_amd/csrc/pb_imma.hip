@@ -422,10 +422,13 @@ static int slice(int cq, int tm) { return (cq + stream_waves(tm) - 1) / stream_w
 // vectors, two waves: one 7.5, two 6.8, four 5.8 us.)
 static int fused_per_cu(int S) { return S >= 4 ? 1 : 8 / S; }
 
-// Weights that are read once (one tile of digit rows): non-temporal loads where they are too many for the L2 caches (32 MB) and few
-// enough to come from the last-level cache on the next call.  (8 bitlayers, two vectors: 8192 x 8192 15.6 -> 14.1 us, but
-// 16384 x 12288 34.7 -> 40.2 and 4616 x 2016, 12 bitlayers, 7.0 -> 8.0 us.)
-static bool streaming(const I8Call &c) { return c.tiles == 1 && c.weights > 32.0 && c.weights <= 80.0; }
+// Weights that are read once (one tile of digit rows): non-temporal loads, which find them in the last-level cache but leave nothing
+// there.  Graph of calls, 8 bitlayers, 8192 columns, two vectors, plain / non-temporal loads in us where something else has put the
+// weights there (packing) / where only the calls themselves read them, after 1 GB of other data:
+//   33 MB 7.9 / 8.0, 8.0 / 10.0    40 MB 11.0 / 11.3, 11.3 / 12.8    48 MB 12.6 / 11.8, 12.8 / 13.1    56 MB 13.4 / 12.9, 13.5 / 14.6
+//   64 MB 14.4 / 13.1, 14.6 / 14.4    76 MB 16.6 / 16.3, 16.6 / 17.2    90 MB 18.2 / 18.6, 18.2 / 19.7
+// (3072 columns, 5 vectors of 16 bits: 34 MB 9.4 / 9.5, 9.4 / 10.4; 48 MB 12.4 / 11.5, 12.5 / 12.1; 64 MB 15.0 / 14.8, 15.2 / 15.4)
+static bool streaming(const I8Call &c) { return c.tiles == 1 && c.weights > 44.0 && c.weights <= 72.0; }
 
 // Which kernel: the one with the least estimated time.  The estimates are in us, fitted to the times of 280 layers on an MI355X (64
 // to 16384 rows, 64 to 32768 columns, 2 to 1024 vectors, 1 to 16 bitlayers, 8, 16 and 32 activation bits, both layouts); the choice

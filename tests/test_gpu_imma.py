@@ -100,9 +100,9 @@ KERNELS = [
     (2091, 16, 17, 9, 1, 8, 4), (430, 68, 443, 8, 8, 32, 16),
     # one tile, converted in the launch
     (16, 16, 2, 1, 1, 8, 4), (18, 16, 2, 8, 5, 8, 4),
-    # ... too many weights for the L2 caches
-    (8200, 8200, 2, 4, 4, 32, 16), (8200, 8200, 2, 4, 4, 16, 12), (8200, 8200, 2, 4, 4, 8, 4), (10694, 1040, 2, 16, 16, 16, 12),
-    (10745, 1035, 6, 16, 16, 8, 4),
+    # ... non-temporal loads of the weights
+    (10700, 8200, 2, 4, 4, 32, 16), (10700, 8200, 2, 4, 4, 16, 12), (10700, 8200, 2, 4, 4, 8, 4), (14713, 1035, 3, 16, 16, 32, 16),
+    (14694, 1040, 2, 16, 16, 16, 12), (14745, 1035, 6, 16, 16, 8, 4),
 ]
 
 

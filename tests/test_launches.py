@@ -139,3 +139,16 @@ def test_the_gpu_tests_reach_every_kernel_for_batches(probe):
     """, json.dumps([products, CELLS]))
     assert len(compiled) > 100
     assert not sorted(set(compiled) - set(reached))
+
+
+def test_non_temporal_loads_only_where_they_pay(probe):
+    """Weights that fit the L2 caches or nearly so are read with plain loads, which keep them there for the next call."""
+    took = probe("""
+        took = []
+        for rows in (2048, 4016, 4880, 5856, 7808, 10976, 16384):          # 17, 33, 40, 48, 64, 90, 134 MB
+            assert L.pb_matmul(F, F, ctypes.byref(desc(rows, 8192, 8, BITS)), 8, F, 2, F, WORK, None) == 0
+            took.append([k for k, _ in launches()])
+        print(json.dumps(took))
+    """)
+    assert all(len(t) == 1 and "k_i8I" in t[0] for t in took)
+    assert [t[0].split("Li")[-1].startswith("2") for t in took] == [False, False, False, True, True, False, False]
