@@ -57,8 +57,12 @@ __host__ __device__ inline int stage_operand(int rows) { return rows * 64 + 16; 
 // the next unit are requested before this one is multiplied: 8 KB in flight per wave, sixteen waves.  Turning the words of a unit
 // into codes takes 180 operations of the vector ALU, its products 16 (one tile) matrix instructions.
 // In a graph, us per call, against the FP4 form that this replaces (two bitlayers and two planes per operand):
-// 1024 x 1024, 8 bitlayers, 16 vectors 7.2 -> 4.4; 4096 x 4096, 4 vectors 7.9 -> 5.9; 8192 x 8192, 4 vectors 17.2 -> 14.8; 135 x 69, 7
-// bitlayers, 113 vectors 14.4 -> 4.9; 2002 x 5817, one bitlayer, 2 vectors 5.2 -> 5.4 (the worst of 170).
+// 1024 x 1024, 8 bitlayers, 16 vectors 7.3 -> 4.3; 4096 x 4096, 4 vectors 8.1 -> 6.1; 8192 x 8192, 4 vectors 17.5 -> 14.7; 135 x 69, 7
+// bitlayers, 113 vectors 14.7 -> 4.6.  The conversion and the codes of a few vectors are more instructions per wave than their FP4
+// operands were, which shows where there is little else: 2 to 4 vectors, one or two bitlayers on wide rows (2002 x 5817, one
+// bitlayer, 2 vectors 5.0 -> 5.4), more than eight bitlayers (67 x 6211, 16 bitlayers, 3 vectors of 8 bits 9.5 -> 11.8), and one vector on
+// the pairs layout (565 x 14030, two bitlayers 5.6 -> 7.9; 4096 x 4096, 8 bitlayers 5.7 -> 5.1).  2148 drawn calls of several vectors
+// are 1.7 times as fast on average, 51 of them slower by more than 1.5 %.
 
 template <int ND, int Q, bool IL, int TM, bool FUSED, int EPI, int POLICY>
 __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
@@ -431,8 +435,12 @@ static int fused_per_cu(int S) { return S >= 4 ? 1 : 8 / S; }
 static bool streaming(const I8Call &c) { return c.tiles == 1 && c.weights > 44.0 && c.weights <= 72.0; }
 
 // Which kernel: the one with the least estimated time.  The estimates are in us, fitted to the times of 280 layers on an MI355X (64
-// to 16384 rows, 64 to 32768 columns, 2 to 1024 vectors, 1 to 16 bitlayers, 8, 16 and 32 activation bits, both layouts); the choice
-// costs 1.5 % on average over the best one, 1.34 times in the worst case.  The bitlayers count by themselves: with one cost for all,
+// to 16384 rows, 64 to 32768 columns, 2 to 1024 vectors, 1 to 16 bitlayers, 8, 16 and 32 activation bits, both layouts).  Over 2148 other
+// calls with every kernel timed, the choice costs 2.6 % on average over the best one, 19 % at the 95th percentile, 1.85 times in
+// the worst case: it is weakest with 8- and 16-bit activations of many vectors on a small matrix, whose conversion one after the other
+// the estimate takes for shorter than it is (284 x 1200, 21 vectors of 8 bits, cell update 12.2 us, from memory 6.9).  A term for that
+// chain, fitted to 900 of the calls, moved 62 of the other 1500 to a kernel over 3 % slower and 48 to one as much faster: left out.
+// The bitlayers count by themselves: with one cost for all,
 // one and two bitlayers of a few vectors went to the wrong kernel (3841 x 7174, one bitlayer, 14 vectors: 13.4 us, here 10.9).
 //   few digit rows: rounds of workgroups over the chip, units (row tile, group, tile of digit rows, chunk), conversion
 //   many:           rounds of workgroups times (start and end + steps), the digits of all vectors through memory

@@ -11,13 +11,18 @@ namespace pb {
 //   and every wave expands one unit (slot, chunk) per step: it loads the words two steps ahead, turns them into codes
 //   one step ahead, and multiplies its own digit rows, which come straight from memory (each byte is used by one
 //   wave only), with the codes of all units of the step.
-// Bound: the matrix instructions at the large end (one in 16 cycles per SIMD; 8192 x 8192, 8 bitlayers, 1024 vectors: 2.3 of the
-// 5 POP/s, the share of its peak that the library's bf16 product reaches on this card); for few vectors the digit rows, which every
+// Bound: the matrix instructions at the large end (one in 16 cycles per SIMD; 8192 x 8192, 8 bitlayers, 1024 vectors: 2.1 of the
+// 5 POP/s, 42 %, where the library's bf16 product reaches 46 % of its peak on this card; the matrix pipes are busy 57 % of the
+// kernel's time); for few vectors the digit rows, which every
 // workgroup reads at 64 bytes per cycle, LDS, the expansion and the matrix instructions, about as long each.  Operands of the codes
 // are read from LDS three (seven) products ahead and the scheduler is kept from moving work across a (t, h): without that barrier
 // the products waited for their operands (64 vectors: 39 -> 32 us).
-// us per call, against the FP4 form that this replaces: 8192 x 8192, 8 bitlayers, 64 vectors 115 -> 29, 256 vectors (pairs layout) 403
-// -> 72, 1024 vectors 1582 -> 243; 16384 x 16384, 64 vectors 430 -> 105; 3795 x 5918, 16 bitlayers, 301 vectors 536 -> 124.
+// us per call in a graph, digits included, against the FP4 form that this replaces: 8192 x 8192, 8 bitlayers, 64 vectors 124 -> 32, 256
+// vectors (pairs layout) 446 -> 72, 1024 vectors 1743 -> 258; 16384 x 16384, 64 vectors 464 -> 112; 3795 x 5918, 16 bitlayers, 301
+// vectors 547 -> 135.
+// The shape of four tiles per wave and eight slots (the one of 1024 vectors) needs more than the 256 registers of a wave: the compiler
+// keeps 32 to 87 of them per lane in scratch memory (132 to 320 bytes), used before and after the loop over the steps, not in it; a
+// kernel with scratch takes 0.3 us longer to launch.
 // Calls with several groups of bitlayers (more than eight bitlayers, scales that do not halve, the parity hooks) give them
 // slots of their own, so that the sums of a row tile's groups meet in a lane.
 template <int Q, bool IL, int NT, int TM, int EPI>

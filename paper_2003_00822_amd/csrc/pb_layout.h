@@ -42,8 +42,8 @@ constexpr int kRing = 8;            // popcount kernel: weight tiles in flight p
 constexpr int kMaxWavesPerWG = 8;   // popcount kernel
 constexpr int kMetaInts = 16;       // per activation vector, in the workspace
 
-constexpr int kTileRows = 16;       // matrix-core kernel: rows per tile
-constexpr int kChunkWords = 16;     // matrix-core kernel: words per row in one block
+constexpr int kTileRows = 16;       // matrix-core kernels: rows per tile
+constexpr int kChunkWords = 16;     // matrix-core kernels: words per row in one block
 constexpr int kMaxSlices = 16;      // kernel for one vector: waves (column slices) per workgroup
 constexpr int kMaxColsTile16 = 32768;     // 16 slices of 2048 columns
 

@@ -33,7 +33,7 @@ def assert_y_close(y_gpu, y_ref, A_ref, scales, frac_bits=16, rtol=1e-5):
 
 
 def pair_sums(A, bits_used):
-    """What the matrix-core kernel accumulates when it multiplies two bitlayers at once, from the oracle's
+    """What the matrix-core kernels accumulate when they multiply two bitlayers at once, from the oracle's
     per-bitlayer sums A [m, N, R]: -2 A[0] + A[1] for the sign pair, 2 A[2p] + A[2p+1] for the others, a last
     single bitlayer if bits_used is odd."""
     m = bits_used

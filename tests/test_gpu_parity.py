@@ -20,8 +20,8 @@ def pb():
     return pbmod
 
 
-# every case runs on the packed layouts: the matrix-core kernel (default), the AND + popcount kernel, and the
-# matrix-core kernel on the layout that stores the digits of the bitlayer pairs
+# every case runs on the packed layouts: the matrix-core kernels (default), the AND + popcount kernel, and the
+# matrix-core kernels for batches on the layout that stores the digits of the bitlayer pairs
 LAYOUTS = {"mfma": 0x50420002, "popc": 0x50420001, "pair": 0x50420004}
 
 
@@ -54,7 +54,7 @@ def run_layer(pb, W, bits, X, m_list, frac_bits=16, act_bits=32, check_y=True, l
         assert not bad.any(), "int64 accumulators differ at %s (R=%d C=%d bits=%d m=%d)" % (
             np.argwhere(bad)[:5].tolist(), R, C, bits, m)
         if lin.desc.layout != LAYOUTS["popc"]:
-            # the sums of the bitlayer pairs, as the matrix-core kernel holds them on its usual route
+            # the sums of the bitlayer pairs, each pair one group of the integer form
             P_gpu = lin.acc_pairs(Xd, m).cpu().numpy()
             bad = P_gpu != pair_sums(ref["A"], m)
             assert not bad.any(), "pair sums differ at %s (R=%d C=%d bits=%d m=%d)" % (
@@ -88,13 +88,13 @@ def test_every_bit_width_and_prefix(pb, layout, bits):
     run_layer(pb, W, bits, X, list(range(1, bits + 1)), layout=layout)
 
 
-TILED = ["mfma", "pair"]    # the two layouts of the matrix-core kernel
+TILED = ["mfma", "pair"]    # two layouts of the matrix-core kernels
 
 
 @pytest.mark.parametrize("lay", TILED)
 @pytest.mark.parametrize("bits", [2, 3, 5, 8])
 def test_scales_that_do_not_halve_are_applied_bitlayer_by_bitlayer(pb, bits, lay):
-    """Any fp32 scales are legal input: the kernel merges bitlayer pairs only if scales[i] == 2 scales[i+1] throughout."""
+    """Any fp32 scales are legal input: the kernel multiplies bitlayers together only if scales[i] == 2 scales[i+1] throughout."""
     W, X = synth.ragged(50, 1500, batch=3, case=40 + bits, xdist="normal")
     lin = pb.PackedLinear(dev(W), bits, max_batch=3, layout=LAYOUTS[lay])
     ref = oracle_reference(W, bits, X, bits)
@@ -117,9 +117,8 @@ def test_scales_that_do_not_halve_are_applied_bitlayer_by_bitlayer(pb, bits, lay
 @pytest.mark.parametrize("lay", TILED)
 @pytest.mark.parametrize("bits", [9, 10, 11, 12, 16])
 def test_pair_groups_share_accumulators(pb, bits, lay):
-    """Batches with scales that halve throughout: up to five bitlayer pairs of a row tile add up in one set of
-    registers (pair p with the factor 4^(last - p), supplied by the block scale of the weight operand), further
-    pairs in a second group; prefixes on both sides of the group boundaries, with and without a last single bitlayer."""
+    """Batches with scales that halve throughout: the first eight bitlayers are one code, the next six a second one, the
+    rest a third; prefixes on both sides of the group boundaries, and every pair (a last single bitlayer included) by itself."""
     for (R, C, N, case) in ((40, 1300, 3, 81), (17, 9000, 5, 82)):
         W, X = synth.ragged(R, C, batch=N, case=case + bits, xdist="wide")
         ms = sorted(m for m in {1, 2, 3, 9, 10, 11, 12, bits - 1, bits} if 1 <= m <= bits)
@@ -130,8 +129,8 @@ def test_pair_groups_share_accumulators(pb, bits, lay):
 @pytest.mark.parametrize("lay", TILED)
 @pytest.mark.parametrize("bits", [10, 11, 16])
 def test_pair_groups_at_their_limits(pb, bits, lay):
-    """A full group of five pairs (and five pairs plus more) at 32768 columns, every weight digit at its maximum,
-    activations saturated: the shared accumulators and the 32-bit halves in LDS are as large as they get
+    """Groups of bitlayers (eight, and one or two more; pairs by themselves) at 32768 columns, the codes at their extremes,
+    activations saturated: the 32-bit sums of digits and codes are as large as they get
     (tests/test_accumulator_bounds.py works the bounds out on the host)."""
     cols = 32768
     X = limit_vectors(cols)
@@ -168,7 +167,7 @@ def test_maximum_batch(pb, layout):
 
 def test_random_configurations(pb):
     """Seeded random shapes, widths, prefixes, batches, activation formats and distributions on the layouts of the
-    matrix-core kernel: codes, per-bitlayer sums, pair sums and outputs against the oracle."""
+    matrix-core kernels: codes, per-bitlayer sums, pair sums and outputs against the oracle."""
     rng = np.random.default_rng(200300822)
     for case in range(120):
         R = int(rng.integers(1, 160))
@@ -330,8 +329,8 @@ def test_partial_sums_at_their_limits(pb, layout, cols):
 @pytest.mark.parametrize("lay", TILED)
 @pytest.mark.parametrize("fk", [(2, 4), (4, 8), (5, 9), (12, 16), (7, 12)])
 def test_vectors_that_share_an_operand(pb, fk, lay):
-    """Activations of at most 16 (8) bits: two (four) vectors travel in one operand of the matrix-core kernel.
-    Batches that fill the operands and that leave sub-vectors or whole operands empty, every route (per-bitlayer
+    """The sixteen digit rows of an operand are the bytes of four vectors of 32 bits, eight of at most 16, sixteen of at most 8.
+    Batches that fill operands and that leave vectors of the last one empty, every route (per-bitlayer
     sums, pair sums, fp32 output), inputs that saturate at k bits."""
     f, k = fk
     for (R, C, N, case) in ((45, 1300, 2, 71), (33, 520, 3, 72), (20, 4200, 4, 73), (50, 300, 5, 74),
@@ -556,12 +555,9 @@ def test_extra_16384(pb, layout):
 
 @pytest.mark.parametrize("lay", TILED)
 def test_wide_rows_in_several_passes(pb, lay):
-    """Batches on rows of more than 8192 columns: the kernel covers the columns in several passes over the same row
-    tiles (16500 columns: five passes of eight operands per wave, or three of four operands where four vectors share
-    an operand), whose sums wait in LDS for the last pass, as many row tiles at a time as have room: 207 row tiles
-    on a few workgroups per vector group make every workgroup go through several such rounds, with every kind of
-    sums (groups of pairs, pair by pair, bitlayer by bitlayer with scales that do not halve) and one, two and four
-    vectors per operand.  The oracle computes sampled rows."""
+    """Large batches on rows of 16500 columns, the last chunk of 512 nearly empty, 207 row tiles that do not divide evenly over the
+    workgroups: every kind of sums (whole codes, pairs, bitlayer by bitlayer with scales that do not halve, whose groups then take
+    several passes over the columns) and activations of one, two and four bytes.  The oracle computes sampled rows."""
     R, C, N, bits = 3300, 16500, 256, 8
     W, X = synth.ragged(R, C, batch=N, case=91, xdist="normal")
     rng = np.random.default_rng(91)
