@@ -7,6 +7,31 @@ namespace pb {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// Cycles that an instruction of the vector ALU takes where two waves or more of a SIMD issue them (measured): 2.5 to 3 for V_AND_B32,
+// V_OR_B32, V_XOR_B32, V_MOV_B32, V_ADD_U32, V_BITOP3_B32 and V_FMA_F32 with every operand in a vector register; 4.3 to 4.7 for those with a
+// constant or a scalar operand, and for V_BFI_B32, V_PERM_B32, V_AND_OR_B32, V_LSHL_OR_B32 and the shifts, those of 64 bits included:
+// two registers next to each other are shifted for the price of one, where what crosses from one to the other is masked away.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t v)
+{
+    uint32_t r;
+    asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));   // (the compiler would use the constant itself)
+    return r;
+}
+template <int N>
+__device__ __forceinline__ uint64_t up(uint64_t v)      // v << N (the compiler takes the shifts apart again)
+{
+    uint64_t r;
+    asm("v_lshlrev_b64 %0, %1, %2" : "=v"(r) : "n"(N), "v"(v));
+    return r;
+}
+template <int N>
+__device__ __forceinline__ uint64_t down(uint64_t v)    // v >> N
+{
+    uint64_t r;
+    asm("v_lshrrev_b64 %0, %1, %2" : "=v"(r) : "n"(N), "v"(v));
+    return r;
+}
+
 // x_q = Int(x * 2^f) as a k-bit two's-complement value: toward zero, saturating, NaN -> 0.  V_CVT_I32_F32 does
 // exactly that for k = 32 (out-of-range inputs saturate, NaN converts to 0); narrower k clamp the integer.
 template <bool NARROW>

@@ -161,12 +161,17 @@ __device__ __forceinline__ v8i as_operand(const u32x4 v)
     return r;
 }
 
-// One packed word -> the B operand: FP4 code 2.0 where the weight bit is set
-__device__ __forceinline__ v8i weight_operand(uint32_t w)
+// Two packed words -> their B operands: FP4 code 2.0 where the weight bit is set.  Register r of an operand holds the columns 4 n + r.
+// The shifts are those of both words at once: eleven operations of the vector ALU instead of fourteen (4096 x 4096, 8 bitlayers 4.8 -> 4.6
+// us, an LSTM step of 6000 x 3000 with 8 bitlayers 6.8 -> 6.35, 500 x 12001, 16 bitlayers 11.9 -> 11.05).  The constant in a vector register, which
+// makes V_AND_B32 by itself faster, measured 0.02 to 0.5 us slower here.
+__device__ __forceinline__ void weight_operands(uint64_t w, v8i &b0, v8i &b1)
 {
-    v8i r = {(int)((w << 2) & 0x44444444u), (int)((w << 1) & 0x44444444u), (int)(w & 0x44444444u),
-             (int)((w >> 1) & 0x44444444u), 0, 0, 0, 0};
-    return r;
+    constexpr uint32_t code = 0x44444444u;
+    const uint64_t r0 = up<2>(w), r1 = up<1>(w), r3 = down<1>(w);
+    b0 = v8i{(int)((uint32_t)r0 & code), (int)((uint32_t)r1 & code), (int)((uint32_t)w & code), (int)((uint32_t)r3 & code), 0, 0, 0, 0};
+    b1 = v8i{(int)((uint32_t)(r0 >> 32) & code), (int)((uint32_t)(r1 >> 32) & code), (int)((uint32_t)(w >> 32) & code),
+             (int)((uint32_t)(r3 >> 32) & code), 0, 0, 0, 0};
 }
 
 // cbsz = blgp = 4: both operands FP4 (E2M1); the E8M0 block scales of the operands are 2^0 (product = digit / 2 * 2).
@@ -397,7 +402,12 @@ __global__ __launch_bounds__(MAXS * 64) void k_mfma(const uint32_t *packed, cons
                 for (int q = 0; q < NQ; ++q) {
                     const u32x4 w = ring[k][q];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) acc = mfma_fp4(as_operand(pa[q][t]), weight_operand(w[t]), acc);
+                    for (int t = 0; t < 4; t += 2) {
+                        v8i b0, b1;
+                        weight_operands((uint64_t)w[t + 1] << 32 | w[t], b0, b1);
+                        acc = mfma_fp4(as_operand(pa[q][t]), b0, acc);
+                        acc = mfma_fp4(as_operand(pa[q][t + 1]), b1, acc);
+                    }
                 }
                 // the end of a bitlayer: the sum of this lane goes to its set in LDS
                 {
