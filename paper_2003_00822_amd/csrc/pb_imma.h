@@ -7,7 +7,7 @@
 // twice its neighbour) are the two's-complement bits of one integer code, so
 //     sum_i scales[i] A_i = scales[last] * sum_c code[c] x_q[c]
 // and up to eight bitlayers are multiplied at once: eight packed words become the codes of 32 columns (a transpose of
-// 8 x 8 bits, 48 operations of the vector ALU) and V_MFMA_I32_16X16X64_I8 multiplies them with the bytes of x_q.
+// 8 x 8 bits, 40 operations of the vector ALU) and V_MFMA_I32_16X16X64_I8 multiplies them with the bytes of x_q.
 // A 32-bit x_q is four byte digits: against the sixteen base-4 digits and bitlayer pairs of the FP4 form that is 4
 // products per weight and activation instead of 64, at half the rate per product.
 //
@@ -122,55 +122,83 @@ __device__ __forceinline__ void byte_digits(const u32x4 (&v)[4], u32x4 (&out)[ND
     }
 }
 
-// (hi & mask) | (lo & ~mask): one V_BFI_B32
-__device__ __forceinline__ uint32_t mix(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
-
-// Four words of adjacent slots (p[0] the highest bit) -> four words of 4-bit codes: nibble n of v[k] holds the bits
-// p[0][c] p[1][c] p[2][c] p[3][c] of column c = 4 n + k.  IL: (p[0], p[1]) and (p[2], p[3]) are the even and the
-// odd columns' digits of a bitlayer pair already, one exchange less.
-template <bool IL>
-__device__ __forceinline__ void nibble_codes(const uint32_t (&p)[4], uint32_t (&v)[4])
+// 130 cycles a word instead of 220 with V_BFI_B32 and shifts of 32 bits (see pb_device.h); of a kernel's time, where the codes are only a
+// part of it: 1500 x 700, 4 bitlayers, 30 vectors of 16 bits 5.84 -> 5.53 us, 2002 x 5817, one bitlayer, 2 vectors 5.33 -> 4.98, 67 x 6211,
+// 16 bitlayers, 3 vectors 11.6 -> 10.7, 8192 x 8192, 4 vectors 14.05 -> 13.9.
+struct Masks { uint32_t m1, m2, m4; };   // 0xAA.., 0xCC.., 0xF0..
+__device__ __forceinline__ Masks make_masks() { return {in_vgpr(0xAAAAAAAAu), in_vgpr(0xCCCCCCCCu), in_vgpr(0xF0F0F0F0u)}; }
+__device__ __forceinline__ uint32_t twice(uint32_t v)
 {
-    uint32_t eh, oh, el, ol;
+    uint32_t r;
+    asm("v_add_u32 %0, %1, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+__device__ __forceinline__ uint64_t both(uint32_t a, uint32_t b) { return (uint64_t)b << 32 | a; }
+// (a & mask) | (b & ~mask)
+__device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t a, uint32_t b) { return __builtin_amdgcn_bitop3_b32(mask, a, b, 0xCA); }
+__device__ __forceinline__ uint64_t mix(uint32_t mask, uint64_t a, uint64_t b)
+{
+    return both(pick(mask, (uint32_t)a, (uint32_t)b), pick(mask, (uint32_t)(a >> 32), (uint32_t)(b >> 32)));
+}
+
+// Two words by N, together or each by itself: the kernel with four tiles of digit rows per wave is faster with the latter (8192 x 8192, 16
+// vectors 24.5 us, together 26.4, V_BFI_B32 24.6), all others with the former.
+template <int N, bool SHIFT64>
+__device__ __forceinline__ uint64_t shifted_up(uint64_t v)
+{
+    return SHIFT64 ? up<N>(v) : both((uint32_t)v << N, (uint32_t)(v >> 32) << N);
+}
+template <int N, bool SHIFT64>
+__device__ __forceinline__ uint64_t shifted_down(uint64_t v)
+{
+    return SHIFT64 ? down<N>(v) : both((uint32_t)v >> N, (uint32_t)(v >> 32) >> N);
+}
+
+// Four words of adjacent slots (p[0] the highest bit) -> four words of 4-bit codes, v[0] = (k = 0, k = 1), v[1] = (k = 2, k = 3): nibble n
+// of word k holds the bits p[0][c] p[1][c] p[2][c] p[3][c] of column c = 4 n + k.  IL: (p[0], p[1]) and (p[2], p[3]) are the even and the
+// odd columns' digits of a bitlayer pair already, one exchange less.
+template <bool IL, bool SHIFT64>
+__device__ __forceinline__ void nibble_codes(const Masks &m, const uint32_t *p, uint64_t (&v)[2])
+{
+    uint64_t h, l;   // (even columns, odd columns) of the upper and of the lower two slots
     if constexpr (IL) {
-        eh = p[0]; oh = p[1]; el = p[2]; ol = p[3];
+        h = both(p[0], p[1]);
+        l = both(p[2], p[3]);
     } else {
-        eh = mix(0xAAAAAAAAu, p[0] << 1, p[1]);
-        oh = mix(0x55555555u, p[1] >> 1, p[0]);
-        el = mix(0xAAAAAAAAu, p[2] << 1, p[3]);
-        ol = mix(0x55555555u, p[3] >> 1, p[2]);
+        h = both(pick(m.m1, twice(p[0]), p[1]), pick(m.m1, p[0], p[1] >> 1));
+        l = both(pick(m.m1, twice(p[2]), p[3]), pick(m.m1, p[2], p[3] >> 1));
     }
-    v[0] = mix(0xCCCCCCCCu, eh << 2, el);
-    v[2] = mix(0x33333333u, el >> 2, eh);
-    v[1] = mix(0xCCCCCCCCu, oh << 2, ol);
-    v[3] = mix(0x33333333u, ol >> 2, oh);
+    v[0] = mix(m.m2, shifted_up<2, SHIFT64>(h), l);
+    v[1] = mix(m.m2, h, shifted_down<2, SHIFT64>(l));
 }
 
 // The words of 4 Q slots (slot 0 = bit 7) of 32 columns -> their codes: byte b of lo[k] is the code of column 8 b + k, byte b of
 // hi[k] that of column 8 b + 4 + k
-template <int Q, bool IL>
-__device__ __forceinline__ void weight_codes(const uint32_t (&w)[4 * Q], v4i &lo, v4i &hi)
+template <int Q, bool IL, bool SHIFT64>
+__device__ __forceinline__ void weight_codes(const Masks &m, const uint32_t (&w)[4 * Q], v4i &lo, v4i &hi)
 {
-    uint32_t a[4];
-    {
-        const uint32_t p[4] = {w[0], w[1], w[2], w[3]};
-        nibble_codes<IL>(p, a);
+    uint64_t a[2], b[2] = {};
+    nibble_codes<IL, SHIFT64>(m, w, a);
+    if constexpr (Q == 2) nibble_codes<IL, SHIFT64>(m, w + 4, b);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const uint64_t l = mix(m.m4, shifted_up<4, SHIFT64>(a[k]), b[k]);
+        const uint64_t h = mix(m.m4, a[k], Q == 2 ? shifted_down<4, SHIFT64>(b[k]) : 0);
+        lo[2 * k] = (int)(uint32_t)l;
+        lo[2 * k + 1] = (int)(l >> 32);
+        hi[2 * k] = (int)(uint32_t)h;
+        hi[2 * k + 1] = (int)(h >> 32);
     }
-    if constexpr (Q == 2) {
-        uint32_t b[4];
-        const uint32_t p[4] = {w[4], w[5], w[6], w[7]};
-        nibble_codes<IL>(p, b);
+}
+// Word t of the slots' pieces.  IL: the sign bitlayer is stored complemented (`flip`), and a pair may hold a bit that does
+// not belong to the group (`mask`)
+template <int Q, bool IL>
+__device__ __forceinline__ void words_of(const u32x4 (&w)[4 * Q], int t, uint32_t flip, const uint32_t (&mask)[2 * Q], uint32_t (&p)[4 * Q])
+{
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            lo[k] = (int)mix(0xF0F0F0F0u, a[k] << 4, b[k]);
-            hi[k] = (int)mix(0x0F0F0F0Fu, b[k] >> 4, a[k]);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            lo[k] = (int)((a[k] << 4) & 0xF0F0F0F0u);
-            hi[k] = (int)(a[k] & 0xF0F0F0F0u);
-        }
+    for (int s = 0; s < 4 * Q; ++s) {
+        p[s] = w[s][t];
+        if constexpr (IL) p[s] = (s < 2 ? p[s] ^ flip : p[s]) & mask[s / 2];
     }
 }
 

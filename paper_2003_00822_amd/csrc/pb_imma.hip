@@ -55,7 +55,7 @@ __host__ __device__ inline int stage_operand(int rows) { return rows * 64 + 16; 
 //   which the matrix instructions read them, and keeps reading them from there.  Else they come from memory (k_digits).
 // Bound: latencies at the small end (launch, activations, weights, barrier), the weight stream at the large end.  The words of
 // the next unit are requested before this one is multiplied: 8 KB in flight per wave, sixteen waves.  Turning the words of a unit
-// into codes takes 180 operations of the vector ALU, its products 16 (one tile) matrix instructions.
+// into codes takes 160 operations of the vector ALU, its products 16 (one tile) matrix instructions.
 // In a graph, us per call, against the FP4 form that this replaces (two bitlayers and two planes per operand):
 // 1024 x 1024, 8 bitlayers, 16 vectors 7.3 -> 4.3; 4096 x 4096, 4 vectors 8.1 -> 6.1; 8192 x 8192, 4 vectors 17.5 -> 14.7; 135 x 69, 7
 // bitlayers, 113 vectors 14.7 -> 4.6.  The conversion and the codes of a few vectors are more instructions per wave than their FP4
@@ -234,6 +234,7 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
     auto first_item = [&]() { return wave - turn + (wave < turn ? nwaves : 0); };
     auto vector_of = [&](int item) { return n0 + item / VPL * VPT + kb * VPL + item % VPL; };
     const v4i one = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    const Masks masks = make_masks();
     load_digits(areg[0], 0, 0);
     while (u.r < rounds) {
 #pragma unroll
@@ -256,16 +257,9 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     uint32_t w[4 * Q];
-#pragma unroll
-                    for (int s = 0; s < 4 * Q; ++s) {
-                        w[s] = ring[k][s][t];
-                        if constexpr (IL) {
-                            if (s < 2) w[s] ^= flip;
-                            w[s] &= mask[s / 2];
-                        }
-                    }
+                    words_of<Q, IL>(ring[k], t, flip, mask, w);
                     v4i b[2];
-                    weight_codes<Q, IL>(w, b[0], b[1]);
+                    weight_codes<Q, IL, (TM < 4)>(masks, w, b[0], b[1]);
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         // the operands of the next step are requested before this step's products

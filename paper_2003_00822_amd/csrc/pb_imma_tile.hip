@@ -48,6 +48,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
     const int rt0 = blockIdx.x * rows_per_wg;
     const int rts = min(rows_per_wg, a.rt_count - rt0);     // >= 1 by construction
     const int steps = (a.cq + WK - 1) / WK;
+    const Masks masks = make_masks();
 
     float scv, scn;
     {
@@ -121,17 +122,12 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
         // word t of the unit of `step` -> codes
         auto expand = [&](int t, int step, int buf) {
             const bool in = step * WK + kg < a.cq;
-            uint32_t p[4 * Q];
+            uint32_t keep[2 * Q], p[4 * Q];
 #pragma unroll
-            for (int s = 0; s < 4 * Q; ++s) {
-                p[s] = w[s][t];
-                if constexpr (IL) {
-                    if (s < 2) p[s] ^= flip;
-                    p[s] &= in ? mask[s / 2] : 0u;
-                }
-            }
+            for (int i = 0; i < 2 * Q; ++i) keep[i] = in ? mask[i] : 0u;
+            words_of<Q, IL>(w, t, flip, keep, p);
             v4i lo, hi;
-            weight_codes<Q, IL>(p, lo, hi);
+            weight_codes<Q, IL, true>(masks, p, lo, hi);
             ones = __builtin_amdgcn_mfma_i32_16x16x64_i8(one, lo, ones, 0, 0, 0);
             ones = __builtin_amdgcn_mfma_i32_16x16x64_i8(one, hi, ones, 0, 0, 0);
             *reinterpret_cast<v4i *>(my_codes + buf * BUF + t * 2048) = lo;
