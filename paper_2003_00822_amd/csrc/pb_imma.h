@@ -64,25 +64,31 @@ __device__ __forceinline__ void load_columns(const ActSource &s, int n, int c, i
         const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(s.X1), 0, (int)((uint32_t)s.batch * (uint32_t)s.cols1 * 4u), 0x00020000);
         const int c1 = c - s.cols0, off1 = (n * s.cols1 + c1) * 4;
-        if ((s.cols0 & 3) == 0 || end - 512 >= s.cols0) {   // four columns lie in one part
+        // (all requests before the first value is used, and three single values where the parts meet in place of sixteen: a step of an LSTM cell
+        // of 279 units and 75 inputs, 35 vectors of 8 bits, 14.5 -> 12.0 us; 177 units and 87 inputs, 3 vectors of 16 bits, 6.5 -> 6.1)
+        u32x4 w[4];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int cb = c1 + 8 * b;
-                const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(
-                    r1, live && cb >= 0 && cb < s.cols1 ? off1 + 32 * b : kNowhere, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[b][r] |= cb + r < s.cols1 ? w[r] : 0u;
-            }
-        } else {
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int cb = c1 + 8 * b + r;
-                    v[b][r] |= __builtin_amdgcn_raw_buffer_load_b32(
-                        r1, live && cb >= 0 && cb < s.cols1 ? off1 + 32 * b + 4 * r : kNowhere, 0, 0);
-                }
+        for (int b = 0; b < 4; ++b) {
+            const int cb = c1 + 8 * b;
+            w[b] = __builtin_amdgcn_raw_buffer_load_b128(r1, live && cb >= 0 && cb < s.cols1 ? off1 + 32 * b : kNowhere, 0, 0);
         }
+        const int lead = s.cols0 & 3;
+        uint32_t e[4] = {};
+        if (lead != 0 && end - 512 < s.cols0) {   // the four columns in which the second part begins: up to three of its values
+#pragma unroll
+            for (int r = 1; r < 4; ++r) {
+                const int x = r - lead;
+                e[r] = __builtin_amdgcn_raw_buffer_load_b32(r1, live && x >= 0 && x < s.cols1 ? (n * s.cols1 + x) * 4 : kNowhere, 0, 0);
+            }
+        }
+        const int b0 = s.cols0 - lead - c;        // (8 b: they are v[b])
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[b][r] |= c1 + 8 * b + r < s.cols1 ? w[b][r] : 0u;
+                if (r > 0) v[b][r] |= b0 == 8 * b ? e[r] : 0u;
+            }
     }
 }
 
