@@ -179,7 +179,8 @@ static int matmul_common(const void *packed, const float *scales, const pb_desc 
     if (digits)
         return hip_status(pb::launch_imma(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
                                           d->act_bits, X0, cols0, X1, cols1,
-                                          static_cast<char *>(workspace) + pb::ws_planes_off(L, batch), false, batch, Y,
+                                          static_cast<char *>(workspace) + pb::ws_planes_off(L, batch),
+                                          static_cast<char *>(workspace) + pb::ws_meta_off(L, batch), false, batch, Y,
                                           reinterpret_cast<long long *>(A), pairs_out, ep, st));
     if (pb::is_tile16(L.layout))   // conversion, bit transpose, product and epilogue in one launch
         return hip_status(pb::launch_mfma(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
@@ -261,7 +262,7 @@ int pb_act_prep(const pb_desc *d, const float *X, int batch, void *workspace, vo
     uint32_t *planes = reinterpret_cast<uint32_t *>(ws + pb::ws_planes_off(L, batch));
     const Issuing issuing(workspace);   // (it writes what a call between its launches may have left there)
     if (pb::takes_digits(L, batch))
-        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, nullptr,
+        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta, nullptr,
                                             static_cast<hipStream_t>(stream)));
     return hip_status(pb::launch_prep(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta,
                                       nullptr, static_cast<hipStream_t>(stream)));
@@ -283,8 +284,8 @@ int pb_matmul_prepared(const void *packed, const float *scales, const pb_desc *d
     const uint32_t *planes = reinterpret_cast<const uint32_t *>(ws + pb::ws_planes_off(L, batch));
     if (pb::takes_digits(L, batch))
         return hip_status(pb::launch_imma(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
-                                          d->act_bits, nullptr, 0, nullptr, 0, ws + pb::ws_planes_off(L, batch), true,
-                                          batch, Y, nullptr, false, pb::Epilogue(), static_cast<hipStream_t>(stream)));
+                                          d->act_bits, nullptr, 0, nullptr, 0, ws + pb::ws_planes_off(L, batch),
+                                          ws + pb::ws_meta_off(L, batch), true, batch, Y, nullptr, false, pb::Epilogue(), static_cast<hipStream_t>(stream)));
     if (pb::is_tile16(L.layout))
         return hip_status(pb::launch_mfma(static_cast<const uint32_t *>(packed), scales, L, bits_used, d->frac_bits,
                                           d->act_bits, nullptr, 0, nullptr, 0, planes, Y, nullptr, pb::Epilogue(),
@@ -307,7 +308,7 @@ int pb_fixed_point(const pb_desc *d, const float *X, int batch, int32_t *xq, voi
     uint32_t *planes = reinterpret_cast<uint32_t *>(ws + pb::ws_planes_off(L, batch));
     const Issuing issuing(workspace);   // (it writes what a call between its launches may have left there)
     if (pb::takes_digits(L, batch))
-        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, xq,
+        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta, xq,
                                             static_cast<hipStream_t>(stream)));
     return hip_status(pb::launch_prep(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta, xq,
                                       static_cast<hipStream_t>(stream)));

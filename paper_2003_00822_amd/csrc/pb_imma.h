@@ -15,6 +15,9 @@
 //     x_q = sum_d 256^d s_d + K,   K = 0x808080 (four bytes), 0x80 (two), 0 (one),
 // and K * sum_c code[c] is added per weight row: one more matrix instruction per weight operand, with an operand of
 // ones, delivers that sum.  |s_d code| <= 2^14, so a sum over all 32768 columns stays below 2^30: int32 is exact.
+// Three of four: a 32-bit x_q in [-2^23, 2^23) is the sum of its lower three bytes with the third one signed as it stands and
+// K = 0x8080.  k_digits leaves the third byte as it stands and notes for four vectors and a chunk of columns whether a value is
+// wider.  Where none is, the top digits are neither read nor multiplied; else the product kernel turns the third digit to u ^ 0x80.
 //
 // Groups.  A group of bitlayers [f, e) is one code: bitlayer i stands at slot i (counted from bit 7 down) in the first
 // group, which may hold eight, and at slot i - f + 2 in the later ones, which hold up to six (the sign bit and the one
@@ -102,8 +105,8 @@ __device__ __forceinline__ void convert_columns(const ActSource &s, u32x4 (&v)[4
 }
 
 // Sixteen fixed-point values, v[b][r] = column 8 b + r, -> their byte digits: word r of out[d] holds digit d of the columns r,
-// 8 + r, 16 + r, 24 + r, the order in which weight_codes() leaves the codes of 32 columns.
-template <int ND>
+// 8 + r, 16 + r, 24 + r, the order in which weight_codes() leaves the codes of 32 columns.  PLAIN2: digit 2 of four as it stands.
+template <int ND, bool PLAIN2 = false>
 __device__ __forceinline__ void byte_digits(const u32x4 (&v)[4], u32x4 (&out)[ND])
 {
 #pragma unroll
@@ -121,7 +124,7 @@ __device__ __forceinline__ void byte_digits(const u32x4 (&v)[4], u32x4 (&out)[ND
                 out[1][r] ^= 0x80808080u;
                 const uint32_t c = __builtin_amdgcn_perm(v[1][r], v[0][r], 0x07030602u);
                 const uint32_t d = __builtin_amdgcn_perm(v[3][r], v[2][r], 0x07030602u);
-                out[2][r] = __builtin_amdgcn_perm(d, c, 0x05040100u) ^ 0x80808080u;
+                out[2][r] = __builtin_amdgcn_perm(d, c, 0x05040100u) ^ (PLAIN2 ? 0u : 0x80808080u);
                 out[3][r] = __builtin_amdgcn_perm(d, c, 0x07060302u);
             }
         }
@@ -208,6 +211,25 @@ __device__ __forceinline__ void words_of(const u32x4 (&w)[4 * Q], int t, uint32_
     }
 }
 
+// The byte digits in memory: [group of 16 vectors][chunk of 512 columns][t = word % 4][h][quad of vectors][digit][kb = word / 4][vector of
+// the quad][16 bytes], the 16 bytes being the columns 8 b + 4 h + r of the word; a last quad of fewer vectors has as many fewer bytes
+// per kb.  An operand of four vectors' four digits is 1 KB in one piece, one of a digit of sixteen vectors is four pieces of 256 bytes.
+// Beside them, for 32-bit values, a byte per quad (64 apart) and chunk: 1 if a value is outside [-2^23, 2^23).
+constexpr int kGroupVectors = 16;
+__host__ __device__ inline int group_vectors(int batch, int group)
+{
+    const int left = batch - group * kGroupVectors;
+    return left < 0 ? 0 : (left < kGroupVectors ? left : kGroupVectors);
+}
+// From one (t, h) to the next, and the sixteen bytes of (digit, kb, vector v of the group) in the first one
+__device__ __forceinline__ uint32_t digits_step(int vectors, int nd) { return (uint32_t)(vectors * nd * 64); }
+__device__ __forceinline__ uint32_t digits_at(int group, int vectors, int cq, int nd, int digit, int kb, int v)
+{
+    const int quad = v & ~3, in_quad = vectors - quad < 4 ? vectors - quad : 4;
+    return (uint32_t)group * (uint32_t)(kGroupVectors * 512 * nd) * (uint32_t)cq +
+           (uint32_t)(quad * nd * 64 + ((digit * 4 + kb) * in_quad + (v & 3)) * 16);
+}
+
 struct I8Args {
     const uint32_t *packed;
     uint32_t packed_bytes;               // (below 2^32)
@@ -230,10 +252,25 @@ struct I8Args {
     int gate_h;
     int R;
     double out_scale;
+    const uint8_t *wide;                 // beside the digits
 };
 
 // What a kernel does with the sums: store Y (bias and ReLU first), update the LSTM cell, store the sums themselves
 enum { kStore = 0, kCell = 1, kSums = 2 };
+
+// Whether one of the values of so many quads of vectors needs four digits (the lanes see one chunk each: there are at most 64)
+template <int QUADS>
+__device__ __forceinline__ uint32_t load_wide(const I8Args &a, int quad, int lane)
+{
+    const __amdgpu_buffer_rsrc_t rw =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.wide), 0, (a.act.batch + 3) / 4 * 64, 0x00020000);
+    uint32_t v = 0;
+#pragma unroll
+    for (int i = 0; i < QUADS; ++i)
+        v |= __builtin_amdgcn_raw_buffer_load_b8(rw, lane < a.cq ? (quad + i) * 64 + lane : kNowhere, 0, 0);
+    return v;
+}
+__device__ __forceinline__ bool is_wide(uint32_t loaded) { return __builtin_amdgcn_ballot_w64(loaded != 0) != 0; }
 
 // A group of bitlayers [f, e): its last bitlayer stands at `slot`, its sum counts `scale`
 struct Group { int f, e, slot; bool first, last; double scale; };
@@ -262,25 +299,25 @@ __device__ __forceinline__ float bias_of(const I8Args &a, int prow)
 
 // The sum of one vector and weight row from its digits' sums d[0 .. nd) and the sum of the row's codes, times the scale of the
 // group (every part is an integer below 2^53 and exact; the last step rounds once if the sum is beyond).  The sum over the groups
-// starts at +0: no zero with the sign of a scale.
+// starts at +0: no zero with the sign of a scale.  `wide`: (four digits) the third one was turned to u ^ 0x80.
 template <int ND>
-__device__ __forceinline__ double scaled_sum(const Group &g, const int *d, int sum1)
+__device__ __forceinline__ double scaled_sum(const Group &g, const int *d, int sum1, bool wide)
 {
     double v = (double)d[0];
     if constexpr (ND == 2) v = fma(256.0, (double)d[1], fma(128.0, (double)sum1, v));
     if constexpr (ND == 4) {
         v = fma(65536.0, (double)d[2], fma(256.0, (double)d[1], v));
-        v = fma(16777216.0, (double)d[3], fma(8421504.0, (double)sum1, v));
+        v = fma(16777216.0, (double)d[3], fma(wide ? 8421504.0 : 32896.0, (double)sum1, v));
     }
     return fma(v, g.scale, 0.0);
 }
 template <int ND>
-__device__ __forceinline__ long long integer_sum(const Group &g, const int *d, int sum1)
+__device__ __forceinline__ long long integer_sum(const Group &g, const int *d, int sum1, bool wide)
 {
     long long v = (long long)d[0];
     if constexpr (ND == 2) v += ((long long)d[1] << 8) + 0x80ll * sum1;
     if constexpr (ND == 4)
-        v += ((long long)d[1] << 8) + ((long long)d[2] << 16) + ((long long)d[3] << 24) + 0x808080ll * sum1;
+        v += ((long long)d[1] << 8) + ((long long)d[2] << 16) + ((long long)d[3] << 24) + (wide ? 0x808080ll : 0x8080ll) * sum1;
     v >>= 7 - g.slot;
     return g.slot == 0 ? -v : v;   // (the sign bitlayer by itself)
 }

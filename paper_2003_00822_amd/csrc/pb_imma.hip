@@ -7,24 +7,23 @@
 
 namespace pb {
 
-// The activations as byte digits in memory, for the calls that read them more than once: per vector and chunk of 512
-// columns ND * 512 bytes, [t = word % 4][h][kb = word / 4][digit][16 bytes], the 16 bytes being the columns 8 b + 4 h + r of the
-// word.  A matrix operand (t, h) is then ND * 64 bytes of every vector, next to each other.
-// A wave does one chunk of two vectors: lane 32 v + 2 word + h.
+// The activations as byte digits in memory, for the calls that read them more than once (pb_imma.h has the order).
+// A workgroup does one chunk of four vectors, each of its two waves the words t, t + 1 (mod 4).  The lanes are in the order in which the
+// digits lie in memory: the order of the activations, two lanes to a word, took 0.2 us longer (56 vectors, 1402 columns).
 template <int ND>
-__global__ __launch_bounds__(256) void k_digits(ActSource s, int cq, uint8_t *__restrict__ digits,
+__global__ __launch_bounds__(128) void k_digits(ActSource s, int cq, uint8_t *__restrict__ digits, uint8_t *__restrict__ wide,
                                                 int32_t *__restrict__ xq_out)
 {
+    __shared__ int s_wide[2];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int q = blockIdx.x;
-    const int n = ((int)blockIdx.y * 4 + wave) * 2 + (lane >> 5);
-    const int word = (lane >> 1) & 15, h = lane & 1;
-    const int c = 512 * q + 32 * word + 4 * h;
+    const int q = blockIdx.x, quad = blockIdx.y, group = quad * 4 / kGroupVectors;
+    const int kb = (lane >> 2) & 3, th = 4 * wave + (lane >> 4), n = 4 * quad + (lane & 3);
+    const int vec = n % kGroupVectors, vectors = group_vectors(s.batch, group);
+    const int c = 512 * q + 32 * (4 * kb + th / 2) + 4 * (th % 2);
     u32x4 v[4];
     load_columns(s, n, c, 512 * (q + 1), v);
-    if (n >= s.batch) return;
     convert_columns(s, v);
-    if (xq_out) {
+    if (xq_out && n < s.batch) {
         const int cols = s.cols0 + s.cols1;
 #pragma unroll
         for (int b = 0; b < 4; ++b)
@@ -33,11 +32,23 @@ __global__ __launch_bounds__(256) void k_digits(ActSource s, int cq, uint8_t *__
                 if (c + 8 * b + r < cols) xq_out[(size_t)n * cols + c + 8 * b + r] = (int32_t)v[b][r];
     }
     u32x4 out[ND];
-    byte_digits<ND>(v, out);
-    u32x4 *dst = reinterpret_cast<u32x4 *>(digits + ((size_t)n * cq + q) * (ND * 512)) +
-                 ((word & 3) * 2 + h) * (ND * 4) + (word >> 2) * ND;
+    byte_digits<ND, true>(v, out);
+    if (vec < vectors) {
+        uint8_t *dst = digits + (size_t)(q * 8 + th) * digits_step(vectors, ND);
 #pragma unroll
-    for (int d = 0; d < ND; ++d) dst[d] = out[d];
+        for (int d = 0; d < ND; ++d) *reinterpret_cast<u32x4 *>(dst + digits_at(group, vectors, cq, ND, d, kb, vec)) = out[d];
+    }
+    if constexpr (ND == 4) {
+        uint32_t high = 0;   // bits that differ from the sign
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) high |= v[b][r] ^ (uint32_t)((int32_t)v[b][r] >> 31);
+        const bool any = __builtin_amdgcn_ballot_w64(high >> 23 != 0) != 0;
+        if (lane == 0) s_wide[wave] = any;
+        __syncthreads();
+        if (threadIdx.x == 0) wide[quad * 64 + q] = (uint8_t)(s_wide[0] | s_wide[1]);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -65,10 +76,17 @@ __host__ __device__ inline int stage_operand(int rows) { return rows * 64 + 16; 
 // are 1.7 times as fast on average, 51 of them slower by more than 1.5 %.
 
 template <int ND, int Q, bool IL, int TM, bool FUSED, int EPI, int POLICY>
-__global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
+// (the waves per SIMD: one tile, digits from memory, has four at most where a row has sixteen slices, and the registers that this leaves
+// let the compiler request the digits earlier: 67 x 4604, 7 vectors of 16 bits 6.4 -> 5.8 us, 913 x 8013, 15 vectors 7.1 -> 6.7)
+__global__ __launch_bounds__(stream_waves(TM) * 64)
+__attribute__((amdgpu_waves_per_eu(stream_waves(TM) / 4, !FUSED && TM == 1 ? 4 : 8))) void k_i8(const I8Args a)
 {
     constexpr int VPT = 16 / ND;            // vectors per tile of sixteen digit rows
     constexpr int VPL = 4 / ND;             // vectors per lane of a result: its four registers are the digits of these
+    // four tiles of four digits: tile d is digit d of sixteen vectors.  Else the rows of a tile are, from memory, a digit of four vectors
+    // after the other (four lanes next to each other read 64 bytes in one piece: otherwise a load takes several times as long), and
+    // as staged a digit of one vector after the other.
+    constexpr bool PLANES = !FUSED && TM == 4 && ND == 4;
     constexpr bool ONES = ND > 1;
     __shared__ int s_sum[2][TM * 4][64];
     __shared__ int s_ones[3][64];           // sums of the codes, per row
@@ -146,6 +164,8 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
         scv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0));
         scn = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + 4, 0, 0));
     }
+    uint32_t wide_here = 0;
+    if constexpr (ND == 4 && !FUSED) wide_here = load_wide<TM * VPT / 4>(a, n0 / 4, lane);
     Unit ld = {0, 0, group_end(0), 0};
     request_group(ld);
 
@@ -200,15 +220,18 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
     __syncthreads();   // (the sums are zero)
 
     // prepared digits: lane 16 kb + row of an operand reads the bytes of digit row % ND of vector row / ND
-    const int dvec = n0 + j / ND;
-    const uint32_t dlane = (uint32_t)(kb * ND + j % ND) * 16u;
+    // (a top digit that no value needs has no records: the load returns 0 and moves no data)
+    const bool wide = ND != 4 || FUSED || is_wide(wide_here);
     const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.digits), 0,
                                                                         (int)a.digits_bytes, 0x00020000);
-    uint32_t doff[TM];
+    uint32_t doff[TM], dstep[TM], turned[TM];
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
-        const int n = dvec + tm * VPT;
-        doff[tm] = n < a.act.batch ? (uint32_t)n * (uint32_t)a.cq * (ND * 512u) + dlane : (uint32_t)kNowhere;
+        const int first = PLANES ? n0 : n0 + tm * VPT, group = first / kGroupVectors, vectors = group_vectors(a.act.batch, group);
+        const int v = first % kGroupVectors + (PLANES ? j : j / (4 * ND) * 4 + j % 4), digit = PLANES ? tm : j / 4 % ND;
+        doff[tm] = v < vectors && (wide || digit < 3) ? digits_at(group, vectors, a.cq, ND, digit, kb, v) : (uint32_t)kNowhere;
+        dstep[tm] = digits_step(vectors, ND);
+        turned[tm] = ND == 4 && !FUSED && wide && digit == 2 ? 0x80808080u : 0u;
     }
     // staged digits (rows beyond the staged ones belong to no vector: any digits do)
     const int staged = kb * kbytes + min(j, a.stage_rows - 1) * 16;
@@ -219,8 +242,8 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
             if constexpr (FUSED)
                 dst[tm] = *reinterpret_cast<const u32x4 *>(my_stage + ((i * TM + tm) * 8 + th) * operand + staged);
             else
-                dst[tm] = __builtin_amdgcn_raw_buffer_load_b128(rd, (int)(doff[tm] + th * (ND * 64)),
-                                                                (int)((uint32_t)(q0 + i) * (ND * 512u)), 0);
+                dst[tm] = __builtin_amdgcn_raw_buffer_load_b128(rd, (int)doff[tm],
+                                                                (int)((uint32_t)((q0 + i) * 8 + th) * dstep[tm]), 0);
         }
     };
 
@@ -232,7 +255,7 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
     float bias_row = 0.0f, c_old = 0.0f;
     // the outputs of a row tile: vectors of a lane, tile after tile; the waves take them in turn
     auto first_item = [&]() { return wave - turn + (wave < turn ? nwaves : 0); };
-    auto vector_of = [&](int item) { return n0 + item / VPL * VPT + kb * VPL + item % VPL; };
+    auto vector_of = [&](int item) { return PLANES ? n0 + kb * 4 + item : n0 + item / VPL * VPT + kb * VPL + item % VPL; };
     const v4i one = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
     const Masks masks = make_masks();
     load_digits(areg[0], 0, 0);
@@ -266,6 +289,11 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
                         if (t < 3 || h == 0) load_digits(areg[h ^ 1], u.i, t * 2 + h + 1);
                         else load_digits(areg[0], ld.i, 0);
                         if constexpr (ONES) ones = __builtin_amdgcn_mfma_i32_16x16x64_i8(one, b[h], ones, 0, 0, 0);
+                        if constexpr (ND == 4 && !FUSED) {
+#pragma unroll
+                            for (int tm = 0; tm < TM; ++tm)
+                                if (!PLANES || tm == 2) areg[h][tm] ^= turned[tm];   // (a branch here costs more: 16 -> 20 us)
+                        }
 #pragma unroll
                         for (int tm = 0; tm < TM; ++tm)
                             acc[tm] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, areg[h][tm]), b[h],
@@ -291,18 +319,21 @@ __global__ __launch_bounds__(stream_waves(TM) * 64) void k_i8(const I8Args a)
                     const int row = a.gate_h ? gates_matrix_row(prow, a.gate_h) : prow;
                     const bool row_ok = row >= 0 && row < a.R;
                     for (int item = first_item(); item < TM * VPL; item += nwaves) {
-                        const int c0 = item / VPL * 4 + item % VPL * ND, n = vector_of(item);
+                        const int n = vector_of(item), v = kb * VPL + item % VPL;
                         int d[ND];
 #pragma unroll
                         for (int c = 0; c < ND; ++c) {
-                            d[c] = s_sum[buf][c0 + c][lane];
-                            s_sum[buf][c0 + c][lane] = 0;
+                            int *const at = PLANES ? &s_sum[buf][item + 4 * c][lane]
+                                            : FUSED || ND == 1 ? &s_sum[buf][item / VPL * 4 + item % VPL * ND + c][lane]
+                                                    : &s_sum[buf][item / VPL * 4 + v % 4][(v / 4 * ND + c) * 16 + j];
+                            d[c] = *at;
+                            *at = 0;
                         }
                         const int sum1 = ONES ? s_ones[buf3][lane] : 0;
                         if constexpr (EPI == kSums) {
-                            store_sum(a, g, row, row_ok, n, integer_sum<ND>(g, d, sum1));
+                            store_sum(a, g, row, row_ok, n, integer_sum<ND>(g, d, sum1, wide));
                         } else {
-                            double v = scaled_sum<ND>(g, d, sum1);
+                            double v = scaled_sum<ND>(g, d, sum1, wide);
                             if (!g.first) v += s_z[item][lane];
                             if (!g.last) {
                                 s_z[item][lane] = v;
@@ -340,15 +371,15 @@ static ActSource act_source(const float *X0, int cols0, const float *X1, int col
 }
 
 int launch_digits(const float *X0, int cols0, const float *X1, int cols1, int batch, const Layout &L, int frac_bits,
-                  int act_bits, void *digits, int32_t *xq_out, hipStream_t st)
+                  int act_bits, void *digits, void *wide, int32_t *xq_out, hipStream_t st)
 {
     const ActSource s = act_source(X0, cols0, X1, cols1, batch, frac_bits, act_bits);
-    const dim3 grid((unsigned)L.cq, (unsigned)((batch + 7) / 8));
-    uint8_t *d = static_cast<uint8_t *>(digits);
+    const dim3 grid((unsigned)L.cq, (unsigned)((batch + 3) / 4));
+    uint8_t *d = static_cast<uint8_t *>(digits), *w = static_cast<uint8_t *>(wide);
     switch (digits_of(act_bits)) {
-        case 1: hipLaunchKernelGGL(k_digits<1>, grid, dim3(256), 0, st, s, L.cq, d, xq_out); break;
-        case 2: hipLaunchKernelGGL(k_digits<2>, grid, dim3(256), 0, st, s, L.cq, d, xq_out); break;
-        default: hipLaunchKernelGGL(k_digits<4>, grid, dim3(256), 0, st, s, L.cq, d, xq_out); break;
+        case 1: hipLaunchKernelGGL(k_digits<1>, grid, dim3(128), 0, st, s, L.cq, d, w, xq_out); break;
+        case 2: hipLaunchKernelGGL(k_digits<2>, grid, dim3(128), 0, st, s, L.cq, d, w, xq_out); break;
+        default: hipLaunchKernelGGL(k_digits<4>, grid, dim3(128), 0, st, s, L.cq, d, w, xq_out); break;
     }
     return (int)hipGetLastError();
 }
@@ -494,8 +525,8 @@ static int pick_way(const I8Call &c, bool prepared, int cus)
 }
 
 int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, int bits_used, int frac_bits, int act_bits,
-                const float *X0, int cols0, const float *X1, int cols1, void *digits, bool prepared, int batch, float *Y,
-                long long *A, bool pairs_out, const Epilogue &ep, hipStream_t st)
+                const float *X0, int cols0, const float *X1, int cols1, void *digits, void *wide, bool prepared, int batch,
+                float *Y, long long *A, bool pairs_out, const Epilogue &ep, hipStream_t st)
 {
     const int nd = digits_of(act_bits);
     I8Args a;
@@ -506,6 +537,7 @@ int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, in
     a.rt_count = L.rt_count; a.cq = L.cq; a.m = bits_used;
     a.digits = static_cast<const uint8_t *>(digits);
     a.digits_bytes = (uint32_t)batch * (uint32_t)L.cq * (uint32_t)(nd * 512);
+    a.wide = static_cast<const uint8_t *>(wide);
     a.act = act_source(X0, cols0, X1, cols1, batch, frac_bits, act_bits);
     a.scales = scales; a.Y = Y; a.A = A; a.pairs_out = (A && pairs_out) ? 1 : 0;
     a.bias = ep.bias; a.relu = ep.relu; a.c_prev = ep.c_prev; a.h_out = ep.h_out; a.c_out = ep.c_out;
@@ -528,7 +560,7 @@ int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, in
     if (way == kFusedNt && (A || ep.c_prev)) way = kFused1;
     const int shape = way - kStreams;
     if (!prepared && !is_fused(way)) {
-        const int e = launch_digits(X0, cols0, X1, cols1, batch, L, frac_bits, act_bits, digits, nullptr, st);
+        const int e = launch_digits(X0, cols0, X1, cols1, batch, L, frac_bits, act_bits, digits, wide, nullptr, st);
         if (e) return e;
     }
     if (shape >= 0) return launch_imma_tile(shape, a, nd, il, st);

@@ -6,23 +6,25 @@
 namespace pb {
 
 // Many digit rows: the eight waves of a workgroup share the expanded weight codes through LDS.
-//   NT waves lie along the digit rows, TM tiles of sixteen each; 8 / NT groups of waves share out the columns.
+//   NT waves lie along the digit rows, TM tiles of sixteen each; 8 / NT groups of waves share out the columns.  A tile is one digit
+//   of sixteen vectors: a wave of four tiles has all digits of sixteen vectors of 32 bits, and of two waves of two tiles one has the
+//   lower two and the other the upper two.  Sixteen vectors that need only three digits cost three tiles: the fourth is neither read
+//   nor multiplied, and the waves are numbered so that every SIMD has as many waves of lower as of upper digits.
 //   NT column slots (a row tile and a group of bitlayers each); a step of a group of waves covers a chunk of 512 columns,
 //   and every wave expands one unit (slot, chunk) per step: it loads the words two steps ahead, turns them into codes
 //   one step ahead, and multiplies its own digit rows, which come straight from memory (each byte is used by one
 //   wave only), with the codes of all units of the step.
-// Bound: the matrix instructions at the large end (one in 16 cycles per SIMD; 8192 x 8192, 8 bitlayers, 1024 vectors: 2.1 of the
-// 5 POP/s, 42 %, where the library's bf16 product reaches 46 % of its peak on this card; the matrix pipes are busy 57 % of the
-// kernel's time); for few vectors the digit rows, which every
+// Bound: the matrix instructions at the large end (one in 16 cycles per SIMD; 8192 x 8192, 8 bitlayers, 1024 vectors of four digits: 2.1 of
+// the 5 POP/s, 42 %, where the library's bf16 product reaches 46 % of its peak on this card); for few vectors the digit rows, which every
 // workgroup reads at 64 bytes per cycle, LDS, the expansion and the matrix instructions, about as long each.  Operands of the codes
 // are read from LDS three (seven) products ahead and the scheduler is kept from moving work across a (t, h): without that barrier
 // the products waited for their operands (64 vectors: 39 -> 32 us).
-// us per call in a graph, digits included, against the FP4 form that this replaces: 8192 x 8192, 8 bitlayers, 64 vectors 124 -> 32, 256
-// vectors (pairs layout) 446 -> 72, 1024 vectors 1743 -> 258; 16384 x 16384, 64 vectors 464 -> 112; 3795 x 5918, 16 bitlayers, 301
-// vectors 547 -> 135.
-// The shape of four tiles per wave and eight slots (the one of 1024 vectors) needs more than the 256 registers of a wave: the compiler
-// keeps 32 to 87 of them per lane in scratch memory (132 to 320 bytes), used before and after the loop over the steps, not in it; a
-// kernel with scratch takes 0.3 us longer to launch.
+// us per call in a graph, digits included, 8192 x 8192, 8 bitlayers, values within three digits, against four digits with a vector's digits
+// next to each other in memory: 16 vectors 24.4 -> 22.3, 64 31.2 -> 28.1, 256 74.9 -> 64.6, 1024 260 -> 214 (pairs layout 261 -> 214);
+// 16384 x 16384, 64 vectors 117 -> 103, 256 255 -> 214.  Vectors of 8 bits, whose rows now are four pieces of 256 bytes and were sixteen
+// of 64: 64 vectors 41.5 -> 23.4, 256 47.2 -> 34.6, 1024 94.6 -> 85.1; of 16 bits 30.8 -> 28.0, 63.7 -> 60.5, 151 -> 149.
+// The shapes of eight waves along the digit rows need more than the 256 registers of a wave: 5 to 18 per lane live in scratch memory (24 to 76
+// bytes), 56 (180 to 196 bytes) with four tiles per wave and eight bitlayers; a kernel with scratch takes 0.3 us longer to launch.
 // Calls with several groups of bitlayers (more than eight bitlayers, scales that do not halve, the parity hooks) give them
 // slots of their own, so that the sums of a row tile's groups meet in a lane.
 template <int Q, bool IL, int NT, int TM, int EPI>
@@ -42,9 +44,18 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % NT, kg = wave / NT;     // (the wave's digit rows and the slot that it expands; its columns)
     const int kb = lane >> 4, j = lane & 15;
-    const int vpt = 16 >> nds;
     const int m = a.m;
-    const int n0 = ((int)blockIdx.y * NT + wm) * (TM * vpt);
+    // its tiles: digit and group of vectors of each
+    const int role = WK == 2 && kg == 1 ? NT - 1 - wm : wm;
+    const bool halves = TM == 2 && nds == 2;      // (two waves share a group's digits)
+    const int half = halves ? role / (NT / 2) : 0;
+    int group[TM], digit[TM];
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+        const int tile = ((int)blockIdx.y * NT + role) * TM + tm;
+        group[tm] = halves ? (int)blockIdx.y * (NT / 2) + role % (NT / 2) : tile >> nds;
+        digit[tm] = halves ? 2 * half + tm : tile & ((1 << nds) - 1);
+    }
     const int rt0 = blockIdx.x * rows_per_wg;
     const int rts = min(rows_per_wg, a.rt_count - rt0);     // >= 1 by construction
     const int steps = (a.cq + WK - 1) / WK;
@@ -57,6 +68,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
         scv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0));
         scn = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + 4, 0, 0));
     }
+    const uint32_t wide_here = nds == 2 ? load_wide<4>(a, group[0] * 4, lane) : 0;
     if (wave == 0 && lane < PB_MAX_BITS) s_scales[lane] = scv;
     bool merged = false;
     if (EPI != kSums) {
@@ -75,14 +87,16 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
     // digit rows
     const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.digits), 0,
                                                                         (int)a.digits_bytes, 0x00020000);
-    uint32_t doff[TM];
+    uint32_t doff[TM], dstep[TM];
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
-        const int n = n0 + tm * vpt + (j >> nds);
-        doff[tm] = n < a.act.batch ? (((uint32_t)n * (uint32_t)a.cq) << (nds + 9)) +
-                                         (uint32_t)((kb << nds) + (j & ((1 << nds) - 1))) * 16u
-                                   : (uint32_t)kNowhere;
+        const int vectors = group_vectors(a.act.batch, group[tm]);
+        doff[tm] = j < vectors ? digits_at(group[tm], vectors, a.cq, 1 << nds, digit[tm], kb, j) : (uint32_t)kNowhere;
+        dstep[tm] = digits_step(vectors, 1 << nds);
     }
+    // whether the top digits count (where a row tile's groups take several passes they always do), and then the digits to be turned
+    const bool wide = nds == 2 && (carry || is_wide(wide_here));
+    const uint32_t turned = wide && digit[TM == 4 ? 2 : 0] == 2 ? 0x80808080u : 0u;
     const char *base = reinterpret_cast<const char *>(a.packed) + (size_t)rt0 * a.round_step;
     const uint32_t avail = (uint32_t)(a.packed_bytes - (size_t)rt0 * a.round_step);
 
@@ -134,12 +148,12 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
             *reinterpret_cast<v4i *>(my_codes + buf * BUF + t * 2048 + 1024) = hi;
         };
         u32x4 ar[AR][TM];
-        auto load_digits = [&](u32x4 (&dst)[TM], int step, int th) {
+        auto load_digits = [&](auto tiles, u32x4 (&dst)[TM], int step, int th) {
             // (beyond the last chunk the codes are zero: any digits do)
             const int q = min(step * WK + kg, a.cq - 1);
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-                dst[tm] = __builtin_amdgcn_raw_buffer_load_b128(rd, (int)doff[tm], (q * 8 + th) << (nds + 6), 0);
+            for (int tm = 0; tm < decltype(tiles)::value; ++tm)
+                dst[tm] = __builtin_amdgcn_raw_buffer_load_b128(rd, (int)doff[tm], (int)((uint32_t)(q * 8 + th) * dstep[tm]), 0);
         };
         v4i acc[TM][NT];
 #pragma unroll
@@ -150,9 +164,9 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
         auto codes = [&](int buf, int th, int nt) {
             return *reinterpret_cast<const v4i *>(lds + buf * BUF + (kg * NT + nt) * UNIT + th * 1024 + lane * 16);
         };
-        auto multiply = [&](const u32x4 (&dig)[TM], const v4i b, int nt) {
+        auto multiply = [&](auto tiles, const u32x4 (&dig)[TM], const v4i b, int nt) {
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
+            for (int tm = 0; tm < decltype(tiles)::value; ++tm)
                 acc[tm][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, dig[tm]), b, acc[tm][nt], 0, 0, 0);
         };
         for (int i = threadIdx.x; i < NT * 64; i += 512) (&s_ones[0][0])[i] = 0;
@@ -163,9 +177,11 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
             s_bias[threadIdx.x / kTileRows][j] = EPI != kSums && a.bias ? bias_of(a, (rt0 + rr) * kTileRows + j) : 0.0f;
         }
         issue(0);
-        if (!carry) {
+        // the steps with the first `tiles` tiles of the wave; `turns`: digits have to be turned
+        auto products = [&](auto tiles, auto turns) {
+            constexpr int XT = TM == 4 ? 2 : 0;     // the tile of digit 2 (if it is of four)
 #pragma unroll
-            for (int k = 0; k < AR - 1; ++k) load_digits(ar[k], 0, k);
+            for (int k = 0; k < AR - 1; ++k) load_digits(tiles, ar[k], 0, k);
 #pragma unroll
             for (int t = 0; t < 4; ++t) expand(t, 0, 0);
             issue(1);
@@ -180,20 +196,28 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
                 for (int th = 0; th < 8; ++th) {
                     // the digit rows of a later (t, h) are requested before this one's products
                     const int nx = th + AR - 1;
-                    if (nx < 8) load_digits(ar[nx % AR], step, nx);
-                    else load_digits(ar[nx % AR], step + 1, nx - 8);
+                    if (nx < 8) load_digits(tiles, ar[nx % AR], step, nx);
+                    else load_digits(tiles, ar[nx % AR], step + 1, nx - 8);
                     if ((th & 1) == 0) expand(th / 2, step + 1, buf ^ 1);
                     if (th == 7) issue(step + 2);
+                    if constexpr (decltype(turns)::value) ar[th % AR][XT] ^= turned;
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) {
                         const int i = th * NT + nt, ahead = i + BR - 1;
                         if (ahead < 8 * NT) br[ahead % BR] = codes(buf, ahead / NT, ahead % NT);
-                        multiply(ar[th % AR], br[i % BR], nt);
+                        multiply(tiles, ar[th % AR], br[i % BR], nt);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 __syncthreads();
             }
+        };
+        const std::integral_constant<int, TM> all;
+        const std::integral_constant<int, TM - 1> but_one;
+        if (!carry) {
+            if (nds == 2 && !wide && (TM == 4 || half == 1)) products(but_one, std::false_type{});
+            else if (TM == 4 || turned) products(all, std::true_type{});
+            else products(all, std::false_type{});
         } else {
             for (int step = 0; step < steps; ++step) {
 #pragma unroll
@@ -201,16 +225,17 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
                 issue(step + 1);
                 __syncthreads();
                 for (int th = 0; th < 8; ++th) {
-                    load_digits(ar[0], step, th);
+                    load_digits(all, ar[0], step, th);
+                    ar[0][TM == 4 ? 2 : 0] ^= turned;
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) multiply(ar[0], codes(0, th, nt), nt);
+                    for (int nt = 0; nt < NT; ++nt) multiply(all, ar[0], codes(0, th, nt), nt);
                 }
                 __syncthreads();
             }
         }
         // ---- the groups of waves add up, then every tile is finished ----
         atomicAdd(&s_ones[wm][lane], ones[0]);
-        int *const part = reinterpret_cast<int *>(lds) + wm * (TM * NT * 4 * 64) + lane;
+        int *const part = reinterpret_cast<int *>(lds) + role * (TM * NT * 4 * 64) + lane;
         for (int k = 1; k < WK; ++k) {
             if (k > 1) __syncthreads();
             if (kg == k) {
@@ -232,52 +257,81 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
             }
         }
         __syncthreads();
+        // Two waves of a group's digits: each finishes every other row tile, and leaves its sums of the others in LDS.
+        int *const shared = reinterpret_cast<int *>(lds) + role % (NT / 2) * (TM * NT * 4 * 64) + lane;
+        auto mine = [&](int rr) { return !halves || ((rr - r) & 1) == half; };
+        if (halves) {
+            if (kg == 0) {
+                int rr = r, gg = g0;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (!mine(rr)) {
+#pragma unroll
+                        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) shared[((nt * TM + tm) * 4 + c) * 64] = acc[tm][nt][c];
+                    }
+                    if (++gg == ng) { gg = 0; ++rr; }
+                }
+            }
+            __syncthreads();
+        }
         if (kg == 0) {
             int rr = r, gg = g0;
             for (int nt = 0; nt < slots; ++nt) {
-                const Group g = make_group(a, group_first(gg), group_end(gg), s_scales);
-                const int sum1 = s_ones[nt][lane];
-                const float bias_row = s_bias[nt][j];
-                int d[TM][4] = {};
+                if (mine(rr)) {
+                    const Group g = make_group(a, group_first(gg), group_end(gg), s_scales);
+                    const int sum1 = s_ones[nt][lane];
+                    const float bias_row = s_bias[nt][j];
+                    int d[TM][4] = {};
 #pragma unroll
-                for (int x = 0; x < NT; ++x)
-                    if (x == nt) {
+                    for (int x = 0; x < NT; ++x)
+                        if (x == nt) {
 #pragma unroll
-                        for (int tm = 0; tm < TM; ++tm)
+                            for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-                            for (int c = 0; c < 4; ++c) d[tm][c] = acc[tm][x][c];
-                    }
-                const int prow = (rt0 + rr) * kTileRows + j;
-                const int row = a.gate_h ? gates_matrix_row(prow, a.gate_h) : prow;
-                const bool row_ok = row >= 0 && row < a.R;
-                auto outputs = [&](auto digits) {
-                    constexpr int ND = decltype(digits)::value, VPL = 4 / ND;
-                    const int n = n0 + kb * VPL;
-                    float c_old[TM][VPL] = {};
-                    if (EPI == kCell && g.last) {
+                                for (int c = 0; c < 4; ++c) d[tm][c] = acc[tm][x][c];
+                        }
+                    const int prow = (rt0 + rr) * kTileRows + j;
+                    const int row = a.gate_h ? gates_matrix_row(prow, a.gate_h) : prow;
+                    const bool row_ok = row >= 0 && row < a.R;
+                    // `digits` tiles of this wave have the digits of four vectors of the lane, the lowest first
+                    auto outputs = [&](auto digits, auto both) {
+                        constexpr int ND = decltype(digits)::value, OWN = decltype(both)::value ? 2 : ND, VECTORS = TM / OWN * 4;
+                        auto vector = [&](int i) { return group[i / 4 * OWN] * kGroupVectors + kb * 4 + i % 4; };
+                        float c_old[VECTORS] = {};
+                        if (EPI == kCell && g.last) {
 #pragma unroll
-                        for (int tm = 0; tm < TM; ++tm)
+                            for (int i = 0; i < VECTORS; ++i) c_old[i] = cell_state(a, lane, row, row_ok, vector(i));
+                        }
 #pragma unroll
-                            for (int p = 0; p < VPL; ++p) c_old[tm][p] = cell_state(a, lane, row, row_ok, n + tm * vpt + p);
-                    }
+                        for (int i = 0; i < VECTORS; ++i) {
+                            int dd[ND];
 #pragma unroll
-                    for (int tm = 0; tm < TM; ++tm)
+                            for (int k = 0; k < OWN; ++k) dd[k] = d[i / 4 * OWN + k][i % 4];
+                            if constexpr (decltype(both)::value) {
 #pragma unroll
-                        for (int p = 0; p < VPL; ++p) {
+                                for (int k = 0; k < 2; ++k) {
+                                    const int own = dd[k], other = shared[((nt * TM + k) * 4 + i) * 64];
+                                    dd[k] = half ? other : own;
+                                    dd[2 + k] = half ? own : other;
+                                }
+                            }
                             if constexpr (EPI == kSums) {
-                                store_sum(a, g, row, row_ok, n + tm * vpt + p, integer_sum<ND>(g, &d[tm][p * ND], sum1));
+                                store_sum(a, g, row, row_ok, vector(i), integer_sum<ND>(g, dd, sum1, wide));
                             } else {
-                                double *z = reinterpret_cast<double *>(lds + BUF) + ((wm * TM + tm) * 4 + p) * 64 + lane;
-                                double v = scaled_sum<ND>(g, &d[tm][p * ND], sum1);
+                                double *z = reinterpret_cast<double *>(lds + BUF) + (wm * TM * 4 + i) * 64 + lane;
+                                double v = scaled_sum<ND>(g, dd, sum1, wide);
                                 if (!g.first) v += *z;
                                 if (!g.last) *z = v;
-                                else finish<EPI>(a, lane, row, row_ok, n + tm * vpt + p, v, bias_row, c_old[tm][p]);
+                                else finish<EPI>(a, lane, row, row_ok, vector(i), v, bias_row, c_old[i]);
                             }
                         }
-                };
-                if (nds == 2) outputs(std::integral_constant<int, 4>{});
-                else if (nds == 1) outputs(std::integral_constant<int, 2>{});
-                else outputs(std::integral_constant<int, 1>{});
+                    };
+                    if (nds == 2) outputs(std::integral_constant<int, 4>{}, std::integral_constant<bool, TM == 2>{});
+                    else if (nds == 1) outputs(std::integral_constant<int, 2>{}, std::false_type{});
+                    else outputs(std::integral_constant<int, 1>{}, std::false_type{});
+                }
                 if (++gg == ng) { gg = 0; ++rr; }
             }
         }

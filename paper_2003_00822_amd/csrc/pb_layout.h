@@ -158,7 +158,8 @@ __host__ __device__ inline void pair_of_digits(uint32_t even, uint32_t odd, uint
 }
 
 // Workspace: [meta: batch * kMetaInts int32][planes: batch * 32 * cwp uint32][gates: batch * rows fp32]; the kernels for batches
-// keep the byte digits of the activations in the place of the planes (at most as many bytes)
+// keep the byte digits of the activations in the place of the planes (at most as many bytes), and in that of the meta data a byte per
+// four vectors (64 apart) and chunk of columns
 inline size_t ws_meta_off(const Layout &, int) { return 0; }
 inline size_t ws_planes_off(const Layout &, int batch) { return ((size_t)batch * kMetaInts * 4 + 255) & ~(size_t)255; }
 inline size_t ws_gates_off(const Layout &L, int batch)

@@ -118,6 +118,39 @@ def test_every_way(pb, case, layout):
     check(pb, R, C, N, bits, m, act_bits, frac_bits, layout, sums=with_sums(R, N))
 
 
+# The kernels that read the digits from memory: rows, columns, vectors, bits, used
+DIGITS = [(2669, 520, 187, 2, 1), (2207, 515, 67, 10, 8), (2207, 515, 70, 8, 8), (2620, 2697, 113, 8, 8), (6326, 1189, 388, 8, 8),
+          (4643, 3250, 491, 1, 1), (4379, 18, 105, 13, 1), (752, 2612, 35, 3, 3), (5782, 16, 34, 11, 9), (100, 9000, 12, 3, 3)]
+
+
+@pytest.mark.parametrize("layout", [BITS, PAIRS])
+@pytest.mark.parametrize("case", DIGITS, ids=lambda c: "x".join(map(str, c[:3])) + "-%d/%d" % (c[4], c[3]))
+def test_three_digits_or_four(pb, case, layout):
+    """Groups of sixteen vectors at both ends of three byte digits, and with one value just beyond in the first, in a middle and
+    in the last chunk: each group is multiplied with the digits that it needs."""
+    R, C, N, bits, m = case
+    print("digits", case, hex(layout), flush=True)
+    g = np.random.default_rng(200300822 + 67)
+    W = g.normal(0, 0.02, size=(R, C)).astype(np.float32)
+    X = g.normal(size=(N, C)).astype(np.float32)
+    for group in range((N + 15) // 16):
+        rows = range(16 * group, min(N, 16 * group + 16))
+        X[rows[0], 0], X[rows[-1], C - 1] = (2 ** 23 - 1) / 65536, -128.0
+        if group % 4 == 1: X[rows[-1], 0] = 128.0
+        if group % 4 == 2: X[rows[0], C // 2] = -(2 ** 23 + 1) / 65536
+        if group % 4 == 3: X[rows[len(rows) // 2], C - 1] = 3e38
+    sample = sorted({0, 1, R // 2, (R - 1) // 16 * 16, R - 1})
+    prep = po.prepare(W[sample + [int(np.abs(W).max(axis=1).argmax())]], bits)
+    lin = pb.PackedLinear(dev(W), bits, max_batch=N, layout=layout)
+    Y = lin(dev(X), m).cpu().numpy()
+    A = lin.acc(dev(X), m).cpu().numpy() if with_sums(R, N) else None
+    xq = po.fixed_point(X, frac_bits=16, act_bits=32)
+    for k, r in enumerate(sample):
+        sub = po.layer_products_direct(prep["layers"][:, k:k + 1, :], m, xq)[:, :, 0]
+        assert_y_close(Y[:, r], po.dequant(sub, prep["scales"], m, frac_bits=16), sub, prep["scales"], frac_bits=16)
+        if A is not None: assert (A[:, :, r] == sub).all(), r
+
+
 # hidden units, inputs, vectors, activation bits, bits, used; from the second line on: each compiled kernel with the cell update
 CELLS = [
     (37, 100, 2, 32, 5, 5), (300, 701, 40, 32, 5, 5), (500, 1500, 100, 16, 5, 5), (600, 79, 11, 8, 5, 5), (40, 1301, 5, 8, 5, 5),
