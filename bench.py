@@ -546,9 +546,10 @@ def size_sweep(torch, pb, dev, layout):
 
 
 def matrix_rate(size, m, N, t, fp4=False):
-    """What the matrix instructions of a call with m bitlayers come to: 16 digit rows per vector and bitlayer in FP4, or 4 byte
-    digits per vector for up to eight bitlayers together."""
-    issued = 2.0 * (16 * m if fp4 else 4) * size * size * N / t / 1e12
+    """What the matrix instructions of a call with m bitlayers come to: 16 digit rows per vector and bitlayer in FP4, or 3 byte
+    digits per vector for up to eight bitlayers together: what values within 128 need (16 fractional bits; the kernels that convert a
+    few vectors in their launch multiply a fourth, which is not counted)."""
+    issued = 2.0 * (16 * m if fp4 else 3) * size * size * N / t / 1e12
     if fp4:
         return {"mfma_issued_TFLOPs": round(issued, 1), "mfma_frac": round(issued / FP4_PEAK_TFLOPS, 4)}
     return {"mfma_issued_TOPs": round(issued, 1), "mfma_frac": round(issued / I8_PEAK_TOPS, 4)}
@@ -559,7 +560,7 @@ def batch_sweep(torch, pb, synth, dev):
     dense contraction.  Both kernels, weights warm (the 64 MiB stay in the last-level cache between the passes
     of one call anyway).  Nominal work = rows * cols * bits_used * 32 planes * batch 1-bit multiply-accumulates.
     Matrix-core rows: the products issued (batch 1 on the default layout: FP4 digits, else whole weight codes times the
-    four bytes of an activation) against the peak of that type.  Popcount rows: the vector-ALU lane
+    three bytes that an activation needs) against the peak of that type.  Popcount rows: the vector-ALU lane
     operations the kernel executes (one AND + one popcount-accumulate per 32-bit weight word and ACTIVE plane: planes
     that are empty or copies of the sign plane are skipped, the count comes from the plane statistics the activation
     kernel leaves in the workspace) against the integer vector-ALU peak.  Narrower activations (Section 3.1, Table 1)

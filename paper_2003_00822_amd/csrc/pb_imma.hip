@@ -465,6 +465,8 @@ static bool streaming(const I8Call &c) { return c.tiles == 1 && c.weights > 44.0
 // the worst case: it is weakest with 8- and 16-bit activations of many vectors on a small matrix, whose conversion one after the other
 // the estimate takes for shorter than it is (284 x 1200, 21 vectors of 8 bits, cell update 12.2 us, from memory 6.9).  A term for that
 // chain, fitted to 900 of the calls, moved 62 of the other 1500 to a kernel over 3 % slower and 48 to one as much faster: left out.
+// With digits by groups of sixteen vectors and three of four, 420 more calls: 3.3 % on average over the best, 19 %, 1.55 times; fitted again to
+// half of them the estimates were no better on the other half (3.1 %, 3.0 % before) and stay.
 // The bitlayers count by themselves: with one cost for all,
 // one and two bitlayers of a few vectors went to the wrong kernel (3841 x 7174, one bitlayer, 14 vectors: 13.4 us, here 10.9).
 //   few digit rows: rounds of workgroups over the chip, units (row tile, group, tile of digit rows, chunk), conversion
