@@ -14,26 +14,33 @@ namespace pb {
 //   and every wave expands one unit (slot, chunk) per step: it loads the words two steps ahead, turns them into codes
 //   one step ahead, and multiplies its own digit rows, which come straight from memory (each byte is used by one
 //   wave only), with the codes of all units of the step.
-// Bound: the matrix instructions at the large end (one in 16 cycles per SIMD; 8192 x 8192, 8 bitlayers, 1024 vectors of four digits: 2.1 of
-// the 5 POP/s, 42 %, where the library's bf16 product reaches 46 % of its peak on this card); for few vectors the digit rows, which every
+// Bound: the matrix instructions at the large end (one in 16 cycles per SIMD); for few vectors the digit rows, which every
 // workgroup reads at 64 bytes per cycle, LDS, the expansion and the matrix instructions, about as long each.  Operands of the codes
-// are read from LDS three (seven) products ahead and the scheduler is kept from moving work across a (t, h): without that barrier
+// are read from LDS three (six, seven) products ahead and the scheduler is kept from moving work across a (t, h): without that barrier
 // the products waited for their operands (64 vectors: 39 -> 32 us).
 // us per call in a graph, digits included, 8192 x 8192, 8 bitlayers, values within three digits, against four digits with a vector's digits
 // next to each other in memory: 16 vectors 24.4 -> 22.3, 64 31.2 -> 28.1, 256 74.9 -> 64.6, 1024 260 -> 214 (pairs layout 261 -> 214);
 // 16384 x 16384, 64 vectors 117 -> 103, 256 255 -> 214.  Vectors of 8 bits, whose rows now are four pieces of 256 bytes and were sixteen
 // of 64: 64 vectors 41.5 -> 23.4, 256 47.2 -> 34.6, 1024 94.6 -> 85.1; of 16 bits 30.8 -> 28.0, 63.7 -> 60.5, 151 -> 149.
-// The shapes of eight waves along the digit rows need more than the 256 registers of a wave: 5 to 18 per lane live in scratch memory (24 to 76
-// bytes), 56 (180 to 196 bytes) with four tiles per wave and eight bitlayers; a kernel with scratch takes 0.3 us longer to launch.
+// Values beyond three digits, one in every sixteen vectors, against four digits of every value as it was: 64 vectors 31.3 -> 30.2, 256 73.9 -> 71.5,
+// 1024 260 -> 248; 3795 x 5918, 16 bitlayers, 301 vectors 133.8 -> 133.6.
+// A kernel for each number of digits: one kernel for all of them had the loop over the steps three times and every kind of output, which
+// filled the registers (scratch memory also in the shape of eight waves and two tiles), and turned a digit of 8- and 16-bit vectors by zero.
+// One kernel -> three: 64 vectors 28.0 -> 27.3, with values beyond three digits 30.8 -> 30.2, 4096 x 4096 16.5 -> 15.8; 1024 vectors of 8 bits 86.4 ->
+// 84.0, 256 34.7 -> 34.0; LSTM step 6000 x 3000, 5 bitlayers, 64 vectors 18.3 -> 17.3.
+// The shape with four tiles per wave still needs more than the 256 registers of a wave (up to 196 bytes of scratch): the loop of three digits
+// has none of them, those of four, two and one reload up to twelve registers in a step of 264 matrix instructions.  A kernel with scratch takes
+// 0.3 us longer to launch.
 // Calls with several groups of bitlayers (more than eight bitlayers, scales that do not halve, the parity hooks) give them
 // slots of their own, so that the sums of a row tile's groups meet in a lane.
-template <int Q, bool IL, int NT, int TM, int EPI>
-__global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, const int rows_per_wg)
+template <int ND, int Q, bool IL, int NT, int TM, int EPI>
+__global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int rows_per_wg)
 {
+    constexpr int nds = ND == 4 ? 2 : ND - 1;
     constexpr int WK = 8 / NT;
     constexpr int UNIT = 8 * 1024;          // codes of a unit: eight operands of 1 KB
     constexpr int BUF = 8 * UNIT;
-    constexpr int BR = TM >= 4 ? 4 : 8;     // operands of codes: ring
+    constexpr int BR = TM >= 4 ? 4 : (NT == 8 ? 7 : 8);     // operands of codes: ring
     constexpr int AR = NT * TM >= 32 ? 2 : 4;     // operands of digit rows: ring of steps (t, h)
     extern __shared__ __align__(16) unsigned char lds[];    // two buffers
     __shared__ int s_ones[NT][64];
@@ -47,7 +54,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
     const int m = a.m;
     // its tiles: digit and group of vectors of each
     const int role = WK == 2 && kg == 1 ? NT - 1 - wm : wm;
-    const bool halves = TM == 2 && nds == 2;      // (two waves share a group's digits)
+    constexpr bool halves = TM == 2 && ND == 4;      // (two waves share a group's digits)
     const int half = halves ? role / (NT / 2) : 0;
     int group[TM], digit[TM];
 #pragma unroll
@@ -96,7 +103,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
     }
     // whether the top digits count (where a row tile's groups take several passes they always do), and then the digits to be turned
     const bool wide = nds == 2 && (carry || is_wide(wide_here));
-    const uint32_t turned = wide && digit[TM == 4 ? 2 : 0] == 2 ? 0x80808080u : 0u;
+    const bool turns = wide && (TM == 4 || half == 1);
     const char *base = reinterpret_cast<const char *>(a.packed) + (size_t)rt0 * a.round_step;
     const uint32_t avail = (uint32_t)(a.packed_bytes - (size_t)rt0 * a.round_step);
 
@@ -177,9 +184,9 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
             s_bias[threadIdx.x / kTileRows][j] = EPI != kSums && a.bias ? bias_of(a, (rt0 + rr) * kTileRows + j) : 0.0f;
         }
         issue(0);
-        // the steps with the first `tiles` tiles of the wave; `turns`: digits have to be turned
-        auto products = [&](auto tiles, auto turns) {
-            constexpr int XT = TM == 4 ? 2 : 0;     // the tile of digit 2 (if it is of four)
+        constexpr int XT = TM == 4 ? 2 : 0;         // the tile of digit 2 (if it is of four)
+        // the steps with the first `tiles` tiles of the wave; `turn`: digit 2 has to be turned
+        auto products = [&](auto tiles, auto turn) {
 #pragma unroll
             for (int k = 0; k < AR - 1; ++k) load_digits(tiles, ar[k], 0, k);
 #pragma unroll
@@ -200,7 +207,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
                     else load_digits(tiles, ar[nx % AR], step + 1, nx - 8);
                     if ((th & 1) == 0) expand(th / 2, step + 1, buf ^ 1);
                     if (th == 7) issue(step + 2);
-                    if constexpr (decltype(turns)::value) ar[th % AR][XT] ^= turned;
+                    if constexpr (decltype(turn)::value) ar[th % AR][XT] ^= 0x80808080u;
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) {
                         const int i = th * NT + nt, ahead = i + BR - 1;
@@ -215,8 +222,9 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
         const std::integral_constant<int, TM> all;
         const std::integral_constant<int, TM - 1> but_one;
         if (!carry) {
-            if (nds == 2 && !wide && (TM == 4 || half == 1)) products(but_one, std::false_type{});
-            else if (TM == 4 || turned) products(all, std::true_type{});
+            if constexpr (ND != 4) products(all, std::false_type{});
+            else if (!wide && (TM == 4 || half == 1)) products(but_one, std::false_type{});
+            else if (turns) products(all, std::true_type{});
             else products(all, std::false_type{});
         } else {
             for (int step = 0; step < steps; ++step) {
@@ -226,7 +234,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
                 __syncthreads();
                 for (int th = 0; th < 8; ++th) {
                     load_digits(all, ar[0], step, th);
-                    ar[0][TM == 4 ? 2 : 0] ^= turned;
+                    if constexpr (ND == 4) ar[0][XT] ^= turns ? 0x80808080u : 0u;
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) multiply(all, ar[0], codes(0, th, nt), nt);
                 }
@@ -297,7 +305,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
                     const bool row_ok = row >= 0 && row < a.R;
                     // `digits` tiles of this wave have the digits of four vectors of the lane, the lowest first
                     auto outputs = [&](auto digits, auto both) {
-                        constexpr int ND = decltype(digits)::value, OWN = decltype(both)::value ? 2 : ND, VECTORS = TM / OWN * 4;
+                        constexpr int OWN = decltype(both)::value ? 2 : ND, VECTORS = TM / OWN * 4;
                         auto vector = [&](int i) { return group[i / 4 * OWN] * kGroupVectors + kb * 4 + i % 4; };
                         float c_old[VECTORS] = {};
                         if (EPI == kCell && g.last) {
@@ -328,9 +336,7 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
                             }
                         }
                     };
-                    if (nds == 2) outputs(std::integral_constant<int, 4>{}, std::integral_constant<bool, TM == 2>{});
-                    else if (nds == 1) outputs(std::integral_constant<int, 2>{}, std::false_type{});
-                    else outputs(std::integral_constant<int, 1>{}, std::false_type{});
+                    outputs(std::integral_constant<int, ND>{}, std::integral_constant<bool, halves>{});
                 }
                 if (++gg == ng) { gg = 0; ++rr; }
             }
@@ -344,35 +350,36 @@ __global__ __launch_bounds__(512) void k_i8_tile(const I8Args a, const int nds, 
 
 // ---------------------------------------------------------------------------------------------------------------
 
-template <int Q, bool IL, int NT, int TM, int EPI>
+template <int ND, int Q, bool IL, int NT, int TM, int EPI>
 static const void *tile_kernel()
 {
     // (the sums themselves are asked for in groups of one or two: four slots)
     if constexpr ((EPI == kSums && Q > 1) || (EPI == kCell && IL)) return nullptr;
-    else return reinterpret_cast<const void *>(k_i8_tile<Q, IL, NT, TM, EPI>);
+    else return reinterpret_cast<const void *>(k_i8_tile<ND, Q, IL, NT, TM, EPI>);
 }
-#define PB_TILE_E(NT, TM, E) {{tile_kernel<1, false, NT, TM, E>(), tile_kernel<1, true, NT, TM, E>()}, \
-                              {tile_kernel<2, false, NT, TM, E>(), tile_kernel<2, true, NT, TM, E>()}}
-#define PB_TILE(NT, TM) {PB_TILE_E(NT, TM, kStore), PB_TILE_E(NT, TM, kCell), PB_TILE_E(NT, TM, kSums)}
-static const void *const kTileFn[kTileShapes][3][2][2] = {PB_TILE(4, 2), PB_TILE(8, 2), PB_TILE(8, 4)};
+#define PB_TILE_E(ND, NT, TM, E) {{tile_kernel<ND, 1, false, NT, TM, E>(), tile_kernel<ND, 1, true, NT, TM, E>()}, \
+                                  {tile_kernel<ND, 2, false, NT, TM, E>(), tile_kernel<ND, 2, true, NT, TM, E>()}}
+#define PB_TILE_ND(ND, NT, TM) {PB_TILE_E(ND, NT, TM, kStore), PB_TILE_E(ND, NT, TM, kCell), PB_TILE_E(ND, NT, TM, kSums)}
+#define PB_TILE(NT, TM) {PB_TILE_ND(1, NT, TM), PB_TILE_ND(2, NT, TM), PB_TILE_ND(4, NT, TM)}
+static const void *const kTileFn[kTileShapes][3][3][2][2] = {PB_TILE(4, 2), PB_TILE(8, 2), PB_TILE(8, 4)};
 constexpr int kTileLds = 128 * 1024;
 
 int launch_imma_tile(int shape, const I8Args &a, int nd, bool il, hipStream_t st)
 {
-    const int epi = a.A ? kSums : (a.c_prev ? kCell : kStore), q = (epi != kSums && a.m > 4) ? 1 : 0;
-    const void *fn = kTileFn[shape][epi][q][il];
-    static bool declared[kTileShapes][3][2][2];
+    const int epi = a.A ? kSums : (a.c_prev ? kCell : kStore), q = (epi != kSums && a.m > 4) ? 1 : 0, ndi = nd == 4 ? 2 : nd - 1;
+    const void *fn = kTileFn[shape][ndi][epi][q][il];
+    static bool declared[kTileShapes][3][3][2][2];
     if (!fn) return (int)hipErrorInvalidValue;
-    if (!__atomic_load_n(&declared[shape][epi][q][il], __ATOMIC_RELAXED)) {
+    if (!__atomic_load_n(&declared[shape][ndi][epi][q][il], __ATOMIC_RELAXED)) {
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds);
         if (e != hipSuccess) return (int)e;
-        __atomic_store_n(&declared[shape][epi][q][il], true, __ATOMIC_RELAXED);
+        __atomic_store_n(&declared[shape][ndi][epi][q][il], true, __ATOMIC_RELAXED);
     }
     const TileShape &t = kTile[shape];
-    int nds = nd == 4 ? 2 : nd - 1, rows_per_wg = tile_rows(t, a.m, epi == kSums);
+    int rows_per_wg = tile_rows(t, a.m, epi == kSums);
     const int vpt = 16 / nd, tiles = (a.act.batch + vpt - 1) / vpt;
     const int groups = (tiles + t.nt * t.tm - 1) / (t.nt * t.tm), wgs = (a.rt_count + rows_per_wg - 1) / rows_per_wg;
-    void *args[] = {const_cast<I8Args *>(&a), &nds, &rows_per_wg};
+    void *args[] = {const_cast<I8Args *>(&a), &rows_per_wg};
     const hipError_t e = hipLaunchKernel(fn, dim3((unsigned)wgs, (unsigned)groups), dim3(512), args, kTileLds, st);
     return (int)(e != hipSuccess ? e : hipGetLastError());
 }

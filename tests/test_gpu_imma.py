@@ -91,6 +91,13 @@ CASES = [
 KERNELS = [
     # many digit rows: four waves along them, eight, eight with four tiles each
     (2669, 520, 187, 2, 1, 32, 16), (2207, 515, 67, 10, 8, 32, 16), (6326, 1189, 388, 8, 8, 32, 16), (4643, 3250, 491, 1, 1, 32, 16),
+    (8119, 28, 59, 13, 10, 32, 16), (10964, 23, 101, 5, 3, 32, 16),
+    (5782, 1101, 117, 1, 1, 16, 12), (11973, 42, 179, 9, 4, 16, 12), (7339, 1071, 599, 1, 1, 16, 12), (3612, 781, 76, 15, 11, 16, 12),
+    (3533, 65, 169, 16, 15, 16, 12), (11768, 1521, 142, 15, 10, 16, 12), (7936, 523, 239, 7, 3, 8, 4), (7100, 18, 600, 14, 3, 8, 4),
+    (8782, 1652, 964, 9, 4, 8, 4), (7045, 1197, 70, 14, 11, 8, 4), (9408, 100, 195, 9, 9, 8, 4), (4681, 689, 436, 15, 15, 8, 4),
+    # ... the sums themselves
+    (1649, 23, 51, 12, 8, 16, 12), (1043, 2813, 438, 7, 5, 16, 12), (1947, 628, 82, 5, 4, 8, 4), (2857, 27, 35, 16, 8, 8, 4),
+    (2310, 25, 276, 16, 8, 8, 4),
     # four tiles per wave
     (4379, 18, 105, 13, 1, 32, 16), (8300, 16, 57, 2, 1, 16, 12), (11051, 19, 81, 13, 5, 8, 4), (752, 2612, 168, 1, 1, 8, 4),
     # one tile, digits from memory
@@ -107,7 +114,7 @@ KERNELS = [
 
 
 def with_sums(R, N):
-    return R * N < 200000
+    return R * N < 700000
 
 
 @pytest.mark.parametrize("layout", [BITS, PAIRS])
@@ -157,6 +164,9 @@ CELLS = [
     (200, 601, 1, 32, 5, 5), (1500, 1500, 64, 8, 5, 5), (1500, 1500, 64, 32, 5, 5),
     # many digit rows
     (575, 39, 219, 32, 2, 1), (487, 31, 514, 32, 3, 1), (92, 18, 695, 32, 15, 15), (1036, 46, 449, 32, 12, 1), (485, 41, 272, 32, 15, 15),
+    (492, 40, 375, 16, 14, 4), (313, 283, 202, 16, 11, 9), (516, 19, 993, 16, 5, 1), (212, 34, 981, 16, 9, 9), (1034, 89, 935, 16, 10, 1),
+    (460, 55, 634, 16, 15, 15), (560, 18, 659, 8, 7, 3), (308, 286, 362, 8, 13, 12), (956, 98, 833, 8, 16, 1), (254, 318, 651, 8, 15, 15),
+    (2087, 57, 863, 8, 1, 1), (608, 20, 837, 8, 16, 15),
     # four tiles per wave
     (1365, 177, 9, 32, 5, 5), (1027, 23, 29, 32, 2, 1), (465, 49, 155, 16, 7, 1), (293, 230, 433, 8, 10, 1),
     # one tile, digits from memory
