@@ -262,7 +262,7 @@ int pb_act_prep(const pb_desc *d, const float *X, int batch, void *workspace, vo
     uint32_t *planes = reinterpret_cast<uint32_t *>(ws + pb::ws_planes_off(L, batch));
     const Issuing issuing(workspace);   // (it writes what a call between its launches may have left there)
     if (pb::takes_digits(L, batch))
-        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta, nullptr,
+        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta, nullptr, true,
                                             static_cast<hipStream_t>(stream)));
     return hip_status(pb::launch_prep(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta,
                                       nullptr, static_cast<hipStream_t>(stream)));
@@ -308,7 +308,7 @@ int pb_fixed_point(const pb_desc *d, const float *X, int batch, int32_t *xq, voi
     uint32_t *planes = reinterpret_cast<uint32_t *>(ws + pb::ws_planes_off(L, batch));
     const Issuing issuing(workspace);   // (it writes what a call between its launches may have left there)
     if (pb::takes_digits(L, batch))
-        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta, xq,
+        return hip_status(pb::launch_digits(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta, xq, true,
                                             static_cast<hipStream_t>(stream)));
     return hip_status(pb::launch_prep(X, d->cols, nullptr, 0, batch, L, d->frac_bits, d->act_bits, planes, meta, xq,
                                       static_cast<hipStream_t>(stream)));

@@ -17,7 +17,8 @@
 // ones, delivers that sum.  |s_d code| <= 2^14, so a sum over all 32768 columns stays below 2^30: int32 is exact.
 // Three of four: a 32-bit x_q in [-2^23, 2^23) is the sum of its lower three bytes with the third one signed as it stands and
 // K = 0x8080.  k_digits leaves the third byte as it stands and notes for four vectors and a chunk of columns whether a value is
-// wider.  Where none is, the top digits are neither read nor multiplied; else the product kernel turns the third digit to u ^ 0x80.
+// wider.  Where none is, the top digits are not read (and not multiplied, in k_i8_tile); else the product kernel turns the third digit
+// to u ^ 0x80.  Where k_i8 with one tile of digit rows follows, all four digits are used and k_digits turns the third.
 //
 // Groups.  A group of bitlayers [f, e) is one code: bitlayer i stands at slot i (counted from bit 7 down) in the first
 // group, which may hold eight, and at slot i - f + 2 in the later ones, which hold up to six (the sign bit and the one
@@ -105,8 +106,8 @@ __device__ __forceinline__ void convert_columns(const ActSource &s, u32x4 (&v)[4
 }
 
 // Sixteen fixed-point values, v[b][r] = column 8 b + r, -> their byte digits: word r of out[d] holds digit d of the columns r,
-// 8 + r, 16 + r, 24 + r, the order in which weight_codes() leaves the codes of 32 columns.  PLAIN2: digit 2 of four as it stands.
-template <int ND, bool PLAIN2 = false>
+// 8 + r, 16 + r, 24 + r, the order in which weight_codes() leaves the codes of 32 columns. 
+template <int ND>
 __device__ __forceinline__ void byte_digits(const u32x4 (&v)[4], u32x4 (&out)[ND])
 {
 #pragma unroll
@@ -124,7 +125,7 @@ __device__ __forceinline__ void byte_digits(const u32x4 (&v)[4], u32x4 (&out)[ND
                 out[1][r] ^= 0x80808080u;
                 const uint32_t c = __builtin_amdgcn_perm(v[1][r], v[0][r], 0x07030602u);
                 const uint32_t d = __builtin_amdgcn_perm(v[3][r], v[2][r], 0x07030602u);
-                out[2][r] = __builtin_amdgcn_perm(d, c, 0x05040100u) ^ (PLAIN2 ? 0u : 0x80808080u);
+                out[2][r] = __builtin_amdgcn_perm(d, c, 0x05040100u) ^ 0x80808080u;
                 out[3][r] = __builtin_amdgcn_perm(d, c, 0x07060302u);
             }
         }

@@ -10,9 +10,10 @@ namespace pb {
 // The activations as byte digits in memory, for the calls that read them more than once (pb_imma.h has the order).
 // A workgroup does one chunk of four vectors, each of its two waves the words t, t + 1 (mod 4).  The lanes are in the order in which the
 // digits lie in memory: the order of the activations, two lanes to a word, took 0.2 us longer (56 vectors, 1402 columns).
+// `turn`: what makes u of the third byte's u ^ 0x80.
 template <int ND>
 __global__ __launch_bounds__(128) void k_digits(ActSource s, int cq, uint8_t *__restrict__ digits, uint8_t *__restrict__ wide,
-                                                int32_t *__restrict__ xq_out)
+                                                int32_t *__restrict__ xq_out, const uint32_t turn)
 {
     __shared__ int s_wide[2];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -32,7 +33,8 @@ __global__ __launch_bounds__(128) void k_digits(ActSource s, int cq, uint8_t *__
                 if (c + 8 * b + r < cols) xq_out[(size_t)n * cols + c + 8 * b + r] = (int32_t)v[b][r];
     }
     u32x4 out[ND];
-    byte_digits<ND, true>(v, out);
+    byte_digits<ND>(v, out);
+    if constexpr (ND == 4) out[2] ^= turn;
     if (vec < vectors) {
         uint8_t *dst = digits + (size_t)(q * 8 + th) * digits_step(vectors, ND);
 #pragma unroll
@@ -75,7 +77,7 @@ __host__ __device__ inline int stage_operand(int rows) { return rows * 64 + 16; 
 // the pairs layout (565 x 14030, two bitlayers 5.6 -> 7.9; 4096 x 4096, 8 bitlayers 5.7 -> 5.1).  2148 drawn calls of several vectors
 // are 1.7 times as fast on average, 51 of them slower by more than 1.5 %.
 
-template <int ND, int Q, bool IL, int TM, bool FUSED, int EPI, int POLICY>
+template <int ND, int Q, bool IL, int TM, bool FUSED, int EPI, int POLICY, bool PLAIN>
 // (the waves per SIMD: one tile, digits from memory, has four at most where a row has sixteen slices, and the registers that this leaves
 // let the compiler request the digits earlier: 67 x 4604, 7 vectors of 16 bits 6.4 -> 5.8 us, 913 x 8013, 15 vectors 7.1 -> 6.7)
 __global__ __launch_bounds__(stream_waves(TM) * 64)
@@ -86,6 +88,10 @@ __attribute__((amdgpu_waves_per_eu(stream_waves(TM) / 4, !FUSED && TM == 1 ? 4 :
     // four tiles of four digits: tile d is digit d of sixteen vectors.  Else the rows of a tile are, from memory, a digit of four vectors
     // after the other (four lanes next to each other read 64 bytes in one piece: otherwise a load takes several times as long), and
     // as staged a digit of one vector after the other.
+    // The digits of one tile are side by side in a register, and the third of four is turned to u ^ 0x80 when they are made: with flags to wait
+    // for and a XOR in the loop, as in PLANES, it was slower than with four digits of every value (977 x 10807, 6 bitlayers, 3 vectors
+    // 8.4 -> 9.1 us, now 8.1; 870 x 9440, 21 vectors 13.2 -> 13.5, now 12.5).  PLAIN: pb_act_prep, which does not know the kernel, leaves
+    // the third digit as it stands, and these few calls pay for that (two products of 977 x 10807, 3 vectors: 14.6 -> 15.5 us).
     constexpr bool PLANES = !FUSED && TM == 4 && ND == 4;
     constexpr bool ONES = ND > 1;
     __shared__ int s_sum[2][TM * 4][64];
@@ -165,7 +171,7 @@ __attribute__((amdgpu_waves_per_eu(stream_waves(TM) / 4, !FUSED && TM == 1 ? 4 :
         scn = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + 4, 0, 0));
     }
     uint32_t wide_here = 0;
-    if constexpr (ND == 4 && !FUSED) wide_here = load_wide<TM * VPT / 4>(a, n0 / 4, lane);
+    if constexpr (PLANES || PLAIN) wide_here = load_wide<TM * VPT / 4>(a, n0 / 4, lane);
     Unit ld = {0, 0, group_end(0), 0};
     request_group(ld);
 
@@ -221,17 +227,17 @@ __attribute__((amdgpu_waves_per_eu(stream_waves(TM) / 4, !FUSED && TM == 1 ? 4 :
 
     // prepared digits: lane 16 kb + row of an operand reads the bytes of digit row % ND of vector row / ND
     // (a top digit that no value needs has no records: the load returns 0 and moves no data)
-    const bool wide = ND != 4 || FUSED || is_wide(wide_here);
+    const bool wide = !(PLANES || PLAIN) || is_wide(wide_here);
     const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.digits), 0,
                                                                         (int)a.digits_bytes, 0x00020000);
-    uint32_t doff[TM], dstep[TM], turned[TM];
+    uint32_t doff[TM], dstep[TM];
+    const uint32_t turned = wide && (PLANES || j / 4 == 2) ? 0x80808080u : 0u;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
         const int first = PLANES ? n0 : n0 + tm * VPT, group = first / kGroupVectors, vectors = group_vectors(a.act.batch, group);
         const int v = first % kGroupVectors + (PLANES ? j : j / (4 * ND) * 4 + j % 4), digit = PLANES ? tm : j / 4 % ND;
         doff[tm] = v < vectors && (wide || digit < 3) ? digits_at(group, vectors, a.cq, ND, digit, kb, v) : (uint32_t)kNowhere;
         dstep[tm] = digits_step(vectors, ND);
-        turned[tm] = ND == 4 && !FUSED && wide && digit == 2 ? 0x80808080u : 0u;
     }
     // staged digits (rows beyond the staged ones belong to no vector: any digits do)
     const int staged = kb * kbytes + min(j, a.stage_rows - 1) * 16;
@@ -289,11 +295,7 @@ __attribute__((amdgpu_waves_per_eu(stream_waves(TM) / 4, !FUSED && TM == 1 ? 4 :
                         if (t < 3 || h == 0) load_digits(areg[h ^ 1], u.i, t * 2 + h + 1);
                         else load_digits(areg[0], ld.i, 0);
                         if constexpr (ONES) ones = __builtin_amdgcn_mfma_i32_16x16x64_i8(one, b[h], ones, 0, 0, 0);
-                        if constexpr (ND == 4 && !FUSED) {
-#pragma unroll
-                            for (int tm = 0; tm < TM; ++tm)
-                                if (!PLANES || tm == 2) areg[h][tm] ^= turned[tm];   // (a branch here costs more: 16 -> 20 us)
-                        }
+                        if constexpr (PLANES || PLAIN) areg[h][PLANES ? 2 : 0] ^= turned;   // (a branch here costs more: 16 -> 20 us)
 #pragma unroll
                         for (int tm = 0; tm < TM; ++tm)
                             acc[tm] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, areg[h][tm]), b[h],
@@ -371,34 +373,36 @@ static ActSource act_source(const float *X0, int cols0, const float *X1, int col
 }
 
 int launch_digits(const float *X0, int cols0, const float *X1, int cols1, int batch, const Layout &L, int frac_bits,
-                  int act_bits, void *digits, void *wide, int32_t *xq_out, hipStream_t st)
+                  int act_bits, void *digits, void *wide, int32_t *xq_out, bool plain, hipStream_t st)
 {
     const ActSource s = act_source(X0, cols0, X1, cols1, batch, frac_bits, act_bits);
     const dim3 grid((unsigned)L.cq, (unsigned)((batch + 3) / 4));
+    const uint32_t turn = plain ? 0x80808080u : 0u;
     uint8_t *d = static_cast<uint8_t *>(digits), *w = static_cast<uint8_t *>(wide);
     switch (digits_of(act_bits)) {
-        case 1: hipLaunchKernelGGL(k_digits<1>, grid, dim3(128), 0, st, s, L.cq, d, w, xq_out); break;
-        case 2: hipLaunchKernelGGL(k_digits<2>, grid, dim3(128), 0, st, s, L.cq, d, w, xq_out); break;
-        default: hipLaunchKernelGGL(k_digits<4>, grid, dim3(128), 0, st, s, L.cq, d, w, xq_out); break;
+        case 1: hipLaunchKernelGGL(k_digits<1>, grid, dim3(128), 0, st, s, L.cq, d, w, xq_out, turn); break;
+        case 2: hipLaunchKernelGGL(k_digits<2>, grid, dim3(128), 0, st, s, L.cq, d, w, xq_out, turn); break;
+        default: hipLaunchKernelGGL(k_digits<4>, grid, dim3(128), 0, st, s, L.cq, d, w, xq_out, turn); break;
     }
     return (int)hipGetLastError();
 }
 
 // [what follows][digits 1, 2, 4][four or eight slots][bits, pairs][way]: digits from memory, one tile or four; converted in the
-// launch, one tile or two, one tile with non-temporal loads of the weights
+// launch, one tile or two, one tile with non-temporal loads of the weights; one tile from the memory that pb_act_prep filled
 // (the sums themselves are asked for in groups of one or two: four slots)
-enum { kMemory1 = 0, kMemory4 = 1, kFused1 = 2, kFused2 = 3, kFusedNt = 4, kStreams = 5 };
+enum { kMemory1 = 0, kMemory4 = 1, kFused1 = 2, kFused2 = 3, kFusedNt = 4, kPlain1 = 5, kStreams = 6 };
 static bool is_fused(int way) { return way >= kFused1 && way <= kFusedNt; }
 static int way_tiles(int way) { return way == kMemory4 ? 4 : (way == kFused2 ? 2 : 1); }
-template <int ND, int Q, bool IL, int TM, bool FUSED, int EPI, int POLICY = 0>
+template <int ND, int Q, bool IL, int TM, bool FUSED, int EPI, int POLICY = 0, bool PLAIN = false>
 static const void *stream_kernel()
 {
-    if constexpr ((EPI == kSums && Q > 1) || (EPI == kCell && IL) || (POLICY && EPI != kStore)) return nullptr;
-    else return reinterpret_cast<const void *>(k_i8<ND, Q, IL, TM, FUSED, EPI, POLICY>);
+    if constexpr ((EPI == kSums && Q > 1) || (EPI == kCell && IL) || ((POLICY || PLAIN) && EPI != kStore) || (PLAIN && ND != 4)) return nullptr;
+    else return reinterpret_cast<const void *>(k_i8<ND, Q, IL, TM, FUSED, EPI, POLICY, PLAIN>);
 }
 #define PB_I8_IL(ND, Q, IL, E)                                                                                     \
     {stream_kernel<ND, Q, IL, 1, false, E>(), stream_kernel<ND, Q, IL, 4, false, E>(),                              \
-     stream_kernel<ND, Q, IL, 1, true, E>(), stream_kernel<ND, Q, IL, 2, true, E>(), stream_kernel<ND, Q, IL, 1, true, E, 2>()}
+     stream_kernel<ND, Q, IL, 1, true, E>(), stream_kernel<ND, Q, IL, 2, true, E>(), stream_kernel<ND, Q, IL, 1, true, E, 2>(), \
+     stream_kernel<ND, Q, IL, 1, false, E, 0, true>()}
 #define PB_I8_ND(ND, E) {{PB_I8_IL(ND, 1, false, E), PB_I8_IL(ND, 1, true, E)}, {PB_I8_IL(ND, 2, false, E), PB_I8_IL(ND, 2, true, E)}}
 #define PB_I8(E) {PB_I8_ND(1, E), PB_I8_ND(2, E), PB_I8_ND(4, E)}
 static const void *const kI8[3][3][2][2][kStreams] = {PB_I8(kStore), PB_I8(kCell), PB_I8(kSums)};
@@ -560,9 +564,10 @@ int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, in
     if (no_device != hipSuccess) return (int)no_device;
     int way = pick_way(c, prepared, cus);
     if (way == kFusedNt && (A || ep.c_prev)) way = kFused1;
+    if (way == kMemory1 && prepared && nd == 4) way = kPlain1;   // (what pb_act_prep leaves)
     const int shape = way - kStreams;
     if (!prepared && !is_fused(way)) {
-        const int e = launch_digits(X0, cols0, X1, cols1, batch, L, frac_bits, act_bits, digits, wide, nullptr, st);
+        const int e = launch_digits(X0, cols0, X1, cols1, batch, L, frac_bits, act_bits, digits, wide, nullptr, way != kMemory1, st);
         if (e) return e;
     }
     if (shape >= 0) return launch_imma_tile(shape, a, nd, il, st);

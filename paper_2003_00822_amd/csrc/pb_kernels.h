@@ -41,14 +41,15 @@ int launch_mfma(const uint32_t *packed, const float *scales, const Layout &L, in
 // pb_imma.hip: the same product as whole weight codes times the bytes of x_q on the 8-bit integer matrix cores, for
 // batches and for PB_LAYOUT_TILE16_PAIRS_V1.  `digits` is the workspace's room for the activations' byte digits (4 bytes per
 // padded column and vector at most) and `wide` a byte per four vectors (64 apart) and 512 columns, both written by
-// launch_digits: before the call (`prepared`) or, where the product kernel does not convert the activations itself, by the call.
+// launch_digits: before the call (`prepared`, with the third of four digits left `plain`) or, where the product kernel does not convert
+// the activations itself, by the call.
 // (`pairs_out`: the sums of bitlayer pairs are asked for)
 inline bool takes_digits(const Layout &L, int batch, bool pairs_out = false)
 {
     return is_tile16(L.layout) && (batch > 1 || is_pairs(L.layout) || pairs_out);
 }
 int launch_digits(const float *X0, int cols0, const float *X1, int cols1, int batch, const Layout &L, int frac_bits,
-                  int act_bits, void *digits, void *wide, int32_t *xq_out, hipStream_t st);
+                  int act_bits, void *digits, void *wide, int32_t *xq_out, bool plain, hipStream_t st);
 int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, int bits_used, int frac_bits, int act_bits,
                 const float *X0, int cols0, const float *X1, int cols1, void *digits, void *wide, bool prepared, int batch,
                 float *Y, long long *A, bool pairs_out, const Epilogue &ep, hipStream_t st);

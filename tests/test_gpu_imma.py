@@ -125,37 +125,91 @@ def test_every_way(pb, case, layout):
     check(pb, R, C, N, bits, m, act_bits, frac_bits, layout, sums=with_sums(R, N))
 
 
-# The kernels that read the digits from memory: rows, columns, vectors, bits, used
+# Rows, columns, vectors, bits, used: between them the calls of more than 16 vectors take every kernel that reads 32-bit digits from memory
+# and stores Y or the sums (test_launches.py works that out)
 DIGITS = [(2669, 520, 187, 2, 1), (2207, 515, 67, 10, 8), (2207, 515, 70, 8, 8), (2620, 2697, 113, 8, 8), (6326, 1189, 388, 8, 8),
-          (4643, 3250, 491, 1, 1), (4379, 18, 105, 13, 1), (752, 2612, 35, 3, 3), (5782, 16, 34, 11, 9), (100, 9000, 12, 3, 3)]
+          (4643, 3250, 491, 1, 1), (4379, 18, 105, 13, 1), (752, 2612, 35, 3, 3), (5782, 16, 34, 11, 9), (100, 9000, 12, 3, 3),
+          # one tile; four; many digit rows; the sums
+          (1177, 1605, 50, 4, 2), (1684, 1581, 33, 8, 5), (2213, 1171, 96, 8, 1), (3595, 1146, 40, 7, 7), (4964, 1119, 161, 1, 1),
+          (8087, 1125, 120, 7, 5), (964, 1573, 36, 5, 2), (1070, 1620, 62, 5, 2), (1720, 1128, 48, 8, 3), (2722, 1163, 51, 10, 4),
+          (2071, 1147, 83, 13, 8)]
+
+
+def widen(X, columns):
+    """Every vector at both ends of three byte digits; of the groups of sixteen vectors the first (and every fourth) keeps to them, the others
+    have one value beyond, in the first, the middle and the last of `columns` in turn."""
+    N = len(X)
+    first, middle, last = columns
+    for group in range((N + 15) // 16):
+        rows = range(16 * group, min(N, 16 * group + 16))
+        X[rows[0], first], X[rows[-1], last] = (2 ** 23 - 1) / 65536, -128.0
+        kind = 0 if group % 4 == 0 else 1 + (group + N) % 3
+        if kind == 1: X[rows[-1], first] = 128.0
+        if kind == 2: X[rows[0], middle] = -(2 ** 23 + 1) / 65536
+        if kind == 3: X[rows[len(rows) // 2], last] = 3e38
 
 
 @pytest.mark.parametrize("layout", [BITS, PAIRS])
 @pytest.mark.parametrize("case", DIGITS, ids=lambda c: "x".join(map(str, c[:3])) + "-%d/%d" % (c[4], c[3]))
 def test_three_digits_or_four(pb, case, layout):
-    """Groups of sixteen vectors at both ends of three byte digits, and with one value just beyond in the first, in a middle and
-    in the last chunk: each group is multiplied with the digits that it needs."""
+    """Each group of sixteen vectors is multiplied with the digits that it needs; the sums of bitlayers and of pairs beside Y."""
     R, C, N, bits, m = case
     print("digits", case, hex(layout), flush=True)
     g = np.random.default_rng(200300822 + 67)
     W = g.normal(0, 0.02, size=(R, C)).astype(np.float32)
     X = g.normal(size=(N, C)).astype(np.float32)
-    for group in range((N + 15) // 16):
-        rows = range(16 * group, min(N, 16 * group + 16))
-        X[rows[0], 0], X[rows[-1], C - 1] = (2 ** 23 - 1) / 65536, -128.0
-        if group % 4 == 1: X[rows[-1], 0] = 128.0
-        if group % 4 == 2: X[rows[0], C // 2] = -(2 ** 23 + 1) / 65536
-        if group % 4 == 3: X[rows[len(rows) // 2], C - 1] = 3e38
+    widen(X, (0, C // 2, C - 1))
     sample = sorted({0, 1, R // 2, (R - 1) // 16 * 16, R - 1})
     prep = po.prepare(W[sample + [int(np.abs(W).max(axis=1).argmax())]], bits)
     lin = pb.PackedLinear(dev(W), bits, max_batch=N, layout=layout)
     Y = lin(dev(X), m).cpu().numpy()
     A = lin.acc(dev(X), m).cpu().numpy() if with_sums(R, N) else None
+    P = lin.acc_pairs(dev(X), m).cpu().numpy() if with_sums(R, N) else None
     xq = po.fixed_point(X, frac_bits=16, act_bits=32)
     for k, r in enumerate(sample):
         sub = po.layer_products_direct(prep["layers"][:, k:k + 1, :], m, xq)[:, :, 0]
         assert_y_close(Y[:, r], po.dequant(sub, prep["scales"], m, frac_bits=16), sub, prep["scales"], frac_bits=16)
-        if A is not None: assert (A[:, :, r] == sub).all(), r
+        if A is not None:
+            assert (A[:, :, r] == sub).all(), r
+            assert (P[:, :, r] == pair_sums(sub[:, :, None], m)[:, :, 0]).all(), r
+
+
+# Rows, columns, vectors, bits, used, activation bits of the two-part calls.  The kernels with one tile of 32-bit digits are compiled for the
+# digits that pb_act_prep leaves: these take each of them.
+PREPARED = [(30, 21, 19, 8, 1, 32), (19, 17, 24, 6, 5, 32), (114, 1387, 37, 2, 1, 32), (666, 1345, 33, 10, 5, 32), (151, 9063, 13, 8, 8, 32),
+            (1231, 1155, 66, 5, 1, 32), (2437, 1135, 393, 1, 1, 32), (700, 1500, 21, 6, 6, 16), (700, 1500, 21, 6, 6, 8)]
+
+
+@pytest.mark.parametrize("layout", [BITS, PAIRS])
+@pytest.mark.parametrize("case", PREPARED, ids=lambda c: "x".join(map(str, c[:3])) + "-%d/%d-a%d" % (c[4], c[3], c[5]))
+def test_prepared_digits(pb, case, layout):
+    """pb_act_prep and pb_matmul_prepared give what pb_matmul gives, whichever kernel reads the digits, and leave them as they are: two
+    matrices on the activations of one preparation."""
+    R, C, N, bits, m, act_bits = case
+    print("prepared", case, hex(layout), flush=True)
+    g = np.random.default_rng(200300822 + 71)
+    X = g.normal(size=(N, C)).astype(np.float32)
+    if act_bits == 32: widen(X, (0, C // 2, C - 1))
+    frac_bits = {32: 16, 16: 12, 8: 4}[act_bits]
+    xq = po.fixed_point(X, frac_bits=frac_bits, act_bits=act_bits)
+    Xd, first = dev(X), None
+    for rows in (R, 2 * R + 5):
+        W = g.normal(0, 0.02, size=(rows, C)).astype(np.float32)
+        lin = pb.PackedLinear(dev(W), bits, max_batch=N, act_bits=act_bits, frac_bits=frac_bits, layout=layout)
+        if first is None:
+            first = lin
+            pb.pb_act_prep(lin.desc, Xd, N, lin.workspace)
+        Y = torch.empty((N, rows), device="cuda")
+        pb.pb_matmul_prepared(lin.packed, lin.scales, lin.desc, m, N, Y, first.workspace)
+        own = torch.empty_like(lin.workspace)
+        want = torch.empty_like(Y)
+        pb.pb_matmul(lin.packed, lin.scales, lin.desc, m, Xd, N, want, own)
+        assert torch.equal(Y, want)
+        sample = sorted({0, 1, rows // 2, rows - 1})
+        prep = po.prepare(W[sample + [int(np.abs(W).max(axis=1).argmax())]], bits)
+        for k, r in enumerate(sample):
+            sub = po.layer_products_direct(prep["layers"][:, k:k + 1, :], m, xq)[:, :, 0]
+            assert_y_close(Y.cpu().numpy()[:, r], po.dequant(sub, prep["scales"], m, frac_bits=frac_bits), sub, prep["scales"], frac_bits=frac_bits)
 
 
 # hidden units, inputs, vectors, activation bits, bits, used; from the second line on: each compiled kernel with the cell update
@@ -177,17 +231,27 @@ CELLS = [
     (518, 20, 17, 8, 4, 1),
     # one tile, converted in the launch
     (16, 16, 2, 32, 8, 1), (16, 17, 2, 16, 15, 5), (16, 16, 2, 16, 13, 1), (16, 17, 2, 8, 9, 1),
+    # 32-bit digits from memory, several groups of vectors and chunks of columns: one tile, four, many digit rows
+    (342, 1593, 41, 32, 4, 1), (546, 635, 33, 32, 6, 5), (525, 1329, 47, 32, 13, 1), (458, 708, 69, 32, 11, 5), (531, 1008, 113, 32, 4, 1),
+    (784, 338, 253, 32, 4, 1), (191, 1553, 53, 32, 15, 15), (140, 1016, 295, 32, 15, 15),
 ]
 
 
 @pytest.mark.parametrize("H,I,N,act_bits,bits,m", CELLS)
 def test_lstm_cell_of_a_batch(pb, H, I, N, act_bits, bits, m):
     """The cell update at the end of every kernel, the second part of the input also at odd columns, in the chunk where it
-    begins and in the chunks behind (2e-6: the bound of the other cell tests)."""
+    begins and in the chunks behind (2e-6: the bound of the other cell tests).  With 32 bits most groups of sixteen vectors have a value
+    beyond three byte digits, in a column of x or of h whose weights are small, so that few gates saturate."""
     g = np.random.default_rng(200300822 + 61)
     frac_bits = {32: 16, 16: 12, 8: 4}[act_bits]
     W = g.uniform(-0.04, 0.04, size=(4 * H, I + H)).astype(np.float32)
     x, h, c = (g.normal(size=(N, n)).astype(np.float32) for n in (I, H, H))
+    if act_bits == 32:
+        wide = (0, I + H // 2, I + H - 1)
+        W[:, wide] *= 0.1
+        xh = np.concatenate([x, h], axis=1)
+        widen(xh, wide)
+        x, h = np.ascontiguousarray(xh[:, :I]), np.ascontiguousarray(xh[:, I:])
     bias = g.normal(0, 0.1, size=4 * H).astype(np.float32)
     prep = po.prepare(W, bits)
     _, Y = po.matmul_words(po.pack_words(prep["layers"]), prep["scales"], m, I + H, np.concatenate([x, h], axis=1),

@@ -2,6 +2,7 @@
 writes launches down (mock_hip.cpp), in a process of its own."""
 import json
 import os
+import re
 import subprocess
 import sys
 import textwrap
@@ -112,10 +113,12 @@ def test_calls_on_one_workspace_do_not_mix_their_launches(probe):
 def test_the_gpu_tests_reach_every_kernel_for_batches(probe):
     """Every compiled kernel for batches is taken by a case that the GPU tests compare with the oracle: the choice of the kernel
     is fitted, and a change to it must not leave one untested (or unreachable) unnoticed."""
-    from tests.test_gpu_imma import CASES, CELLS, KERNELS, with_sums
+    from tests.test_gpu_imma import CASES, CELLS, DIGITS, KERNELS, PREPARED, with_sums
     products = [c[:6] + (with_sums(c[0], c[2]),) for c in CASES + KERNELS]
-    reached, compiled = probe("""
-        products, cells = json.loads(sys.argv[3])
+    digits = [c + (32, with_sums(c[0], c[2])) for c in DIGITS if c[2] > 16]
+    wide_cells = [c for c in CELLS if c[3] == 32 and c[2] > 16]
+    code = """
+        products, cells, prepared = json.loads(sys.argv[3])
         reached, ref = set(), ctypes.byref
         def took():
             got = {k for k, _ in launches()}
@@ -134,11 +137,21 @@ def test_the_gpu_tests_reach_every_kernel_for_batches(probe):
             assert L.pb_lstm_cell(F, F, ref(d), m, F, I, ctypes.c_void_p(0x50000000), F, None, ctypes.c_void_p(0x60000000), F, N,
                                   WORK, None) == 0
             took()
+        for R, C, N, bits, m, act in prepared:
+            for layout in (BITS, PAIRS):
+                assert L.pb_matmul_prepared(F, F, ref(desc(R, C, bits, layout, act)), m, N, F, WORK, None) == 0
+                took()
         compiled = [mock.mock_kernel(i).decode() for i in range(mock.mock_kernels())]
         print(json.dumps([sorted(reached), [k for k in compiled if "k_i8" in k or "k_digits" in k]]))
-    """, json.dumps([products, CELLS]))
+    """
+    reached, compiled = probe(code, json.dumps([products, CELLS, PREPARED]))
     assert len(compiled) > 100
     assert not sorted(set(compiled) - set(reached))
+    # 32-bit digits from memory: three of four and all of them, which a call of more than one group of sixteen vectors compares there
+    reached, _ = probe(code, json.dumps([digits, wide_cells, PREPARED]))
+    both = [k for k in compiled if re.search(r"k_i8_tileILi4E|k_i8ILi4ELi\dELb\dELi\dELb0E", k)]     # digits 4, digits from memory
+    assert len(both) > 30
+    assert not sorted(set(both) - set(reached))
 
 
 def test_non_temporal_loads_only_where_they_pay(probe):
