@@ -18,7 +18,7 @@
 // Three of four: a 32-bit x_q in [-2^23, 2^23) is the sum of its lower three bytes with the third one signed as it stands and
 // K = 0x8080.  k_digits leaves the third byte as it stands and notes for four vectors and a chunk of columns whether a value is
 // wider.  Where none is, the top digits are not read (and not multiplied, in k_i8_tile); else the product kernel turns the third digit
-// to u ^ 0x80.  Where k_i8 with one tile of digit rows follows, all four digits are used and k_digits turns the third.
+// to u ^ 0x80.  Where k_i8 with one tile of digit rows follows, mostly all four digits are used and k_digits turns the third.
 //
 // Groups.  A group of bitlayers [f, e) is one code: bitlayer i stands at slot i (counted from bit 7 down) in the first
 // group, which may hold eight, and at slot i - f + 2 in the later ones, which hold up to six (the sign bit and the one

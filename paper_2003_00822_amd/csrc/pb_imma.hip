@@ -90,8 +90,8 @@ __attribute__((amdgpu_waves_per_eu(stream_waves(TM) / 4, !FUSED && TM == 1 ? 4 :
     // as staged a digit of one vector after the other.
     // The digits of one tile are side by side in a register, and the third of four is turned to u ^ 0x80 when they are made: with flags to wait
     // for and a XOR in the loop, as in PLANES, it was slower than with four digits of every value (977 x 10807, 6 bitlayers, 3 vectors
-    // 8.4 -> 9.1 us, now 8.1; 870 x 9440, 21 vectors 13.2 -> 13.5, now 12.5).  PLAIN: pb_act_prep, which does not know the kernel, leaves
-    // the third digit as it stands, and these few calls pay for that (two products of 977 x 10807, 3 vectors: 14.6 -> 15.5 us).
+    // 8.4 -> 9.1 us, now 8.1; 870 x 9440, 21 vectors 13.2 -> 13.5, now 12.5).  PLAIN: with them all the same, see launch_imma (pb_act_prep
+    // does not know the kernel: two products of 977 x 10807, 3 vectors 14.6 -> 15.5 us).
     constexpr bool PLANES = !FUSED && TM == 4 && ND == 4;
     constexpr bool ONES = ND > 1;
     __shared__ int s_sum[2][TM * 4][64];
@@ -388,7 +388,7 @@ int launch_digits(const float *X0, int cols0, const float *X1, int cols1, int ba
 }
 
 // [what follows][digits 1, 2, 4][four or eight slots][bits, pairs][way]: digits from memory, one tile or four; converted in the
-// launch, one tile or two, one tile with non-temporal loads of the weights; one tile from the memory that pb_act_prep filled
+// launch, one tile or two, one tile with non-temporal loads of the weights; one tile, digits from memory, the third as it stands
 // (the sums themselves are asked for in groups of one or two: four slots)
 enum { kMemory1 = 0, kMemory4 = 1, kFused1 = 2, kFused2 = 3, kFusedNt = 4, kPlain1 = 5, kStreams = 6 };
 static bool is_fused(int way) { return way >= kFused1 && way <= kFusedNt; }
@@ -564,7 +564,10 @@ int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, in
     if (no_device != hipSuccess) return (int)no_device;
     int way = pick_way(c, prepared, cus);
     if (way == kFusedNt && (A || ep.c_prev)) way = kFused1;
-    if (way == kMemory1 && prepared && nd == 4) way = kPlain1;   // (what pb_act_prep leaves)
+    // Third digits as they stand: what pb_act_prep leaves; and with at most four bitlayers and more than four tiles, whose digits take longer to read
+    // than flags and XOR (1291 x 9493, 4 bitlayers, 17 vectors 11.5 us, all four digits 12.4; 393 x 14185, 2 bitlayers, 29 vectors 9.5, 9.9;
+    // but 16337 x 1799, 4 bitlayers, 3 vectors 6.9, 6.5, and 870 x 9440, 8 bitlayers, 21 vectors 13.5, 12.5).
+    if (way == kMemory1 && nd == 4 && (prepared || (c.tiles > 4 && bits_used <= 4 && !A && !ep.c_prev))) way = kPlain1;
     const int shape = way - kStreams;
     if (!prepared && !is_fused(way)) {
         const int e = launch_digits(X0, cols0, X1, cols1, batch, L, frac_bits, act_bits, digits, wide, nullptr, way != kMemory1, st);

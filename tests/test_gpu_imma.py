@@ -125,25 +125,25 @@ def test_every_way(pb, case, layout):
     check(pb, R, C, N, bits, m, act_bits, frac_bits, layout, sums=with_sums(R, N))
 
 
-# Rows, columns, vectors, bits, used: between them the calls of more than 16 vectors take every kernel that reads 32-bit digits from memory
-# and stores Y or the sums (test_launches.py works that out)
+# Rows, columns, vectors, bits, used: between them these calls take every kernel that reads 32-bit digits from memory and stores Y or the sums, those
+# of more than 16 vectors every one that may leave out a digit (test_launches.py works that out)
 DIGITS = [(2669, 520, 187, 2, 1), (2207, 515, 67, 10, 8), (2207, 515, 70, 8, 8), (2620, 2697, 113, 8, 8), (6326, 1189, 388, 8, 8),
           (4643, 3250, 491, 1, 1), (4379, 18, 105, 13, 1), (752, 2612, 35, 3, 3), (5782, 16, 34, 11, 9), (100, 9000, 12, 3, 3),
           # one tile; four; many digit rows; the sums
-          (1177, 1605, 50, 4, 2), (1684, 1581, 33, 8, 5), (2213, 1171, 96, 8, 1), (3595, 1146, 40, 7, 7), (4964, 1119, 161, 1, 1),
+          (1496, 10977, 5, 4, 4), (16337, 1799, 3, 4, 4), (1177, 1605, 50, 4, 2), (1684, 1581, 33, 8, 5), (2213, 1171, 96, 8, 1), (3595, 1146, 40, 7, 7), (4964, 1119, 161, 1, 1),
           (8087, 1125, 120, 7, 5), (964, 1573, 36, 5, 2), (1070, 1620, 62, 5, 2), (1720, 1128, 48, 8, 3), (2722, 1163, 51, 10, 4),
           (2071, 1147, 83, 13, 8)]
 
 
 def widen(X, columns):
-    """Every vector at both ends of three byte digits; of the groups of sixteen vectors the first (and every fourth) keeps to them, the others
-    have one value beyond, in the first, the middle and the last of `columns` in turn."""
+    """Every vector at both ends of three byte digits; of the groups of sixteen vectors the first (and every fourth) keeps to them, where
+    there are several; the others have one value beyond, in the first, the middle and the last of `columns` in turn."""
     N = len(X)
     first, middle, last = columns
     for group in range((N + 15) // 16):
         rows = range(16 * group, min(N, 16 * group + 16))
         X[rows[0], first], X[rows[-1], last] = (2 ** 23 - 1) / 65536, -128.0
-        kind = 0 if group % 4 == 0 else 1 + (group + N) % 3
+        kind = 0 if group % 4 == 0 and N > 16 else 1 + (group + N) % 3
         if kind == 1: X[rows[-1], first] = 128.0
         if kind == 2: X[rows[0], middle] = -(2 ** 23 + 1) / 65536
         if kind == 3: X[rows[len(rows) // 2], last] = 3e38

@@ -115,8 +115,8 @@ def test_the_gpu_tests_reach_every_kernel_for_batches(probe):
     is fitted, and a change to it must not leave one untested (or unreachable) unnoticed."""
     from tests.test_gpu_imma import CASES, CELLS, DIGITS, KERNELS, PREPARED, with_sums
     products = [c[:6] + (with_sums(c[0], c[2]),) for c in CASES + KERNELS]
-    digits = [c + (32, with_sums(c[0], c[2])) for c in DIGITS if c[2] > 16]
-    wide_cells = [c for c in CELLS if c[3] == 32 and c[2] > 16]
+    digits = [c + (32, with_sums(c[0], c[2])) for c in DIGITS]
+    wide_cells = [c for c in CELLS if c[3] == 32]
     code = """
         products, cells, prepared = json.loads(sys.argv[3])
         reached, ref = set(), ctypes.byref
@@ -147,11 +147,15 @@ def test_the_gpu_tests_reach_every_kernel_for_batches(probe):
     reached, compiled = probe(code, json.dumps([products, CELLS, PREPARED]))
     assert len(compiled) > 100
     assert not sorted(set(compiled) - set(reached))
-    # 32-bit digits from memory: three of four and all of them, which a call of more than one group of sixteen vectors compares there
+    # 32-bit digits from memory: calls with values beyond three digits reach all; where the top digit may be left out (not in one tile with
+    # all four) calls of more than one group of sixteen vectors do, which compare both
+    memory = [k for k in compiled if re.search(r"k_i8_tileILi4E|k_i8ILi4ELi\dELb\dELi\dELb0E", k)]
+    four = [k for k in memory if re.search(r"k_i8ILi4ELi\dELb\dELi1ELb0E.*Lb0EEE", k)]
+    assert len(memory) > 30 and len(four) == 8
     reached, _ = probe(code, json.dumps([digits, wide_cells, PREPARED]))
-    both = [k for k in compiled if re.search(r"k_i8_tileILi4E|k_i8ILi4ELi\dELb\dELi\dELb0E", k)]     # digits 4, digits from memory
-    assert len(both) > 30
-    assert not sorted(set(both) - set(reached))
+    assert not sorted(set(memory) - set(reached))
+    reached, _ = probe(code, json.dumps([[c for c in digits if c[2] > 16], [c for c in wide_cells if c[2] > 16], [c for c in PREPARED if c[2] > 16]]))
+    assert not sorted(set(memory) - set(four) - set(reached))
 
 
 def test_non_temporal_loads_only_where_they_pay(probe):
