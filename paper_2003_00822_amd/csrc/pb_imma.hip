@@ -58,6 +58,12 @@ __global__ __launch_bounds__(128) void k_digits(ActSource s, int cq, uint8_t *__
 // Waves of a workgroup at most: sixteen have 128 registers each, which four tiles of digit rows exceed
 __host__ __device__ constexpr int stream_waves(int tm) { return tm >= 4 ? 8 : 16; }
 
+// LDS of a workgroup beside the staged digits: sums, sums of the codes, sums over the groups, scales
+__host__ __device__ constexpr int stream_lds(int nd, int tm, int epi)
+{
+    return 2 * tm * 4 * 256 + (nd > 1 ? 3 * 256 : 0) + (epi == kSums ? 0 : tm * (4 / nd) * 512) + PB_MAX_BITS * 4;
+}
+
 // Bytes of one staged operand of `rows` digit rows (64 each, and 16 more so that the eight operands that a group of eight
 // lanes writes to start in different banks); a tile of a chunk has eight of them
 __host__ __device__ inline int stage_operand(int rows) { return rows * 64 + 16; }
@@ -99,6 +105,7 @@ __attribute__((amdgpu_waves_per_eu(stream_waves(TM) / 4, !FUSED && TM == 1 ? 4 :
     __shared__ double s_z[TM * VPL][64];
     __shared__ float s_scales[PB_MAX_BITS];
     extern __shared__ __align__(16) unsigned char stage[];
+    static_assert(sizeof s_sum + ONES * sizeof s_ones + (EPI != kSums) * sizeof s_z + sizeof s_scales == stream_lds(ND, TM, EPI), "LDS");
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -410,8 +417,7 @@ static const void *const kI8[3][3][2][2][kStreams] = {PB_I8(kStore), PB_I8(kCell
 // Staged digits of a workgroup at most (a compute unit has 160 KB of LDS)
 constexpr int kMaxStage = 140 * 1024;
 
-// Compute units (at least one, or an error), and workgroups of a kernel that fit on the device at once (0: the query failed);
-// neither changes while the process lives
+// Compute units (at least one, or an error); their number does not change while the process lives
 static hipError_t compute_units(int *cus)
 {
     static int cache;
@@ -425,14 +431,28 @@ static hipError_t compute_units(int *cus)
     __atomic_store_n(&cache, *cus, __ATOMIC_RELAXED);
     return hipSuccess;
 }
-static int resident(const void *fn, int threads, size_t lds, int cus, int *slot)
+// Workgroups of a kernel that a compute unit runs at once (0: the query failed; the answer does not change either).  The query is too high
+// twice (256 n workgroups of a kernel that only computes take twice as long from the n on where one more has to wait):
+//   It divides the waves of the unit by those of the workgroup.  A workgroup of five to eight waves takes two on every SIMD, one of nine to
+//   twelve three: with three places a SIMD one workgroup of five waves runs, not two; with four places two, not three.
+//   LDS is given out by 1280 bytes: eleven workgroups of 13120 bytes run, not twelve.
+// A grid made for more leaves a rest that runs by itself: 12135 x 2547, 8 bitlayers, 13 vectors (five waves) for two per unit 15.7 us, for one
+// 12.5; 10440 x 2457, 6 bitlayers, 55 vectors of 8 bits 16.4, 12.7; 9551 x 2050, 2 bitlayers, 13 vectors of 16 bits for three 9.9, for two 8.8;
+// 1731 x 276, 6 bitlayers, 887 vectors of 16 bits (13120 bytes) 19.0, 15.8.
+constexpr size_t kLds = 160 * 1024, kLdsPiece = 1280;
+static int per_unit(const void *fn, int threads, size_t lds, size_t stage, int *slot)
 {
     int v = __atomic_load_n(slot, __ATOMIC_RELAXED);
     if (v > 0) return v;
-    int per_cu = 0;
-    if (lds && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxStage) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess) return 0;
-    v = cus * per_cu;
+    if (stage && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxStage) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, fn, threads, stage) != hipSuccess) return 0;
+    auto at_most = [&](int n) { v = n < 1 ? 1 : (n < v ? n : v); };
+    if (v > 1 && threads > 256) {
+        int places = 0;     // waves of a SIMD: workgroups of four waves
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&places, fn, 256, stage) != hipSuccess) return 0;
+        at_most(places / ((threads + 255) / 256));
+    }
+    if (v > 1) at_most((int)(kLds / ((lds + stage + kLdsPiece - 1) / kLdsPiece * kLdsPiece)));
     if (v > 0) __atomic_store_n(slot, v, __ATOMIC_RELAXED);
     return v;
 }
@@ -584,15 +604,24 @@ int launch_imma(const uint32_t *packed, const float *scales, const Layout &L, in
     const int S = (L.cq + a.chunks_per_wave - 1) / a.chunks_per_wave;
     const size_t lds = is_fused(way) ? stage_bytes(c, tm) : 0;
     static int cache[3][3][2][2][kStreams][17][24];   // (the last index: LDS in steps of 6 KB)
-    int capacity = resident(fn, S * 64, lds, cus, &cache[epi][ndi][q][il][way][S][lds / 6144]);
-    if (capacity < 1) return (int)hipErrorInvalidValue;
-    if (is_fused(way) && capacity > cus * fused_per_cu(S)) capacity = cus * fused_per_cu(S);
+    int most = per_unit(fn, S * 64, (size_t)stream_lds(nd, tm, epi), lds, &cache[epi][ndi][q][il][way][S][lds / 6144]);
+    if (most < 1) return (int)hipErrorInvalidValue;
+    if (is_fused(way) && most > fused_per_cu(S)) most = fused_per_cu(S);
     const int groups = (c.tiles + tm - 1) / tm;
-    int wgs = capacity / groups;
-    if (wgs < 1) wgs = 1;
-    if (wgs > L.rt_count) wgs = L.rt_count;
-    a.rounds_per_wg = (L.rt_count + wgs - 1) / wgs;
-    wgs = (L.rt_count + a.rounds_per_wg - 1) / a.rounds_per_wg;
+    // Workgroups, and the row tiles of each: as many as run at once.  Of those with more than four waves fewer where the unit that does the most
+    // then has fewer row tiles to do: 9619 x 11869, one bitlayer, 16 vectors (eight waves, pairs layout) two workgroups of two row tiles 33.6 us, one
+    // of three 30.1; 5888 x 3649, 3 bitlayers, 11 vectors of 16 bits 9.0, 8.5.  With as many to do, two at once are faster than one:
+    // 14587 x 2129, 3 bitlayers, 51 vectors of 8 bits (five waves) two of two 12.4, one of four 15.5.
+    int wgs = 1;
+    for (int n = most, least = INT32_MAX; n >= 1; --n) {
+        int w = cus * n / groups;
+        w = w < 1 ? 1 : (w < L.rt_count ? w : L.rt_count);
+        const int rounds = (L.rt_count + w - 1) / w;
+        w = (L.rt_count + rounds - 1) / rounds;
+        const int cost = rounds * (6 + (w * groups + cus - 1) / cus * S);
+        if (cost < least) { least = cost; wgs = w; a.rounds_per_wg = rounds; }
+        if (S <= 4 || is_fused(way)) break;
+    }
     void *args[] = {&a};
     const hipError_t e = hipLaunchKernel(fn, dim3((unsigned)wgs, (unsigned)groups), dim3((unsigned)S * 64), args, lds, st);
     return (int)(e != hipSuccess ? e : hipGetLastError());

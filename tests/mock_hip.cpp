@@ -26,6 +26,7 @@ std::map<const void *, std::string> &names()
 }
 std::vector<Launch> g_launches;
 int g_pause = 0;
+int g_places = 0;      // waves that fit a SIMD; 0: one workgroup a compute unit
 thread_local int t_caller = 0;
 thread_local std::vector<Config> t_configs;
 
@@ -65,10 +66,15 @@ int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }   // (only t
 int hipFuncSetAttribute(const void *, int, int) { return 0; }
 int hipGetLastError() { return 0; }
 int hipGetSymbolAddress(void **p, const void *) { *p = reinterpret_cast<void *>(0x100000); return 0; }
-int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = 1; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int threads, size_t)
+{
+    *n = g_places ? g_places * 4 / ((threads + 63) / 64) : 1;
+    return 0;
+}
 
 void mock_pause(int ms) { g_pause = ms; }
 void mock_caller(int id) { t_caller = id; }
+void mock_places(int n) { g_places = n; }
 int mock_launches() { std::lock_guard<std::mutex> lock(g_mutex); return (int)g_launches.size(); }
 const char *mock_launch(int i, int *out)   // out: grid x, y, block, LDS, caller
 {

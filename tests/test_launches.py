@@ -169,3 +169,25 @@ def test_non_temporal_loads_only_where_they_pay(probe):
     """)
     assert all(len(t) == 1 and "k_i8I" in t[0] for t in took)
     assert [t[0].split("Li")[-1].startswith("2") for t in took] == [False, False, False, True, True, False, False]
+
+
+@pytest.mark.parametrize("places,rows,cols,batch,act_bits,bits,layout,want", [
+    (3, 12135, 2547, 13, 32, 8, "BITS", 253),      # five waves, two on one SIMD: one workgroup a unit, three row tiles each (380 of two)
+    (4, 9551, 2050, 13, 16, 2, "BITS", 199),       # ... two a unit, three row tiles each (299 of two)
+    (3, 9000, 9000, 12, 32, 5, "BITS", 188),       # six waves: one
+    (3, 1731, 276, 887, 16, 6, "PAIRS", 55),       # one wave, 13120 bytes of LDS in pieces of 1280: eleven a unit
+    (4, 9619, 11869, 16, 32, 1, "PAIRS", 201),     # eight waves, two a unit: one with three row tiles is done sooner than two with two
+    (4, 14587, 2129, 51, 8, 3, "PAIRS", 456),      # five waves, two a unit with two row tiles each: as many as one with four
+])
+def test_a_grid_that_runs_at_once(probe, places, rows, cols, batch, act_bits, bits, layout, want):
+    """The workgroups along the rows are no more than the compute units run at once: a rest would run by itself."""
+    got = probe("""
+        places, rows, cols, batch, act, bits, layout = json.loads(sys.argv[3])
+        mock.mock_places(places)
+        assert L.pb_matmul(F, F, ctypes.byref(desc(rows, cols, bits, globals()[layout], act)), bits, F, batch, F, WORK, None) == 0
+        out = (ctypes.c_int * 5)()
+        name = mock.mock_launch(mock.mock_launches() - 1, out).decode()
+        print(json.dumps([name, out[0]]))
+    """, json.dumps([places, rows, cols, batch, act_bits, bits, layout]))
+    assert re.search(r"k_i8ILi\dELi\dELb\dELi\dELb0E", got[0]), got     # digits from memory
+    assert got[1] == want, got
