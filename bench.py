@@ -393,7 +393,7 @@ def same_gpu_references(torch, dev, W, X, per_m):
 
 def mfma_calibration(torch, pb, dev):
     """The rate of the product kernel's FP4 matrix instruction on this GPU (the calibration loop of `paper_2003_00822_amd/csrc/calib`, a
-    library of its own beside the product: constant operands, two waves per SIMD on every compute unit): alone, with the expansion of one packed weight word per four
+    library of its own beside the product: constant operands, two waves per SIMD on every compute unit): alone, with the expansion of two packed weight words per eight
     instructions, and with the kernel's epilogue per chain of four.  On a SIMD the matrix and the vector-ALU
     instructions take turns, so the third figure is the ceiling of the batched regime with this much ALU work."""
     from paper_2003_00822_amd import calib
@@ -546,21 +546,21 @@ def size_sweep(torch, pb, dev, layout):
 
 
 def matrix_rate(size, m, N, t, fp4=False):
-    """What the matrix instructions of a call with m bitlayers come to: 16 digit rows per vector and bitlayer in FP4, or 3 byte
-    digits per vector for up to eight bitlayers together: what values within 128 need (16 fractional bits; the kernels that convert a
-    few vectors in their launch multiply a fourth, which is not counted)."""
-    issued = 2.0 * (16 * m if fp4 else 3) * size * size * N / t / 1e12
+    """What the matrix products of a call with m bitlayers come to.  FP4: 16 digit rows per vector and bitlayer, all issued.  Integers: the 3 byte
+    digits per vector that values within 128 need (16 fractional bits), for up to eight bitlayers together; the kernels for few vectors issue
+    a fourth, which counts as nothing here."""
+    ops = 2.0 * (16 * m if fp4 else 3) * size * size * N / t / 1e12
     if fp4:
-        return {"mfma_issued_TFLOPs": round(issued, 1), "mfma_frac": round(issued / FP4_PEAK_TFLOPS, 4)}
-    return {"mfma_issued_TOPs": round(issued, 1), "mfma_frac": round(issued / I8_PEAK_TOPS, 4)}
+        return {"mfma_issued_TFLOPs": round(ops, 1), "mfma_frac": round(ops / FP4_PEAK_TFLOPS, 4)}
+    return {"mfma_needed_TOPs": round(ops, 1), "mfma_needed_frac": round(ops / I8_PEAK_TOPS, 4)}
 
 
 def batch_sweep(torch, pb, synth, dev):
     """Large FC layer (8192 x 8192, B = 8, bits_used = 8) at batch 1 .. 1024: the regime where the product is a
     dense contraction.  Both kernels, weights warm (the 64 MiB stay in the last-level cache between the passes
     of one call anyway).  Nominal work = rows * cols * bits_used * 32 planes * batch 1-bit multiply-accumulates.
-    Matrix-core rows: the products issued (batch 1 on the default layout: FP4 digits, else whole weight codes times the
-    three bytes that an activation needs) against the peak of that type.  Popcount rows: the vector-ALU lane
+    Matrix-core rows: the products (batch 1 on the default layout: FP4 digits as issued, else whole weight codes times the
+    three bytes that an activation needs, see matrix_rate) against the peak of that type.  Popcount rows: the vector-ALU lane
     operations the kernel executes (one AND + one popcount-accumulate per 32-bit weight word and ACTIVE plane: planes
     that are empty or copies of the sign plane are skipped, the count comes from the plane statistics the activation
     kernel leaves in the workspace) against the integer vector-ALU peak.  Narrower activations (Section 3.1, Table 1)
