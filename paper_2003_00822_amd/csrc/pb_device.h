@@ -7,10 +7,11 @@ namespace pb {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Cycles that an instruction of the vector ALU takes where two waves or more of a SIMD issue them (measured): 2.5 to 3 for V_AND_B32,
-// V_OR_B32, V_XOR_B32, V_MOV_B32, V_ADD_U32, V_BITOP3_B32 and V_FMA_F32 with every operand in a vector register; 4.3 to 4.7 for those with a
-// constant or a scalar operand, and for V_BFI_B32, V_PERM_B32, V_AND_OR_B32, V_LSHL_OR_B32 and the shifts, those of 64 bits included:
-// two registers next to each other are shifted for the price of one, where what crosses from one to the other is masked away.
+// Cycles that an instruction of the vector ALU takes where two waves or more of a SIMD issue them (profiles/vector_alu_issue.txt): 2.4 to 2.6 for
+// V_AND_B32, V_OR_B32, V_XOR_B32, V_MOV_B32, V_ADD_U32 and V_LSHRREV_B32 of vector registers, 2.5 to 4 for V_BITOP3_B32 and V_FMA_F32, by the
+// registers that they read; 4.2 to 4.5 with a scalar register, and for V_BFI_B32, V_PERM_B32, V_AND_OR_B32, V_LSHL_OR_B32, V_LSHLREV_B32 and the
+// shifts of 64 bits: two registers next to each other are shifted up for the price of one, where what crosses from one to the other is
+// masked away.
 __device__ __forceinline__ uint32_t in_vgpr(uint32_t v)
 {
     uint32_t r;

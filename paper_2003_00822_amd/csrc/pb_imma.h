@@ -152,7 +152,7 @@ __device__ __forceinline__ uint64_t mix(uint32_t mask, uint64_t a, uint64_t b)
 }
 
 // Two words by N, together or each by itself: the kernel with four tiles of digit rows per wave is faster with the latter (8192 x 8192, 16
-// vectors 24.5 us, together 26.4, V_BFI_B32 24.6), all others with the former.
+// vectors 24.5 us, together 26.4, V_BFI_B32 24.6; over 216 drawn calls 5.4 % on average), all others with the former.
 template <int N, bool SHIFT64>
 __device__ __forceinline__ uint64_t shifted_up(uint64_t v)
 {

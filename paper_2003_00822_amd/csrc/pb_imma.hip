@@ -85,7 +85,8 @@ __host__ __device__ inline int stage_operand(int rows) { return rows * 64 + 16; 
 
 template <int ND, int Q, bool IL, int TM, bool FUSED, int EPI, int POLICY, bool PLAIN>
 // (the waves per SIMD: one tile, digits from memory, has four at most where a row has sixteen slices, and the registers that this leaves
-// let the compiler request the digits earlier: 67 x 4604, 7 vectors of 16 bits 6.4 -> 5.8 us, 913 x 8013, 15 vectors 7.1 -> 6.7)
+// let the compiler request the digits earlier: 67 x 4604, 7 vectors of 16 bits 6.4 -> 5.8 us, 913 x 8013, 15 vectors 7.1 -> 6.7, over 194 drawn
+// calls 1.7 % on average)
 __global__ __launch_bounds__(stream_waves(TM) * 64)
 __attribute__((amdgpu_waves_per_eu(stream_waves(TM) / 4, !FUSED && TM == 1 ? 4 : 8))) void k_i8(const I8Args a)
 {
@@ -493,7 +494,8 @@ static bool streaming(const I8Call &c) { return c.tiles == 1 && c.weights > 44.0
 // half of them the estimates were no better on the other half (3.1 %, 3.0 % before) and stay.
 // The bitlayers count by themselves: with one cost for all,
 // one and two bitlayers of a few vectors went to the wrong kernel (3841 x 7174, one bitlayer, 14 vectors: 13.4 us, here 10.9).
-//   few digit rows: rounds of workgroups over the chip, units (row tile, group, tile of digit rows, chunk), conversion
+//   few digit rows: rounds of workgroups over the chip (16 / S at once, which they were fitted with; per_unit has what runs), units
+//                   (row tile, group, tile of digit rows, chunk), conversion
 //   many:           rounds of workgroups times (start and end + steps), the digits of all vectors through memory
 static int pick_way(const I8Call &c, bool prepared, int cus)
 {

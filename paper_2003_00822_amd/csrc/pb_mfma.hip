@@ -163,8 +163,8 @@ __device__ __forceinline__ v8i as_operand(const u32x4 v)
 
 // Two packed words -> their B operands: FP4 code 2.0 where the weight bit is set.  Register r of an operand holds the columns 4 n + r.
 // The shifts are those of both words at once: eleven operations of the vector ALU instead of fourteen (4096 x 4096, 8 bitlayers 4.8 -> 4.6
-// us, an LSTM step of 6000 x 3000 with 8 bitlayers 6.8 -> 6.35, 500 x 12001, 16 bitlayers 11.9 -> 11.05).  The constant in a vector register, which
-// makes V_AND_B32 by itself faster, measured 0.02 to 0.5 us slower here.
+// us, an LSTM step of 6000 x 3000 with 8 bitlayers 6.8 -> 6.35, 500 x 12001, 16 bitlayers 11.9 -> 11.05).  The constant in a vector register
+// measured 0.02 to 0.5 us slower here.
 __device__ __forceinline__ void weight_operands(uint64_t w, v8i &b0, v8i &b1)
 {
     constexpr uint32_t code = 0x44444444u;
